@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libattn_gfx950.so")
-SOURCES = ["attn_api.hip", "prefill_f32.hip", "prefill_bf16.hip", "prefill_bf16_ring.hip", "prefill_f16_ring.hip", "prefill_f16.hip", "decode_bf16.hip", "decode_f16.hip", "rmsnorm.hip", "kv_write.hip"]
+SOURCES = ["attn_api.hip", "prefill_f32.hip", "prefill_bf16.hip", "prefill_bf16_ring.hip", "prefill_f16_ring.hip", "prefill_f16.hip", "prefill_split.hip", "decode_bf16.hip", "decode_f16.hip", "rmsnorm.hip", "kv_write.hip"]
 # the benchmark's measurement aids: a library of their own, outside the attention ABI
 PROBE_LIB = os.path.join(HERE, "libprobe_gfx950.so")
 # Packed fp32 instructions (v_pk_fma_f32 and friends) are switched off on purpose: some of their forms

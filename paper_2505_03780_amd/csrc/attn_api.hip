@@ -244,12 +244,30 @@ int find_instance(int is_decode, const KParams &p, int waves, int hpw, int bn, i
     return -1;
 }
 
+// Whether a prefill call has too few query rows to fill the chip with the other kernels' 128- and 256-row
+// workgroups, and enough keys that splitting them over the wavefronts of a 32-row workgroup pays
+// (prefill_split.hip).  Measured on random shapes against the ring kernel (GPU time, 32/8, 64/8, 16/16, 16/4 and 8/2
+// heads, bf16, D = 128), where the lines below lie:
+//  * up to one workgroup per compute unit the split is ahead from 160 keys on: 200 keys 1.0-1.07x, 500 keys
+//    1.3x (13.6 -> 10.3 us), 2000 keys 2x (31 -> 15 us), 8000-15000 keys 2.6-3.6x (322 -> 90 us); below 160 keys level;
+//  * up to two per compute unit it loses up to about 1000 keys (24.6 against 22.0 us) and is ahead from
+//    2048 on, where the ring kernel goes over to one large workgroup per compute unit (4500 keys: 59
+//    against 102 us); beyond two the ring is ahead but for the longest contexts.
+bool few_rows_many_keys(const KParams &p)
+{
+    const int heads = std::min(p.group & -p.group, 32), tok = 32 / heads;
+    const int64_t wgs = (int64_t)p.num_seqs * ((p.max_q_len + tok - 1) / tok) * (p.num_q_heads / heads);
+    return (p.max_kv_len >= 160 && wgs <= compute_units()) || (p.max_kv_len > 2048 && wgs <= 2 * compute_units());
+}
+
 int heuristic(const KParams &p, int is_decode)
 {
     int n;
     const Instance *t = instances(is_decode, &n);
     int id = -1;
     if (!is_decode) {
+        if (few_rows_many_keys(p)) id = find_instance(0, p, 8, 0, 32, 32, 0);  // wavefronts split the keys
+        if (id >= 0) return id;
         // pack as many heads of a KV head as divide the group: they share every K/V tile
         int hpw = p.group % 4 == 0 ? 4 : (p.group % 2 == 0 ? 2 : 1);
         // The rules below come from tuning a batch x length grid (profiles: configuration portability).
@@ -1042,6 +1060,8 @@ const Instance *prefill_instances(int *count)
         t = prefill_ring_f16_instances(&n);
         v.insert(v.end(), t, t + n);
         t = prefill_staged_f16_instances(&n);
+        v.insert(v.end(), t, t + n);
+        t = prefill_split_instances(&n);
         v.insert(v.end(), t, t + n);
         return v;
     }();

@@ -21,7 +21,7 @@ import tempfile
 from .build import CSRC, EXTRA, FLAGS, SOURCES
 
 _INSTR = re.compile(r"^\t([a-z][a-z0-9_]+)\b")
-_FAMILIES = (("prefill_ring_kernel", "prefill ring"), ("prefill_bf16_kernel", "prefill staged"), ("prefill_f32_kernel", "prefill fp32"),
+_FAMILIES = (("prefill_ring_kernel", "prefill ring"), ("prefill_split_kernel", "prefill key split"), ("prefill_bf16_kernel", "prefill staged"), ("prefill_f32_kernel", "prefill fp32"),
              ("decode_bf16_kernel", "decode fixed split"), ("decode_seq_kernel", "decode wave per head"),
              ("decode_balanced_kernel", "decode token-balanced"), ("combine_kernel", "decode merge"),
              ("rmsnorm_kernel", "rms norm"), ("kv_cache_write_kernel", "kv write"))
