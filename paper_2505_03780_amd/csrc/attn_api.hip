@@ -244,20 +244,23 @@ int find_instance(int is_decode, const KParams &p, int waves, int hpw, int bn, i
     return -1;
 }
 
-// Whether a prefill call has too few query rows to fill the chip with the other kernels' 128- and 256-row
+// Whether a prefill call has too few query rows to fill the chip with the ring kernel's 128- and 256-row
 // workgroups, and enough keys that splitting them over the wavefronts of a 32-row workgroup pays
 // (prefill_split.hip).  Measured on random shapes against the ring kernel (GPU time, 32/8, 64/8, 16/16, 16/4 and 8/2
-// heads, bf16, D = 128), where the lines below lie:
-//  * up to one workgroup per compute unit the split is ahead from 160 keys on: 200 keys 1.0-1.07x, 500 keys
-//    1.3x (13.6 -> 10.3 us), 2000 keys 2x (31 -> 15 us), 8000-15000 keys 2.6-3.6x (322 -> 90 us); below 160 keys level;
-//  * up to two per compute unit it loses up to about 1000 keys (24.6 against 22.0 us) and is ahead from
-//    2048 on, where the ring kernel goes over to one large workgroup per compute unit (4500 keys: 59
-//    against 102 us); beyond two the ring is ahead but for the longest contexts.
+// heads, bf16), where the lines below lie:
+//  * up to one workgroup per compute unit the split is ahead from 160 keys on: at D = 128 200 keys 1.02-1.16x,
+//    500 keys 1.2-1.4x (13.6 -> 10.3 us), 2000 keys 2x (31 -> 15 us), 8000-15000 keys 2.6-3.6x (322 -> 90 us), at
+//    D = 64 1.15x, 1.4x (10.0 -> 7.1 us), 2x and 2.1-3.3x; below 160 keys they are level;
+//  * up to two per compute unit it loses below about 1000 keys (D = 128: 24.6 against 22.0 us at 1121
+//    keys, D = 64: 9.2 against 7.6 us at 252) and gains above (D = 128: 43 against 51 us at 1486 keys, 59
+//    against 102 us at 4450; D = 64: 14.3 against 16.4 us at 1055, 32 against 84 us at 7700); beyond two the
+//    ring is ahead but for the longest contexts.
 bool few_rows_many_keys(const KParams &p)
 {
     const int heads = std::min(p.group & -p.group, 32), tok = 32 / heads;
     const int64_t wgs = (int64_t)p.num_seqs * ((p.max_q_len + tok - 1) / tok) * (p.num_q_heads / heads);
-    return (p.max_kv_len >= 160 && wgs <= compute_units()) || (p.max_kv_len > 2048 && wgs <= 2 * compute_units());
+    const int two_from = p.head_dim == 64 ? 1024 : 1536;
+    return (p.max_kv_len >= 160 && wgs <= compute_units()) || (p.max_kv_len > two_from && wgs <= 2 * compute_units());
 }
 
 int heuristic(const KParams &p, int is_decode)
@@ -277,7 +280,11 @@ int heuristic(const KParams &p, int is_decode)
         const int order = (prefix || p.max_kv_len >= 4096 || p.num_seqs >= 32) ? 1 : 0;
         // Short sequences: two small workgroups per compute unit hide each other's prologue and
         // epilogue; long ones: one large workgroup with the deeper ring.
-        const bool small_wg = p.max_kv_len <= 2048;
+        // At D = 64 the small workgroup (128 rows, three per compute unit) also stays ahead on long contexts
+        // until there are 256-row tiles for every compute unit four times over: 2 x 1000 tokens behind 3000 keys
+        // 74.6 against 88.6 us, one sequence of 8191 tokens (1024 tiles) 292 against 286 us.
+        const int64_t tiles256 = (int64_t)p.num_seqs * ((p.max_q_len + 256 / hpw - 1) / (256 / hpw)) * (p.num_q_heads / hpw);
+        const bool small_wg = p.max_kv_len <= 2048 || (p.head_dim == 64 && tiles256 < 4 * compute_units());
         // a paged context adds the table entry to every transfer's address chain: the deepest prefetch
         // (8 units) measured up to 10 % ahead of 5 on the slower machines there, level elsewhere
         if (!small_wg && p.block_table) id = find_instance(0, p, 8, hpw, 32, 256, 0, order, 8);

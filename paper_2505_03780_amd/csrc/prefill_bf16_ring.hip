@@ -18,7 +18,16 @@
 //    (then O and l are rescaled); otherwise exponentials are taken against the stale
 //    reference.  The result is unchanged, because numerator and denominator
 //    carry the same reference, and the rescale of the accumulators becomes rare.
-//  * The output tile is transposed through LDS and written as whole 256-byte rows.
+//  * The output tile is transposed through LDS and written as whole rows.
+//
+// Head sizes 128 and 64.  At D = 64 a unit has half the MFMAs for the same softmax, so the vector ALU is the bound
+// (16 MFMAs of two row blocks: 512 cycles of matrix pipe, about 780 of the vector issue port); a wave takes two
+// 32-row blocks (QB = 2) where there is work enough, which halves its LDS reads and transfers per flop with the same
+// registers as one block at D = 128, and four waves (a 1 KB transfer moves eight 128-byte rows, so that is
+// how many share a unit).  Against the register-staged kernel that served D = 64 before (32/8 heads, same box):
+// 6 fp16 sequences of 300-3000 tokens 472 -> 163 us (289 -> 838 TFLOP/s), one bf16 sequence of 8191 tokens 283 us
+// (980 TFLOP/s).  An eight-slot ring with five units in flight is 2-6 % ahead of four slots there; one row block with
+// four slots and three workgroups per compute unit leads up to about four 256-row tiles per compute unit.
 #include "kernel_params.hpp"
 
 namespace attn {
@@ -55,10 +64,7 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) const void gbl_void;
 
-constexpr int kHD = 128;
 constexpr int kUnit = 32;          // keys per pipeline unit
-constexpr int kSlotBytes = 16384;  // 32 K rows + 32 V rows of 256 bytes
-constexpr int kVOff = 8192;
 constexpr float kSlack = 8.f;      // log2 of the largest weight tolerated before the reference moves
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -103,6 +109,20 @@ __device__ __forceinline__ u32x4 lds_read_b128_untracked(unsigned addr)
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "n"(OFFSET) : "memory");
     return r;
 }
+// V^T image fragment f: the index becomes the instruction's immediate offset
+__device__ __forceinline__ u32x4 lds_read_fragment(unsigned img, int f)
+{
+    switch (f) {
+        case 0: return lds_read_b128_untracked<0 * 1024>(img);
+        case 1: return lds_read_b128_untracked<1 * 1024>(img);
+        case 2: return lds_read_b128_untracked<2 * 1024>(img);
+        case 3: return lds_read_b128_untracked<3 * 1024>(img);
+        case 4: return lds_read_b128_untracked<4 * 1024>(img);
+        case 5: return lds_read_b128_untracked<5 * 1024>(img);
+        case 6: return lds_read_b128_untracked<6 * 1024>(img);
+        default: return lds_read_b128_untracked<7 * 1024>(img);
+    }
+}
 __device__ __forceinline__ void lds_write_b128_untracked(unsigned addr, s16x8 v)
 {
     asm volatile("ds_write_b128 %0, %1" : : "v"(addr), "v"(v) : "memory");
@@ -131,40 +151,57 @@ __device__ __forceinline__ void wait_vmcnt()
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
 }
 
-// chunk swizzle of a row inside a unit: rows r..r+15 get 16 distinct values (128-bit K reads),
-// rows r..r+3 differ in the upper two bits (64-bit transposing V reads)
-__device__ __forceinline__ int swz(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
+// 16-byte chunk swizzle of a row inside a unit (XOR).  D = 128, rows of 256 bytes: rows r..r+15 get 16 distinct
+// values (128-bit K reads), rows r..r+3 differ in the upper two bits (64-bit transposing V reads).  D = 64, two
+// rows in 256 bytes: the eight row pairs of rows r..r+15 get eight distinct values, and the pairs of rows
+// r..r+3 differ in the upper bit.
+template <int HD>
+__device__ __forceinline__ int swz(int row)
+{
+    if (HD == 64) return (((row >> 1) & 1) << 2) | (((row >> 2) & 1) << 1) | ((row >> 3) & 1);
+    return ((row & 3) << 2) | ((row >> 2) & 3);
+}
 
-template <int QB, int HPW, int NSLOT, int PF, int WAVES>
+template <int HD, int QB, int HPW, int NSLOT, int PF, int WAVES>
 struct RingCfg {
     static constexpr int kWaves = WAVES;
+    static constexpr int kRowBytes = HD * 2;
+    static constexpr int kVOff = kUnit * kRowBytes;      // V rows behind the K rows of a slot
+    static constexpr int kSlotBytes = 2 * kVOff;         // 32 K rows + 32 V rows
+    static constexpr int kRowsPerDma = 1024 / kRowBytes;
     static constexpr int kRowsPerWave = kUnit / WAVES;   // rows of a unit that one wave transfers
-    static constexpr int kDmaPerWave = kRowsPerWave / 4;  // 1 KB transfers per wave, for K and again for V
+    static constexpr int kDmaPerWave = kRowsPerWave / kRowsPerDma;  // 1 KB transfers per wave, for K and again for V
     static constexpr int kTSub = kWaves / HPW;
     static constexpr int kWaveTok = 32 * QB;
     static constexpr int kTok = kTSub * kWaveTok;
     static constexpr int kThreads = WAVES * 64;
-    static constexpr int kImgBytes = 8192;               // V^T fragments of one unit, in MFMA operand order
-    static constexpr int kFragsPerWave = 8 / WAVES;      // fragments each wave transposes per unit
+    static constexpr int kFrags = HD / 16;               // V^T fragments of one unit (1 KB each)
+    static constexpr int kImgBytes = kFrags * 1024;      // all of them, in MFMA operand order
+    static constexpr int kFragsPerWave = kFrags / WAVES; // fragments each wave transposes per unit
+    // two waves per SIMD for the small workgroups (four of one row block at D = 64: 40 KB of LDS, 168 registers)
+    static constexpr int kMinWaves = WAVES == 4 && QB == 1 && HD == 64 ? 3 : WAVES == 4 && QB * HD <= 128 ? 2 : 1;
     static constexpr size_t kLdsBytes = (size_t)NSLOT * kSlotBytes + 2 * kImgBytes;
     static_assert(WAVES == 4 || WAVES == 8, "4 or 8 wavefronts");
+    static_assert(kDmaPerWave >= 1 && kFragsPerWave >= 1, "every wave transfers and transposes its share");
     // during iteration u the slots of units u+1 (V, transposed for the next iteration) and u+2 (K) are
     // read and units u+3..u+PF are in flight; unit u+PF reuses the slot of unit u+PF-NSLOT <= u
     static_assert(NSLOT >= PF, "ring too small for the prefetch distance");
     static_assert(PF >= 3, "K of unit u+2 is read one iteration ahead, so three units must be resident");
     static_assert(kWaves % HPW == 0, "waves must split evenly over heads");
-    static_assert(kLdsBytes >= (size_t)kWaves * kWaveTok * kHD * 2, "epilogue staging must fit in the ring");
+    static_assert(kLdsBytes >= (size_t)kWaves * kWaveTok * HD * 2, "epilogue staging must fit in the ring");
 };
 
-template <typename E, int QB, int HPW, int NSLOT, int PF, int WAVES, bool PAGED>
-__global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void prefill_ring_kernel(const KParams p)
+template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES, bool PAGED>
+__global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>::kMinWaves)) void prefill_ring_kernel(const KParams p)
 {
-    using C = RingCfg<QB, HPW, NSLOT, PF, WAVES>;
+    using C = RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>;
     using elem = typename E::elem;
     using x8 = typename E::x8;
     using x2 = typename E::x2;
-    constexpr int KSTEPS = kHD / 16;
-    constexpr int DB = kHD / 32;
+    constexpr int KSTEPS = HD / 16;
+    constexpr int DB = HD / 32;
+    constexpr int CPR = HD / 8;  // 16-byte chunks of a row
+    constexpr int kRowBytes = C::kRowBytes, kSlotBytes = C::kSlotBytes, kVOff = C::kVOff;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
 
     // ---- which (head group, sequence, query tile) ---------------------------------------------
@@ -250,10 +287,10 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
 
     elem *obase = (elem *)p.out;
     if (n_units <= 0) {  // no visible key at all (an empty context; also lengths that break seq_lens >= n_q): zeros
-        for (int i = lane; i < C::kWaveTok * (kHD / 8); i += 64) {
-            const int t = t0w + i / (kHD / 8);
+        for (int i = lane; i < C::kWaveTok * CPR; i += 64) {
+            const int t = t0w + i / CPR;
             if (t < n_q)
-                *(u32x4 *)(obase + (int64_t)(q0 + t) * p.o_stride_tok + (int64_t)head * p.o_stride_head + 8 * (i % (kHD / 8))) =
+                *(u32x4 *)(obase + (int64_t)(q0 + t) * p.o_stride_tok + (int64_t)head * p.o_stride_head + 8 * (i % CPR)) =
                     u32x4{0u, 0u, 0u, 0u};
         }
         return;
@@ -271,7 +308,7 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
         qrel[qb] = lim - 4 * lhalf;
     }
 
-    // ---- DMA of one unit: wave w moves rows 8w..8w+7 of K and of V (2 x 1 KB each) -------------
+    // ---- DMA of one unit: wave w moves its share of the rows of K and of V, 1 KB a transfer -------------
     // The address of a transfer is a wave-uniform 64-bit base (SGPRs: pool block or packed row of the
     // unit, KV head) plus a 32-bit per-lane offset (row inside the block, swizzled 16-byte chunk).
     // The rows of a wave never straddle a 16-key block, so the table entry is wave-uniform.
@@ -284,7 +321,8 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
     typedef const __attribute__((address_space(4))) int32_t *table_ptr;
     const table_ptr bt_row = PAGED ? (table_ptr)(p.block_table + (int64_t)s * p.block_table_stride) : (table_ptr) nullptr;
     constexpr int RPW = C::kRowsPerWave, NDMA = C::kDmaPerWave;
-    const int dma_row = RPW * wave + (lane >> 4);  // + 4*i, row inside the unit
+    constexpr int RPD = C::kRowsPerDma;
+    const int dma_row = RPW * wave + lane / CPR;  // + RPD*i, row inside the unit
     const uint32_t tok_bytes = (uint32_t)p.kv_stride_tok * 2;
     const int last_unit0 = (n_kv - 1) & ~(kUnit - 1);  // first key of the last unit that holds a real key
     // Per-lane byte offset of a transfer from the first row of this wave's share of a unit: the lane's
@@ -298,9 +336,9 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
         const int wrow_last = last_unit0 + RPW * wave < n_kv ? last_unit0 + RPW * wave : n_kv - 1;
 #pragma unroll
         for (int i = 0; i < NDMA; ++i) {
-            const uint32_t chunk = 16 * ((lane & 15) ^ swz(dma_row + 4 * i));
-            dma_off[i] = (uint32_t)((lane >> 4) + 4 * i) * tok_bytes + chunk;
-            int row = last_unit0 + dma_row + 4 * i;
+            const uint32_t chunk = 16 * ((lane % CPR) ^ swz<HD>(dma_row + RPD * i));
+            dma_off[i] = (uint32_t)(lane / CPR + RPD * i) * tok_bytes + chunk;
+            int row = last_unit0 + dma_row + RPD * i;
             row = row < n_kv ? row : n_kv - 1;
             dma_off_last[i] = (uint32_t)(row - wrow_last) * tok_bytes + chunk;
         }
@@ -326,7 +364,7 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
         return r;
     };
     auto issue_unit = [&](int unit, int entry) {
-        unsigned char *slot = lds + (unit % NSLOT) * kSlotBytes + RPW * wave * 256;
+        unsigned char *slot = lds + (unit % NSLOT) * kSlotBytes + RPW * wave * kRowBytes;
         const int u0 = unit * kUnit < last_unit0 ? unit * kUnit : last_unit0;  // units past the end repeat the last one
         const bool ragged = u0 + kUnit > n_kv;
         int wrow = u0 + RPW * wave;  // first row of this wave's share
@@ -341,8 +379,8 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
             // (kept opaque: a loop-invariant offset would be widened and added to the array bases once, and
             // the transfers would then carry 64-bit per-lane addresses instead of scalar base + 32-bit offset)
             asm volatile("" : "+v"(o));
-            __builtin_amdgcn_global_load_lds((gbl_void *)(kb + o), (lds_void *)(slot + 4 * i * 256), 16, 0, 0);
-            __builtin_amdgcn_global_load_lds((gbl_void *)(vb + o), (lds_void *)(slot + kVOff + 4 * i * 256), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((gbl_void *)(kb + o), (lds_void *)(slot + 1024 * i), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((gbl_void *)(vb + o), (lds_void *)(slot + kVOff + 1024 * i), 16, 0, 0);
         }
     };
 
@@ -370,9 +408,10 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
         const int db = f % DB, ks2 = f / DB;
         const int a = l16 >> 2, h1 = (lane >> 4) & 1, h0 = (lane & 3) >> 1;
 #pragma unroll
-        for (int rd = 0; rd < 2; ++rd)
-            tr_off[i][rd] = kVOff + (8 * rd + 4 * lhalf + a) * 256 + 16 * (((db ^ a) << 2) | (2 * (h1 ^ rd)) | (h0 ^ lhalf)) + 8 * (lane & 1) +
-                            ks2 * 16 * 256;
+        for (int rd = 0; rd < 2; ++rd) {
+            const int row = 16 * ks2 + 8 * rd + 4 * lhalf + a;
+            tr_off[i][rd] = kVOff + row * kRowBytes + 16 * ((4 * db + 2 * h1 + h0) ^ swz<HD>(row)) + 8 * (lane & 1);
+        }
     }
     auto transpose_load = [&](int unit, s16x4 (&raw)[C::kFragsPerWave][2]) {
         const unsigned char *vt = lds + (unit % NSLOT) * kSlotBytes;
@@ -396,9 +435,9 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
     // ---- per-lane LDS read offsets ----------------------------------------------------------------
     int koff[KSTEPS];
     {
-        const int kx = swz(l32);
+        const int kx = swz<HD>(l32);
 #pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) koff[ks] = l32 * 256 + 16 * ((2 * ks + lhalf) ^ kx);
+        for (int ks = 0; ks < KSTEPS; ++ks) koff[ks] = l32 * kRowBytes + 16 * ((2 * ks + lhalf) ^ kx);
     }
     // ---- state ---------------------------------------------------------------------------------------
     f32x16 oacc[QB][DB];
@@ -452,11 +491,8 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
                 for (int v = 0; v < 16; ++v) oacc[qb][db][v] *= alpha;
         }
     };
-    auto move_reference = [&](const float (&bm)[QB]) {
-        if (reference_outgrown(bm)) rescale_to(bm);
-    };
-    // Row maxima of a fresh score tile (masked if MASK), then move the reference if a row outgrew it.
-    // With MASK the tile is left scaled (x = c*s, masked entries -inf); without, it stays raw.
+    // Row maxima of the first score tile (masked if MASK), which set the reference (0 for a row of nothing but
+    // -inf).  With MASK the tile is left scaled (x = c*s, masked entries -inf); without, it stays raw.
     auto settle = [&](int unit, f32x16 (&sacc)[QB], auto mask_tag) {
         constexpr bool MASK = decltype(mask_tag)::value;
         float bm[QB];
@@ -477,7 +513,7 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
             mx = swap32_max(mx);
             bm[qb] = MASK ? mx : mx * c;
         }
-        move_reference(bm);
+        rescale_to(bm);
     };
     // ---- prologue: PF units in flight, S(0) ready ------------------------------------------------
 #pragma unroll
@@ -521,7 +557,7 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
     // re-read rows of a dummy transfer and every entry is masked): no branch inside the iteration.
     // LDS operations of one iteration, in issue order (the same in every iteration, so the position of
     // an operation of the previous iteration is known too):
-    //   phase X: V^T image fragments f = 0..7 (one per 1/8 of the phase), after fragment 1 the wave's
+    //   phase X: V^T image fragments f = 0..7 (one per 1/8 of the phase), after fragment kTrAfter the wave's
     //            transposing reads of V(u+1) (2 per fragment it owns), after fragment kWriteAfter the
     //            wave's image stores of V(u+1);
     //   phase Y: K(u+2) fragments ks = 0..7, kKPerGroup per group from the first group on.
@@ -529,8 +565,9 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
     // needs.  Nothing in the loop waits for "all": the image stores are older than the last image
     // fragments the same wave waits for in phase Y, so they have been performed when the wave reaches
     // the barrier; the K reads stay in flight across the barrier.
-    constexpr int kWriteAfter = 5;
-    constexpr int kXOps = 8 + 3 * C::kFragsPerWave;  // LDS operations of phase X
+    // (at D = 64 a unit has four image fragments and four K fragments: the transposing reads go behind
+    // fragment 0, the stores behind fragment 2)
+    constexpr int kTrAfter = HD == 64 ? 0 : 1, kWriteAfter = HD == 64 ? 2 : 5;
     constexpr int kKPerGroup = 2;
     // Block-table entry of the unit that the next iteration transfers (entry_cur, set up in the prologue):
     // requested (scalar cache) at the top of an iteration, awaited at its barrier -- the one place where
@@ -544,14 +581,15 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
     for (int ks = 0; ks < KSTEPS; ++ks) {
         kaddr[ks] = lds_addr(lds + koff[ks]);
         kaddr_far[ks] = kaddr[ks] + 65536u;
-        if (NSLOT > 4) asm volatile("" : "+v"(kaddr_far[ks]));  // a register of its own, not an addition at every use
+        if (NSLOT * kSlotBytes > 65536) asm volatile("" : "+v"(kaddr_far[ks]));  // a register of its own, not an addition at every use
     }
     // SLOT2 >= 0: the ring slot of unit u+2, known at compile time
     auto iteration = [&](int u, f32x16 (&cur)[QB], f32x16 (&nxt)[QB], auto cur_tag, auto nxt_tag, auto slot_tag) {
         constexpr bool CUR_MASK = decltype(cur_tag)::value;
         constexpr bool NXT_MASK = decltype(nxt_tag)::value;
         constexpr int SLOT2 = decltype(slot_tag)::value;
-        constexpr int G = 8 * QB;  // MFMAs per product
+        constexpr int G = KSTEPS * QB;  // MFMAs per product
+        static_assert(KSTEPS == 2 * DB, "as many MFMAs per row block in O += V P as in S = K Q^T");
         const unsigned img_rd = lds_addr(img_base + (u & 1) * C::kImgBytes + lane * 16);
         const unsigned img_wr = lds_addr(img_base + ((u + 1) & 1) * C::kImgBytes + lane * 16);
         const unsigned char *kt2 = lds + ((u + 2) % NSLOT) * kSlotBytes;
@@ -571,16 +609,17 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
         // Two steps, a group apart: the exponentials are issued under one MFMA and their results are
         // rounded and summed under the next, so that nothing waits for the transcendental unit's
         // latency (a wavefront issues in order: a use right behind the exponential stalls it).
-        float e_pending[QB][2];
+        float e_pending[QB][2][2];  // two pairs may be pending (D = 64)
         auto exp_issue = [&](int qb, int pair) {
             const int v = 2 * pair;
-            e_pending[qb][0] = fast_exp2(CUR_MASK ? cur[qb][v] - m_ref[qb] : __builtin_fmaf(cur[qb][v], c, -m_ref[qb]));
-            e_pending[qb][1] = fast_exp2(CUR_MASK ? cur[qb][v + 1] - m_ref[qb] : __builtin_fmaf(cur[qb][v + 1], c, -m_ref[qb]));
-            asm volatile("" : "+v"(e_pending[qb][0]), "+v"(e_pending[qb][1]));  // issued here, not where they are used
+            float(&e)[2] = e_pending[qb][pair & 1];
+            e[0] = fast_exp2(CUR_MASK ? cur[qb][v] - m_ref[qb] : __builtin_fmaf(cur[qb][v], c, -m_ref[qb]));
+            e[1] = fast_exp2(CUR_MASK ? cur[qb][v + 1] - m_ref[qb] : __builtin_fmaf(cur[qb][v + 1], c, -m_ref[qb]));
+            asm volatile("" : "+v"(e[0]), "+v"(e[1]));  // issued here, not where they are used
         };
         auto exp_finish = [&](int qb, int pair) {
             const int v = 2 * pair;
-            const float e0 = e_pending[qb][0], e1 = e_pending[qb][1];
+            const float e0 = e_pending[qb][pair & 1][0], e1 = e_pending[qb][pair & 1][1];
             x2 pr;
             pr[0] = (elem)e0;
             pr[1] = (elem)e1;
@@ -600,25 +639,19 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
             if (qb == 0) lds_wait_upto((KSTEPS - 1 - ks) + seq, kf[ks]);
             nxt[qb] = E::mfma(__builtin_bit_cast(x8, kf[ks]), qf[qb][ks], ks == 0 ? zero : nxt[qb]);
             // weights of keys 0..15 (the B operand of the first four PV MFMAs): issued under the even steps,
-            // finished under the odd ones
-            if (ks % 2 == 0)
+            // finished under the odd ones (D = 64, half as many MFMAs for the same weights: one pair per step)
+            if (HD == 64) {
+                if (ks > 0) exp_finish(qb, ks - 1);
+                exp_issue(qb, ks);
+            } else if (ks % 2 == 0)
                 exp_issue(qb, ks / 2);
             else
                 exp_finish(qb, ks / 2);
-            if (g * 8 / G != (g + 1) * 8 / G) {
-                const int f = g * 8 / G;
-                switch (f) {  // the fragment index becomes the instruction's immediate offset
-                    case 0: vfrag[0] = lds_read_b128_untracked<0 * 1024>(img_rd); break;
-                    case 1: vfrag[1] = lds_read_b128_untracked<1 * 1024>(img_rd); break;
-                    case 2: vfrag[2] = lds_read_b128_untracked<2 * 1024>(img_rd); break;
-                    case 3: vfrag[3] = lds_read_b128_untracked<3 * 1024>(img_rd); break;
-                    case 4: vfrag[4] = lds_read_b128_untracked<4 * 1024>(img_rd); break;
-                    case 5: vfrag[5] = lds_read_b128_untracked<5 * 1024>(img_rd); break;
-                    case 6: vfrag[6] = lds_read_b128_untracked<6 * 1024>(img_rd); break;
-                    default: vfrag[7] = lds_read_b128_untracked<7 * 1024>(img_rd); break;
-                }
+            if (qb == QB - 1) {
+                const int f = ks;
+                vfrag[f] = lds_read_fragment(img_rd, f);
                 vpos[f] = seq++;
-                if (f == 1) {  // this wave's share of V(u+1): transposed here, stored a few groups later
+                if (f == kTrAfter) {  // this wave's share of V(u+1): transposed here, stored a few groups later
                     transpose_load(u + 1, raw);
                     seq += 2 * C::kFragsPerWave;
                     tr_last = seq - 1;
@@ -647,14 +680,25 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
             const int f = g / QB, qb = g % QB;  // f = ks2 * DB + db
             // weights of keys 16..31, needed from the fifth PV MFMA on: each pair is finished a group after
             // it was issued (the last one just ahead of the MFMA that needs it)
-            if (f >= 1 && f <= DB) exp_finish(qb, 3 + f);
+            if (HD == 64) {
+                if (f == 0) exp_finish(qb, 3);
+                if (f == 1 || f == 2) {
+                    exp_finish(qb, 2 + 2 * f);
+                    exp_finish(qb, 3 + 2 * f);
+                }
+            } else if (f >= 1 && f <= DB)
+                exp_finish(qb, 3 + f);
             if (qb == 0) lds_wait_upto(seq - 1 - vpos[f], vfrag[f]);
             oacc[qb][f % DB] = E::mfma(__builtin_bit_cast(x8, vfrag[f]), pf[qb][f / DB], oacc[qb][f % DB]);
-            if (f < DB) exp_issue(qb, 4 + f);
+            if (HD == 64 && f < DB) {
+                exp_issue(qb, 4 + 2 * f);
+                exp_issue(qb, 5 + 2 * f);
+            } else if (f < DB)
+                exp_issue(qb, 4 + f);
             // The second half of the phase (the last S MFMAs have drained) has vector slots to spare: the row
             // maxima of S(u+1), eight scores per group, and right behind them the test whether a reference
             // has to move, so that the answer is there when the last MFMA of the iteration has been issued.
-            const int sl = g - 4 * QB;
+            const int sl = HD == 64 ? g - (G - 2 * QB - 1) : g - 4 * QB;
             if (sl >= 0 && sl < 2 * QB) {
                 const int q2 = sl / 2, v0 = 8 * (sl % 2);
                 if (NXT_MASK) {
@@ -686,7 +730,8 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
                     if (SLOT2 < 0)
                         kf[ks] = lds_read_b128_untracked<0>(lds_addr(kt2 + koff[ks]));
                     else
-                        kf[ks] = lds_read_b128_untracked<(SLOT2 < 0 ? 0 : SLOT2 % 4) * kSlotBytes>(SLOT2 >= 4 ? kaddr_far[ks] : kaddr[ks]);
+                        kf[ks] = lds_read_b128_untracked<(SLOT2 < 0 ? 0 : SLOT2 * kSlotBytes % 65536)>(SLOT2 * kSlotBytes >= 65536 ? kaddr_far[ks]
+                                                                                                                                  : kaddr[ks]);
                     ++seq;
                 }
             }
@@ -749,14 +794,17 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
     // The last iteration's K reads are still in flight and nobody will use them: wait for them here,
     // with their registers tied, so that the compiler cannot hand those registers to anything else
     // while a read may still land in them.
-    asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]), "+v"(kf[4]), "+v"(kf[5]), "+v"(kf[6]), "+v"(kf[7])::"memory");
-    static_assert(KSTEPS == 8, "the drain above names eight fragments");
+    static_assert(KSTEPS == 8 || KSTEPS == 4, "the drain below names every fragment");
+    if constexpr (KSTEPS == 8)
+        asm volatile("s_waitcnt lgkmcnt(0)"
+                     : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]), "+v"(kf[4]), "+v"(kf[5]), "+v"(kf[6]), "+v"(kf[7])::"memory");
+    else
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3])::"memory");
 
     // ---- epilogue: O / l, transposed through LDS, whole rows to HBM ------------------------------
     wait_vmcnt<0>();
     __syncthreads();  // the ring is free: every wave is past its last V read and no DMA is in flight
-    unsigned char *stage = lds + wave * (C::kWaveTok * kHD * 2);  // [token][128] bf16, chunk-swizzled by token
+    unsigned char *stage = lds + wave * (C::kWaveTok * kRowBytes);  // [token][HD] elements, chunk-swizzled by token
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         const float l = swap32_sum(l_run[qb]);
@@ -775,53 +823,54 @@ __global__ __launch_bounds__(WAVES * 64, (QB == 1 && WAVES == 4) ? 2 : 1) void p
                 u32x2 w;
                 w[0] = __builtin_bit_cast(uint32_t, a);
                 w[1] = __builtin_bit_cast(uint32_t, b);
-                *(u32x2 *)(stage + tl * 256 + 16 * (chunk ^ (tl & 15)) + 8 * lhalf) = w;
+                *(u32x2 *)(stage + tl * kRowBytes + 16 * (chunk ^ (tl % CPR)) + 8 * lhalf) = w;
             }
         }
     }
     // wave-private staging: the wave's own LDS writes are ordered before its reads
 #pragma unroll
-    for (int i = 0; i < C::kWaveTok / 4; ++i) {
-        const int tl = 4 * i + (lane >> 4);
-        const int chunk = lane & 15;
-        const u32x4 row = *(const u32x4 *)(stage + tl * 256 + 16 * (chunk ^ (tl & 15)));
+    for (int i = 0; i < C::kWaveTok * CPR / 64; ++i) {
+        const int tl = (64 / CPR) * i + lane / CPR;
+        const int chunk = lane % CPR;
+        const u32x4 row = *(const u32x4 *)(stage + tl * kRowBytes + 16 * (chunk ^ (tl % CPR)));
         const int t = t0w + tl;
         if (t < n_q)
             *(u32x4 *)(obase + (int64_t)(q0 + t) * p.o_stride_tok + (int64_t)head * p.o_stride_head + 8 * chunk) = row;
     }
 }
 
-template <typename E, int QB, int HPW, int NSLOT, int PF, int WAVES>
+template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES>
 bool ring_valid(const KParams &p)
 {
-    // (a cache block of 4 GiB or more would need 64-bit block arithmetic in the transfers)
-    return p.dtype == E::kDtype && p.head_dim == kHD && p.group % HPW == 0 && (!p.block_table || (uint64_t)p.kv_stride_block * 2 < (1ull << 32));
+    // (a cache block of 4 GiB or more would need 64-bit block arithmetic in the transfers, and so would rows 128 MiB apart)
+    return p.dtype == E::kDtype && p.head_dim == HD && p.group % HPW == 0 && (!p.block_table || (uint64_t)p.kv_stride_block * 2 < (1ull << 32)) &&
+           (uint64_t)p.kv_stride_tok * 2 * kUnit < (1ull << 32);
 }
 
-template <typename E, int QB, int HPW, int NSLOT, int PF, int WAVES, bool PAGED>
+template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES, bool PAGED>
 hipError_t ring_launch_impl(const KParams &p, hipStream_t stream, int64_t blocks)
 {
-    using C = RingCfg<QB, HPW, NSLOT, PF, WAVES>;
-    auto kern = prefill_ring_kernel<E, QB, HPW, NSLOT, PF, WAVES, PAGED>;
+    using C = RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>;
+    auto kern = prefill_ring_kernel<E, HD, QB, HPW, NSLOT, PF, WAVES, PAGED>;
     static hipError_t attr = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::kLdsBytes);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(C::kThreads), C::kLdsBytes, stream, p);
     return hipGetLastError();
 }
 
-template <typename E, int QB, int HPW, int NSLOT, int PF, int WAVES, int ORDER>
+template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES, int ORDER>
 hipError_t ring_launch(const KParams &p_in, hipStream_t stream)
 {
     KParams p = p_in;
     p.tile_order = ORDER;
-    using C = RingCfg<QB, HPW, NSLOT, PF, WAVES>;
+    using C = RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>;
     const int64_t q_tiles = (p.max_q_len + C::kTok - 1) / C::kTok;
     const int64_t nhg = (int64_t)p.num_kv_heads * (p.group / HPW);
     const int64_t blocks = q_tiles * p.num_seqs * nhg;
     if (blocks <= 0) return hipSuccess;
     if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
-    return p.block_table ? ring_launch_impl<E, QB, HPW, NSLOT, PF, WAVES, true>(p, stream, blocks)
-                         : ring_launch_impl<E, QB, HPW, NSLOT, PF, WAVES, false>(p, stream, blocks);
+    return p.block_table ? ring_launch_impl<E, HD, QB, HPW, NSLOT, PF, WAVES, true>(p, stream, blocks)
+                         : ring_launch_impl<E, HD, QB, HPW, NSLOT, PF, WAVES, false>(p, stream, blocks);
 }
 
 // This file is compiled twice: as it stands for bf16, and included by prefill_f16_ring.hip with
@@ -834,15 +883,15 @@ hipError_t ring_launch(const KParams &p_in, hipStream_t stream)
 #define RING_NAME "prefill_bf16_ring"
 #endif
 
-#define RING_ONE(QB, HPW, NSLOT, PF, WAVES, ORDER, TAG)                                                            \
+#define RING_ONE(HD, QB, HPW, NSLOT, PF, WAVES, ORDER, TAG)                                                        \
     {                                                                                                              \
-        RING_NAME " d128 qb" #QB " w" #WAVES " hpw" #HPW " slots" #NSLOT " pf" #PF TAG, WAVES * 32 * QB, kUnit, WAVES, \
-            HPW, PF, 0, ring_valid<RING_ELEM, QB, HPW, NSLOT, PF, WAVES>,                                          \
-            ring_launch<RING_ELEM, QB, HPW, NSLOT, PF, WAVES, ORDER>, ORDER                                        \
+        RING_NAME " d" #HD " qb" #QB " w" #WAVES " hpw" #HPW " slots" #NSLOT " pf" #PF TAG, WAVES * 32 * QB, kUnit, WAVES, \
+            HPW, PF, 0, ring_valid<RING_ELEM, HD, QB, HPW, NSLOT, PF, WAVES>,                                      \
+            ring_launch<RING_ELEM, HD, QB, HPW, NSLOT, PF, WAVES, ORDER>, ORDER                                    \
     }
 // both grid orders of one compiled kernel
-#define RING_INSTANCE(QB, HPW, NSLOT, PF, WAVES) \
-    RING_ONE(QB, HPW, NSLOT, PF, WAVES, 0, ""), RING_ONE(QB, HPW, NSLOT, PF, WAVES, 1, " seqmajor")
+#define RING_INSTANCE(HD, QB, HPW, NSLOT, PF, WAVES) \
+    RING_ONE(HD, QB, HPW, NSLOT, PF, WAVES, 0, ""), RING_ONE(HD, QB, HPW, NSLOT, PF, WAVES, 1, " seqmajor")
 
 }  // namespace
 
@@ -850,9 +899,11 @@ hipError_t ring_launch(const KParams &p_in, hipStream_t stream)
 const Instance *prefill_ring_f16_instances(int *count)
 {
     static const Instance table[] = {
-        RING_INSTANCE(1, 4, 8, 5, 8), RING_INSTANCE(1, 2, 8, 5, 8), RING_INSTANCE(1, 1, 8, 5, 8),
-        RING_INSTANCE(1, 4, 8, 6, 8), RING_INSTANCE(1, 4, 4, 4, 4), RING_INSTANCE(1, 2, 4, 4, 4),
-        RING_INSTANCE(1, 1, 4, 4, 4),
+        RING_INSTANCE(128, 1, 4, 8, 5, 8), RING_INSTANCE(128, 1, 2, 8, 5, 8), RING_INSTANCE(128, 1, 1, 8, 5, 8),
+        RING_INSTANCE(128, 1, 4, 8, 6, 8), RING_INSTANCE(128, 1, 4, 4, 4, 4), RING_INSTANCE(128, 1, 2, 4, 4, 4),
+        RING_INSTANCE(128, 1, 1, 4, 4, 4),
+        RING_INSTANCE(64, 2, 4, 8, 5, 4), RING_INSTANCE(64, 2, 2, 8, 5, 4), RING_INSTANCE(64, 2, 1, 8, 5, 4),
+        RING_INSTANCE(64, 1, 4, 4, 4, 4), RING_INSTANCE(64, 1, 2, 4, 4, 4), RING_INSTANCE(64, 1, 1, 4, 4, 4),
     };
     *count = (int)(sizeof(table) / sizeof(table[0]));
     return table;
@@ -861,10 +912,12 @@ const Instance *prefill_ring_f16_instances(int *count)
 const Instance *prefill_ring_instances(int *count)
 {
     static const Instance table[] = {
-        RING_INSTANCE(1, 4, 8, 5, 8), RING_INSTANCE(1, 8, 8, 5, 8),
-        RING_INSTANCE(1, 2, 8, 5, 8), RING_INSTANCE(1, 1, 8, 5, 8), RING_INSTANCE(1, 4, 8, 6, 8),
-        RING_INSTANCE(1, 4, 8, 8, 8), RING_INSTANCE(1, 1, 8, 8, 8), RING_INSTANCE(1, 4, 4, 4, 4),
-        RING_INSTANCE(1, 1, 4, 4, 4), RING_INSTANCE(1, 2, 4, 4, 4),
+        RING_INSTANCE(128, 1, 4, 8, 5, 8), RING_INSTANCE(128, 1, 8, 8, 5, 8),
+        RING_INSTANCE(128, 1, 2, 8, 5, 8), RING_INSTANCE(128, 1, 1, 8, 5, 8), RING_INSTANCE(128, 1, 4, 8, 6, 8),
+        RING_INSTANCE(64, 2, 4, 8, 5, 4), RING_INSTANCE(64, 2, 2, 8, 5, 4), RING_INSTANCE(64, 2, 1, 8, 5, 4),
+        RING_INSTANCE(64, 1, 4, 4, 4, 4), RING_INSTANCE(64, 1, 2, 4, 4, 4), RING_INSTANCE(64, 1, 1, 4, 4, 4),
+        RING_INSTANCE(128, 1, 4, 8, 8, 8), RING_INSTANCE(128, 1, 1, 8, 8, 8), RING_INSTANCE(128, 1, 4, 4, 4, 4),
+        RING_INSTANCE(128, 1, 1, 4, 4, 4), RING_INSTANCE(128, 1, 2, 4, 4, 4),
     };
     *count = (int)(sizeof(table) / sizeof(table[0]));
     return table;

@@ -26,7 +26,9 @@ def test_rule_on_the_host():
     assert "keysplit" in name(_args(num_seqs=1, total_q=256, max_q_len=256, max_kv_len=256))
     assert "ring" in name(_args(num_seqs=1, total_q=257, max_q_len=257, max_kv_len=257))
     many = dict(num_seqs=8, total_q=512, max_q_len=64, block_table_stride=1024)  # 512 workgroups
-    assert "keysplit" in name(_paged(max_kv_len=2049, **many)) and "ring" in name(_paged(max_kv_len=2048, **many))
+    assert "keysplit" in name(_paged(max_kv_len=1537, **many)) and "ring" in name(_paged(max_kv_len=1536, **many))
+    small = dict(many, head_dim=64)
+    assert name(_paged(max_kv_len=1025, **small)) == "prefill_bf16_keysplit d64 w8" and "ring d64" in name(_paged(max_kv_len=1024, **small))
     assert "ring" in name(_paged(max_kv_len=9000, **dict(many, max_q_len=65)))
     # head groups that are no power of two split into the largest power of two that divides them
     assert "keysplit" in name(_paged(max_kv_len=8000, num_q_heads=24, **turn))
