@@ -663,9 +663,68 @@ __device__ __forceinline__ void merge_head(const float *r, int parts, int64_t st
     *(exC *)o = w;
 }
 
+// The same merge for sequences of few parts, BLK at a time: every lane fetches all (m, l) pairs of a block itself
+// (one address for the whole half, a broadcast), so there is no cross-lane step, and registers for BLK
+// partial outputs instead of 32 leave room for four to eight wavefronts per SIMD.  Index and weight are
+// clamped, not branched on, so that all loads of a block are in flight together.
+template <int HD, int BLK>
+__device__ __forceinline__ void merge_head_few(const float *r, int parts, int64_t stride, int lane, elem_t *o)
+{
+    constexpr int CPL = HD / 32;
+    const int sub = lane & 31;
+    float acc[CPL];
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
+    float M = -INFINITY, L = 0.f;
+    for (int b0 = 0; b0 < parts; b0 += BLK) {
+        float2 ml[BLK], d[BLK][CPL / 2];
+#pragma unroll
+        for (int j = 0; j < BLK; ++j) {
+            const float *rj = r + (int64_t)(b0 + j < parts ? b0 + j : parts - 1) * stride;
+            ml[j] = *(const float2 *)(rj + HD);
+#pragma unroll
+            for (int c = 0; c < CPL / 2; ++c) d[j][c] = *(const float2 *)(rj + CPL * sub + 2 * c);
+        }
+        float m_new = M;
+#pragma unroll
+        for (int j = 0; j < BLK; ++j) {
+            if (b0 + j >= parts) ml[j].x = -INFINITY;
+            m_new = fmaxf(m_new, ml[j].x);
+        }
+        if (m_new == -INFINITY) continue;  // nothing but empty parts so far (uniform over the half)
+        const float keep = fast_exp2(M - m_new);  // 0 for the first block
+        M = m_new;
+        L *= keep;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) acc[c] *= keep;
+#pragma unroll
+        for (int j = 0; j < BLK; ++j) {
+            const float w = fast_exp2(ml[j].x - m_new);  // 0 past the last part and for empty parts
+            L += ml[j].y * w;
+#pragma unroll
+            for (int c = 0; c < CPL / 2; ++c) {
+                acc[2 * c] += d[j][c].x * w;
+                acc[2 * c + 1] += d[j][c].y * w;
+            }
+        }
+    }
+    const float inv = L > 0.f ? 1.f / L : 0.f;
+    typedef elem_t exC __attribute__((ext_vector_type(CPL)));
+    exC w;
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) w[c] = (elem_t)(acc[c] * inv);
+    *(exC *)o = w;
+}
+
+// How many parts a merge kernel takes per round trip, from the number it expects of a sequence (any number is
+// merged correctly).  Kernel times before (32 for all, 252 registers) and now: 200 contexts of 20-800 keys, two or three
+// parts each, 12.1 -> 4.7 us; 64 contexts of 512-4096, five parts, 6.3 -> 4.7 us; one context of 1900, eight parts,
+// 4.2 -> 2.9 us.  From nine parts on one round trip of 32 is kept (16 contexts, 17 parts: 6.8 us).
+inline int merge_block(int64_t parts) { return parts <= 4 ? 4 : parts <= 8 ? 8 : 32; }
+
 // One wavefront merges query heads 2*pair and 2*pair + 1 of the G heads of (sequence s, KV head kvh).
 // rec = record of part 0 at this KV head's first query head; head_stride / part_stride in floats.
-template <int HD>
+template <int HD, int BLK>
 __device__ __forceinline__ void merge_pair(const KParams &p, int lane, int s, int kvh, int pair, const float *rec, int parts,
                                            int64_t head_stride, int64_t part_stride)
 {
@@ -673,7 +732,10 @@ __device__ __forceinline__ void merge_pair(const KParams &p, int lane, int s, in
     const int hl = 2 * pair + (lane >> 5);
     const int hc = hl < G ? hl : G - 1;  // an idle half repeats the last head (same values, same address)
     elem_t *o = (elem_t *)p.out + (int64_t)s * p.o_stride_tok + (int64_t)(kvh * G + hc) * p.o_stride_head + (HD / 32) * (lane & 31);
-    merge_head<HD>(rec + (int64_t)hc * head_stride, parts, part_stride, lane, o);
+    if (BLK < 32)
+        merge_head_few<HD, BLK>(rec + (int64_t)hc * head_stride, parts, part_stride, lane, o);
+    else
+        merge_head<HD>(rec + (int64_t)hc * head_stride, parts, part_stride, lane, o);
 }
 
 // Where a workgroup's run of chunks starts, for the token-balanced kernels: the batch's 32-key chunks
@@ -816,7 +878,7 @@ __global__ __launch_bounds__(WAVES * 64, 8 / WAVES) void decode_balanced_kernel(
 // chunk range, at record indices workgroup + s.  One wavefront per (sequence, KV head, pair of query heads).
 constexpr int kMergeWaves = 4;  // (sequence, KV head, head pair) units per merge workgroup
 
-template <int HD>
+template <int HD, int BLK>
 __global__ __launch_bounds__(64 * kMergeWaves) void decode_balanced_combine_kernel(const KParams p)
 {
     const int pairs = (p.group + 1) / 2;
@@ -836,12 +898,12 @@ __global__ __launch_bounds__(64 * kMergeWaves) void decode_balanced_combine_kern
     const int parts = c1 > c0 ? run_of(total, num_wgs, c1 - 1) - w0 + 1 : 0;
     if (parts == 1) return;  // the main kernel wrote this sequence itself
     const int64_t stride = (int64_t)p.num_q_heads * (HD + 2);
-    merge_pair<HD>(p, lane, s, kvh, pair, p.workspace + (int64_t)(w0 + s) * stride + (int64_t)kvh * p.group * (HD + 2), parts, HD + 2, stride);
+    merge_pair<HD, BLK>(p, lane, s, kvh, pair, p.workspace + (int64_t)(w0 + s) * stride + (int64_t)kvh * p.group * (HD + 2), parts, HD + 2, stride);
 }
 
 // Combine for the fixed-split kernels, one wavefront per (sequence, KV head, pair of query heads): records are laid out
 // [sequence][head][part].  Parts that hold no key were never written and are not read.
-template <int HD>
+template <int HD, int BLK>
 __global__ __launch_bounds__(64 * kMergeWaves) void decode_combine_kernel(const KParams p)
 {
     const int pairs = (p.group + 1) / 2;
@@ -856,7 +918,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void decode_combine_kernel(const 
     int parts = (n_kv + p.split_len - 1) / p.split_len;
     parts = parts < 1 ? 1 : parts;  // part 0 is always written (m = -inf, l = 0 for an empty context)
     const int64_t head_stride = (int64_t)p.num_splits * (HD + 2);
-    merge_pair<HD>(p, lane, s, kvh, pair, p.workspace + ((int64_t)s * p.num_q_heads + (int64_t)kvh * p.group) * head_stride, parts,
+    merge_pair<HD, BLK>(p, lane, s, kvh, pair, p.workspace + ((int64_t)s * p.num_q_heads + (int64_t)kvh * p.group) * head_stride, parts,
                           head_stride, HD + 2);
 }
 
@@ -901,9 +963,39 @@ hipError_t decode_balanced_launch(const KParams &p, hipStream_t stream)
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t units = (int64_t)p.num_seqs * p.num_kv_heads * ((p.group + 1) / 2);
-    hipLaunchKernelGGL(decode_balanced_combine_kernel<HD>, dim3((unsigned)((units + kMergeWaves - 1) / kMergeWaves)), dim3(64 * kMergeWaves), 0,
-                       stream, p);
+    const dim3 grid((unsigned)((units + kMergeWaves - 1) / kMergeWaves)), block(64 * kMergeWaves);
+    // num_splits runs over num_seqs sequences: a sequence is cut at about as many places as its share of the runs
+    const int blk = merge_block((p.num_splits + p.num_seqs - 1) / p.num_seqs + 1);
+    if (blk == 4)
+        hipLaunchKernelGGL((decode_balanced_combine_kernel<HD, 4>), grid, block, 0, stream, p);
+    else if (blk == 8)
+        hipLaunchKernelGGL((decode_balanced_combine_kernel<HD, 8>), grid, block, 0, stream, p);
+    else
+        hipLaunchKernelGGL((decode_balanced_combine_kernel<HD, 32>), grid, block, 0, stream, p);
     return hipGetLastError();
+}
+
+template <int HD>
+hipError_t combine_launch_hd(const KParams &p, hipStream_t stream, unsigned blocks)
+{
+    const dim3 grid(blocks), block(64 * kMergeWaves);
+    switch (merge_block(p.num_splits)) {
+        case 4: hipLaunchKernelGGL((decode_combine_kernel<HD, 4>), grid, block, 0, stream, p); break;
+        case 8: hipLaunchKernelGGL((decode_combine_kernel<HD, 8>), grid, block, 0, stream, p); break;
+        default: hipLaunchKernelGGL((decode_combine_kernel<HD, 32>), grid, block, 0, stream, p); break;
+    }
+    return hipGetLastError();
+}
+
+// The merge behind the fixed-split kernels.
+hipError_t combine_launch(const KParams &p, hipStream_t stream)
+{
+    const int64_t blocks = ((int64_t)p.num_seqs * p.num_kv_heads * ((p.group + 1) / 2) + kMergeWaves - 1) / kMergeWaves;
+    if (blocks <= 0) return hipSuccess;
+    if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
+    if (p.head_dim == 128) return combine_launch_hd<128>(p, stream, (unsigned)blocks);
+    if (p.head_dim == 64) return combine_launch_hd<64>(p, stream, (unsigned)blocks);
+    return hipErrorInvalidValue;
 }
 
 // SPLIT < 0 marks the token-balanced variant with -SPLIT workgroups per compute unit
@@ -927,19 +1019,7 @@ hipError_t decode_balanced_launch(const KParams &p, hipStream_t stream)
 }  // namespace
 
 #ifdef ATTN_DECODE_ELEM_F16
-hipError_t launch_decode_combine_f16(const KParams &p, hipStream_t stream)
-{
-    const int64_t blocks = ((int64_t)p.num_seqs * p.num_kv_heads * ((p.group + 1) / 2) + kMergeWaves - 1) / kMergeWaves;
-    if (blocks <= 0) return hipSuccess;
-    if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
-    if (p.head_dim == 128)
-        hipLaunchKernelGGL(decode_combine_kernel<128>, dim3((unsigned)blocks), dim3(64 * kMergeWaves), 0, stream, p);
-    else if (p.head_dim == 64)
-        hipLaunchKernelGGL(decode_combine_kernel<64>, dim3((unsigned)blocks), dim3(64 * kMergeWaves), 0, stream, p);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
-}
+hipError_t launch_decode_combine_f16(const KParams &p, hipStream_t stream) { return combine_launch(p, stream); }
 
 const Instance *decode_f16_instances(int *count)
 {
@@ -955,19 +1035,7 @@ const Instance *decode_f16_instances(int *count)
 }
 
 #else
-hipError_t launch_decode_combine(const KParams &p, hipStream_t stream)
-{
-    const int64_t blocks = ((int64_t)p.num_seqs * p.num_kv_heads * ((p.group + 1) / 2) + kMergeWaves - 1) / kMergeWaves;
-    if (blocks <= 0) return hipSuccess;
-    if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
-    if (p.head_dim == 128)
-        hipLaunchKernelGGL(decode_combine_kernel<128>, dim3((unsigned)blocks), dim3(64 * kMergeWaves), 0, stream, p);
-    else if (p.head_dim == 64)
-        hipLaunchKernelGGL(decode_combine_kernel<64>, dim3((unsigned)blocks), dim3(64 * kMergeWaves), 0, stream, p);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
-}
+hipError_t launch_decode_combine(const KParams &p, hipStream_t stream) { return combine_launch(p, stream); }
 
 const Instance *decode_instances(int *count)
 {
