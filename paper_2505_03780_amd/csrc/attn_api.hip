@@ -45,6 +45,10 @@ std::string build_id();
 // kMaxPartsPerSeq parts, and a batch into at most two parts per compute unit in all (more parts add
 // workspace traffic and merge work, never parallelism: every part already is Hkv workgroups).
 constexpr int kMaxPartsPerSeq = 64;
+// The record array of attn_decode_paged_static.
+constexpr size_t kScratchBytes = (size_t)16 << 20;
+// Instance::stages of the decode kernels that keep two register sets in flight (one wavefront per head)
+constexpr int kStagesPerHead = 3;
 
 std::mutex g_mu;
 std::unordered_map<std::string, int> g_winner[2];  // [is_decode]: bucket key -> instance id
@@ -230,6 +234,8 @@ void apply_split(KParams &p, const Instance &inst)
     }
 }
 
+size_t instance_workspace_bytes(const Instance &inst, const KParams &p_in);
+
 // ---- built-in heuristic (used until a bucket has been tuned) -----------------------------------
 int find_instance(int is_decode, const KParams &p, int waves, int hpw, int bn, int bm, int split_len, int variant = 0, int stages = 0)
 {
@@ -293,39 +299,71 @@ int heuristic(const KParams &p, int is_decode)
         if (id < 0) id = find_instance(0, p, 4, hpw, 32, 256, 0, order);
         if (id < 0) id = find_instance(0, p, 4, hpw, 64, 64 * 4, 0);  // register-staged kernel
     } else {
-        // With four or more KV heads and enough keys to give every compute unit a long run, a workgroup
-        // owns whole cache blocks (one wavefront per head): the token-balanced kernel, one workgroup
-        // per compute unit.  Small batches of short contexts start and finish faster with one KV head
-        // per workgroup and fixed parts: enough workgroups to fill the chip several times over, parts
-        // no shorter than 256 keys.
-        const int64_t key_bound = (int64_t)p.num_seqs * p.max_kv_len;
-        if (p.num_kv_heads >= 4 && key_bound >= 100000) {
+        // Lines from two sweeps of about 1600 random shapes each (batch 1-256, longest context 16-32768 keys, 2-16 KV
+        // heads of 1-8 query heads, bf16 and fp16, D = 64 and 128), every instance timed in a graph; against the
+        // fastest instance of its shape the choice takes 1.03x on average and 1.14x at the 95th percentile (the
+        // rule before, batch x keys alone, 1.08x and 1.36x).  units = workgroups of the kernels that take one KV head
+        // each; kv = longest context.
+        const int64_t units = (int64_t)p.num_seqs * p.num_kv_heads, kv = p.max_kv_len;
+        // Enough keys to give every compute unit a long run: a workgroup owns whole cache blocks (one
+        // wavefront per head), the token-balanced kernel (with four KV heads or more; fewer leave its wavefronts
+        // idle).  In between, from 500 000 keys over all heads on (64 units: 8000 keys, 512 units: 1000 keys)
+        // it is level with the split kernels or up to 1.2x ahead; a few sequences of more than 8192 keys do
+        // better with long parts (3 contexts of 24000 keys 1.2x).
+        // Here and below a choice that the fixed splits made before does not go to an instance whose records
+        // exceed the array of attn_decode_paged_static, which would then refuse the call.
+        auto fits_static = [&](int i) { return i >= 0 && instance_workspace_bytes(t[i], p) <= kScratchBytes ? i : -1; };
+        const bool very_long_runs = (int64_t)p.num_seqs * kv >= 100000;
+        if (p.num_kv_heads >= 4 && (very_long_runs || (kv > 512 && kv <= 8192 && units * kv >= 500000))) {
             // two workgroups of four heads per compute unit measured 0.5-2 % ahead of one of eight from
             // eight KV heads on, 1-2 % behind at four
             if (p.num_kv_heads >= 8) id = find_instance(1, p, 4, 16, 32, 0, -1);
             if (id < 0) id = find_instance(1, p, 8, 16, 32, 0, -1);
+            if (!very_long_runs) id = fits_static(id);
         }
+        // Many short contexts: whole contexts, one wavefront per head, so that a workgroup reads whole cache
+        // blocks and has no cross-wave reduction (1.1-1.5x at 1024 units or below 64 keys).
+        if (id < 0 && p.num_kv_heads >= 4 && ((units >= 1024 && kv <= 512) || (units >= 512 && kv <= 64)))
+            id = find_instance(1, p, 4, 16, 32, 0, 512, 0, kStagesPerHead);
+        // Short contexts are not split: the merge and its launch cost more than the walk (one context of 200 keys
+        // 6.7 -> 5.7 us, 40 of 100-400 17.2 -> 14.3 us).  Where there are units enough to hide one another's
+        // latency that holds up to 1024 keys.  Eight wavefronts per workgroup above 128 keys, four where there is
+        // a unit for every compute unit.
+        if (id < 0 && kv <= (units >= 128 ? 1024 : p.head_dim == 64 ? 896 : 640))
+            id = find_instance(1, p, kv > 128 && (units < 256 || kv > 512) ? 8 : 4, 16, 32, 0, 0);
         if (id < 0) {
-            const int64_t units = (int64_t)p.num_seqs * p.num_kv_heads;
-            int64_t want = units * (int64_t)p.max_kv_len / 2048;
+            // one KV head per workgroup and fixed parts: enough workgroups to fill the chip several times over,
+            // parts no shorter than 256 keys
+            int64_t want = units * kv / 2048;
             int sl = 256;
             while (sl * 2 <= want && sl < 4096) sl *= 2;
-            if (sl >= p.max_kv_len) sl = 0;
-            // the merge takes 32 parts per round trip: a long context in few units gets longer parts and
-            // eight waves per workgroup rather than more parts
+            if (sl >= kv) sl = 0;
+            // a long context in few units gets longer parts and eight waves per workgroup rather than more
+            // than 32 parts
             bool wide = false;
-            while (sl > 0 && sl < 4096 && (p.max_kv_len + sl - 1) / sl > 32) {
+            auto parts = [&]() { return (kv + sl - 1) / sl; };
+            while (sl > 0 && sl < 4096 && parts() > 32) {
                 sl *= 2;
                 wide = true;
             }
-            // and the batch at most two parts per compute unit in all (the bound `usable` enforces)
-            while (sl > 0 && sl < 4096 && (int64_t)p.num_seqs * ((p.max_kv_len + sl - 1) / sl) > 2 * compute_units()) sl *= 2;
-            if (sl >= p.max_kv_len || (sl > 0 && (int64_t)p.num_seqs * ((p.max_kv_len + sl - 1) / sl) > 2 * compute_units())) sl = 0;
-            if (wide) id = find_instance(1, p, 8, 16, 32, 0, sl);
+            // and the batch at most two parts per compute unit in all (the bound `usable` enforces); where fp16 and
+            // D = 64 were not split before they also stay within the static record array
+            const bool bounded = p.dtype == kDtypeF16 || p.head_dim == 64;
+            auto too_many = [&]() {
+                return p.num_seqs * parts() > 2 * compute_units() ||
+                       (bounded && p.num_seqs * parts() * p.num_q_heads * partial_stride(p.head_dim) * (int64_t)sizeof(float) > (int64_t)kScratchBytes);
+            };
+            while (sl > 0 && sl < 4096 && too_many()) sl *= 2;
+            if (sl >= kv || (sl > 0 && too_many())) sl = 0;
+            // many long contexts of one or two KV heads, too many to split: still better than a serial walk of
+            // each (142 contexts of 2000-15000 keys, 8/2 heads, D = 64: 1.8x)
+            if (sl == 0 && kv > 2048) {
+                id = fits_static(find_instance(1, p, 4, 16, 32, 0, -2));
+                if (id < 0) id = fits_static(find_instance(1, p, 8, 16, 32, 0, -1));
+            }
+            if (id < 0 && wide) id = find_instance(1, p, 8, 16, 32, 0, sl);
             if (id < 0) id = find_instance(1, p, 4, 16, 32, 0, sl);
             if (id < 0) id = find_instance(1, p, 4, 16, 32, 0, 0);
-            if (id < 0) id = find_instance(1, p, 8, 16, 32, 0, sl);  // fp16 has the wave-per-head family only
-            if (id < 0) id = find_instance(1, p, 8, 16, 32, 0, 0);
         }
     }
     if (id >= 0) return id;
@@ -1084,7 +1122,6 @@ using namespace attn;
 // Split-K records of attn_decode_paged_static live in this array instead of a caller workspace.  Every
 // GPU the library runs on holds its own copy, at its own address, until the process ends.  In host
 // code the name `scratch` is only a handle for hipGetSymbolAddress, never a device address.
-constexpr size_t kScratchBytes = (size_t)16 << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {

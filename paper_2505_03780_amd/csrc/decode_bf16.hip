@@ -1006,7 +1006,7 @@ hipError_t combine_launch(const KParams &p, hipStream_t stream)
     }
 #define DECODE_SEQ_INSTANCE(HD, WAVES, SPLIT)                                                                  \
     {                                                                                                          \
-        DECODE_NAME "_seq d" #HD " w" #WAVES " split" #SPLIT, 16, kChunk, WAVES, 16, 2, SPLIT, decode_valid<HD, WAVES>, \
+        DECODE_NAME "_seq d" #HD " w" #WAVES " split" #SPLIT, 16, kChunk, WAVES, 16, 3, SPLIT, decode_valid<HD, WAVES>, \
             decode_seq_launch<HD, WAVES>                                                                       \
     }
 
@@ -1024,6 +1024,14 @@ hipError_t launch_decode_combine_f16(const KParams &p, hipStream_t stream) { ret
 const Instance *decode_f16_instances(int *count)
 {
     static const Instance table[] = {
+        DECODE_INSTANCE(128, 4, 0),    DECODE_INSTANCE(128, 4, 256),  DECODE_INSTANCE(128, 4, 512),
+        DECODE_INSTANCE(128, 4, 1024), DECODE_INSTANCE(128, 4, 2048), DECODE_INSTANCE(128, 4, 4096),
+        DECODE_INSTANCE(128, 8, 0),    DECODE_INSTANCE(128, 8, 512),  DECODE_INSTANCE(128, 8, 1024),
+        DECODE_INSTANCE(128, 8, 2048), DECODE_INSTANCE(128, 8, 4096), DECODE_INSTANCE(64, 4, 0),
+        DECODE_INSTANCE(64, 4, 256),   DECODE_INSTANCE(64, 4, 512),   DECODE_INSTANCE(64, 4, 1024),
+        DECODE_INSTANCE(64, 4, 2048),  DECODE_INSTANCE(64, 4, 4096),  DECODE_INSTANCE(64, 8, 0),
+        DECODE_INSTANCE(64, 8, 512),   DECODE_INSTANCE(64, 8, 1024),  DECODE_INSTANCE(64, 8, 2048),
+        DECODE_INSTANCE(64, 8, 4096),
         DECODE_SEQ_INSTANCE(128, 8, 0),    DECODE_SEQ_INSTANCE(128, 8, 256),  DECODE_SEQ_INSTANCE(128, 8, 512),
         DECODE_SEQ_INSTANCE(128, 8, 1024), DECODE_SEQ_INSTANCE(128, 8, 2048), DECODE_SEQ_INSTANCE(128, 4, 256),
         DECODE_SEQ_INSTANCE(128, 4, 512),  DECODE_SEQ_INSTANCE(128, 4, 1024), DECODE_SEQ_INSTANCE(64, 8, 256),
@@ -1045,7 +1053,10 @@ const Instance *decode_instances(int *count)
         DECODE_INSTANCE(128, 8, 0),    DECODE_INSTANCE(128, 8, 512),  DECODE_INSTANCE(128, 8, 1024),
         DECODE_INSTANCE(128, 8, 2048), DECODE_INSTANCE(128, 8, 4096), DECODE_INSTANCE(128, 2, 256),
         DECODE_INSTANCE(128, 2, 512),  DECODE_INSTANCE(128, 2, 1024), DECODE_INSTANCE(64, 4, 0),
-        DECODE_INSTANCE(64, 4, 512),   DECODE_INSTANCE(64, 4, 2048),
+        DECODE_INSTANCE(64, 4, 256),   DECODE_INSTANCE(64, 4, 512),   DECODE_INSTANCE(64, 4, 1024),
+        DECODE_INSTANCE(64, 4, 2048),  DECODE_INSTANCE(64, 4, 4096),  DECODE_INSTANCE(64, 8, 0),
+        DECODE_INSTANCE(64, 8, 512),   DECODE_INSTANCE(64, 8, 1024),  DECODE_INSTANCE(64, 8, 2048),
+        DECODE_INSTANCE(64, 8, 4096),
         DECODE_SEQ_INSTANCE(128, 8, 0),    DECODE_SEQ_INSTANCE(128, 8, 128),  DECODE_SEQ_INSTANCE(128, 8, 256),
         DECODE_SEQ_INSTANCE(128, 8, 512),  DECODE_SEQ_INSTANCE(128, 8, 1024), DECODE_SEQ_INSTANCE(128, 8, 2048),
         DECODE_SEQ_INSTANCE(128, 4, 256),  DECODE_SEQ_INSTANCE(128, 4, 512),  DECODE_SEQ_INSTANCE(128, 4, 1024),
