@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import Optional
 
 ATTN_F32, ATTN_BF16, ATTN_F16 = 0, 1, 2
@@ -15,6 +16,7 @@ ATTN_F32, ATTN_BF16, ATTN_F16 = 0, 1, 2
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libattn_gfx950.so")
 _lib = None
+_hot = {}  # entry point name -> the same function taking the packed argument struct
 
 
 class AttnError(RuntimeError):
@@ -117,6 +119,14 @@ def load_library():
     lib.rmsnorm_selected_instance.argtypes = [R]
     lib.rmsnorm_force_instance.restype = None
     lib.rmsnorm_force_instance.argtypes = [ctypes.c_int]
+    # The calls with tensors hand the argument struct over as packed bytes: one struct.pack instead of thirty
+    # ctypes field stores (with the checks in one condition and the raw stream handle, a call whose kernel is shorter than its host time takes
+    # 5.0-6.6 us instead of 8.3-10.9).
+    for name in ("attn_prefill_varlen", "attn_decode_paged", "attn_decode_paged_static", "attn_kv_cache_write", "rmsnorm_fused_add"):
+        f = lib[name]  # (a function object of its own: the attribute of that name keeps its argument types)
+        f.restype = ctypes.c_int
+        f.argtypes = [ctypes.c_char_p, ctypes.c_void_p]
+        _hot[name] = f
     _lib = lib
     return lib
 
@@ -167,86 +177,123 @@ def attn_status_string(status: int) -> str:
     return load_library().attn_status_string(int(status)).decode()
 
 
+_codes = None
+
+
+def _dtype_codes():
+    """torch dtype -> attn_dtype (torch is imported by the first call that sees a tensor)."""
+    global _codes, _int32, _raw_stream, _current_stream, _current_device
+    if _codes is None:
+        import torch
+
+        _int32 = torch.int32
+        _current_stream, _current_device = torch.cuda.current_stream, torch.cuda.current_device
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # (current_stream() builds a Python object)
+        _codes = {torch.bfloat16: ATTN_BF16, torch.float32: ATTN_F32, torch.float16: ATTN_F16}
+    return _codes
+
+
 def _dtype_code(t) -> int:
-    import torch
-
-    if t.dtype == torch.bfloat16:
-        return ATTN_BF16
-    if t.dtype == torch.float32:
-        return ATTN_F32
-    if t.dtype == torch.float16:
-        return ATTN_F16
-    raise TypeError("tensors must be bfloat16, float16 or float32")
+    code = _dtype_codes().get(t.dtype)
+    if code is None:
+        raise TypeError("tensors must be bfloat16, float16 or float32")
+    return code
 
 
-def _ptr(t) -> Optional[int]:
-    return None if t is None else int(t.data_ptr())
+def _refuse_attn(q, k, v, out, seq_lens, query_start_loc, kv_start_loc, block_table):
+    """Raises for the first check of an attention call that fails."""
+    for name, t in (("q", q), ("k", k), ("v", v), ("out", out)):
+        if t.stride(-1) != 1:
+            raise ValueError("%s: head_dim must be contiguous" % name)
+    for name, t in (("seq_lens", seq_lens), ("query_start_loc", query_start_loc), ("kv_start_loc", kv_start_loc),
+                    ("block_table", block_table)):
+        if t is not None and (t.dtype != _int32 or not t.is_contiguous()):
+            raise TypeError("%s must be a contiguous int32 tensor" % name)
+    if k.dtype != q.dtype or v.dtype != q.dtype or out.dtype != q.dtype:
+        raise TypeError("q, k, v, out must share a dtype")
+    if k.stride() != v.stride() or k.shape != v.shape:
+        raise ValueError("k and v must have the same shape and strides")
+    _dtype_code(q)
+
+
+def _attn_fields(q, k, v, out, seq_lens, scale, max_q_len, max_kv_len, query_start_loc, kv_start_loc, block_table, causal, workspace):
+    """The checked field values of an AttnArgs, in order (null pointers as 0)."""
+    codes = _codes or _dtype_codes()
+    qs, ks, os_ = q.stride(), k.stride(), out.stride()
+    dtype, qshape, kshape = q.dtype, q.shape, k.shape
+    code = codes.get(dtype)
+    # (one condition over all checks: the loops that name the culprit only run for a call that is wrong)
+    if (qs[-1] != 1 or ks[-1] != 1 or os_[-1] != 1 or v.stride() != ks or v.shape != kshape or code is None
+            or k.dtype != dtype or v.dtype != dtype or out.dtype != dtype
+            or seq_lens.dtype != _int32 or not seq_lens.is_contiguous()
+            or (query_start_loc is not None and (query_start_loc.dtype != _int32 or not query_start_loc.is_contiguous()))
+            or (kv_start_loc is not None and (kv_start_loc.dtype != _int32 or not kv_start_loc.is_contiguous()))
+            or (block_table is not None and (block_table.dtype != _int32 or not block_table.is_contiguous()))):
+        _refuse_attn(q, k, v, out, seq_lens, query_start_loc, kv_start_loc, block_table)
+    if block_table is not None:
+        if len(kshape) != 4:
+            raise ValueError("paged k/v must be [num_blocks, block_size, Hkv, D]")
+        num_blocks, block_size, hkv, _ = kshape
+        kv_block, kv_tok, kv_head, _ = ks
+        table, table_stride = block_table.data_ptr(), block_table.stride(0)
+    else:
+        if len(kshape) != 3:
+            raise ValueError("contiguous k/v must be [total_kv, Hkv, D]")
+        hkv = kshape[1]
+        kv_block, kv_tok, kv_head = 0, ks[0], ks[1]
+        table = table_stride = block_size = num_blocks = 0
+    if workspace is None:
+        ws = ws_bytes = 0
+    else:
+        ws, ws_bytes = workspace.data_ptr(), workspace.nbytes
+    return (_ATTN_BYTES, code, seq_lens.shape[0], qshape[1], hkv, qshape[2], qshape[0], int(max_q_len), int(max_kv_len),
+            q.data_ptr(), qs[0], qs[1], out.data_ptr(), os_[0], os_[1], k.data_ptr(), v.data_ptr(), kv_block, kv_tok, kv_head,
+            table, table_stride, block_size, num_blocks,
+            0 if query_start_loc is None else query_start_loc.data_ptr(), 0 if kv_start_loc is None else kv_start_loc.data_ptr(),
+            seq_lens.data_ptr(), float(scale), 1 if causal else 0, ws, ws_bytes)
+
+
+_ATTN_BYTES = ctypes.sizeof(AttnArgs)
+_pack_attn = struct.Struct("@I8iPqqPqqPPqqqPiiiPPPfiPQ").pack
+_pack_kv_write = struct.Struct("@I7iPPqqPPqqqP").pack
+_pack_rmsnorm = struct.Struct("@IiiiPqPqPPqf4x").pack
+
+
+def _packed(pack, cls, fields) -> bytes:
+    try:
+        return pack(*fields)
+    except (struct.error, OverflowError):  # a value that does not fit its field: ctypes' conversion decides
+        return bytes(cls(*fields))
 
 
 def make_args(q, k, v, out, seq_lens, scale, *, max_q_len, max_kv_len, query_start_loc=None, kv_start_loc=None,
               block_table=None, causal=True, workspace=None, is_decode=False) -> AttnArgs:
     """Fill an AttnArgs from device tensors.  q/out: [total_q, Hq, D]; k/v: [total_kv, Hkv, D] or,
     with block_table, [num_blocks, block_size, Hkv, D].  Only strides and pointers are read."""
-    import torch
-
-    for name, t in (("q", q), ("k", k), ("v", v), ("out", out)):
-        if t.stride(-1) != 1:
-            raise ValueError("%s: head_dim must be contiguous" % name)
-    for name, t in (("seq_lens", seq_lens), ("query_start_loc", query_start_loc), ("kv_start_loc", kv_start_loc),
-                    ("block_table", block_table)):
-        if t is not None and (t.dtype != torch.int32 or not t.is_contiguous()):
-            raise TypeError("%s must be a contiguous int32 tensor" % name)
-    if k.dtype != q.dtype or v.dtype != q.dtype or out.dtype != q.dtype:
-        raise TypeError("q, k, v, out must share a dtype")
-    if k.stride() != v.stride() or k.shape != v.shape:
-        raise ValueError("k and v must have the same shape and strides")
-    a = AttnArgs()
-    a.struct_bytes = ctypes.sizeof(AttnArgs)
-    a.dtype = _dtype_code(q)
-    a.num_seqs = int(seq_lens.shape[0])
-    a.num_q_heads, a.head_dim = int(q.shape[1]), int(q.shape[2])
-    a.num_kv_heads = int(k.shape[-2])
-    a.total_q = int(q.shape[0])
-    a.max_q_len, a.max_kv_len = int(max_q_len), int(max_kv_len)
-    a.q, a.q_stride_tok, a.q_stride_head = _ptr(q), q.stride(0), q.stride(1)
-    a.out, a.o_stride_tok, a.o_stride_head = _ptr(out), out.stride(0), out.stride(1)
-    a.k, a.v = _ptr(k), _ptr(v)
-    if block_table is not None:
-        if k.dim() != 4:
-            raise ValueError("paged k/v must be [num_blocks, block_size, Hkv, D]")
-        a.kv_stride_block, a.kv_stride_tok, a.kv_stride_head = k.stride(0), k.stride(1), k.stride(2)
-        a.block_table = _ptr(block_table)
-        a.block_table_stride = int(block_table.stride(0))
-        a.block_size, a.num_blocks = int(k.shape[1]), int(k.shape[0])
-    else:
-        if k.dim() != 3:
-            raise ValueError("contiguous k/v must be [total_kv, Hkv, D]")
-        a.kv_stride_block, a.kv_stride_tok, a.kv_stride_head = 0, k.stride(0), k.stride(1)
-        a.block_table, a.block_table_stride, a.block_size, a.num_blocks = None, 0, 0, 0
-    a.query_start_loc = _ptr(query_start_loc)
-    a.kv_start_loc = _ptr(kv_start_loc)
-    a.seq_lens = _ptr(seq_lens)
-    a.scale = float(scale)
-    a.causal = 1 if causal else 0
-    a.workspace = _ptr(workspace)
-    a.workspace_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    return a
+    return AttnArgs(*_attn_fields(q, k, v, out, seq_lens, scale, max_q_len, max_kv_len, query_start_loc, kv_start_loc, block_table,
+                                  causal, workspace))
 
 
 def _stream_ptr(stream) -> int:
-    import torch
-
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return int(stream.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    if _codes is None:
+        _dtype_codes()
+    if _raw_stream is None:
+        return int(_current_stream().cuda_stream)
+    return _raw_stream(_current_device())
 
 
 def attn_prefill_varlen(q, k, v, out, query_start_loc, seq_lens, scale, *, max_q_len, max_kv_len, causal=True,
                         block_table=None, kv_start_loc=None, stream=None, args: Optional[AttnArgs] = None) -> None:
     """Enqueue causal variable-length (or chunked, over a paged prefix) prefill on ``stream``."""
-    a = args or make_args(q, k, v, out, seq_lens, scale, max_q_len=max_q_len, max_kv_len=max_kv_len,
-                          query_start_loc=query_start_loc, kv_start_loc=kv_start_loc, block_table=block_table, causal=causal)
-    rc = load_library().attn_prefill_varlen(ctypes.byref(a), _stream_ptr(stream))
+    lib = _lib or load_library()
+    if args:
+        rc = lib.attn_prefill_varlen(ctypes.byref(args), _stream_ptr(stream))
+    else:
+        a = _packed(_pack_attn, AttnArgs, _attn_fields(q, k, v, out, seq_lens, scale, max_q_len, max_kv_len, query_start_loc, kv_start_loc,
+                                                       block_table, causal, None))
+        rc = _hot["attn_prefill_varlen"](a, _stream_ptr(stream))
     if rc != 0:
         raise AttnError(rc, "attn_prefill_varlen")
 
@@ -254,9 +301,13 @@ def attn_prefill_varlen(q, k, v, out, query_start_loc, seq_lens, scale, *, max_q
 def attn_decode_paged(q, k_cache, v_cache, out, block_table, seq_lens, scale, *, max_kv_len, workspace=None, stream=None,
                       args: Optional[AttnArgs] = None) -> None:
     """Enqueue paged-KV decode (one query token per sequence) on ``stream``."""
-    a = args or make_args(q, k_cache, v_cache, out, seq_lens, scale, max_q_len=1, max_kv_len=max_kv_len,
-                          block_table=block_table, causal=True, workspace=workspace, is_decode=True)
-    rc = load_library().attn_decode_paged(ctypes.byref(a), _stream_ptr(stream))
+    lib = _lib or load_library()
+    if args:
+        rc = lib.attn_decode_paged(ctypes.byref(args), _stream_ptr(stream))
+    else:
+        a = _packed(_pack_attn, AttnArgs, _attn_fields(q, k_cache, v_cache, out, seq_lens, scale, 1, max_kv_len, None, None, block_table,
+                                                       True, workspace))
+        rc = _hot["attn_decode_paged"](a, _stream_ptr(stream))
     if rc != 0:
         raise AttnError(rc, "attn_decode_paged")
 
@@ -265,9 +316,13 @@ def attn_decode_paged_static(q, k_cache, v_cache, out, block_table, seq_lens, sc
                              args: Optional[AttnArgs] = None) -> None:
     """attn_decode_paged with the split-K records in the library's own static device array: no workspace
     argument, nothing allocated."""
-    a = args or make_args(q, k_cache, v_cache, out, seq_lens, scale, max_q_len=1, max_kv_len=max_kv_len,
-                          block_table=block_table, causal=True, is_decode=True)
-    rc = load_library().attn_decode_paged_static(ctypes.byref(a), _stream_ptr(stream))
+    lib = _lib or load_library()
+    if args:
+        rc = lib.attn_decode_paged_static(ctypes.byref(args), _stream_ptr(stream))
+    else:
+        a = _packed(_pack_attn, AttnArgs, _attn_fields(q, k_cache, v_cache, out, seq_lens, scale, 1, max_kv_len, None, None, block_table,
+                                                       True, None))
+        rc = _hot["attn_decode_paged_static"](a, _stream_ptr(stream))
     if rc != 0:
         raise AttnError(rc, "attn_decode_paged_static")
 
@@ -323,27 +378,37 @@ def attn_force_instance(is_decode: bool, idx: int) -> None:
 
 # ---- fused RMS layer norm (include/rmsnorm.h) ------------------------------------------------------
 
+def _rmsnorm_fields(x, weight, out, eps, residual):
+    """The checked field values of an RmsNormArgs, in order."""
+    codes = _codes or _dtype_codes()
+    xs, os_ = x.stride(), out.stride()
+    rs = None if residual is None else residual.stride()
+    for name, st in (("x", xs), ("out", os_), ("residual", rs), ("weight", weight.stride())):
+        if st is not None and st[-1] != 1:
+            raise ValueError("%s: the hidden dimension must be contiguous" % name)
+    code = codes.get(x.dtype)
+    if code is None:
+        raise TypeError("tensors must be bfloat16, float16 or float32")
+    tokens, hidden = x.shape[:2]
+    return (_RMSNORM_BYTES, code, tokens, hidden, x.data_ptr(), xs[0], 0 if residual is None else residual.data_ptr(),
+            0 if rs is None else rs[0], weight.data_ptr(), out.data_ptr(), os_[0], float(eps))
+
+
+_RMSNORM_BYTES = ctypes.sizeof(RmsNormArgs)
+
+
 def make_rmsnorm_args(x, weight, out, eps, residual=None) -> RmsNormArgs:
     """x, out, residual: [T, H] device tensors with a contiguous last dimension; weight: [H]."""
-    for name, t in (("x", x), ("out", out), ("residual", residual), ("weight", weight)):
-        if t is not None and t.stride(-1) != 1:
-            raise ValueError("%s: the hidden dimension must be contiguous" % name)
-    a = RmsNormArgs()
-    a.struct_bytes = ctypes.sizeof(RmsNormArgs)
-    a.dtype = _dtype_code(x)
-    a.num_tokens, a.hidden = int(x.shape[0]), int(x.shape[1])
-    a.x, a.x_stride = _ptr(x), x.stride(0)
-    a.residual, a.residual_stride = _ptr(residual), (0 if residual is None else residual.stride(0))
-    a.weight = _ptr(weight)
-    a.out, a.out_stride = _ptr(out), out.stride(0)
-    a.eps = float(eps)
-    return a
+    return RmsNormArgs(*_rmsnorm_fields(x, weight, out, eps, residual))
 
 
 def rmsnorm_fused_add(x, weight, out, eps, residual=None, stream=None, args: Optional[RmsNormArgs] = None) -> None:
     """Enqueue out = rmsnorm(x + residual) * weight and residual <- x + residual (residual optional)."""
-    a = args or make_rmsnorm_args(x, weight, out, eps, residual)
-    rc = load_library().rmsnorm_fused_add(ctypes.byref(a), _stream_ptr(stream))
+    lib = _lib or load_library()
+    if args:
+        rc = lib.rmsnorm_fused_add(ctypes.byref(args), _stream_ptr(stream))
+    else:
+        rc = _hot["rmsnorm_fused_add"](_packed(_pack_rmsnorm, RmsNormArgs, _rmsnorm_fields(x, weight, out, eps, residual)), _stream_ptr(stream))
     if rc != 0:
         raise AttnError(rc, "rmsnorm_fused_add")
 
@@ -377,33 +442,41 @@ def rmsnorm_force_instance(idx: int) -> None:
 
 # ---- KV-cache write ----------------------------------------------------------------------------------
 
+def _kv_write_fields(k_new, v_new, k_cache, v_cache, slot_mapping):
+    """The checked field values of a KvWriteArgs, in order."""
+    codes = _codes or _dtype_codes()
+    if slot_mapping.dtype != _int32 or not slot_mapping.is_contiguous():
+        raise TypeError("slot_mapping must be a contiguous int32 tensor")
+    kn, vn, kc, vc = k_new.stride(), v_new.stride(), k_cache.stride(), v_cache.stride()
+    for name, st in (("k_new", kn), ("v_new", vn), ("k_cache", kc), ("v_cache", vc)):
+        if st[-1] != 1:
+            raise ValueError("%s: head_dim must be contiguous" % name)
+    if kn != vn or kc != vc:
+        raise ValueError("K and V must share their strides")
+    code = codes.get(k_new.dtype)
+    if code is None:
+        raise TypeError("tensors must be bfloat16, float16 or float32")
+    tokens, hkv, d = k_new.shape[:3]
+    num_blocks, block_size = k_cache.shape[:2]
+    return (_KV_WRITE_BYTES, code, tokens, hkv, d, block_size, num_blocks, 0, k_new.data_ptr(), v_new.data_ptr(), kn[0], kn[1],
+            k_cache.data_ptr(), v_cache.data_ptr(), kc[0], kc[1], kc[2], slot_mapping.data_ptr())
+
+
+_KV_WRITE_BYTES = ctypes.sizeof(KvWriteArgs)
+
+
 def make_kv_write_args(k_new, v_new, k_cache, v_cache, slot_mapping) -> KvWriteArgs:
     """k_new, v_new: [T, Hkv, D]; caches: [num_blocks, block_size, Hkv, D]; slot_mapping: int32 [T]."""
-    import torch
-
-    if slot_mapping.dtype != torch.int32 or not slot_mapping.is_contiguous():
-        raise TypeError("slot_mapping must be a contiguous int32 tensor")
-    for name, t in (("k_new", k_new), ("v_new", v_new), ("k_cache", k_cache), ("v_cache", v_cache)):
-        if t.stride(-1) != 1:
-            raise ValueError("%s: head_dim must be contiguous" % name)
-    if k_new.stride() != v_new.stride() or k_cache.stride() != v_cache.stride():
-        raise ValueError("K and V must share their strides")
-    a = KvWriteArgs()
-    a.struct_bytes = ctypes.sizeof(KvWriteArgs)
-    a.dtype = _dtype_code(k_new)
-    a.num_tokens, a.num_kv_heads, a.head_dim = int(k_new.shape[0]), int(k_new.shape[1]), int(k_new.shape[2])
-    a.block_size, a.num_blocks = int(k_cache.shape[1]), int(k_cache.shape[0])
-    a.k_new, a.v_new = _ptr(k_new), _ptr(v_new)
-    a.new_stride_tok, a.new_stride_head = k_new.stride(0), k_new.stride(1)
-    a.k_cache, a.v_cache = _ptr(k_cache), _ptr(v_cache)
-    a.kv_stride_block, a.kv_stride_tok, a.kv_stride_head = k_cache.stride(0), k_cache.stride(1), k_cache.stride(2)
-    a.slot_mapping = _ptr(slot_mapping)
-    return a
+    return KvWriteArgs(*_kv_write_fields(k_new, v_new, k_cache, v_cache, slot_mapping))
 
 
 def attn_kv_cache_write(k_new, v_new, k_cache, v_cache, slot_mapping, stream=None, args: Optional[KvWriteArgs] = None) -> None:
     """Enqueue the scatter of new keys/values into the paged caches."""
-    a = args or make_kv_write_args(k_new, v_new, k_cache, v_cache, slot_mapping)
-    rc = load_library().attn_kv_cache_write(ctypes.byref(a), _stream_ptr(stream))
+    lib = _lib or load_library()
+    if args:
+        rc = lib.attn_kv_cache_write(ctypes.byref(args), _stream_ptr(stream))
+    else:
+        a = _packed(_pack_kv_write, KvWriteArgs, _kv_write_fields(k_new, v_new, k_cache, v_cache, slot_mapping))
+        rc = _hot["attn_kv_cache_write"](a, _stream_ptr(stream))
     if rc != 0:
         raise AttnError(rc, "attn_kv_cache_write")
