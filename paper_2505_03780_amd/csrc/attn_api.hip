@@ -361,6 +361,10 @@ int heuristic(const KParams &p, int is_decode)
                 id = fits_static(find_instance(1, p, 4, 16, 32, 0, -2));
                 if (id < 0) id = fits_static(find_instance(1, p, 8, 16, 32, 0, -1));
             }
+            // eight waves, one chunk each, also where every part has a compute unit to itself: one context of 1900
+            // keys 10.9 -> 10.0 us, 3 of 1900 10.6 -> 9.9; two workgroups per unit lose (8 of 1900: 15.8 -> 18.0), and
+            // from 4096 keys on the two are within 3 %
+            wide |= sl == 256 && kv < 4096 && units * parts() <= compute_units();
             if (id < 0 && wide) id = find_instance(1, p, 8, 16, 32, 0, sl);
             if (id < 0) id = find_instance(1, p, 4, 16, 32, 0, sl);
             if (id < 0) id = find_instance(1, p, 4, 16, 32, 0, 0);

@@ -1026,7 +1026,7 @@ const Instance *decode_f16_instances(int *count)
     static const Instance table[] = {
         DECODE_INSTANCE(128, 4, 0),    DECODE_INSTANCE(128, 4, 256),  DECODE_INSTANCE(128, 4, 512),
         DECODE_INSTANCE(128, 4, 1024), DECODE_INSTANCE(128, 4, 2048), DECODE_INSTANCE(128, 4, 4096),
-        DECODE_INSTANCE(128, 8, 0),    DECODE_INSTANCE(128, 8, 512),  DECODE_INSTANCE(128, 8, 1024),
+        DECODE_INSTANCE(128, 8, 256),  DECODE_INSTANCE(64, 8, 256),   DECODE_INSTANCE(128, 8, 0),    DECODE_INSTANCE(128, 8, 512),  DECODE_INSTANCE(128, 8, 1024),
         DECODE_INSTANCE(128, 8, 2048), DECODE_INSTANCE(128, 8, 4096), DECODE_INSTANCE(64, 4, 0),
         DECODE_INSTANCE(64, 4, 256),   DECODE_INSTANCE(64, 4, 512),   DECODE_INSTANCE(64, 4, 1024),
         DECODE_INSTANCE(64, 4, 2048),  DECODE_INSTANCE(64, 4, 4096),  DECODE_INSTANCE(64, 8, 0),
@@ -1050,7 +1050,7 @@ const Instance *decode_instances(int *count)
     static const Instance table[] = {
         DECODE_INSTANCE(128, 4, 0),    DECODE_INSTANCE(128, 4, 256),  DECODE_INSTANCE(128, 4, 512),
         DECODE_INSTANCE(128, 4, 1024), DECODE_INSTANCE(128, 4, 2048), DECODE_INSTANCE(128, 4, 4096),
-        DECODE_INSTANCE(128, 8, 0),    DECODE_INSTANCE(128, 8, 512),  DECODE_INSTANCE(128, 8, 1024),
+        DECODE_INSTANCE(128, 8, 256),  DECODE_INSTANCE(64, 8, 256),   DECODE_INSTANCE(128, 8, 0),    DECODE_INSTANCE(128, 8, 512),  DECODE_INSTANCE(128, 8, 1024),
         DECODE_INSTANCE(128, 8, 2048), DECODE_INSTANCE(128, 8, 4096), DECODE_INSTANCE(128, 2, 256),
         DECODE_INSTANCE(128, 2, 512),  DECODE_INSTANCE(128, 2, 1024), DECODE_INSTANCE(64, 4, 0),
         DECODE_INSTANCE(64, 4, 256),   DECODE_INSTANCE(64, 4, 512),   DECODE_INSTANCE(64, 4, 1024),

@@ -20,7 +20,9 @@ def test_lines_of_the_rule(dtype, D, unsplit):
     d = "d%d " % D
     # short contexts are not split, in workgroups of four wavefronts up to 128 keys
     assert n(1, 128) == d + "w4 split0" and n(1, 129) == d + "w8 split0"
-    assert n(1, unsplit) == d + "w8 split0" and n(1, unsplit + 1) == d + "w4 split256"
+    assert n(1, unsplit) == d + "w8 split0" and n(1, unsplit + 1) == d + "w8 split256"
+    assert n(4, 2048) == d + "w8 split256" and n(4, 2049) == d + "w4 split256"  # a compute unit for every part
+    assert n(1, 4095) == d + "w8 split256" and n(1, 4096) == d + "w4 split256"
     assert n(16, 1024) == d + "w8 split0" and n(16, 1025) == d + "w4 split256"
     assert n(32, 512) == d + "w4 split0"  # a unit for every compute unit
     # many short contexts: one wavefront per head
