@@ -60,7 +60,7 @@ typedef enum attn_status {
 } attn_status;
 
 typedef enum attn_dtype {
-    ATTN_F32 = 0, /* q, k, v, out are IEEE fp32; arithmetic is fp32 FMA */
+    ATTN_F32 = 0, /* q, k, v, out are IEEE fp32; exact fp32 products, fp32 accumulation and softmax */
     ATTN_BF16 = 1, /* q, k, v, out are bfloat16; products on bf16 MFMA, fp32 accumulation and softmax */
     ATTN_F16 = 2   /* q, k, v, out are IEEE fp16; products on fp16 MFMA, fp32 accumulation and softmax */
 } attn_dtype;
