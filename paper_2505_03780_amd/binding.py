@@ -383,7 +383,7 @@ def _rmsnorm_fields(x, weight, out, eps, residual):
     codes = _codes or _dtype_codes()
     xs, os_ = x.stride(), out.stride()
     rs = None if residual is None else residual.stride()
-    for name, st in (("x", xs), ("out", os_), ("residual", rs), ("weight", weight.stride())):
+    for name, st in (("x", xs), ("out", os_), ("residual", rs), ("weight", None if weight is None else weight.stride())):
         if st is not None and st[-1] != 1:
             raise ValueError("%s: the hidden dimension must be contiguous" % name)
     code = codes.get(x.dtype)
@@ -391,7 +391,7 @@ def _rmsnorm_fields(x, weight, out, eps, residual):
         raise TypeError("tensors must be bfloat16, float16 or float32")
     tokens, hidden = x.shape[:2]
     return (_RMSNORM_BYTES, code, tokens, hidden, x.data_ptr(), xs[0], 0 if residual is None else residual.data_ptr(),
-            0 if rs is None else rs[0], weight.data_ptr(), out.data_ptr(), os_[0], float(eps))
+            0 if rs is None else rs[0], 0 if weight is None else weight.data_ptr(), out.data_ptr(), os_[0], float(eps))
 
 
 _RMSNORM_BYTES = ctypes.sizeof(RmsNormArgs)

@@ -9,6 +9,10 @@ import paper_2505_03780_amd as A
 from paper_2505_03780_amd import binding as B
 
 
+class _NoStream:
+    cuda_stream = 0
+
+
 def _case(paged=True, dtype=torch.bfloat16):
     q = torch.zeros(3, 4, 136, dtype=dtype)[:, :, :128]
     kv = (torch.zeros(5, 16, 2, 128, dtype=dtype), torch.zeros(5, 16, 2, 128, dtype=dtype)) if paged else \
@@ -53,6 +57,8 @@ def test_wrong_arguments_are_refused(name, value, error):
     c = dict(_case(), **{name: value})
     with pytest.raises(error):
         B._attn_fields(*c.values())
+    with pytest.raises(A.AttnError):  # a missing weight is the library's to refuse
+        A.rmsnorm_fused_add(torch.zeros(1, 64, dtype=torch.bfloat16), None, torch.zeros(1, 64, dtype=torch.bfloat16), 1e-5, stream=_NoStream)
     for bad in (torch.float64, torch.int16):
         with pytest.raises(TypeError):
             B._attn_fields(*_case(dtype=bad).values())
