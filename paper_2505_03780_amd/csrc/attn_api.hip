@@ -288,7 +288,7 @@ int heuristic(const KParams &p, int is_decode)
         // epilogue; long ones: one large workgroup with the deeper ring.
         // At D = 64 the small workgroup (128 rows, three per compute unit) also stays ahead on long contexts
         // until there are 256-row tiles for every compute unit four times over: 2 x 1000 tokens behind 3000 keys
-        // 74.6 against 88.6 us, one sequence of 8191 tokens (1024 tiles) 292 against 286 us.
+        // 88 against 97 us, one sequence of 8191 tokens (1024 tiles) 331 against 318 us.
         const int64_t tiles256 = (int64_t)p.num_seqs * ((p.max_q_len + 256 / hpw - 1) / (256 / hpw)) * (p.num_q_heads / hpw);
         const bool small_wg = p.max_kv_len <= 2048 || (p.head_dim == 64 && tiles256 < 4 * compute_units());
         // a paged context adds the table entry to every transfer's address chain: the deepest prefetch

@@ -14,19 +14,20 @@
 //  * The unit loop is software pipelined: while the MFMAs of S(u+1) = K(u+1) Q^T run,
 //    the ALU exponentiates S(u); while the MFMAs of O += V(u) P(u) run, it takes the
 //    row maxima of S(u+1) and applies the masks.
-//  * The running maximum is only moved when it would grow by more than 2^kSlack
+//  * At D = 128 the running maximum is only moved when it would grow by more than 2^kSlack
 //    (then O and l are rescaled); otherwise exponentials are taken against the stale
-//    reference.  The result is unchanged, because numerator and denominator
-//    carry the same reference, and the rescale of the accumulators becomes rare.
+//    reference.  Numerator and denominator carry the same reference, so only the rounding
+//    of the weights differs, and the rescale of the accumulators becomes rare.
 //  * The output tile is transposed through LDS and written as whole rows.
 //
 // Head sizes 128 and 64.  At D = 64 a unit has half the MFMAs for the same softmax, so the vector ALU is the bound
-// (16 MFMAs of two row blocks: 512 cycles of matrix pipe, about 780 of the vector issue port); a wave takes two
+// (16 MFMAs of two row blocks: 512 cycles of matrix pipe, about 780 of the vector issue port, and 128 more for each
+// block whose reference moves, which on a flat softmax is nearly every unit of the first thousand keys); a wave takes two
 // 32-row blocks (QB = 2) where there is work enough, which halves its LDS reads and transfers per flop with the same
 // registers as one block at D = 128, and four waves (a 1 KB transfer moves eight 128-byte rows, so that is
-// how many share a unit).  Against the register-staged kernel that served D = 64 before (32/8 heads, same box):
-// 6 fp16 sequences of 300-3000 tokens 472 -> 163 us (289 -> 838 TFLOP/s), one bf16 sequence of 8191 tokens 283 us
-// (980 TFLOP/s).  An eight-slot ring with five units in flight is 2-6 % ahead of four slots there; one row block with
+// how many share a unit).  Against the register-staged kernel that served D = 64 before (32/8 heads, calls in turn):
+// 6 fp16 sequences of 300-3000 tokens 473 -> 190 us (289 -> 718 TFLOP/s; 171 us with a reference that may lag by 2^8, see
+// kSlack), one bf16 sequence of 8191 tokens 318 us (864 TFLOP/s).  An eight-slot ring with five units in flight is 2-6 % ahead of four slots there; one row block with
 // four slots and three workgroups per compute unit leads up to about four 256-row tiles per compute unit.
 #include "kernel_params.hpp"
 
@@ -65,7 +66,12 @@ typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) const void gbl_void;
 
 constexpr int kUnit = 32;          // keys per pipeline unit
-constexpr float kSlack = 8.f;      // log2 of the largest weight tolerated before the reference moves
+// log2 of the largest weight tolerated before the reference moves.  At D = 64 the reference follows the running maximum,
+// so that the heaviest weight of a row is exactly 1 and those next to it lie at the top of their binade: with a
+// slack of 8 the rounding of the weights cost 3-6 % of error against 64 bits on a flat softmax of 256 to 3000 keys and
+// 15-23 % on a peaked one (scale 4 / sqrt(D)).
+template <int HD>
+constexpr float kSlack = HD == 64 ? 0.f : 8.f;
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -469,33 +475,24 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
             for (int qb = 0; qb < QB; ++qb) sacc[qb] = E::mfma(kf[ks], qf[qb][ks], sacc[qb]);
         }
     };
-    // Move the reference of the rows whose new maximum outgrew it by more than the slack; rare, and
-    // wave-uniform, so the accumulators are only touched when needed.
-    auto reference_outgrown = [&](const float (&bm)[QB]) -> bool {
-        bool grow = false;
+    // Move the reference of the rows whose new maximum outgrew it by more than the slack; wave-uniform per
+    // row block, so that a block's accumulators are only touched when one of its rows needs it.
+    auto reference_outgrown = [&](int qb, float bm) -> bool { return __builtin_amdgcn_ballot_w64(bm > m_ref[qb] + kSlack<HD>) != 0; };
+    auto rescale_to = [&](int qb, float bm) {
+        float m_new = fmaxf(m_ref[qb], bm);
+        m_new = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = fast_exp2(m_ref[qb] - m_new);
+        m_ref[qb] = m_new;
+        l_run[qb] *= alpha;
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) grow |= bm[qb] > m_ref[qb] + kSlack;
-        return __builtin_amdgcn_ballot_w64(grow) != 0;
-    };
-    auto rescale_to = [&](const float (&bm)[QB]) {
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            float m_new = fmaxf(m_ref[qb], bm[qb]);
-            m_new = m_new == -INFINITY ? 0.f : m_new;
-            const float alpha = fast_exp2(m_ref[qb] - m_new);
-            m_ref[qb] = m_new;
-            l_run[qb] *= alpha;
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) oacc[qb][db][v] *= alpha;
-        }
+            for (int v = 0; v < 16; ++v) oacc[qb][db][v] *= alpha;
     };
     // Row maxima of the first score tile (masked if MASK), which set the reference (0 for a row of nothing but
     // -inf).  With MASK the tile is left scaled (x = c*s, masked entries -inf); without, it stays raw.
     auto settle = [&](int unit, f32x16 (&sacc)[QB], auto mask_tag) {
         constexpr bool MASK = decltype(mask_tag)::value;
-        float bm[QB];
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
             if (MASK) {
@@ -511,9 +508,8 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
             for (int v = 3; v < 15; v += 2) mx = fmaxf(fmaxf(mx, sacc[qb][v]), sacc[qb][v + 1]);
             mx = fmaxf(mx, sacc[qb][15]);
             mx = swap32_max(mx);
-            bm[qb] = MASK ? mx : mx * c;
+            rescale_to(qb, MASK ? mx : mx * c);
         }
-        rescale_to(bm);
     };
     // ---- prologue: PF units in flight, S(0) ready ------------------------------------------------
 #pragma unroll
@@ -671,7 +667,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
         }
 
         float mx[QB], bm[QB];
-        bool outgrown = false;
+        bool outgrown[QB];
         int rel[QB];
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) rel[qb] = qrel[qb] - (u + 1) * kUnit;
@@ -718,8 +714,8 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
                 for (int q2 = 0; q2 < QB; ++q2) {
                     const float m = swap32_max(mx[q2]);
                     bm[q2] = NXT_MASK ? m : m * c;
+                    outgrown[q2] = reference_outgrown(q2, bm[q2]);
                 }
-                outgrown = reference_outgrown(bm);
             }
             // K fragments of unit u+2 (the fragments of u+1 were consumed in phase X), in order, early in
             // the phase: they are a few groups old when the next iteration asks for them
@@ -739,8 +735,10 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) l_run[qb] += sum[qb][0] + sum[qb][1];
-        if (outgrown) rescale_to(bm);
+        for (int qb = 0; qb < QB; ++qb) {
+            l_run[qb] += sum[qb][0] + sum[qb][1];
+            if (outgrown[qb]) rescale_to(qb, bm[qb]);
+        }
         // Publish.  This wave's transfers of every unit but the newest PF-3 have landed (see ring_barrier);
         // its image stores have been performed (phase Y waited for younger reads); its K reads may still
         // be in flight, they target a slot that no transfer touches before the barrier after next.

@@ -56,7 +56,9 @@ struct SplitF16 {
 constexpr int kRows = 32;    // query rows (heads x tokens) of a workgroup
 constexpr int kChunk = 32;   // keys per wavefront step
 constexpr int kWaves = 8;
-constexpr float kSlack = 8.f;  // log2 of the largest weight tolerated before the reference moves
+// log2 of the largest weight tolerated before the reference moves, as in the ring kernel
+template <int HD>
+constexpr float kSlack = HD == 64 ? 0.f : 8.f;
 
 template <int HD>
 struct SplitCfg {
@@ -249,7 +251,7 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_split_kernel(const KParam
 #pragma unroll
         for (int v = 3; v < 15; v += 2) mx = fmaxf(fmaxf(mx, sacc[v]), sacc[v + 1]);
         mx = swap32_max(fmaxf(mx, sacc[15]));
-        if (__builtin_amdgcn_ballot_w64(mx > m_ref + kSlack) != 0) {
+        if (__builtin_amdgcn_ballot_w64(mx > m_ref + kSlack<HD>) != 0) {
             const float m_new = fmaxf(m_ref, mx);
             // (a row that has seen no key yet keeps -inf: a later chunk may hold its first one)
             const float alpha = m_new == -INFINITY ? 0.f : fast_exp2(m_ref - m_new);
