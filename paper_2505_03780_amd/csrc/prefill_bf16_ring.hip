@@ -72,6 +72,9 @@ constexpr int kUnit = 32;          // keys per pipeline unit
 // 15-23 % on a peaked one (scale 4 / sqrt(D)).
 template <int HD>
 constexpr float kSlack = HD == 64 ? 0.f : 8.f;
+// Reference of a row that has seen nothing but -inf scores: finite, so that -inf minus it stays -inf, and below
+// every later score, so that the first finite one becomes the reference.
+constexpr float kLowest = -3.0e38f;
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -480,7 +483,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     auto reference_outgrown = [&](int qb, float bm) -> bool { return __builtin_amdgcn_ballot_w64(bm > m_ref[qb] + kSlack<HD>) != 0; };
     auto rescale_to = [&](int qb, float bm) {
         float m_new = fmaxf(m_ref[qb], bm);
-        m_new = m_new == -INFINITY ? 0.f : m_new;
+        m_new = fmaxf(m_new, kLowest);
         const float alpha = fast_exp2(m_ref[qb] - m_new);
         m_ref[qb] = m_new;
         l_run[qb] *= alpha;
@@ -489,8 +492,8 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
 #pragma unroll
             for (int v = 0; v < 16; ++v) oacc[qb][db][v] *= alpha;
     };
-    // Row maxima of the first score tile (masked if MASK), which set the reference (0 for a row of nothing but
-    // -inf).  With MASK the tile is left scaled (x = c*s, masked entries -inf); without, it stays raw.
+    // Row maxima of the first score tile (masked if MASK), which set the reference (kLowest for a row of nothing
+    // but -inf).  With MASK the tile is left scaled (x = c*s, masked entries -inf); without, it stays raw.
     auto settle = [&](int unit, f32x16 (&sacc)[QB], auto mask_tag) {
         constexpr bool MASK = decltype(mask_tag)::value;
 #pragma unroll
