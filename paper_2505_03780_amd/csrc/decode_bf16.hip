@@ -63,6 +63,9 @@ __device__ __forceinline__ u32x4 kv_load(const void *src)
 }
 
 constexpr int kChunk = 32;  // keys per wavefront step
+// Running maximum while a wavefront has met nothing but scores of -inf: finite, so that their weights are 2^(-inf) = 0
+// and not 2^(-inf + inf).
+constexpr float kLowest = -3.0e38f;
 
 template <int HD, int WAVES>
 struct DecodeCfg {
@@ -210,7 +213,7 @@ __global__ __launch_bounds__(WAVES * 64) void decode_bf16_kernel(const KParams p
             }
         mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
         mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
-        const float m_new = fmaxf(m_run, mloc);  // finite: key c0 < k_hi is unmasked
+        const float m_new = fmaxf(fmaxf(m_run, mloc), kLowest);
         const float alpha = fast_exp2(m_run - m_new);
         m_run = m_new;
         ex8 pf;
@@ -482,7 +485,7 @@ __device__ __forceinline__ void decode_stream_run(const KParams &p, unsigned cha
             }
         mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
         mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
-        const float m_new = fmaxf(m_run, mloc);  // finite: key c0 < c_hi is unmasked
+        const float m_new = fmaxf(fmaxf(m_run, mloc), kLowest);
         const float alpha = fast_exp2(m_run - m_new);
         m_run = m_new;
         ex8 pf;
