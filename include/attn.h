@@ -112,6 +112,9 @@ typedef struct attn_args {
  * is never materialised.  Sequences with n_q = 0 write nothing.  A query with
  * no visible key (possible only when causal == 0 and seq_len == 0) gets zeros.
  * dtype ATTN_BF16 (D = 128 or 64), ATTN_F16 (D = 128 or 64) or ATTN_F32 (D = 64 or 128).
+ * Infinities and NaN: in fp32 a value of V reaches only the queries that see its key.  The 16-bit
+ * kernels multiply the keys of a tile that a query does not see by a weight of zero, so a non-finite
+ * value in V can also make NaN of queries shortly before its key (never of another sequence's).
  * Returns ATTN_OK after enqueueing, or a negative attn_status.
  */
 int attn_prefill_varlen(const attn_args *args, void *hip_stream);

@@ -83,12 +83,13 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_f32_kernel(const KParams 
     f32x4 qf[KJ];
 #pragma unroll
     for (int j = 0; j < KJ; ++j) qf[j] = *(const f32x4u *)(qrow + 16 * j);
-    // keys that the row sees, and that any row of the tile sees
-    int limit = n_kv, kv_end = n_kv;
+    // keys that the row sees, that any row of the tile sees, and that every row sees
+    int limit = n_kv, kv_end = n_kv, open_end = n_kv;
     if (p.causal) {
         const int off = n_kv - n_q, last_tok = t0 + tok < n_q ? t0 + tok : n_q;
         limit = off + t + 1 < n_kv ? off + t + 1 : n_kv;
         kv_end = off + last_tok < n_kv ? off + last_tok : n_kv;
+        open_end = off + t0 + 1 < n_kv ? off + t0 + 1 : n_kv;
     }
 
     const float *kbase = (const float *)p.k + (int64_t)kvh * p.kv_stride_head + 4 * g;
@@ -126,6 +127,44 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_f32_kernel(const KParams 
         for (int e = 0; e < 4; ++e) oacc[j][e] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, l = 0.f;  // l: this lane's keys only
 
+    // A chunk with keys that some row does not see (or past the end): the products below multiply those by a weight of
+    // zero, which turns an infinity or NaN in V into NaN.  Non-finite values are therefore taken out of the operand and
+    // added, key by key, to the rows that see them.  Rare: a test per value of such a chunk is all that finite inputs pay.
+    auto keep_apart = [&](int c0, const float (&w)[4]) {
+        auto finite = [](float x) { return (__float_as_uint(x) & 0x7f800000u) != 0x7f800000u; };
+        float probe = 0.f;  // NaN once a value is not finite
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int j = 0; j < VJ; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) probe = __builtin_fmaf(vf[v][j][e], 0.f, probe);
+        if (__builtin_amdgcn_ballot_w64(!finite(probe)) == 0) return;
+#pragma unroll 1
+        for (int kg = 0; kg < 4; ++kg) {
+#pragma unroll
+            for (int kv = 0; kv < 4; ++kv) {  // key c0 + 4 kg + kv: its weights and values lie in the lanes of group kg
+                const float wk = __shfl(w[kv], 16 * kg + i);
+                const bool sees = c0 + 4 * kg + kv < limit;
+#pragma unroll
+                for (int j = 0; j < VJ; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const float x = __shfl(vf[kv][j][e], 16 * kg + 4 * g + v);
+                            if (sees && !finite(x)) oacc[j][e][v] += wk * x;
+                        }
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int j = 0; j < VJ; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) vf[v][j][e] = finite(vf[v][j][e]) ? vf[v][j][e] : 0.f;
+    };
+
     // one chunk; MORE: the registers of K, then of V, take the wave's next chunk as soon as they are free
     constexpr int kStep = kWaves * kChunk;
     int64_t next_base = 0;
@@ -157,8 +196,12 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_f32_kernel(const KParams 
 #pragma unroll
         for (int j = 0; j < VJ; ++j)
 #pragma unroll
+            for (int e = 0; e < 4; ++e) oacc[j][e] *= alpha;
+        if (c0 + kChunk > open_end) keep_apart(c0, w);
+#pragma unroll
+        for (int j = 0; j < VJ; ++j)
+#pragma unroll
             for (int e = 0; e < 4; ++e) {
-                oacc[j][e] *= alpha;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) oacc[j][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[v][j][e], w[v], oacc[j][e], 0, 0, 0);
             }

@@ -36,3 +36,29 @@ def test_dword_aligned_views():
     got = to_host_f64(dw.run(False))
     assert np.array_equal(got, aligned)
     assert_close(got, ref, "f32")
+
+
+@pytest.mark.parametrize("Hq,Hkv,D", [(4, 4, 64), (4, 2, 128)])
+@pytest.mark.parametrize("paged", [False, True])
+def test_non_finite_values_reach_only_the_rows_that_see_them(Hq, Hkv, D, paged):
+    """Infinities and NaN in V of one token (mid-tile, last of the sequence), causal: earlier rows stay what they are, later
+    ones get what the sum over their visible keys gives."""
+    lens, bad = [40, 33, 150], [(20, np.inf), (32, -np.inf), (130, np.nan)]
+    if paged:
+        wl = W.make_paged(103, "prefill", lens, lens, Hq, Hkv, D, 16, sum(-(-n // 16) for n in lens) + 1)
+        wl = W.Workload("f32", "prefill", "f32", *(W.bf16_bits_to_f32(x) for x in (wl.q, wl.k, wl.v)), wl.query_start_loc, wl.seq_lens, wl.scale, True,
+                        block_table=wl.block_table, block_size=16)
+        at = lambda s, t: (int(wl.block_table[s, t // 16]), t % 16)
+    else:
+        wl = W.make_prefill_contiguous(103, lens, Hq, Hkv, D, dtype="f32")
+        at = lambda s, t: (int(wl.query_start_loc[s]) + t,)
+    dw = DeviceWorkload(wl)
+    clean = to_host_f64(dw.run(False))
+    for s, (t, x) in enumerate(bad):
+        dw.v[at(s, t)][Hkv - 1, 5::16] = x
+    got = to_host_f64(dw.run(False)).reshape(-1, Hkv, Hq // Hkv, D)
+    want = clean.reshape(got.shape).copy()
+    for s, (t, x) in enumerate(bad):
+        q0 = int(wl.query_start_loc[s])
+        want[q0 + t:q0 + lens[s], Hkv - 1, :, 5::16] = x
+    assert np.array_equal(got, want, equal_nan=True)
