@@ -9,6 +9,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 namespace attn {
 
 // element types of q, k, v, out (the values of attn_dtype in the C ABI)
@@ -73,6 +75,20 @@ const Instance *decode_f16_instances(int *count);   // fp16: the wave-per-head a
 hipError_t launch_prefill_f32(const KParams &, hipStream_t);
 hipError_t launch_decode_combine(const KParams &, hipStream_t);
 hipError_t launch_decode_combine_f16(const KParams &, hipStream_t);
+
+// Lets `kernel` be launched with `bytes` of dynamic LDS on the current device.  HIP keeps this permission per device, so
+// it is asked for on the first launch on each (bit d of `granted`, one word per kernel, stands for device d).
+inline hipError_t allow_dynamic_lds(const void *kernel, size_t bytes, std::atomic<uint64_t> &granted)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0;
+    if (granted.load(std::memory_order_relaxed) & bit) return hipSuccess;
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e == hipSuccess) granted.fetch_or(bit, std::memory_order_relaxed);
+    return e;
+}
 
 // Floats per (sequence, query head, split) in the split-K workspace: D partial
 // outputs followed by the running max and the running sum.

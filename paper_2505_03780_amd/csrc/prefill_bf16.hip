@@ -321,8 +321,9 @@ hipError_t prefill_launch(const KParams &p, hipStream_t stream)
 {
     using C = PrefillCfg<HD, BN, QB, WAVES, HPW>;
     auto kern = prefill_bf16_kernel<HD, BN, QB, WAVES, HPW>;
-    static hipError_t attr = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::kLdsBytes);
-    if (attr != hipSuccess) return attr;
+    static std::atomic<uint64_t> granted{0};
+    const hipError_t allowed = allow_dynamic_lds((const void *)kern, C::kLdsBytes, granted);
+    if (allowed != hipSuccess) return allowed;
     const int64_t q_tiles = (p.max_q_len + C::kTok - 1) / C::kTok;
     const int64_t nhg = (int64_t)p.num_kv_heads * (p.group / HPW);
     const int64_t blocks = q_tiles * p.num_seqs * nhg;

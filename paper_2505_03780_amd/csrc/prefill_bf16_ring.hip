@@ -853,8 +853,9 @@ hipError_t ring_launch_impl(const KParams &p, hipStream_t stream, int64_t blocks
 {
     using C = RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>;
     auto kern = prefill_ring_kernel<E, HD, QB, HPW, NSLOT, PF, WAVES, PAGED>;
-    static hipError_t attr = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::kLdsBytes);
-    if (attr != hipSuccess) return attr;
+    static std::atomic<uint64_t> granted{0};
+    const hipError_t allowed = allow_dynamic_lds((const void *)kern, C::kLdsBytes, granted);
+    if (allowed != hipSuccess) return allowed;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(C::kThreads), C::kLdsBytes, stream, p);
     return hipGetLastError();
 }

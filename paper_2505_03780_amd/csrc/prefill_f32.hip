@@ -260,8 +260,9 @@ template <int HD>
 hipError_t f32_launch(const KParams &p, hipStream_t stream, unsigned blocks)
 {
     auto kern = prefill_f32_kernel<HD>;
-    static hipError_t attr = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)F32Cfg<HD>::kLdsBytes);
-    if (attr != hipSuccess) return attr;
+    static std::atomic<uint64_t> granted{0};
+    const hipError_t allowed = allow_dynamic_lds((const void *)kern, F32Cfg<HD>::kLdsBytes, granted);
+    if (allowed != hipSuccess) return allowed;
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(kWaves * 64), F32Cfg<HD>::kLdsBytes, stream, p);
     return hipGetLastError();
 }

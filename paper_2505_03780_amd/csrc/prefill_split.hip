@@ -356,8 +356,9 @@ template <typename E, int HD, bool PAGED>
 hipError_t split_launch_impl(const KParams &p, hipStream_t stream, int64_t blocks)
 {
     auto kern = prefill_split_kernel<E, HD, PAGED>;
-    static hipError_t attr = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SplitCfg<HD>::kLdsBytes);
-    if (attr != hipSuccess) return attr;
+    static std::atomic<uint64_t> granted{0};
+    const hipError_t allowed = allow_dynamic_lds((const void *)kern, SplitCfg<HD>::kLdsBytes, granted);
+    if (allowed != hipSuccess) return allowed;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kWaves * 64), SplitCfg<HD>::kLdsBytes, stream, p);
     return hipGetLastError();
 }
