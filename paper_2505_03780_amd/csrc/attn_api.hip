@@ -500,11 +500,13 @@ void maybe_load_env_cache()
 // instead of building the bucket string, taking the lock and walking the instance table.
 struct SelectKey {
     int32_t dtype, head_dim, num_q_heads, num_kv_heads, paged, block_size, causal, num_seqs, max_q_len, max_kv_len;
+    int64_t kv_stride_block, kv_stride_tok;  // (kernels with 32-bit offsets inside a block refuse large ones)
     bool operator==(const SelectKey &o) const
     {
         return dtype == o.dtype && head_dim == o.head_dim && num_q_heads == o.num_q_heads && num_kv_heads == o.num_kv_heads &&
                paged == o.paged && block_size == o.block_size && causal == o.causal && num_seqs == o.num_seqs &&
-               max_q_len == o.max_q_len && max_kv_len == o.max_kv_len;
+               max_q_len == o.max_q_len && max_kv_len == o.max_kv_len && kv_stride_block == o.kv_stride_block &&
+               kv_stride_tok == o.kv_stride_tok;
     }
 };
 struct SelectMemo {
@@ -580,7 +582,7 @@ int select_instance(const KParams &p, int dtype, int is_decode)
     static thread_local SelectMemo memo[2];
     SelectMemo &m = memo[is_decode];
     const SelectKey key{dtype, p.head_dim, p.num_q_heads, p.num_kv_heads, p.block_table ? 1 : 0, p.block_size, p.causal,
-                        p.num_seqs, p.max_q_len, p.max_kv_len};
+                        p.num_seqs, p.max_q_len, p.max_kv_len, p.kv_stride_block, p.kv_stride_tok};
     const uint64_t gen = g_generation.load(std::memory_order_acquire);
     if (m.generation == gen && m.key == key) return m.id;
     const int id = select_instance_slow(p, dtype, is_decode);
