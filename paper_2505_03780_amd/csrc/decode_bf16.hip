@@ -931,6 +931,13 @@ bool decode_valid(const KParams &p)
     return p.dtype == kElemDtype && p.head_dim == HD && p.group <= 16 && p.block_table != nullptr && p.block_size >= 16;
 }
 
+// (decode_stream_run keeps a lane's byte offset inside a 16-key group in 32 bits)
+template <int HD, int WAVES>
+bool decode_stream_valid(const KParams &p)
+{
+    return decode_valid<HD, WAVES>(p) && (uint64_t)p.kv_stride_tok * 2 * 16 < (1ull << 32);
+}
+
 template <int HD, int WAVES>
 hipError_t decode_launch(const KParams &p, hipStream_t stream)
 {
@@ -1005,11 +1012,11 @@ hipError_t combine_launch(const KParams &p, hipStream_t stream)
 #define DECODE_BAL_INSTANCE(HD, WAVES, PER_CU)                                                                  \
     {                                                                                                          \
         DECODE_NAME "_balanced d" #HD " w" #WAVES " percu" #PER_CU, 16, kChunk, WAVES, 16, 2, -PER_CU,           \
-            decode_valid<HD, WAVES>, decode_balanced_launch<HD, WAVES>                                  \
+            decode_stream_valid<HD, WAVES>, decode_balanced_launch<HD, WAVES>                                  \
     }
 #define DECODE_SEQ_INSTANCE(HD, WAVES, SPLIT)                                                                  \
     {                                                                                                          \
-        DECODE_NAME "_seq d" #HD " w" #WAVES " split" #SPLIT, 16, kChunk, WAVES, 16, 3, SPLIT, decode_valid<HD, WAVES>, \
+        DECODE_NAME "_seq d" #HD " w" #WAVES " split" #SPLIT, 16, kChunk, WAVES, 16, 3, SPLIT, decode_stream_valid<HD, WAVES>, \
             decode_seq_launch<HD, WAVES>                                                                       \
     }
 
