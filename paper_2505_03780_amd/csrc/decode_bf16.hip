@@ -670,15 +670,27 @@ __device__ __forceinline__ void merge_head(const float *r, int parts, int64_t st
 // (one address for the whole half, a broadcast), so there is no cross-lane step, and registers for BLK
 // partial outputs instead of 32 leave room for four to eight wavefronts per SIMD.  Index and weight are
 // clamped, not branched on, so that all loads of a block are in flight together.
+// MergeState: reference, sum and this lane's channels of what has been merged so far.
+template <int HD>
+struct MergeState {
+    static constexpr int CPL = HD / 32;
+    float M = -INFINITY, L = 0.f;
+    float acc[CPL] = {};
+    __device__ __forceinline__ void store(elem_t *o) const
+    {
+        const float inv = L > 0.f ? 1.f / L : 0.f;
+        typedef elem_t exC __attribute__((ext_vector_type(CPL)));
+        exC w;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) w[c] = (elem_t)(acc[c] * inv);
+        *(exC *)o = w;
+    }
+};
 template <int HD, int BLK>
-__device__ __forceinline__ void merge_head_few(const float *r, int parts, int64_t stride, int lane, elem_t *o)
+__device__ __forceinline__ void merge_parts(MergeState<HD> &st, const float *r, int parts, int64_t stride, int lane)
 {
     constexpr int CPL = HD / 32;
     const int sub = lane & 31;
-    float acc[CPL];
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
-    float M = -INFINITY, L = 0.f;
     for (int b0 = 0; b0 < parts; b0 += BLK) {
         float2 ml[BLK], d[BLK][CPL / 2];
 #pragma unroll
@@ -688,39 +700,33 @@ __device__ __forceinline__ void merge_head_few(const float *r, int parts, int64_
 #pragma unroll
             for (int c = 0; c < CPL / 2; ++c) d[j][c] = *(const float2 *)(rj + CPL * sub + 2 * c);
         }
-        float m_new = M;
+        float m_new = st.M;
 #pragma unroll
         for (int j = 0; j < BLK; ++j) {
             if (b0 + j >= parts) ml[j].x = -INFINITY;
             m_new = fmaxf(m_new, ml[j].x);
         }
         if (m_new == -INFINITY) continue;  // nothing but empty parts so far (uniform over the half)
-        const float keep = fast_exp2(M - m_new);  // 0 for the first block
-        M = m_new;
-        L *= keep;
+        const float keep = fast_exp2(st.M - m_new);  // 0 for the first block
+        st.M = m_new;
+        st.L *= keep;
 #pragma unroll
-        for (int c = 0; c < CPL; ++c) acc[c] *= keep;
+        for (int c = 0; c < CPL; ++c) st.acc[c] *= keep;
 #pragma unroll
         for (int j = 0; j < BLK; ++j) {
             const float w = fast_exp2(ml[j].x - m_new);  // 0 past the last part and for empty parts
-            L += ml[j].y * w;
+            st.L += ml[j].y * w;
 #pragma unroll
             for (int c = 0; c < CPL / 2; ++c) {
-                acc[2 * c] += d[j][c].x * w;
-                acc[2 * c + 1] += d[j][c].y * w;
+                st.acc[2 * c] += d[j][c].x * w;
+                st.acc[2 * c + 1] += d[j][c].y * w;
             }
         }
     }
-    const float inv = L > 0.f ? 1.f / L : 0.f;
-    typedef elem_t exC __attribute__((ext_vector_type(CPL)));
-    exC w;
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) w[c] = (elem_t)(acc[c] * inv);
-    *(exC *)o = w;
 }
 
 // How many parts a merge kernel takes per round trip, from the number it expects of a sequence (any number is
-// merged correctly).  Kernel times before (32 for all, 252 registers) and now: 200 contexts of 20-800 keys, two or three
+// merged correctly; for sequences of far more parts than that see decode_balanced_combine_kernel).  Kernel times before (32 for all, 252 registers) and now: 200 contexts of 20-800 keys, two or three
 // parts each, 12.1 -> 4.7 us; 64 contexts of 512-4096, five parts, 6.3 -> 4.7 us; one context of 1900, eight parts,
 // 4.2 -> 2.9 us.  From nine parts on one round trip of 32 is kept (16 contexts, 17 parts: 6.8 us).
 inline int merge_block(int64_t parts) { return parts <= 4 ? 4 : parts <= 8 ? 8 : 32; }
@@ -735,10 +741,13 @@ __device__ __forceinline__ void merge_pair(const KParams &p, int lane, int s, in
     const int hl = 2 * pair + (lane >> 5);
     const int hc = hl < G ? hl : G - 1;  // an idle half repeats the last head (same values, same address)
     elem_t *o = (elem_t *)p.out + (int64_t)s * p.o_stride_tok + (int64_t)(kvh * G + hc) * p.o_stride_head + (HD / 32) * (lane & 31);
-    if (BLK < 32)
-        merge_head_few<HD, BLK>(rec + (int64_t)hc * head_stride, parts, part_stride, lane, o);
-    else
+    if (BLK < 32) {
+        MergeState<HD> st;
+        merge_parts<HD, BLK>(st, rec + (int64_t)hc * head_stride, parts, part_stride, lane);
+        st.store(o);
+    } else {
         merge_head<HD>(rec + (int64_t)hc * head_stride, parts, part_stride, lane, o);
+    }
 }
 
 // Where a workgroup's run of chunks starts, for the token-balanced kernels: the batch's 32-key chunks
@@ -881,26 +890,94 @@ __global__ __launch_bounds__(WAVES * 64, 8 / WAVES) void decode_balanced_kernel(
 // chunk range, at record indices workgroup + s.  One wavefront per (sequence, KV head, pair of query heads).
 constexpr int kMergeWaves = 4;  // (sequence, KV head, head pair) units per merge workgroup
 
+// With many sequences for the runs (BLK < 32) a sequence has few parts on average, but one long context among many short
+// ones may span most runs, and one wavefront would walk its records BLK at a time, a round trip each.  A sequence of
+// more than kLongParts parts is therefore left to a workgroup of its own per head pair, whose four wavefronts take a quarter of
+// the records each.  Helper j of a head pair looks at the sequence that lies across the end of run kLongParts * j; a
+// sequence of more than kLongParts runs lies across at least one such end and belongs to the first.  The helpers stand
+// behind the ordinary workgroups, where most of them find nothing and end (in front they cost 0.3 us).
+// One context of 32768 keys among 255 of 64 (32/8 heads), whole call: 70 -> 46 us at D = 128, 56 -> 30 at D = 64 (60 and 36
+// with 32 records per round trip for every sequence); even batches are level (200 contexts of 20-800 keys 63.7 us, 64 of
+// 512-4096 104.3 -> 104.5).
+constexpr int kLongParts = 16;
+inline int64_t long_helpers(int num_wgs) { return (num_wgs + kLongParts - 1) / kLongParts; }
+
+// largest s with prefix[s] <= chunk, for chunk < prefix[B] (so sequence s holds it): 64 places per round trip
+__device__ __forceinline__ int sequence_of_chunk(const int32_t *prefix, int B, int chunk, int lane)
+{
+    int lo = 0, len = B;  // the answer lies in [lo, lo + len)
+    while (len > 1) {
+        const int step = (len + 63) / 64, end = lo + len;
+        const bool at_or_below = lane * step < len && prefix[lo + lane * step] <= chunk;  // (true for lane 0)
+        lo += (__builtin_popcountll(__builtin_amdgcn_ballot_w64(at_or_below)) - 1) * step;
+        len = step < end - lo ? step : end - lo;
+    }
+    return lo;
+}
+
 template <int HD, int BLK>
 __global__ __launch_bounds__(64 * kMergeWaves) void decode_balanced_combine_kernel(const KParams p)
 {
     const int pairs = (p.group + 1) / 2;
     const int lane = threadIdx.x & 63;
-    int bid = blockIdx.x * kMergeWaves + (threadIdx.x >> 6);
-    if (bid >= p.num_seqs * p.num_kv_heads * pairs) return;
+    const int wave = threadIdx.x >> 6;
+    const int num_wgs = p.num_splits;
+    const int B = p.num_seqs;
+    const int32_t *prefix = (const int32_t *)(p.workspace + (int64_t)(num_wgs + B) * p.num_q_heads * (HD + 2));
+    const int64_t stride = (int64_t)p.num_q_heads * (HD + 2);
+    const int merge_blocks = (B * p.num_kv_heads * pairs + kMergeWaves - 1) / kMergeWaves;
+    if (BLK < 32) {
+        if ((int)blockIdx.x >= merge_blocks) {
+            const int units = p.num_kv_heads * pairs, h = blockIdx.x - merge_blocks;
+            const int j = h / units, unit = h % units;
+            const int total = prefix[B];
+            const int end = run_begin(total, num_wgs, j * kLongParts + 1);  // first chunk behind run j * kLongParts
+            if (end <= 0 || end >= total) return;
+            const int s = sequence_of_chunk(prefix, B, end, lane);
+            const int c0 = prefix[s], c1 = prefix[s + 1];
+            const int w0 = run_of(total, num_wgs, c0), parts = run_of(total, num_wgs, c1 - 1) - w0 + 1;
+            if (parts <= kLongParts || j * kLongParts < w0 || j * kLongParts - w0 >= kLongParts) return;  // (the same for all wavefronts)
+            const int kvh = unit / pairs, hl = 2 * (unit % pairs) + (lane >> 5);  // (an idle half repeats the last head)
+            const int hc = hl < p.group ? hl : p.group - 1;
+            const int per = (parts + kMergeWaves - 1) / kMergeWaves, first = wave * per;
+            const int mine = first >= parts ? 0 : parts - first < per ? parts - first : per;
+            MergeState<HD> st;
+            merge_parts<HD, 8>(st, p.workspace + (int64_t)(w0 + first + s) * stride + (int64_t)(kvh * p.group + hc) * (HD + 2), mine, stride, lane);
+            constexpr int CPL = HD / 32;
+            __shared__ float quarter[kMergeWaves][CPL + 2][64];
+            quarter[wave][CPL][lane] = st.M;
+            quarter[wave][CPL + 1][lane] = st.L;
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) quarter[wave][c][lane] = st.acc[c];
+            __syncthreads();
+            if (wave != 0) return;
+            MergeState<HD> all;
+#pragma unroll
+            for (int w = 0; w < kMergeWaves; ++w) all.M = fmaxf(all.M, quarter[w][CPL][lane]);
+#pragma unroll
+            for (int w = 0; w < kMergeWaves; ++w) {
+                const float m = quarter[w][CPL][lane];
+                const float sc = m == -INFINITY ? 0.f : fast_exp2(m - all.M);
+                all.L += quarter[w][CPL + 1][lane] * sc;
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) all.acc[c] += quarter[w][c][lane] * sc;
+            }
+            all.store((elem_t *)p.out + (int64_t)s * p.o_stride_tok + (int64_t)(kvh * p.group + hc) * p.o_stride_head + (HD / 32) * (lane & 31));
+            return;
+        }
+    }
+    int bid = blockIdx.x * kMergeWaves + wave;
+    if (bid >= B * p.num_kv_heads * pairs) return;
     const int pair = bid % pairs;
     bid /= pairs;
     const int kvh = bid % p.num_kv_heads;
     const int s = bid / p.num_kv_heads;
-    const int num_wgs = p.num_splits;
-    const int B = p.num_seqs;
-    const int32_t *prefix = (const int32_t *)(p.workspace + (int64_t)(num_wgs + B) * p.num_q_heads * (HD + 2));
     const int c0 = prefix[s], c1 = prefix[s + 1], total = prefix[B];
     // an empty context has no piece: parts = 0 makes the merge write zeros
     const int w0 = c1 > c0 ? run_of(total, num_wgs, c0) : 0;
     const int parts = c1 > c0 ? run_of(total, num_wgs, c1 - 1) - w0 + 1 : 0;
     if (parts == 1) return;  // the main kernel wrote this sequence itself
-    const int64_t stride = (int64_t)p.num_q_heads * (HD + 2);
+    if (BLK < 32 && parts > kLongParts) return;  // left to a helper
     merge_pair<HD, BLK>(p, lane, s, kvh, pair, p.workspace + (int64_t)(w0 + s) * stride + (int64_t)kvh * p.group * (HD + 2), parts, HD + 2, stride);
 }
 
@@ -972,10 +1049,12 @@ hipError_t decode_balanced_launch(const KParams &p, hipStream_t stream)
     hipLaunchKernelGGL((decode_balanced_kernel<HD, WAVES>), dim3((unsigned)blocks), dim3(WAVES * 64), 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int64_t units = (int64_t)p.num_seqs * p.num_kv_heads * ((p.group + 1) / 2);
-    const dim3 grid((unsigned)((units + kMergeWaves - 1) / kMergeWaves)), block(64 * kMergeWaves);
+    const int64_t pairs = (int64_t)p.num_kv_heads * ((p.group + 1) / 2);
     // num_splits runs over num_seqs sequences: a sequence is cut at about as many places as its share of the runs
     const int blk = merge_block((p.num_splits + p.num_seqs - 1) / p.num_seqs + 1);
+    const int64_t merge_blocks = (p.num_seqs * pairs + kMergeWaves - 1) / kMergeWaves + (blk < 32 ? long_helpers(p.num_splits) * pairs : 0);
+    if (merge_blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
+    const dim3 grid((unsigned)merge_blocks), block(64 * kMergeWaves);
     if (blk == 4)
         hipLaunchKernelGGL((decode_balanced_combine_kernel<HD, 4>), grid, block, 0, stream, p);
     else if (blk == 8)

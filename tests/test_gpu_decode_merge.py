@@ -51,3 +51,57 @@ def test_token_balanced(lens, dtype, D):
         _check(wl)
     finally:
         A.attn_force_instance(True, -1)
+
+
+@pytest.mark.parametrize("dtype,D,Hq,Hkv", [("bf16", 128, 8, 2), ("f16", 64, 3, 1)])
+@pytest.mark.parametrize("lens", [
+    [32 * 256 - 32 * 99] + [32] * 99,     # one chunk per run: the long context at the front, 157 parts
+    [32] * 60 + [32 * 150] + [1] * 46,    # in the middle
+    [0] * 30 + [32] * 200 + [32 * 17],    # at the end, 17 parts: one more than a wavefront of the ordinary merge takes on
+    [32] * 200 + [32 * 16] + [0] * 30,    # 16 parts: the most that it does
+    [32 * 40, 1, 32 * 40, 0, 32 * 40] + [20] * 95,  # several long ones next to each other
+    [32 * 16 + 1] * 15 + [5] * 70])       # every helper's sequence is another one, 17 chunks each
+def test_token_balanced_long_among_short(lens, dtype, D, Hq, Hkv):
+    """Sequences of more parts than one wavefront merges, among many of one part."""
+    wl = W.make_paged(98, "decode", np.ones(len(lens), np.int32), lens, Hq, Hkv, D, 16, sum(-(-n // 16) for n in lens) + 1, causal=False)
+    if dtype == "f16":
+        wl = W.as_f16(wl)
+    _force("decode_%s_balanced d%d w8 percu1" % (dtype, D))
+    try:
+        _check(wl)
+    finally:
+        A.attn_force_instance(True, -1)
+
+
+def test_merge_of_a_long_context_among_short_ones_is_not_serial():
+    """One context of 32768 keys among 255 of 64 against 256 equal contexts of as many keys in all: the kernels that walk the keys
+    take the same time, and so must the merge, within a factor of two of the whole (it was 3.3 with the long context's 170
+    records walked four at a time, and is 1.6)."""
+    import torch
+
+    def median_us(lens):
+        wl = W.make_paged(99, "decode", np.ones(len(lens), np.int32), lens, 32, 8, 64, 16, sum(-(-n // 16) for n in lens) + 1, causal=False)
+        dw = DeviceWorkload(wl)
+        a = dw.args(True)
+        assert "balanced" in A.attn_instance_name(True, A.attn_selected_instance(a, True))
+        run = lambda: A.attn_decode_paged(None, None, None, None, None, None, None, max_kv_len=0, args=a)
+        times = []
+        for _ in range(30):
+            e0, e1 = torch.cuda.Event(True), torch.cuda.Event(True)
+            for _ in range(3):
+                run()
+            e0.record()
+            for _ in range(10):
+                run()
+            e1.record()
+            e1.synchronize()
+            times.append(100 * e0.elapsed_time(e1))
+        return sorted(times)[15]
+
+    A.attn_force_instance(True, next(i for i in range(A.attn_num_instances(True)) if A.attn_instance_name(True, i) == "decode_bf16_balanced d64 w8 percu1"))
+    try:
+        skewed, even = median_us([32768] + [64] * 255), median_us([192] * 256)
+    finally:
+        A.attn_force_instance(True, -1)
+    print("skewed %.1f us, even %.1f us" % (skewed, even), flush=True)
+    assert skewed <= 2.0 * even
