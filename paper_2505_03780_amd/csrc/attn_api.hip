@@ -353,14 +353,22 @@ int heuristic(const KParams &p, int is_decode)
                 return p.num_seqs * parts() > 2 * compute_units() ||
                        (bounded && p.num_seqs * parts() * p.num_q_heads * partial_stride(p.head_dim) * (int64_t)sizeof(float) > (int64_t)kScratchBytes);
             };
+            const int wanted = sl;
             while (sl > 0 && sl < 4096 && too_many()) sl *= 2;
             if (sl >= kv || (sl > 0 && too_many())) sl = 0;
-            // many long contexts of one or two KV heads, too many to split: still better than a serial walk of
+            // many long contexts of few KV heads, too many to split: still better than a serial walk of
             // each (142 contexts of 2000-15000 keys, 8/2 heads, D = 64: 1.8x)
             if (sl == 0 && kv > 2048) {
                 id = fits_static(find_instance(1, p, 4, 16, 32, 0, -2));
                 if (id < 0) id = fits_static(find_instance(1, p, 8, 16, 32, 0, -1));
             }
+            // For fp16 at D = 64 also where the bound leaves parts of 1024 keys or more: one long context among many
+            // short ones would be walked in two or three serial parts.  8/2 heads, token-balanced against parts: 175
+            // contexts, one of 3338 keys among 50s 11.5 against 25 us, 800-3338 evenly 47 against 43; 120 contexts, one
+            // of 9000 14.6 against 46 us, evenly 77 against 79.  (The other types keep the parts, whose error against 64
+            // bits is 2-7 % smaller, and so does one KV head, which leaves seven of eight wavefronts idle: 75 against 58.)
+            if (sl > wanted && sl >= 1024 && p.num_kv_heads > 1 && p.dtype == kDtypeF16 && p.head_dim == 64)
+                id = fits_static(find_instance(1, p, 8, 16, 32, 0, -1));
             // eight waves, one chunk each, also where every part has a compute unit to itself: one context of 1900
             // keys 10.9 -> 10.0 us, 3 of 1900 10.6 -> 9.9; two workgroups per unit lose (8 of 1900: 15.8 -> 18.0), and
             // from 4096 keys on the two are within 3 %

@@ -38,3 +38,13 @@ def test_lines_of_the_rule(dtype, D, unsplit):
 def test_balanced_records_stay_within_the_static_array_where_splits_ran_before():
     """50 contexts of 1300 keys: under 128 query heads the balanced kernel's records exceed the 16 MiB array."""
     assert _name(50, 1300, Hq=128) == "d128 w4 split256" and "balanced" in _name(50, 1300, Hq=64)
+
+
+def test_long_parts_of_few_heads():
+    """fp16, D = 64: where the batch's bound leaves parts of 1024 keys or more, the token-balanced kernel (whole-context skew)."""
+    n = lambda B, kv, **k: _name(B, kv, D=64, dtype=A.ATTN_F16, **k)
+    two = dict(Hq=8, Hkv=2)
+    assert "balanced" in n(175, 3338, **two) and "balanced" in n(120, 9000, **two) and "balanced" in n(200, 1800, **two)
+    assert "split512" in n(130, 1300, **two)  # parts shorter than 1024 keys
+    assert "split" in n(175, 3338, Hq=4, Hkv=1)
+    assert _name(175, 3338, D=128, dtype=A.ATTN_F16, **two) == "d128 w4 split2048"
