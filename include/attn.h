@@ -125,7 +125,9 @@ int attn_prefill_varlen(const attn_args *args, void *hip_stream);
  * paper cites PagedAttention for this setting; layout above).  Long contexts
  * are split along the key axis; each part writes an fp32 (max, sum, partial
  * output) triple into `workspace` and a second kernel merges them.  The caller
- * provides at least attn_workspace_bytes(args, 1) bytes, 8-byte aligned.  dtype ATTN_BF16 or ATTN_F16.
+ * provides at least attn_workspace_bytes(args, 1) bytes, 8-byte aligned.  With less (or NULL) the call returns
+ * ATTN_ERR_WORKSPACE unless the built-in choice needs none, or the batch is one that fixed parts would leave
+ * whole (many long contexts, and most at D = 64): that one is decoded unsplit.  dtype ATTN_BF16 or ATTN_F16.
  */
 int attn_decode_paged(const attn_args *args, void *hip_stream);
 

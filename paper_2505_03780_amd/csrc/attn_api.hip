@@ -269,6 +269,52 @@ bool few_rows_many_keys(const KParams &p)
     return (p.max_kv_len >= 160 && wgs <= compute_units()) || (p.max_kv_len > two_from && wgs <= 2 * compute_units());
 }
 
+// Part length of the fixed splits (0: whole contexts): enough workgroups to fill the chip several times over, parts no
+// shorter than 256 keys.
+struct FixedParts {
+    int length = 256;
+    bool wide = false;        // a long context in few units: longer parts and eight waves per workgroup rather than more than 32 parts
+    bool lengthened = false;  // by the bounds of the whole batch
+};
+FixedParts fixed_part_length(const KParams &p, size_t record_bytes)
+{
+    const int64_t kv = p.max_kv_len, want = (int64_t)p.num_seqs * p.num_kv_heads * kv / 2048;
+    FixedParts f;
+    int &sl = f.length;
+    auto parts = [&]() { return (kv + sl - 1) / sl; };
+    while (sl * 2 <= want && sl < 4096) sl *= 2;
+    if (sl >= kv) sl = 0;
+    while (sl > 0 && sl < 4096 && parts() > 32) {
+        sl *= 2;
+        f.wide = true;
+    }
+    // at most two parts per compute unit in all (the bound `usable` enforces), and records of at most record_bytes
+    auto too_many = [&]() {
+        return p.num_seqs * parts() > 2 * compute_units() ||
+               (uint64_t)(p.num_seqs * parts()) * p.num_q_heads * partial_stride(p.head_dim) * sizeof(float) > record_bytes;
+    };
+    while (sl > 0 && sl < 4096 && too_many()) {
+        sl *= 2;
+        f.lengthened = true;
+    }
+    if (sl >= kv || (sl > 0 && too_many())) sl = 0;
+    return f;
+}
+
+// Token-balanced decode pays from this many keys of the batch on, whatever the number of heads.
+bool very_long_runs(const KParams &p) { return (int64_t)p.num_seqs * p.max_kv_len >= 100000; }
+
+// Whether a decode call without (enough) workspace is served by the unsplit kernel: where the fixed parts alone, without the
+// token-balanced kernels' and the short contexts' rules, come to whole contexts, or to a length that the type and head
+// size had no split kernel for when callers could first leave the workspace out.  Other calls are refused.
+bool served_without_workspace(const KParams &p)
+{
+    if (p.num_kv_heads >= 4 && very_long_runs(p)) return false;
+    const int sl = fixed_part_length(p, SIZE_MAX).length;
+    if (p.dtype == kDtypeF16) return p.head_dim == 128 && (sl == 0 || sl == 4096);
+    return sl == 0 || (p.head_dim == 64 && sl != 512 && sl != 2048);
+}
+
 int heuristic(const KParams &p, int is_decode)
 {
     int n;
@@ -311,15 +357,17 @@ int heuristic(const KParams &p, int is_decode)
         // it is level with the split kernels or up to 1.2x ahead; a few sequences of more than 8192 keys do
         // better with long parts (3 contexts of 24000 keys 1.2x).
         // Here and below a choice that the fixed splits made before does not go to an instance whose records
-        // exceed the array of attn_decode_paged_static, which would then refuse the call.
+        // exceed the array of attn_decode_paged_static, which would then refuse the call; attn_decode_paged makes the
+        // same choice, because the two entry points give the same bits.  That is only reached with very many query
+        // heads; under 128 (8 KV heads, D = 128), token-balanced against split: 50 contexts of 325-1300 keys 44 against
+        // 47 us, one such among 50s 18 against 19; 20 of 1000-4000 50 against 59, one such among 50s 31 against 17.
         auto fits_static = [&](int i) { return i >= 0 && instance_workspace_bytes(t[i], p) <= kScratchBytes ? i : -1; };
-        const bool very_long_runs = (int64_t)p.num_seqs * kv >= 100000;
-        if (p.num_kv_heads >= 4 && (very_long_runs || (kv > 512 && kv <= 8192 && units * kv >= 500000))) {
+        if (p.num_kv_heads >= 4 && (very_long_runs(p) || (kv > 512 && kv <= 8192 && units * kv >= 500000))) {
             // two workgroups of four heads per compute unit measured 0.5-2 % ahead of one of eight from
             // eight KV heads on, 1-2 % behind at four
             if (p.num_kv_heads >= 8) id = find_instance(1, p, 4, 16, 32, 0, -1);
             if (id < 0) id = find_instance(1, p, 8, 16, 32, 0, -1);
-            if (!very_long_runs) id = fits_static(id);
+            if (!very_long_runs(p)) id = fits_static(id);
         }
         // Many short contexts: whole contexts, one wavefront per head, so that a workgroup reads whole cache
         // blocks and has no cross-wave reduction (1.1-1.5x at 1024 units or below 64 keys).
@@ -332,30 +380,11 @@ int heuristic(const KParams &p, int is_decode)
         if (id < 0 && kv <= (units >= 128 ? 1024 : p.head_dim == 64 ? 896 : 640))
             id = find_instance(1, p, kv > 128 && (units < 256 || kv > 512) ? 8 : 4, 16, 32, 0, 0);
         if (id < 0) {
-            // one KV head per workgroup and fixed parts: enough workgroups to fill the chip several times over,
-            // parts no shorter than 256 keys
-            int64_t want = units * kv / 2048;
-            int sl = 256;
-            while (sl * 2 <= want && sl < 4096) sl *= 2;
-            if (sl >= kv) sl = 0;
-            // a long context in few units gets longer parts and eight waves per workgroup rather than more
-            // than 32 parts
-            bool wide = false;
-            auto parts = [&]() { return (kv + sl - 1) / sl; };
-            while (sl > 0 && sl < 4096 && parts() > 32) {
-                sl *= 2;
-                wide = true;
-            }
-            // and the batch at most two parts per compute unit in all (the bound `usable` enforces); where fp16 and
-            // D = 64 were not split before they also stay within the static record array
+            // one KV head per workgroup and fixed parts; where fp16 and D = 64 were not split before they also stay
+            // within the static record array
             const bool bounded = p.dtype == kDtypeF16 || p.head_dim == 64;
-            auto too_many = [&]() {
-                return p.num_seqs * parts() > 2 * compute_units() ||
-                       (bounded && p.num_seqs * parts() * p.num_q_heads * partial_stride(p.head_dim) * (int64_t)sizeof(float) > (int64_t)kScratchBytes);
-            };
-            const int wanted = sl;
-            while (sl > 0 && sl < 4096 && too_many()) sl *= 2;
-            if (sl >= kv || (sl > 0 && too_many())) sl = 0;
+            const FixedParts fixed = fixed_part_length(p, bounded ? kScratchBytes : SIZE_MAX);
+            const int sl = fixed.length;
             // many long contexts of few KV heads, too many to split: still better than a serial walk of
             // each (142 contexts of 2000-15000 keys, 8/2 heads, D = 64: 1.8x)
             if (sl == 0 && kv > 2048) {
@@ -367,12 +396,12 @@ int heuristic(const KParams &p, int is_decode)
             // contexts, one of 3338 keys among 50s 11.5 against 25 us, 800-3338 evenly 47 against 43; 120 contexts, one
             // of 9000 14.6 against 46 us, evenly 77 against 79.  (The other types keep the parts, whose error against 64
             // bits is 2-7 % smaller, and so does one KV head, which leaves seven of eight wavefronts idle: 75 against 58.)
-            if (sl > wanted && sl >= 1024 && p.num_kv_heads > 1 && p.dtype == kDtypeF16 && p.head_dim == 64)
+            if (fixed.lengthened && sl >= 1024 && p.num_kv_heads > 1 && p.dtype == kDtypeF16 && p.head_dim == 64)
                 id = fits_static(find_instance(1, p, 8, 16, 32, 0, -1));
             // eight waves, one chunk each, also where every part has a compute unit to itself: one context of 1900
             // keys 10.9 -> 10.0 us, 3 of 1900 10.6 -> 9.9; two workgroups per unit lose (8 of 1900: 15.8 -> 18.0), and
             // from 4096 keys on the two are within 3 %
-            wide |= sl == 256 && kv < 4096 && units * parts() <= compute_units();
+            const bool wide = fixed.wide || (sl == 256 && kv < 4096 && units * ((kv + sl - 1) / sl) <= compute_units());
             if (id < 0 && wide) id = find_instance(1, p, 8, 16, 32, 0, sl);
             if (id < 0) id = find_instance(1, p, 4, 16, 32, 0, sl);
             if (id < 0) id = find_instance(1, p, 4, 16, 32, 0, 0);
@@ -692,12 +721,16 @@ int run(const attn_args *a, int is_decode, hipStream_t stream, int instance_over
     if (id < 0) return id;
     if (id >= n || !usable(t[id], p, is_decode)) return ATTN_ERR_UNSUPPORTED;
     if (is_decode) {
-        const size_t need = instance_workspace_bytes(t[id], p);
-        apply_split(p, t[id]);
-        if (need > 0) {
-            if (!a->workspace || a->workspace_bytes < need) return ATTN_ERR_WORKSPACE;
-            if ((uintptr_t)a->workspace & 7) return ATTN_ERR_WORKSPACE;  // records are accessed as 8-byte pairs
+        size_t need = instance_workspace_bytes(t[id], p);
+        if (need > 0 && (!a->workspace || a->workspace_bytes < need)) {
+            // (only the built-in choice gives way: neither a tuned nor a forced instance is replaced)
+            const int plain = served_without_workspace(p) ? find_instance(1, p, 4, 16, 32, 0, 0) : -1;
+            if (plain < 0 || instance_override >= 0 || g_forced[1].load() >= 0 || id != heuristic(p, 1)) return ATTN_ERR_WORKSPACE;
+            id = plain;
+            need = 0;
         }
+        apply_split(p, t[id]);
+        if (need > 0 && ((uintptr_t)a->workspace & 7)) return ATTN_ERR_WORKSPACE;  // records are accessed as 8-byte pairs
     }
     if (t[id].launch(p, stream) != hipSuccess) return ATTN_ERR_HIP;
     // fixed-split decode merges its parts with a second kernel (the token-balanced launcher brings its own)
