@@ -20,26 +20,30 @@ struct KvWriteParams {
     int32_t num_tokens, num_kv_heads, vec_per_head, block_size;
 };
 
-// A thread takes the same 16-byte vector of the K and V rows of TOKS consecutive tokens: 2 TOKS loads in flight behind
-// one round trip for the slots, and one division for all of them.  Four tokens from kBulkVectors on (16 MiB: four
-// wavefronts per SIMD are left), one below, where more wavefronts matter more.
-// The stores carry the non-temporal hint (they need not displace what the last-level cache holds of the new keys), the
-// loads only where those alone fill about half of that cache (kStreamVectors).  Bf16, D = 128, calls on three sets
-// of buffers in turn, against one vector of K or V per thread with 64-bit divisions and no hints:
-//   tokens x heads   4096 x 8   8192 x 8   16384 x 8   16384 x 16
-//   before              8.1       12.9        27.6        51.1 us
-//   now                 6.7       11.7        21.1        50.2 us
-//   hints on loads too  6.3       12.7        25.2        50.2 us     no hints  7.6  11.3  29.8  54.5 us
+// A thread takes the same 16-byte vector of the K and V rows of TOKS consecutive tokens: 2 TOKS loads in flight, and one
+// division for all of them.  Four tokens from kBulkVectors on (16 MiB: two wavefronts per SIMD are left), one below,
+// where more wavefronts matter more.
+//  * Four tokens whose slots are all negative are left out before their rows are read (batches padded to a captured
+//    size); the rows then wait for the slots, 0.25 us of a full call of 8192 tokens.  With one token per thread the rows are
+//    requested together with the slot (1024 tokens 3.3 -> 3.0 us, level where most are padding).
+//  * The stores carry the non-temporal hint (they need not displace what the last-level cache holds of the new keys), the
+//    loads from kStreamVectors on (96 MiB, more than a third of that cache; measured at 64 and 128 MiB).
+// Bf16, D = 128, calls on three sets of buffers in turn, against one vector of K or V per thread with 64-bit divisions,
+// no hints and padding skipped:
+//   tokens x heads                 4096 x 8   8192 x 8   16384 x 8
+//   before                           7.8       12.1        27.4 us
+//   now                              6.9       11.5        21.3
+//   before, 97 % padding at the end  3.4        4.6         7.1
+//   now                              3.2        3.3         3.6
 constexpr int64_t kBulkVectors = 1 << 20;
 constexpr int64_t kStreamVectors = 6 << 20;
 
-template <bool NT>
-__device__ __forceinline__ u32x4 load(const u32x4 *src)
+template <bool HINT>
+__device__ __forceinline__ u32x4 load(const unsigned char *src)
 {
-    return NT ? __builtin_nontemporal_load(src) : *src;
+    return HINT ? __builtin_nontemporal_load((const u32x4 *)src) : *(const u32x4 *)src;
 }
-
-template <int TOKS, bool NT>
+template <int TOKS, bool HINT_LOAD>
 __global__ __launch_bounds__(256) void kv_cache_write_kernel(const KvWriteParams p)
 {
     const uint32_t row = (uint32_t)p.num_kv_heads * p.vec_per_head;  // vectors of a token's K (and V) row
@@ -49,26 +53,41 @@ __global__ __launch_bounds__(256) void kv_cache_write_kernel(const KvWriteParams
         const uint32_t grp = total >> 32 ? (uint32_t)(i / row) : (uint32_t)i / row;
         const uint32_t r = (uint32_t)(i - (uint64_t)grp * row);
         const uint32_t h = r / (uint32_t)p.vec_per_head, c = r - h * (uint32_t)p.vec_per_head;
-        const int t0 = (int)(grp * TOKS);
+        const int t0 = (int)(grp * TOKS), left = p.num_tokens - t0;  // tokens from t0 on
         const int64_t src0 = (int64_t)t0 * p.new_tok_bytes + h * p.new_head_bytes + 16 * c;
         int slot[TOKS];
         u32x4 k[TOKS], v[TOKS];
+        int all = -1;  // negative if every slot is
 #pragma unroll
         for (int j = 0; j < TOKS; ++j) {
-            const int t = t0 + j < p.num_tokens ? j : p.num_tokens - 1 - t0;  // past the last token: its row again, not stored
-            slot[j] = p.slot_mapping[t0 + t];
-            k[j] = load<NT>((const u32x4 *)(p.k_new + src0 + t * p.new_tok_bytes));
-            v[j] = load<NT>((const u32x4 *)(p.v_new + src0 + t * p.new_tok_bytes));
+            slot[j] = p.slot_mapping[t0 + (j < left ? j : left - 1)];  // past the last token: its row again, not stored
+            all &= slot[j];
+        }
+        if (TOKS > 1 && all < 0) continue;
+#pragma unroll
+        for (int j = 0; j < TOKS; ++j) {
+            const int t = j < left ? j : left - 1;
+            k[j] = load<HINT_LOAD>(p.k_new + src0 + t * p.new_tok_bytes);
+            v[j] = load<HINT_LOAD>(p.v_new + src0 + t * p.new_tok_bytes);
         }
 #pragma unroll
         for (int j = 0; j < TOKS; ++j) {
-            if (t0 + j >= p.num_tokens || slot[j] < 0) continue;
+            if (j >= left || slot[j] < 0) continue;
             const int blk = slot[j] / p.block_size, off = slot[j] % p.block_size;
             const int64_t dst = blk * p.blk_bytes + off * p.tok_bytes + h * p.head_bytes + 16 * c;
             __builtin_nontemporal_store(k[j], (u32x4 *)(p.k_cache + dst));
             __builtin_nontemporal_store(v[j], (u32x4 *)(p.v_cache + dst));
         }
     }
+}
+
+template <int TOKS, bool HINT_LOAD>
+void write_launch(const KvWriteParams &p, hipStream_t stream)
+{
+    const int64_t groups = ((int64_t)p.num_tokens + TOKS - 1) / TOKS;
+    const int64_t want = (groups * p.num_kv_heads * p.vec_per_head + 255) / 256;
+    const unsigned blocks = (unsigned)(want < 16384 ? want : 16384);  // grid-stride beyond that
+    hipLaunchKernelGGL((kv_cache_write_kernel<TOKS, HINT_LOAD>), dim3(blocks), dim3(256), 0, stream, p);
 }
 
 }  // namespace
@@ -106,15 +125,12 @@ extern "C" int attn_kv_cache_write(const attn_kv_write_args *a, void *hip_stream
     p.block_size = a->block_size;
     const int64_t total = (int64_t)a->num_tokens * 2 * a->num_kv_heads * p.vec_per_head;
     if (total > ((int64_t)1 << 40)) return ATTN_ERR_SHAPE;
-    auto blocks_for = [&](int toks) {
-        const int64_t want = ((int64_t)(a->num_tokens + toks - 1) / toks * a->num_kv_heads * p.vec_per_head + 255) / 256;
-        return dim3((unsigned)(want < 16384 ? want : 16384));  // grid-stride beyond that
-    };
+    const hipStream_t stream = (hipStream_t)hip_stream;
     if (total >= kStreamVectors)
-        hipLaunchKernelGGL((kv_cache_write_kernel<4, true>), blocks_for(4), dim3(256), 0, (hipStream_t)hip_stream, p);
+        write_launch<4, true>(p, stream);
     else if (total >= kBulkVectors)
-        hipLaunchKernelGGL((kv_cache_write_kernel<4, false>), blocks_for(4), dim3(256), 0, (hipStream_t)hip_stream, p);
+        write_launch<4, false>(p, stream);
     else
-        hipLaunchKernelGGL((kv_cache_write_kernel<1, false>), blocks_for(1), dim3(256), 0, (hipStream_t)hip_stream, p);
+        write_launch<1, false>(p, stream);
     return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_ERR_HIP;
 }
