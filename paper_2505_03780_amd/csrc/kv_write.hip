@@ -26,8 +26,12 @@ struct KvWriteParams {
 //  * Four tokens whose slots are all negative are left out before their rows are read (batches padded to a captured
 //    size); the rows then wait for the slots, 0.25 us of a full call of 8192 tokens.  With one token per thread the rows are
 //    requested together with the slot (1024 tokens 3.3 -> 3.0 us, level where most are padding).
-//  * The stores carry the non-temporal hint (they need not displace what the last-level cache holds of the new keys), the
-//    loads from kStreamVectors on (96 MiB, more than a third of that cache; measured at 64 and 128 MiB).
+//  * The stores of calls from kHintVectors on carry the non-temporal hint (they need not displace what the last-level
+//    cache holds of the new keys).  Below, the call that reads the keys next pays for it: a write of 64 tokens and the
+//    prefill over them 11.05 us with the hint, 10.80 without, one token and a decode step over 20 keys 6.78 and 6.63; 256
+//    tokens and their decode step 32.1 and 32.6, a write of 2048 tokens alone 3.7 and 4.3.  The loads carry it from
+//    kStreamVectors on (96 MiB, more than a third of that cache; measured at 64 and 128 MiB).  A prefill over what a
+//    bulk call wrote takes the same time within 1 %.
 // Bf16, D = 128, calls on three sets of buffers in turn, against one vector of K or V per thread with 64-bit divisions,
 // no hints and padding skipped:
 //   tokens x heads                 4096 x 8   8192 x 8   16384 x 8
@@ -35,6 +39,7 @@ struct KvWriteParams {
 //   now                              6.9       11.5        21.3
 //   before, 97 % padding at the end  3.4        4.6         7.1
 //   now                              3.2        3.3         3.6
+constexpr int64_t kHintVectors = 1 << 15;
 constexpr int64_t kBulkVectors = 1 << 20;
 constexpr int64_t kStreamVectors = 6 << 20;
 
@@ -43,7 +48,16 @@ __device__ __forceinline__ u32x4 load(const unsigned char *src)
 {
     return HINT ? __builtin_nontemporal_load((const u32x4 *)src) : *(const u32x4 *)src;
 }
-template <int TOKS, bool HINT_LOAD>
+template <bool HINT>
+__device__ __forceinline__ void store(unsigned char *dst, u32x4 v)
+{
+    if (HINT)
+        __builtin_nontemporal_store(v, (u32x4 *)dst);
+    else
+        *(u32x4 *)dst = v;
+}
+
+template <int TOKS, bool HINT_LOAD, bool HINT_STORE>
 __global__ __launch_bounds__(256) void kv_cache_write_kernel(const KvWriteParams p)
 {
     const uint32_t row = (uint32_t)p.num_kv_heads * p.vec_per_head;  // vectors of a token's K (and V) row
@@ -75,19 +89,19 @@ __global__ __launch_bounds__(256) void kv_cache_write_kernel(const KvWriteParams
             if (j >= left || slot[j] < 0) continue;
             const int blk = slot[j] / p.block_size, off = slot[j] % p.block_size;
             const int64_t dst = blk * p.blk_bytes + off * p.tok_bytes + h * p.head_bytes + 16 * c;
-            __builtin_nontemporal_store(k[j], (u32x4 *)(p.k_cache + dst));
-            __builtin_nontemporal_store(v[j], (u32x4 *)(p.v_cache + dst));
+            store<HINT_STORE>(p.k_cache + dst, k[j]);
+            store<HINT_STORE>(p.v_cache + dst, v[j]);
         }
     }
 }
 
-template <int TOKS, bool HINT_LOAD>
+template <int TOKS, bool HINT_LOAD, bool HINT_STORE>
 void write_launch(const KvWriteParams &p, hipStream_t stream)
 {
     const int64_t groups = ((int64_t)p.num_tokens + TOKS - 1) / TOKS;
     const int64_t want = (groups * p.num_kv_heads * p.vec_per_head + 255) / 256;
     const unsigned blocks = (unsigned)(want < 16384 ? want : 16384);  // grid-stride beyond that
-    hipLaunchKernelGGL((kv_cache_write_kernel<TOKS, HINT_LOAD>), dim3(blocks), dim3(256), 0, stream, p);
+    hipLaunchKernelGGL((kv_cache_write_kernel<TOKS, HINT_LOAD, HINT_STORE>), dim3(blocks), dim3(256), 0, stream, p);
 }
 
 }  // namespace
@@ -127,10 +141,12 @@ extern "C" int attn_kv_cache_write(const attn_kv_write_args *a, void *hip_stream
     if (total > ((int64_t)1 << 40)) return ATTN_ERR_SHAPE;
     const hipStream_t stream = (hipStream_t)hip_stream;
     if (total >= kStreamVectors)
-        write_launch<4, true>(p, stream);
+        write_launch<4, true, true>(p, stream);
     else if (total >= kBulkVectors)
-        write_launch<4, false>(p, stream);
+        write_launch<4, false, true>(p, stream);
+    else if (total >= kHintVectors)
+        write_launch<1, false, true>(p, stream);
     else
-        write_launch<1, false>(p, stream);
+        write_launch<1, false, false>(p, stream);
     return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_ERR_HIP;
 }
