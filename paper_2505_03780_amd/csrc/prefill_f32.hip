@@ -132,14 +132,14 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_f32_kernel(const KParams 
     // added, key by key, to the rows that see them.  Rare: a test per value of such a chunk is all that finite inputs pay.
     auto keep_apart = [&](int c0, const float (&w)[4]) {
         auto finite = [](float x) { return (__float_as_uint(x) & 0x7f800000u) != 0x7f800000u; };
-        float probe = 0.f;  // NaN once a value is not finite
+        float probe[4] = {0.f, 0.f, 0.f, 0.f};  // NaN once a value is not finite
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
+        for (int j = 0; j < VJ; ++j)
 #pragma unroll
-            for (int j = 0; j < VJ; ++j)
+            for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) probe = __builtin_fmaf(vf[v][j][e], 0.f, probe);
-        if (__builtin_amdgcn_ballot_w64(!finite(probe)) == 0) return;
+                for (int v = 0; v < 4; ++v) probe[v] = __builtin_fmaf(vf[v][j][e], 0.f, probe[v]);
+        if (__builtin_amdgcn_ballot_w64(!finite((probe[0] + probe[1]) + (probe[2] + probe[3]))) == 0) return;
 #pragma unroll 1
         for (int kg = 0; kg < 4; ++kg) {
 #pragma unroll
