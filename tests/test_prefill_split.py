@@ -35,13 +35,24 @@ def test_rule_on_the_host():
 
 
 SHAPES = [  # Hq, Hkv, D, block (0: packed), new tokens, keys
+    (8, 2, 128, 0, [1, 7, 8, 9, 33], [1, 7, 8, 9, 33]),          # no prefix
+    (2, 2, 64, 0, [1, 65], [1, 65]),
     (8, 2, 128, 0, [1, 7, 8, 9, 33], [1, 31, 32, 33, 257]),      # 4 heads x 8 tokens a tile; chunk edges
+    (8, 2, 128, 0, [5, 1, 9, 8], [255, 256, 300, 520]),          # a wavefront's second and third chunk
     (4, 4, 128, 16, [31, 32, 33, 1], [255, 256, 257, 1030]),     # 1 head x 32 tokens; eight chunks exactly, one less, one more
     (6, 2, 128, 32, [5, 2, 70], [5, 700, 300]),                  # group of 3: one head a tile, three sub-groups
     (64, 1, 128, 16, [1, 2], [600, 17]),                         # group of 64: 32 heads x 1 token, two sub-groups
     (16, 2, 64, 128, [3, 4, 5, 0], [3, 290, 2000, 64]),          # D = 64, 8 heads x 4 tokens, an empty query
-    (2, 2, 64, 0, [1, 65], [40, 65]),
+    (2, 2, 64, 0, [1, 65, 2, 31, 33], [40, 65, 255, 257, 520]),
 ]
+
+
+def _packed(wl):
+    """The keys of a paged workload laid end to end."""
+    rows = [np.concatenate([x[wl.block_table[s, :-(-int(n) // wl.block_size)]].reshape(-1, *x.shape[2:])[:n] for s, n in enumerate(wl.seq_lens)])
+            for x in (wl.k, wl.v)]
+    start = np.concatenate([[0], np.cumsum(wl.seq_lens)]).astype(np.int32)
+    return W.Workload("packed", wl.kind, wl.dtype, wl.q, rows[0], rows[1], wl.query_start_loc, wl.seq_lens, wl.scale, wl.causal, kv_start_loc=start)
 
 
 @pytest.mark.gpu
@@ -52,16 +63,16 @@ def test_edges_against_the_oracle(shape, causal, scale, dtype):
     from attn_testlib import check_full
 
     Hq, Hkv, D, block, new, keys = SHAPES[shape]
-    keys = keys if block else new
     scale /= np.sqrt(float(D))  # (-6: a peaked softmax, and the sign moves into Q)
+    bs = block or 16
+    wl = W.make_paged(70 + shape, "prefill", new, keys, Hq, Hkv, D, bs, sum(-(-n // bs) for n in keys) + 3, scale=scale, causal=causal)
     if block:
-        wl = W.make_paged(70 + shape, "prefill", new, keys, Hq, Hkv, D, block, sum(-(-n // block) for n in keys) + 3, scale=scale, causal=causal)
         for s, n in enumerate(keys):  # slots past the end of a sequence hold NaN: nothing may read them
             b = wl.block_table[s, (n - 1) // block]
             wl.k[b, (n - 1) % block + 1:] = 0x7FC0
             wl.v[b, (n - 1) % block + 1:] = 0x7FC0
     else:
-        wl = W.make_prefill_contiguous(70 + shape, new, Hq, Hkv, D, scale=scale, causal=causal)
+        wl = _packed(wl)
     if dtype == "f16":
         wl = W.as_f16(wl)
     A.attn_force_instance(False, _instance(dtype, D))
@@ -83,11 +94,7 @@ def test_layouts_give_the_same_bits():
     A.attn_force_instance(False, _instance("bf16", 128))
     try:
         ref = to_host_f64(dw.run(False))
-        rows = [np.concatenate([x[paged.block_table[s, :-(-n // 16)]].reshape(-1, 2, 128)[:n] for s, n in enumerate(kv_lens)])
-                for x in (paged.k, paged.v)]
-        start = np.array([0, 900, 1233], np.int32)
-        packed = W.Workload("packed", "prefill", "bf16", paged.q, rows[0], rows[1], paged.query_start_loc, paged.seq_lens, paged.scale,
-                            True, kv_start_loc=start)
+        packed = _packed(paged)
         assert np.array_equal(to_host_f64(DeviceWorkload(packed).run(False)), ref)
         wide = torch.zeros(49, 8, 264, dtype=torch.bfloat16, device="cuda")
         wide[:, :, 128:256] = dw.q
