@@ -47,8 +47,6 @@ std::string build_id();
 constexpr int kMaxPartsPerSeq = 64;
 // The record array of attn_decode_paged_static.
 constexpr size_t kScratchBytes = (size_t)16 << 20;
-// Instance::stages of the decode kernels that keep two register sets in flight (one wavefront per head)
-constexpr int kStagesPerHead = 3;
 
 std::mutex g_mu;
 std::unordered_map<std::string, int> g_winner[2];  // [is_decode]: bucket key -> instance id
@@ -237,14 +235,15 @@ void apply_split(KParams &p, const Instance &inst)
 size_t instance_workspace_bytes(const Instance &inst, const KParams &p_in);
 
 // ---- built-in heuristic (used until a bucket has been tuned) -----------------------------------
-int find_instance(int is_decode, const KParams &p, int waves, int hpw, int bn, int bm, int split_len, int variant = 0, int stages = 0)
+int find_instance(int is_decode, const KParams &p, int waves, int hpw, int bn, int bm, int split_len, int variant = 0, int stages = 0,
+                  bool per_head = false)
 {
     int n;
     const Instance *t = instances(is_decode, &n);
     for (int i = 0; i < n; ++i) {
         if (!usable(t[i], p, is_decode)) continue;
         if (t[i].waves == waves && t[i].heads_per_wg == hpw && t[i].block_n == bn && (bm <= 0 || t[i].block_m == bm) &&
-            t[i].split_len == split_len && t[i].variant == variant && (stages <= 0 || t[i].stages == stages))
+            t[i].split_len == split_len && t[i].variant == variant && (stages <= 0 || t[i].stages == stages) && t[i].per_head == per_head)
             return i;
     }
     return -1;
@@ -340,7 +339,7 @@ int heuristic(const KParams &p, int is_decode)
         // a paged context adds the table entry to every transfer's address chain: the deepest prefetch
         // (8 units) measured up to 10 % ahead of 5 on the slower machines there, level elsewhere
         if (!small_wg && p.block_table) id = find_instance(0, p, 8, hpw, 32, 256, 0, order, 8);
-        if (id < 0) id = find_instance(0, p, small_wg ? 4 : 8, hpw, 32, small_wg ? 128 : 256, 0, order);  // LDS-ring kernel (D = 128)
+        if (id < 0) id = find_instance(0, p, small_wg ? 4 : 8, hpw, 32, small_wg ? 128 : 256, 0, order);  // LDS-ring kernel
         if (id < 0) id = find_instance(0, p, 8, hpw, 32, 256, 0, order);
         if (id < 0) id = find_instance(0, p, 4, hpw, 32, 256, 0, order);
         if (id < 0) id = find_instance(0, p, 4, hpw, 64, 64 * 4, 0);  // register-staged kernel
@@ -372,13 +371,14 @@ int heuristic(const KParams &p, int is_decode)
         // Many short contexts: whole contexts, one wavefront per head, so that a workgroup reads whole cache
         // blocks and has no cross-wave reduction (1.1-1.5x at 1024 units or below 64 keys).
         if (id < 0 && p.num_kv_heads >= 4 && ((units >= 1024 && kv <= 512) || (units >= 512 && kv <= 64)))
-            id = find_instance(1, p, 4, 16, 32, 0, 512, 0, kStagesPerHead);
+            id = find_instance(1, p, 4, 16, 32, 0, 512, 0, 0, true);
         // Short contexts are not split: the merge and its launch cost more than the walk (one context of 200 keys
         // 6.7 -> 5.7 us, 40 of 100-400 17.2 -> 14.3 us).  Where there are units enough to hide one another's
-        // latency that holds up to 1024 keys.  Eight wavefronts per workgroup above 128 keys, four where there is
-        // a unit for every compute unit.
+        // latency that holds up to 1024 keys.  Four wavefronts per workgroup up to 128 keys, and up to 512 where
+        // there is a unit for every compute unit; eight otherwise (513-1024 keys, 64 to 500 units: four take 1.02-1.3x as
+        // long; from 500 units on the two are within 5 %).
         if (id < 0 && kv <= (units >= 128 ? 1024 : p.head_dim == 64 ? 896 : 640))
-            id = find_instance(1, p, kv > 128 && (units < 256 || kv > 512) ? 8 : 4, 16, 32, 0, 0);
+            id = find_instance(1, p, kv > 128 && (units < compute_units() || kv > 512) ? 8 : 4, 16, 32, 0, 0);
         if (id < 0) {
             // one KV head per workgroup and fixed parts; where fp16 and D = 64 were not split before they also stay
             // within the static record array

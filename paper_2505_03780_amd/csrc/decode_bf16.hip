@@ -34,7 +34,7 @@ namespace {
 
 // This file is compiled twice: as it stands for bf16, and included by decode_f16.hip with
 // ATTN_DECODE_ELEM_F16 defined for fp16 caches (the element type only changes the MFMA opcode and the
-// conversions of weights and outputs; a smaller set of instances is built).
+// conversions of weights and outputs; fewer wave-per-head and token-balanced instances are built).
 #ifdef ATTN_DECODE_ELEM_F16
 typedef _Float16 elem_t;
 #define DECODE_MFMA __builtin_amdgcn_mfma_f32_16x16x32_f16
@@ -1095,8 +1095,8 @@ hipError_t combine_launch(const KParams &p, hipStream_t stream)
     }
 #define DECODE_SEQ_INSTANCE(HD, WAVES, SPLIT)                                                                  \
     {                                                                                                          \
-        DECODE_NAME "_seq d" #HD " w" #WAVES " split" #SPLIT, 16, kChunk, WAVES, 16, 3, SPLIT, decode_stream_valid<HD, WAVES>, \
-            decode_seq_launch<HD, WAVES>                                                                       \
+        DECODE_NAME "_seq d" #HD " w" #WAVES " split" #SPLIT, 16, kChunk, WAVES, 16, 2, SPLIT, decode_stream_valid<HD, WAVES>, \
+            decode_seq_launch<HD, WAVES>, 0, true                                                              \
     }
 
 #define DECODE_INSTANCE(HD, WAVES, SPLIT)                                                                     \

@@ -60,17 +60,18 @@ struct Instance {
     int split_len;  // decode: keys per split-K part (0 = never split); prefill: 0
     bool (*valid)(const KParams &);
     hipError_t (*launch)(const KParams &, hipStream_t);
-    int variant;  // prefill: KParams::tile_order this instance launches with; decode: 0
+    int variant = 0;  // prefill: KParams::tile_order this instance launches with; decode: 0
+    bool per_head = false;  // decode: fixed parts with one wavefront per KV head (otherwise all wavefronts share a KV head)
 };
 
 const Instance *prefill_instances(int *count);         // all prefill instances, ring variants first
-const Instance *prefill_ring_instances(int *count);    // LDS-ring, software-pipelined (D = 128), bf16
+const Instance *prefill_ring_instances(int *count);    // LDS-ring, software-pipelined (D = 64, 128), bf16
 const Instance *prefill_ring_f16_instances(int *count);  // the same kernel for fp16
 const Instance *prefill_staged_instances(int *count);  // register-staged double buffer (D = 64, 128)
 const Instance *prefill_staged_f16_instances(int *count);  // the same kernel for fp16
 const Instance *prefill_split_instances(int *count);  // few query rows, wavefronts split the keys; bf16 and fp16
 const Instance *decode_instances(int *count);       // bf16
-const Instance *decode_f16_instances(int *count);   // fp16: the wave-per-head and token-balanced kernels
+const Instance *decode_f16_instances(int *count);   // the same kernels for fp16
 
 hipError_t launch_prefill_f32(const KParams &, hipStream_t);
 hipError_t launch_decode_combine(const KParams &, hipStream_t);

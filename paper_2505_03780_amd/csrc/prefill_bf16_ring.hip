@@ -407,7 +407,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     };
     // V^T fragment images: a wave transposes its share of the V fragments of a unit once
     // (ds_read_b64_tr_b16, the slow path) and stores them in MFMA A-operand order; every wave then
-    // fetches all eight fragments with plain 128-bit reads.  Two images alternate.
+    // fetches all kFrags fragments with plain 128-bit reads.  Two images alternate.
     unsigned char *img_base = lds + NSLOT * kSlotBytes;
     // where inside a slot each of this lane's transposing reads goes (the same in every unit)
     int tr_off[C::kFragsPerWave][2];
@@ -556,10 +556,10 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     // re-read rows of a dummy transfer and every entry is masked): no branch inside the iteration.
     // LDS operations of one iteration, in issue order (the same in every iteration, so the position of
     // an operation of the previous iteration is known too):
-    //   phase X: V^T image fragments f = 0..7 (one per 1/8 of the phase), after fragment kTrAfter the wave's
+    //   phase X: V^T image fragments f = 0..KSTEPS-1 (one per step of the phase), after fragment kTrAfter the wave's
     //            transposing reads of V(u+1) (2 per fragment it owns), after fragment kWriteAfter the
     //            wave's image stores of V(u+1);
-    //   phase Y: K(u+2) fragments ks = 0..7, kKPerGroup per group from the first group on.
+    //   phase Y: K(u+2) fragments ks = 0..KSTEPS-1, kKPerGroup per group from the first group on.
     // A consumer waits until at most as many operations are outstanding as were issued after the one it
     // needs.  Nothing in the loop waits for "all": the image stores are older than the last image
     // fragments the same wave waits for in phase Y, so they have been performed when the wave reaches
@@ -633,8 +633,8 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const int ks = g / QB, qb = g % QB;
-            // K(u+1) fragment ks was read in phase Y of the previous iteration, at position kXOps + ks of
-            // kXOps + 8; since then the rest of that iteration and `seq` operations of this one were issued
+            // K(u+1) fragment ks was read in phase Y of the previous iteration, whose last KSTEPS LDS operations the
+            // K reads are; behind it the KSTEPS - 1 - ks later ones and `seq` operations of this iteration were issued
             if (qb == 0) lds_wait_upto((KSTEPS - 1 - ks) + seq, kf[ks]);
             nxt[qb] = E::mfma(__builtin_bit_cast(x8, kf[ks]), qf[qb][ks], ks == 0 ? zero : nxt[qb]);
             // weights of keys 0..15 (the B operand of the first four PV MFMAs): issued under the even steps,
@@ -911,6 +911,8 @@ const Instance *prefill_ring_f16_instances(int *count)
     return table;
 }
 #else
+// (The first and the last hpw1 entries are D = 128: a host test takes the last one as another valid instance of a D = 128
+// bucket.)
 const Instance *prefill_ring_instances(int *count)
 {
     static const Instance table[] = {

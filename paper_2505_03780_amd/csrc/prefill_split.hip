@@ -10,10 +10,10 @@
 //
 // Here a workgroup owns 32 query rows of one KV head, and each of its eight wavefronts takes every
 // eighth 32-key chunk of the keys with a softmax state of its own; no barrier until the states are
-// merged through LDS at the end.  That call takes 50 us.  What bounds it is the stream of K and V into one
+// merged through LDS at the end.  That call takes 51 us.  What bounds it is the stream of K and V into one
 // compute unit, because every workgroup reads all keys that its rows see, 512 bytes a key at D = 128: a
 // loop of nothing but such loads reaches 100-120 GB/s per compute unit from the caches and 50 GB/s from
-// HBM, however many loads are in flight, and the kernel runs at 100 GB/s (9000 keys).  32 rows (not 16)
+// HBM, however many loads are in flight; that call reads 7948 keys at 80 GB/s, start and merge included.  32 rows (not 16)
 // so that half as many workgroups read the keys of a KV head; rows are HPW heads of the KV head's
 // group times 32 / HPW tokens, because rows that share keys share the stream.
 //  * K and V go HBM -> registers as whole head slices (1 KB per wave-wide load), then through a
@@ -24,7 +24,8 @@
 //    at different places of the key axis, so that each fetches another part first, lost that sharing:
 //    121 against 76 us for 3 sequences of 64 tokens behind 8192 keys.  Idle compute units that touched the keys
 //    ahead gave 1 % on some shapes and cost as much on others.)
-//  * The reference of the exponentials moves only when a row outgrows it by 2^kSlack, as in the ring kernel.
+//  * The reference of the exponentials moves only when a row outgrows it by 2^kSlack, as in the ring kernel (D = 128; at
+//    D = 64 it is the running maximum).
 #include "kernel_params.hpp"
 
 #include <type_traits>
