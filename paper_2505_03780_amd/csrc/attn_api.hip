@@ -359,7 +359,7 @@ int heuristic(const KParams &p, int is_decode)
         // exceed the array of attn_decode_paged_static, which would then refuse the call; attn_decode_paged makes the
         // same choice, because the two entry points give the same bits.  That is only reached with very many query
         // heads; under 128 (8 KV heads, D = 128), token-balanced against split: 50 contexts of 325-1300 keys 44 against
-        // 47 us, one such among 50s 18 against 19; 20 of 1000-4000 50 against 59, one such among 50s 31 against 17.
+        // 47 us, one such among 50s 18 against 19; 20 of 1000-4000 49 against 57, one such among 50s 20 against 17.
         auto fits_static = [&](int i) { return i >= 0 && instance_workspace_bytes(t[i], p) <= kScratchBytes ? i : -1; };
         if (p.num_kv_heads >= 4 && (very_long_runs(p) || (kv > 512 && kv <= 8192 && units * kv >= 500000))) {
             // two workgroups of four heads per compute unit measured 0.5-2 % ahead of one of eight from

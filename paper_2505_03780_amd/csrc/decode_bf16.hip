@@ -890,17 +890,17 @@ __global__ __launch_bounds__(WAVES * 64, 8 / WAVES) void decode_balanced_kernel(
 // chunk range, at record indices workgroup + s.  One wavefront per (sequence, KV head, pair of query heads).
 constexpr int kMergeWaves = 4;  // (sequence, KV head, head pair) units per merge workgroup
 
-// With many sequences for the runs (BLK < 32) a sequence has few parts on average, but one long context among many short
-// ones may span most runs, and one wavefront would walk its records BLK at a time, a round trip each.  A sequence of
-// more than kLongParts parts is therefore left to a workgroup of its own per head pair, whose four wavefronts take a quarter of
-// the records each.  Helper j of a head pair looks at the sequence that lies across the end of run kLongParts * j; a
-// sequence of more than kLongParts runs lies across at least one such end and belongs to the first.  The helpers stand
-// behind the ordinary workgroups, where most of them find nothing and end (in front they cost 0.3 us).
-// One context of 32768 keys among 255 of 64 (32/8 heads), whole call: 70 -> 46 us at D = 128, 56 -> 30 at D = 64 (60 and 36
-// with 32 records per round trip for every sequence); even batches are level (200 contexts of 20-800 keys 63.7 us, 64 of
-// 512-4096 104.3 -> 104.5).
-constexpr int kLongParts = 16;
-inline int64_t long_helpers(int num_wgs) { return (num_wgs + kLongParts - 1) / kLongParts; }
+// A sequence has few parts on average, but one long context among short ones spans most runs, and one wavefront
+// would walk its records BLK at a time, a round trip each.  A sequence of more than long_parts(BLK) parts is therefore left
+// to a workgroup of its own per head pair, whose four wavefronts take a quarter of the records each.  Helper j of a head
+// pair looks at the sequence that lies across the end of run long_parts * j; a sequence of more than long_parts runs
+// lies across at least one such end and belongs to the first.  The helpers stand behind the ordinary workgroups, where
+// most of them find nothing and end (in front they cost 0.3 us).
+// Whole calls, one long context among short ones, 32/8 heads, D = 128, without helpers and with: 32768 keys among 255 of 64 70 ->
+// 46 us (D = 64 56 -> 30), 8000 among 25 of 100 34 -> 19, 8000 among 11 of 100 41 -> 20, 16000 among 10 of 300 47 -> 27; even
+// batches are level (200 contexts of 20-800 keys 63.7 us, 64 of 512-4096 104.3 -> 104.5, 16 of 16384-32768 244.6).
+constexpr int long_parts(int blk) { return blk < 32 ? 16 : 32; }
+inline int64_t long_helpers(int num_wgs, int blk) { return (num_wgs + long_parts(blk) - 1) / long_parts(blk); }
 
 // largest s with prefix[s] <= chunk, for chunk < prefix[B] (so sequence s holds it): 64 places per round trip
 __device__ __forceinline__ int sequence_of_chunk(const int32_t *prefix, int B, int chunk, int lane)
@@ -926,45 +926,44 @@ __global__ __launch_bounds__(64 * kMergeWaves) void decode_balanced_combine_kern
     const int32_t *prefix = (const int32_t *)(p.workspace + (int64_t)(num_wgs + B) * p.num_q_heads * (HD + 2));
     const int64_t stride = (int64_t)p.num_q_heads * (HD + 2);
     const int merge_blocks = (B * p.num_kv_heads * pairs + kMergeWaves - 1) / kMergeWaves;
-    if (BLK < 32) {
-        if ((int)blockIdx.x >= merge_blocks) {
-            const int units = p.num_kv_heads * pairs, h = blockIdx.x - merge_blocks;
-            const int j = h / units, unit = h % units;
-            const int total = prefix[B];
-            const int end = run_begin(total, num_wgs, j * kLongParts + 1);  // first chunk behind run j * kLongParts
-            if (end <= 0 || end >= total) return;
-            const int s = sequence_of_chunk(prefix, B, end, lane);
-            const int c0 = prefix[s], c1 = prefix[s + 1];
-            const int w0 = run_of(total, num_wgs, c0), parts = run_of(total, num_wgs, c1 - 1) - w0 + 1;
-            if (parts <= kLongParts || j * kLongParts < w0 || j * kLongParts - w0 >= kLongParts) return;  // (the same for all wavefronts)
-            const int kvh = unit / pairs, hl = 2 * (unit % pairs) + (lane >> 5);  // (an idle half repeats the last head)
-            const int hc = hl < p.group ? hl : p.group - 1;
-            const int per = (parts + kMergeWaves - 1) / kMergeWaves, first = wave * per;
-            const int mine = first >= parts ? 0 : parts - first < per ? parts - first : per;
-            MergeState<HD> st;
-            merge_parts<HD, 8>(st, p.workspace + (int64_t)(w0 + first + s) * stride + (int64_t)(kvh * p.group + hc) * (HD + 2), mine, stride, lane);
-            constexpr int CPL = HD / 32;
-            __shared__ float quarter[kMergeWaves][CPL + 2][64];
-            quarter[wave][CPL][lane] = st.M;
-            quarter[wave][CPL + 1][lane] = st.L;
+    constexpr int kLongParts = long_parts(BLK);
+    if ((int)blockIdx.x >= merge_blocks) {
+        const int units = p.num_kv_heads * pairs, h = blockIdx.x - merge_blocks;
+        const int j = h / units, unit = h % units;
+        const int total = prefix[B];
+        const int end = run_begin(total, num_wgs, j * kLongParts + 1);  // first chunk behind run j * kLongParts
+        if (end <= 0 || end >= total) return;
+        const int s = sequence_of_chunk(prefix, B, end, lane);
+        const int c0 = prefix[s], c1 = prefix[s + 1];
+        const int w0 = run_of(total, num_wgs, c0), parts = run_of(total, num_wgs, c1 - 1) - w0 + 1;
+        if (parts <= kLongParts || j * kLongParts < w0 || j * kLongParts - w0 >= kLongParts) return;  // (the same for all wavefronts)
+        const int kvh = unit / pairs, hl = 2 * (unit % pairs) + (lane >> 5);  // (an idle half repeats the last head)
+        const int hc = hl < p.group ? hl : p.group - 1;
+        const int per = (parts + kMergeWaves - 1) / kMergeWaves, first = wave * per;
+        const int mine = first >= parts ? 0 : parts - first < per ? parts - first : per;
+        MergeState<HD> st;
+        merge_parts<HD, BLK < 32 ? 8 : 16>(st, p.workspace + (int64_t)(w0 + first + s) * stride + (int64_t)(kvh * p.group + hc) * (HD + 2), mine, stride, lane);
+        constexpr int CPL = HD / 32;
+        __shared__ float quarter[kMergeWaves][CPL + 2][64];
+        quarter[wave][CPL][lane] = st.M;
+        quarter[wave][CPL + 1][lane] = st.L;
 #pragma unroll
-            for (int c = 0; c < CPL; ++c) quarter[wave][c][lane] = st.acc[c];
-            __syncthreads();
-            if (wave != 0) return;
-            MergeState<HD> all;
+        for (int c = 0; c < CPL; ++c) quarter[wave][c][lane] = st.acc[c];
+        __syncthreads();
+        if (wave != 0) return;
+        MergeState<HD> all;
 #pragma unroll
-            for (int w = 0; w < kMergeWaves; ++w) all.M = fmaxf(all.M, quarter[w][CPL][lane]);
+        for (int w = 0; w < kMergeWaves; ++w) all.M = fmaxf(all.M, quarter[w][CPL][lane]);
 #pragma unroll
-            for (int w = 0; w < kMergeWaves; ++w) {
-                const float m = quarter[w][CPL][lane];
-                const float sc = m == -INFINITY ? 0.f : fast_exp2(m - all.M);
-                all.L += quarter[w][CPL + 1][lane] * sc;
+        for (int w = 0; w < kMergeWaves; ++w) {
+            const float m = quarter[w][CPL][lane];
+            const float sc = m == -INFINITY ? 0.f : fast_exp2(m - all.M);
+            all.L += quarter[w][CPL + 1][lane] * sc;
 #pragma unroll
-                for (int c = 0; c < CPL; ++c) all.acc[c] += quarter[w][c][lane] * sc;
-            }
-            all.store((elem_t *)p.out + (int64_t)s * p.o_stride_tok + (int64_t)(kvh * p.group + hc) * p.o_stride_head + (HD / 32) * (lane & 31));
-            return;
+            for (int c = 0; c < CPL; ++c) all.acc[c] += quarter[w][c][lane] * sc;
         }
+        all.store((elem_t *)p.out + (int64_t)s * p.o_stride_tok + (int64_t)(kvh * p.group + hc) * p.o_stride_head + (HD / 32) * (lane & 31));
+        return;
     }
     int bid = blockIdx.x * kMergeWaves + wave;
     if (bid >= B * p.num_kv_heads * pairs) return;
@@ -977,7 +976,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void decode_balanced_combine_kern
     const int w0 = c1 > c0 ? run_of(total, num_wgs, c0) : 0;
     const int parts = c1 > c0 ? run_of(total, num_wgs, c1 - 1) - w0 + 1 : 0;
     if (parts == 1) return;  // the main kernel wrote this sequence itself
-    if (BLK < 32 && parts > kLongParts) return;  // left to a helper
+    if (parts > kLongParts) return;  // left to a helper
     merge_pair<HD, BLK>(p, lane, s, kvh, pair, p.workspace + (int64_t)(w0 + s) * stride + (int64_t)kvh * p.group * (HD + 2), parts, HD + 2, stride);
 }
 
@@ -1052,7 +1051,7 @@ hipError_t decode_balanced_launch(const KParams &p, hipStream_t stream)
     const int64_t pairs = (int64_t)p.num_kv_heads * ((p.group + 1) / 2);
     // num_splits runs over num_seqs sequences: a sequence is cut at about as many places as its share of the runs
     const int blk = merge_block((p.num_splits + p.num_seqs - 1) / p.num_seqs + 1);
-    const int64_t merge_blocks = (p.num_seqs * pairs + kMergeWaves - 1) / kMergeWaves + (blk < 32 ? long_helpers(p.num_splits) * pairs : 0);
+    const int64_t merge_blocks = (p.num_seqs * pairs + kMergeWaves - 1) / kMergeWaves + long_helpers(p.num_splits, blk) * pairs;
     if (merge_blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)merge_blocks), block(64 * kMergeWaves);
     if (blk == 4)

@@ -60,7 +60,9 @@ def test_token_balanced(lens, dtype, D):
     [0] * 30 + [32] * 200 + [32 * 17],    # at the end, 17 parts: one more than a wavefront of the ordinary merge takes on
     [32] * 200 + [32 * 16] + [0] * 30,    # 16 parts: the most that it does
     [32 * 40, 1, 32 * 40, 0, 32 * 40] + [20] * 95,  # several long ones next to each other
-    [32 * 16 + 1] * 15 + [5] * 70])       # every helper's sequence is another one, 17 chunks each
+    [32 * 16 + 1] * 15 + [5] * 70,        # every helper's sequence is another one, 17 chunks each
+    [32] * 5 + [32 * 32] + [0, 32],       # few sequences: 32 parts, the most that an ordinary merge takes on
+    [32 * 33, 32], [32 * 100, 1, 32 * 99, 3], [32 * 256], [32 * 300, 5]])  # 33, two next to each other, a run each and more
 def test_token_balanced_long_among_short(lens, dtype, D, Hq, Hkv):
     """Sequences of more parts than one wavefront merges, among many of one part."""
     wl = W.make_paged(98, "decode", np.ones(len(lens), np.int32), lens, Hq, Hkv, D, 16, sum(-(-n // 16) for n in lens) + 1, causal=False)
@@ -73,14 +75,15 @@ def test_token_balanced_long_among_short(lens, dtype, D, Hq, Hkv):
         A.attn_force_instance(True, -1)
 
 
-def test_merge_of_a_long_context_among_short_ones_is_not_serial():
-    """One context of 32768 keys among 255 of 64 against 256 equal contexts of as many keys in all: the kernels that walk the keys
-    take the same time, and so must the merge, within a factor of two of the whole (it was 3.3 with the long context's 170
-    records walked four at a time, and is 1.6)."""
+@pytest.mark.parametrize("skew,equal,name", [([32768] + [64] * 255, [192] * 256, "d64 w8 percu1"), ([8000] + [100] * 11, [758] * 12, "d128 w4 percu1")])
+def test_merge_of_a_long_context_among_short_ones_is_not_serial(skew, equal, name):
+    """One long context among short ones against equal contexts of as many keys in all: the kernels that walk the keys take the same
+    time, and so must the merge, within a factor of two of the whole (with the long context's records walked block by block by one
+    wavefront it was 2.6 and 2.4; it is 1.4 and 1.1)."""
     import torch
 
     def median_us(lens):
-        wl = W.make_paged(99, "decode", np.ones(len(lens), np.int32), lens, 32, 8, 64, 16, sum(-(-n // 16) for n in lens) + 1, causal=False)
+        wl = W.make_paged(99, "decode", np.ones(len(lens), np.int32), lens, 32, 8, int(name[1:4]), 16, sum(-(-n // 16) for n in lens) + 1, causal=False)
         dw = DeviceWorkload(wl)
         a = dw.args(True)
         assert "balanced" in A.attn_instance_name(True, A.attn_selected_instance(a, True))
@@ -98,9 +101,9 @@ def test_merge_of_a_long_context_among_short_ones_is_not_serial():
             times.append(100 * e0.elapsed_time(e1))
         return sorted(times)[15]
 
-    A.attn_force_instance(True, next(i for i in range(A.attn_num_instances(True)) if A.attn_instance_name(True, i) == "decode_bf16_balanced d64 w8 percu1"))
+    A.attn_force_instance(True, next(i for i in range(A.attn_num_instances(True)) if A.attn_instance_name(True, i) == "decode_bf16_balanced " + name))
     try:
-        skewed, even = median_us([32768] + [64] * 255), median_us([192] * 256)
+        skewed, even = median_us(skew), median_us(equal)
     finally:
         A.attn_force_instance(True, -1)
     print("skewed %.1f us, even %.1f us" % (skewed, even), flush=True)
