@@ -86,6 +86,8 @@ def load_library():
     lib.attn_static_scratch_bytes.argtypes = []
     lib.attn_workspace_bytes.restype = ctypes.c_size_t
     lib.attn_workspace_bytes.argtypes = [P, ctypes.c_int]
+    lib.attn_prefill_scratch_bytes.restype = ctypes.c_size_t
+    lib.attn_prefill_scratch_bytes.argtypes = [P]
     lib.attn_tune.restype = ctypes.c_int
     lib.attn_tune.argtypes = [P, ctypes.c_int, ctypes.c_char_p, ctypes.c_int, ctypes.c_int]
     lib.attn_environment_key.restype = ctypes.c_int
@@ -127,6 +129,10 @@ def load_library():
         f.restype = ctypes.c_int
         f.argtypes = [ctypes.c_char_p, ctypes.c_void_p]
         _hot[name] = f
+    f = lib["attn_prefill_scratch_bytes"]
+    f.restype = ctypes.c_size_t
+    f.argtypes = [ctypes.c_char_p]
+    _hot["attn_prefill_scratch_bytes"] = f
     _lib = lib
     return lib
 
@@ -255,6 +261,7 @@ def _attn_fields(q, k, v, out, seq_lens, scale, max_q_len, max_kv_len, query_sta
 
 _ATTN_BYTES = ctypes.sizeof(AttnArgs)
 _pack_attn = struct.Struct("@I8iPqqPqqPPqqqPiiiPPPfiPQ").pack
+_pack_workspace = struct.Struct("@PQ").pack  # the last two fields of AttnArgs
 _pack_kv_write = struct.Struct("@I7iPPqqPPqqqP").pack
 _pack_rmsnorm = struct.Struct("@IiiiPqPqPPqf4x").pack
 
@@ -284,15 +291,46 @@ def _stream_ptr(stream) -> int:
     return _raw_stream(_current_device())
 
 
+def _prefill_scratch(packed: bytes, stream):
+    """A workspace for the prefill call described by ``packed`` on ``stream``, or None.  The block belongs to that stream's pool
+    of the caching allocator: once freed it is only handed out to later work of the same stream."""
+    n = _hot["attn_prefill_scratch_bytes"](packed)
+    if n == 0:
+        return None
+    import torch
+
+    if stream is not None:
+        with torch.cuda.stream(stream):
+            return _scratch_block(torch, n)
+    return _scratch_block(torch, n)
+
+
+def _scratch_block(torch, n: int):
+    if torch.cuda.is_current_stream_capturing():
+        return None
+    try:
+        return torch.empty(n, dtype=torch.uint8, device="cuda")
+    except torch.cuda.OutOfMemoryError:
+        return None  # the call runs without
+
+
 def attn_prefill_varlen(q, k, v, out, query_start_loc, seq_lens, scale, *, max_q_len, max_kv_len, causal=True,
                         block_table=None, kv_start_loc=None, stream=None, args: Optional[AttnArgs] = None) -> None:
-    """Enqueue causal variable-length (or chunked, over a paged prefix) prefill on ``stream``."""
+    """Enqueue causal variable-length (or chunked, over a paged prefix) prefill on ``stream``.
+
+    A call of few query rows over many keys takes a workspace from torch's caching allocator for its time on the
+    stream, so that its keys can be split over the whole GPU; not under graph capture, where nobody would hold the memory for
+    the replays (pass ``args`` with a workspace of attn_prefill_scratch_bytes there)."""
     lib = _lib or load_library()
     if args:
         rc = lib.attn_prefill_varlen(ctypes.byref(args), _stream_ptr(stream))
     else:
         a = _packed(_pack_attn, AttnArgs, _attn_fields(q, k, v, out, seq_lens, scale, max_q_len, max_kv_len, query_start_loc, kv_start_loc,
                                                        block_table, causal, None))
+        # (necessary conditions of the library's own rule, to save short calls the question)
+        scratch = _prefill_scratch(a, stream) if max_kv_len > 1024 and q.shape[0] * q.shape[1] <= 16384 else None
+        if scratch is not None:
+            a = a[:-16] + _pack_workspace(scratch.data_ptr(), scratch.nbytes)
         rc = _hot["attn_prefill_varlen"](a, _stream_ptr(stream))
     if rc != 0:
         raise AttnError(rc, "attn_prefill_varlen")
@@ -333,6 +371,10 @@ def attn_static_scratch_bytes() -> int:
 
 def attn_workspace_bytes(args: AttnArgs, is_decode: bool) -> int:
     return int(load_library().attn_workspace_bytes(ctypes.byref(args), 1 if is_decode else 0))
+
+
+def attn_prefill_scratch_bytes(args: AttnArgs) -> int:
+    return int(load_library().attn_prefill_scratch_bytes(ctypes.byref(args)))
 
 
 def attn_tune(args: AttnArgs, is_decode: bool, cache_path: Optional[str] = None, iters: int = 20, flags: int = 0) -> None:

@@ -135,6 +135,7 @@ KParams to_kparams(const attn_args *a, int is_decode)
     p.block_table_stride = a->block_table_stride;
     p.block_size = a->block_table ? a->block_size : 0;
     p.block_shift = a->block_table ? ilog2_ceil(a->block_size) : 0;
+    p.total_q = a->total_q;
     p.max_q_len = is_decode ? 1 : a->max_q_len;
     p.max_kv_len = a->max_kv_len;
     p.scale = a->scale;
@@ -262,10 +263,44 @@ int find_instance(int is_decode, const KParams &p, int waves, int hpw, int bn, i
 //    ring is ahead but for the longest contexts.
 bool few_rows_many_keys(const KParams &p)
 {
-    const int heads = std::min(p.group & -p.group, 32), tok = 32 / heads;
-    const int64_t wgs = (int64_t)p.num_seqs * ((p.max_q_len + tok - 1) / tok) * (p.num_q_heads / heads);
+    const int64_t wgs = split_workgroups(p);
     const int two_from = p.head_dim == 64 ? 1024 : 1536;
     return (p.max_kv_len >= 160 && wgs <= compute_units()) || (p.max_kv_len > two_from && wgs <= 2 * compute_units());
+}
+
+// Parts into which the key-split prefill kernel cuts the keys of a call that brings a workspace, and the bytes of their records.
+// The number that a model of the call's time finds shortest: one workgroup per compute unit at a time, 4 us for its start and
+// its merge through LDS, 1.5 us (D = 64: 1 us) for each 256 keys, 5 us for the second kernel, and 8 % ahead of whole key
+// ranges (25 % from half a workgroup per compute unit on, where uneven lengths decide) or not at all.  Over 4000 random shapes
+// (batch 1-32, 1-1024 new tokens, 1024-16384 keys, up to two workgroups per compute unit) its choice takes 1.02x the time of the
+// best number of parts measured, 1.10x at the 95th percentile, and whole key ranges take 1.3x on average: 2 x 4 tokens behind
+// 5900 keys 46 -> 24 us, 1 x 4 behind 3300 25 -> 13, 2 x 9-12 behind 14000-18700 138 -> 48.
+constexpr int kMaxKeyParts = 32;
+int key_parts(const KParams &p)
+{
+    const int64_t cus = compute_units();
+    // workgroups that find work: the grid has the longest query's tiles for every sequence
+    const int heads = split_heads(p.group), tok = kSplitRows / heads;
+    const int64_t wgs = std::min(split_workgroups(p), ((int64_t)p.total_q / tok + p.num_seqs) * (p.num_q_heads / heads));
+    const double step_us = p.head_dim == 64 ? 1.0 : 1.5;
+    auto model_us = [&](int parts) {
+        const int64_t rounds = (wgs * parts + cus - 1) / cus, steps = ((p.max_kv_len + parts - 1) / parts + 255) / 256;
+        return (double)rounds * (4.0 + step_us * (double)steps) + (parts > 1 ? 5.0 : 0.0);
+    };
+    int best = 1;
+    double best_us = model_us(1) / (2 * wgs > cus ? 1.25 : 1.08);
+    for (int parts = 2; parts <= kMaxKeyParts && split_workgroups(p) * parts <= 4 * cus; ++parts) {
+        const double us = model_us(parts);
+        if (us < best_us) {
+            best = parts;
+            best_us = us;
+        }
+    }
+    return best;
+}
+size_t key_parts_bytes(const KParams &p, int parts)
+{
+    return parts <= 1 ? 0 : (size_t)split_workgroups(p) * parts * kSplitRows * partial_stride(p.head_dim) * sizeof(float);
 }
 
 // Part length of the fixed splits (0: whole contexts): enough workgroups to fill the chip several times over, parts no
@@ -731,6 +766,9 @@ int run(const attn_args *a, int is_decode, hipStream_t stream, int instance_over
         }
         apply_split(p, t[id]);
         if (need > 0 && ((uintptr_t)a->workspace & 7)) return ATTN_ERR_WORKSPACE;  // records are accessed as 8-byte pairs
+    } else if (t[id].key_parts && a->workspace && ((uintptr_t)a->workspace & 15) == 0) {
+        const int parts = key_parts(p);
+        if (parts > 1 && a->workspace_bytes >= key_parts_bytes(p, parts)) p.num_splits = parts;  // (else: whole key ranges)
     }
     if (t[id].launch(p, stream) != hipSuccess) return ATTN_ERR_HIP;
     // fixed-split decode merges its parts with a second kernel (the token-balanced launcher brings its own)
@@ -898,7 +936,8 @@ int tune(const attn_args *shape, int is_decode, const char *cache_path, int iter
 
     int rc = validate(&a, is_decode);
     if (rc != ATTN_OK) return rc;
-    const size_t ws_bytes = is_decode ? decode_workspace_bytes(to_kparams(&a, is_decode)) : 0;
+    const KParams sized = to_kparams(&a, is_decode);
+    const size_t ws_bytes = is_decode ? decode_workspace_bytes(sized) : key_parts_bytes(sized, key_parts(sized));
     if (dws.alloc(ws_bytes) != hipSuccess) {
         (void)hipGetLastError();
         return ATTN_ERR_HIP;
@@ -1242,6 +1281,21 @@ size_t attn_workspace_bytes(const attn_args *a, int is_decode)
         p.block_shift = ilog2_ceil(p.block_size);
     }
     return decode_workspace_bytes(p);
+}
+
+size_t attn_prefill_scratch_bytes(const attn_args *a)
+{
+    if (!a || a->struct_bytes != sizeof(attn_args)) return 0;
+    if (a->num_seqs <= 0 || a->total_q <= 0 || a->num_q_heads <= 0 || a->num_kv_heads <= 0 || a->num_q_heads % a->num_kv_heads ||
+        a->max_q_len < 0 || a->max_kv_len < 0 || (a->head_dim != 64 && a->head_dim != 128) || !is16(a->dtype))
+        return 0;
+    const KParams p = to_kparams(a, 0);
+    const int parts = key_parts(p);
+    if (parts <= 1) return 0;
+    int n;
+    const Instance *t = instances(0, &n);
+    const int id = select_instance(p, a->dtype, 0);
+    return id >= 0 && id < n && t[id].key_parts ? key_parts_bytes(p, parts) : 0;
 }
 
 int attn_tune(const attn_args *shape_like, int is_decode, const char *cache_path, int iters, int flags)

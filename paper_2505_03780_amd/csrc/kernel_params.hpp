@@ -33,11 +33,11 @@ struct KParams {
     int32_t group;  // Hq / Hkv
     int32_t block_table_stride;
     int32_t block_size, block_shift;  // block_size == 1 << block_shift when block_shift >= 0
-    int32_t max_q_len, max_kv_len;
+    int32_t total_q, max_q_len, max_kv_len;
     float scale;        // softmax scale
     float scale_log2e;  // scale * log2(e): scores are exponentiated with exp2
     int32_t causal;
-    // split-K decode
+    // split-K decode, and prefill of few query rows over many keys
     float *workspace;
     int32_t num_splits;  // parts the key axis is cut into (grid dimension)
     int32_t split_len;   // keys per part, a multiple of the kernel's key tile
@@ -62,6 +62,7 @@ struct Instance {
     hipError_t (*launch)(const KParams &, hipStream_t);
     int variant = 0;  // prefill: KParams::tile_order this instance launches with; decode: 0
     bool per_head = false;  // decode: fixed parts with one wavefront per KV head (otherwise all wavefronts share a KV head)
+    bool key_parts = false;  // prefill: the keys may be cut into KParams::num_splits parts, whose records go to the workspace
 };
 
 const Instance *prefill_instances(int *count);         // all prefill instances, ring variants first
@@ -94,5 +95,19 @@ inline hipError_t allow_dynamic_lds(const void *kernel, size_t bytes, std::atomi
 // Floats per (sequence, query head, split) in the split-K workspace: D partial
 // outputs followed by the running max and the running sum.
 inline int partial_stride(int head_dim) { return head_dim + 2; }
+
+// The key-split prefill kernel (prefill_split.hip): rows (heads x tokens) of a workgroup, the query heads that share one
+// (a power of two, at most 32, that divides the group), and the workgroups of a call whose keys are not cut into parts.
+constexpr int kSplitRows = 32;
+__host__ __device__ inline int split_heads(int group)
+{
+    const int h = group & -group;
+    return h < kSplitRows ? h : kSplitRows;
+}
+inline int64_t split_workgroups(const KParams &p)
+{
+    const int heads = split_heads(p.group), tok = kSplitRows / heads;
+    return (int64_t)p.num_seqs * ((p.max_q_len + tok - 1) / tok) * (p.num_q_heads / heads);
+}
 
 }  // namespace attn

@@ -24,6 +24,10 @@
 //    at different places of the key axis, so that each fetches another part first, lost that sharing:
 //    121 against 76 us for 3 sequences of 64 tokens behind 8192 keys.  Idle compute units that touched the keys
 //    ahead gave 1 % on some shapes and cost as much on others.)
+//  * Where even these workgroups leave compute units idle, a call that brings a workspace has the keys of every
+//    sequence cut into parts (grid dimension y): a part's workgroups leave records, which
+//    prefill_split_merge_kernel merges (about 5 us with its launch).  2 x 4 tokens behind 5900 keys: 46 -> 24 us in
+//    eight parts, 2 x 9-12 behind 14000-18700 138 -> 48 us; key_parts in attn_api.hip has the rule.
 //  * The reference of the exponentials moves only when a row outgrows it by 2^kSlack, as in the ring kernel (D = 128; at
 //    D = 64 it is the running maximum).
 #include "kernel_params.hpp"
@@ -54,9 +58,10 @@ struct SplitF16 {
     static __device__ __forceinline__ f32x16 mfma(x8 a, x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
 };
 
-constexpr int kRows = 32;    // query rows (heads x tokens) of a workgroup
+constexpr int kRows = kSplitRows;  // query rows (heads x tokens) of a workgroup
 constexpr int kChunk = 32;   // keys per wavefront step
 constexpr int kWaves = 8;
+constexpr int kStep = kWaves * kChunk;  // keys per step of all wavefronts
 // log2 of the largest weight tolerated before the reference moves, as in the ring kernel
 template <int HD>
 constexpr float kSlack = HD == 64 ? 0.f : 8.f;
@@ -89,12 +94,49 @@ __device__ __forceinline__ float swap32_sum(float x)
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// hpw (a power of two, at most 32, divides the group) query heads of one KV head x 32 / hpw tokens per workgroup
-__host__ __device__ inline int split_heads(int group)
+// What a workgroup of the unsplit grid (index w) stands for: hpw query heads of one KV head x tok tokens of one sequence.
+struct SplitTile {
+    int hpw, log_hpw, tok;
+    int kvh, head0, s, q0, n_q, n_kv, off, t0;
+    int kv_end;    // keys that any row of the tile sees
+    int part_len;  // keys of a part, a multiple of kStep
+    int n_parts;   // parts of the tile that hold keys it sees (at least 1)
+};
+__device__ __forceinline__ SplitTile split_tile(const KParams &p, int w)
 {
-    int h = group & -group;
-    return h < kRows ? h : kRows;
+    SplitTile t;
+    t.hpw = split_heads(p.group);
+    t.log_hpw = __builtin_ctz(t.hpw);
+    t.tok = kRows >> t.log_hpw;
+    const int hsubs = p.group >> t.log_hpw;
+    const int q_tiles = (p.max_q_len + t.tok - 1) / t.tok;
+    t.kvh = w % p.num_kv_heads;  // KV head fastest, as in the other kernels
+    w /= p.num_kv_heads;
+    t.head0 = t.kvh * p.group + ((w % hsubs) << t.log_hpw);
+    w /= hsubs;
+    t.s = w % p.num_seqs;
+    t.t0 = (q_tiles - 1 - w / p.num_seqs) * t.tok;  // costly (late) tiles first
+    t.q0 = p.query_start_loc[t.s];
+    t.n_q = p.query_start_loc[t.s + 1] - t.q0;
+    t.n_kv = p.seq_lens[t.s];
+    t.off = t.n_kv - t.n_q;
+    t.kv_end = t.n_kv;
+    if (p.causal) {
+        const int last_tok = t.t0 + t.tok < t.n_q ? t.t0 + t.tok : t.n_q;
+        t.kv_end = t.off + last_tok < t.n_kv ? t.off + last_tok : t.n_kv;
+    }
+    // equal parts of the sequence (not of the tile: the tiles of a sequence then read the same keys at about the same time)
+    t.part_len = t.n_kv;
+    t.n_parts = 1;
+    if (p.num_splits > 1) {
+        t.part_len = ((t.n_kv + p.num_splits - 1) / p.num_splits + kStep - 1) & ~(kStep - 1);
+        if (t.kv_end > t.part_len) t.n_parts = (t.kv_end + t.part_len - 1) / t.part_len;
+    }
+    return t;
 }
+// Record of a part of a tile: kRows rows of HD unnormalised outputs, then (reference, sum) of every row.
+template <int HD>
+constexpr int kRecordFloats = kRows *(HD + 2);
 
 template <typename E, int HD, bool PAGED>
 __global__ __launch_bounds__(kWaves * 64) void prefill_split_kernel(const KParams p)
@@ -109,32 +151,21 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_split_kernel(const KParam
     constexpr int NLD = kChunk / RPL;        // loads per lane, for K and again for V
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
 
-    // ---- which (KV head, head sub-group, sequence, query tile): KV head fastest, as in the other kernels ----
-    const int hpw = split_heads(p.group);
-    const int log_hpw = __builtin_ctz(hpw);
-    const int tok = kRows >> log_hpw;  // tokens of a workgroup
-    const int hsubs = p.group >> log_hpw;
-    const int q_tiles = (p.max_q_len + tok - 1) / tok;
-    int bid = blockIdx.x;
-    const int kvh = bid % p.num_kv_heads;
-    bid /= p.num_kv_heads;
-    const int hsub = bid % hsubs;
-    bid /= hsubs;
-    const int s = bid % p.num_seqs;
-    const int r = bid / p.num_seqs;  // costly (late) tiles first
-    const int q0 = p.query_start_loc[s];
-    const int n_q = p.query_start_loc[s + 1] - q0;
-    const int n_kv = p.seq_lens[s];
-    const int off = n_kv - n_q;
-    const int t0 = (q_tiles - 1 - r) * tok;
-    if (t0 >= n_q) return;
+    // ---- which part of the keys (outermost: the tiles of a sequence walk a part side by side) of which tile ----
+    const int part = (int)blockIdx.y, w = (int)blockIdx.x;
+    const SplitTile T = split_tile(p, w);
+    const int hpw = T.hpw, log_hpw = T.log_hpw;
+    const int kvh = T.kvh, head0 = T.head0, s = T.s;
+    const int q0 = T.q0, n_q = T.n_q, n_kv = T.n_kv, off = T.off, t0 = T.t0;
+    if (t0 >= n_q || part >= T.n_parts) return;
+    const int kv_begin = part * T.part_len;
+    const int kv_end = T.kv_end < kv_begin + T.part_len ? T.kv_end : kv_begin + T.part_len;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lhalf = lane >> 5;
     const int l32 = lane & 31;
-    const int head0 = kvh * p.group + (hsub << log_hpw);
 
     // scores are exponentiated as 2^(c*s - ref); a negative scale is moved into Q (sign flips are exact)
     const float c = fabsf(p.scale_log2e);
@@ -156,13 +187,9 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_split_kernel(const KParam
         limit = p.causal && off + t < n_kv - 1 ? off + t : n_kv - 1;
     }
 
-    // ---- keys that any row of the tile sees, and the first key that some row does not see ----
-    int kv_end = n_kv, open_end = n_kv;
-    if (p.causal) {
-        const int last_tok = t0 + tok < n_q ? t0 + tok : n_q;
-        kv_end = off + last_tok < n_kv ? off + last_tok : n_kv;
-        open_end = off + t0 + 1 < n_kv ? off + t0 + 1 : n_kv;
-    }
+    // ---- the first key that some row of the tile does not see ----
+    int open_end = n_kv;
+    if (p.causal) open_end = off + t0 + 1 < n_kv ? off + t0 + 1 : n_kv;
 
     // ---- loads: a wave-uniform base per 16-key group plus a 32-bit offset per lane ----
     const unsigned char *kbase = (const unsigned char *)p.k + (int64_t)kvh * p.kv_stride_head * 2;
@@ -214,7 +241,6 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_split_kernel(const KParam
     unsigned char *v_wr = tile + ld_row * C::kVPitch + ld_col;
 
     u32x4 kreg[NLD], vreg[NLD];
-    constexpr int kStep = kWaves * kChunk;
     // one chunk: multiply, and (MORE) request the wave's next one, whose bases are in bn
     Bases bn{0, 0};
     auto step = [&](int c0, auto more_tag) {
@@ -287,7 +313,7 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_split_kernel(const KParam
             }
         }
     };
-    int c0 = wave * kChunk;
+    int c0 = kv_begin + wave * kChunk;
     if (c0 < kv_end) {
         const Bases b = bases(c0);
         load_chunk(kreg, kbase, b, c0);
@@ -335,6 +361,13 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_split_kernel(const KParam
             a += *(const f32x4 *)red;
             b += *(const f32x4 *)(red + 4);
         }
+        if (T.n_parts > 1) {  // one of several parts: left for the merge
+            float *rec = p.workspace + ((int64_t)w * p.num_splits + part) * kRecordFloats<HD>;
+            *(f32x4 *)(rec + row * HD + ch) = a;
+            *(f32x4 *)(rec + row * HD + ch + 4) = b;
+            if (ch == 0) *(float2 *)(rec + kRows * HD + 2 * row) = float2{M, L};
+            continue;
+        }
         const float inv = L > 0.f ? 1.f / L : 0.f;  // (a query without a visible key gets zeros)
         x8 o;
 #pragma unroll
@@ -346,6 +379,58 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_split_kernel(const KParam
     }
 }
 
+// Merges the parts of a tile: a thread owns four channels of a row and fetches up to eight records at a time, so that
+// a row costs one or a few round trips.  Bound by latency (a launch, the lengths, the records).
+constexpr int kMergeThreads = 256;
+template <int HD>
+constexpr int kMergeBlocks = kRows * HD / 4 / kMergeThreads;  // workgroups per tile
+
+template <typename E, int HD>
+__global__ __launch_bounds__(kMergeThreads) void prefill_split_merge_kernel(const KParams p)
+{
+    using elem = typename E::elem;
+    typedef elem x4 __attribute__((ext_vector_type(4)));
+    const int w = (int)blockIdx.x / kMergeBlocks<HD>;
+    const SplitTile T = split_tile(p, w);
+    const int i = (int)blockIdx.x % kMergeBlocks<HD> * kMergeThreads + (int)threadIdx.x;
+    const int row = i / (HD / 4), ch = 4 * (i % (HD / 4));
+    const int t = T.t0 + (row >> T.log_hpw);
+    if (T.n_parts <= 1 || t >= T.n_q) return;
+    const float *rec = p.workspace + (int64_t)w * p.num_splits * kRecordFloats<HD>;
+    float M = -INFINITY, L = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    constexpr int kBlock = 8;
+    for (int b = 0; b < T.n_parts; b += kBlock) {
+        float2 ml[kBlock];
+        f32x4 o[kBlock];
+#pragma unroll
+        for (int j = 0; j < kBlock; ++j) {  // (past the last part: that part again, with weight zero)
+            const float *r = rec + (int64_t)(b + j < T.n_parts ? b + j : T.n_parts - 1) * kRecordFloats<HD>;
+            ml[j] = *(const float2 *)(r + kRows * HD + 2 * row);
+            o[j] = *(const f32x4 *)(r + row * HD + ch);
+        }
+        float m_new = M;
+#pragma unroll
+        for (int j = 0; j < kBlock; ++j) m_new = fmaxf(m_new, ml[j].x);
+        // (a part without a visible key for the row has sum 0 and reference -inf)
+        const float keep = M == -INFINITY ? 0.f : fast_exp2(M - m_new);
+        M = m_new;
+        L *= keep;
+        acc *= keep;
+#pragma unroll
+        for (int j = 0; j < kBlock; ++j) {
+            const float f = b + j < T.n_parts && ml[j].y > 0.f ? fast_exp2(ml[j].x - M) : 0.f;
+            L += ml[j].y * f;
+            acc += o[j] * f;
+        }
+    }
+    const float inv = L > 0.f ? 1.f / L : 0.f;
+    x4 out;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) out[e] = (elem)(acc[e] * inv);
+    *(x4 *)((elem *)p.out + (int64_t)(T.q0 + t) * p.o_stride_tok + (int64_t)(T.head0 + (row & (T.hpw - 1))) * p.o_stride_head + ch) = out;
+}
+
 template <typename E, int HD>
 bool split_valid(const KParams &p)
 {
@@ -354,29 +439,32 @@ bool split_valid(const KParams &p)
 }
 
 template <typename E, int HD, bool PAGED>
-hipError_t split_launch_impl(const KParams &p, hipStream_t stream, int64_t blocks)
+hipError_t split_launch_impl(const KParams &p, hipStream_t stream, unsigned tiles)
 {
     auto kern = prefill_split_kernel<E, HD, PAGED>;
     static std::atomic<uint64_t> granted{0};
     const hipError_t allowed = allow_dynamic_lds((const void *)kern, SplitCfg<HD>::kLdsBytes, granted);
     if (allowed != hipSuccess) return allowed;
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kWaves * 64), SplitCfg<HD>::kLdsBytes, stream, p);
+    hipLaunchKernelGGL(kern, dim3(tiles, (unsigned)p.num_splits), dim3(kWaves * 64), SplitCfg<HD>::kLdsBytes, stream, p);
     return hipGetLastError();
 }
 
 template <typename E, int HD>
 hipError_t split_launch(const KParams &p, hipStream_t stream)
 {
-    const int hpw = split_heads(p.group), tok = kRows / hpw;
-    const int64_t blocks = (int64_t)((p.max_q_len + tok - 1) / tok) * p.num_seqs * p.num_kv_heads * (p.group / hpw);
-    if (blocks <= 0) return hipSuccess;
-    if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
-    return p.block_table ? split_launch_impl<E, HD, true>(p, stream, blocks) : split_launch_impl<E, HD, false>(p, stream, blocks);
+    const int64_t tiles = split_workgroups(p);
+    if (tiles <= 0) return hipSuccess;
+    if (tiles > 0x7fffffff) return hipErrorInvalidConfiguration;
+    const hipError_t e = p.block_table ? split_launch_impl<E, HD, true>(p, stream, (unsigned)tiles)
+                                       : split_launch_impl<E, HD, false>(p, stream, (unsigned)tiles);
+    if (e != hipSuccess || p.num_splits <= 1) return e;
+    hipLaunchKernelGGL((prefill_split_merge_kernel<E, HD>), dim3((unsigned)(tiles * kMergeBlocks<HD>)), dim3(kMergeThreads), 0, stream, p);
+    return hipGetLastError();
 }
 
 #define SPLIT_INSTANCE(E, NAME, HD)                                                                      \
     {                                                                                                    \
-        NAME "_keysplit d" #HD " w8", kRows, kChunk, kWaves, 0, 2, 0, split_valid<E, HD>, split_launch<E, HD> \
+        NAME "_keysplit d" #HD " w8", kRows, kChunk, kWaves, 0, 2, 0, split_valid<E, HD>, split_launch<E, HD>, 0, false, true \
     }
 
 }  // namespace

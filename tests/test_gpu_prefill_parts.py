@@ -1,0 +1,117 @@
+"""Key-split prefill with its keys cut into parts over workgroups (a call that brings a workspace): results at the edges of tiles
+and parts against the fp64 oracle, the calls that take a workspace, and those that must do without."""
+import numpy as np
+import pytest
+
+import paper_2505_03780_amd as A
+import workloads as W
+from test_host_api import _paged
+from test_prefill_split import _instance, _packed
+
+
+def test_calls_that_take_a_workspace():
+    A.attn_clear_cache()
+    A.attn_force_instance(False, -1)
+    turn = dict(num_seqs=2, total_q=60, block_table_stride=2048, max_q_len=32)  # 64 tiles
+    a = _paged(max_kv_len=8000, **turn)
+    assert A.attn_prefill_scratch_bytes(a) == 64 * 4 * 32 * 130 * 4  # four parts: one workgroup per compute unit
+    assert A.attn_prefill_scratch_bytes(_paged(max_kv_len=8000, head_dim=64, **turn)) == 64 * 4 * 32 * 66 * 4
+    assert A.attn_workspace_bytes(a, False) == 0  # needed: none
+    assert A.attn_prefill_scratch_bytes(_paged(max_kv_len=1024, **turn)) == 0  # nothing to gain
+    assert A.attn_prefill_scratch_bytes(_paged(max_kv_len=8000, num_seqs=8, total_q=512, max_q_len=64, block_table_stride=2048)) == 0
+    one = _paged(num_seqs=1, total_q=1, block_table_stride=1 << 16, max_q_len=1, max_kv_len=1 << 20)
+    assert A.attn_prefill_scratch_bytes(one) == 8 * 32 * 32 * 130 * 4  # 32 parts at most
+    a.struct_bytes += 8
+    assert A.attn_prefill_scratch_bytes(a) == 0
+
+
+SHAPES = [  # Hq, Hkv, D, block (0: packed), new tokens, keys; 1025 keys or more are cut
+    (8, 2, 128, 16, [9, 1, 8], [1025, 1300, 40]),           # parts of 256; a sequence shorter than a part
+    (8, 2, 64, 0, [9, 1, 33], [2049, 1792, 257]),
+    (4, 4, 128, 64, [33, 2], [3000, 2999]),                 # a second tile of one row
+    (6, 2, 128, 0, [5, 0, 12], [2305, 64, 2304]),           # one head a tile, an empty query; a part of one key
+    (64, 1, 128, 16, [1, 2], [5000, 17]),                   # two sub-groups of 32 heads
+    (2, 2, 64, 512, [2000], [4000]),                        # a late part that the early tiles do not see at all
+]
+
+
+def _run(dw, ws, nbytes=None):
+    a = dw.args(False)
+    a.workspace, a.workspace_bytes = ws.data_ptr(), ws.nbytes if nbytes is None else nbytes
+    dw.out.fill_(float("nan"))
+    A.attn_prefill_varlen(None, None, None, None, None, None, None, max_q_len=0, max_kv_len=0, args=a)
+    return dw.out
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("causal,scale", [(True, 1.0), (False, -6.0)])
+@pytest.mark.parametrize("shape", range(len(SHAPES)))
+def test_parts_against_the_oracle(shape, causal, scale, dtype):
+    import torch
+    from attn_testlib import TOL, DeviceWorkload, oracle_problem, to_host_f64
+
+    import oracle
+
+    Hq, Hkv, D, block, new, keys = SHAPES[shape]
+    bs = block or 16
+    wl = W.make_paged(170 + shape, "prefill", new, keys, Hq, Hkv, D, bs, sum(-(-n // bs) for n in keys) + 3, scale=scale / np.sqrt(D), causal=causal)
+    if block:
+        for s, n in enumerate(keys):  # slots past the end of a sequence hold NaN: nothing may read them
+            b = wl.block_table[s, (n - 1) // block]
+            wl.k[b, (n - 1) % block + 1:] = 0x7FC0
+            wl.v[b, (n - 1) % block + 1:] = 0x7FC0
+    else:
+        wl = _packed(wl)
+    if dtype == "f16":
+        wl = W.as_f16(wl)
+    dw = DeviceWorkload(wl)
+    ref = oracle.attention(oracle_problem(wl))
+    A.attn_force_instance(False, _instance(dtype, D))
+    try:
+        need = A.attn_prefill_scratch_bytes(dw.args(False))
+        assert need > 0
+        ws = torch.full((need // 4,), float("nan"), dtype=torch.float32, device="cuda")  # needs no initialisation
+        split = to_host_f64(_run(dw, ws))
+        again = to_host_f64(_run(dw, ws))
+        whole = to_host_f64(_run(dw, ws, need - 1))  # too small: ignored
+        assert np.array_equal(whole, to_host_f64(dw.run(False)))
+    finally:
+        A.attn_force_instance(False, -1)
+    assert np.array_equal(split, again)
+    # tolerances of the element type, derived in attn_testlib
+    for got in (split, whole):
+        assert np.abs(got - ref).max() <= TOL[dtype][0] and np.linalg.norm(got - ref) <= TOL[dtype][1] * np.linalg.norm(ref)
+
+
+@pytest.mark.gpu
+def test_tensor_call_takes_and_leaves_the_workspace():
+    """A call with tensors gives the bits of a call with a workspace, on a side stream too; under capture it does without."""
+    import torch
+    from attn_testlib import DeviceWorkload
+
+    dw = DeviceWorkload(W.make_paged(180, "prefill", [5, 3], [4000, 3000], 8, 2, 128, 16, 450))
+    call = dict(max_q_len=dw.max_q, max_kv_len=dw.max_kv, causal=True, block_table=dw.bt)
+    run = lambda **kw: A.attn_prefill_varlen(dw.q, dw.k, dw.v, dw.out, dw.qsl, dw.seq_lens, dw.wl.scale, **call, **kw)
+    need = A.attn_prefill_scratch_bytes(dw.args(False))
+    assert need > 0
+    split = _run(dw, torch.empty(need, dtype=torch.uint8, device="cuda")).clone()
+    whole = dw.run(False).clone()
+    assert not torch.equal(split, whole)  # (other rounding: the two are told apart below)
+    dw.out.fill_(float("nan"))
+    run()
+    assert torch.equal(dw.out, split)
+    side = torch.cuda.Stream()
+    dw.out.fill_(float("nan"))
+    torch.cuda.synchronize()
+    run(stream=side)
+    torch.cuda.synchronize()
+    assert torch.equal(dw.out, split)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run()
+    for _ in range(3):
+        dw.out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(dw.out, whole)
