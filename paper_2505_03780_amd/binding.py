@@ -328,7 +328,7 @@ def attn_prefill_varlen(q, k, v, out, query_start_loc, seq_lens, scale, *, max_q
         a = _packed(_pack_attn, AttnArgs, _attn_fields(q, k, v, out, seq_lens, scale, max_q_len, max_kv_len, query_start_loc, kv_start_loc,
                                                        block_table, causal, None))
         # (necessary conditions of the library's own rule, to save short calls the question)
-        scratch = _prefill_scratch(a, stream) if max_kv_len > 1024 and q.shape[0] * q.shape[1] <= 16384 else None
+        scratch = _prefill_scratch(a, stream) if max_kv_len > 1024 and q.shape[0] * q.shape[1] <= 131072 else None
         if scratch is not None:
             a = a[:-16] + _pack_workspace(scratch.data_ptr(), scratch.nbytes)
         rc = _hot["attn_prefill_varlen"](a, _stream_ptr(stream))

@@ -250,6 +250,11 @@ int find_instance(int is_decode, const KParams &p, int waves, int hpw, int bn, i
     return -1;
 }
 
+// Heads of a KV head that a ring workgroup packs: as many as divide the group, they share every K/V tile.
+int ring_heads(const KParams &p) { return p.group % 4 == 0 ? 4 : p.group % 2 == 0 ? 2 : 1; }
+// The ring kernel's 128-row workgroup with the tiles of a sequence side by side, whose keys can be cut into parts (-1: none).
+int small_ring_instance(const KParams &p) { return find_instance(0, p, 4, ring_heads(p), 32, 128, 0, 1, 4); }
+
 // Whether a prefill call has too few query rows to fill the chip with the ring kernel's 128- and 256-row
 // workgroups, and enough keys that splitting them over the wavefronts of a 32-row workgroup pays
 // (prefill_split.hip).  Measured on random shapes against the ring kernel (GPU time, 32/8, 64/8, 16/16, 16/4 and 8/2
@@ -268,39 +273,105 @@ bool few_rows_many_keys(const KParams &p)
     return (p.max_kv_len >= 160 && wgs <= compute_units()) || (p.max_kv_len > two_from && wgs <= 2 * compute_units());
 }
 
-// Parts into which the key-split prefill kernel cuts the keys of a call that brings a workspace, and the bytes of their records.
-// The number that a model of the call's time finds shortest: one workgroup per compute unit at a time, 4 us for its start and
-// its merge through LDS, 1.5 us (D = 64: 1 us) for each 256 keys, 5 us for the second kernel, and 8 % ahead of whole key
-// ranges (25 % from half a workgroup per compute unit on, where uneven lengths decide) or not at all.  Over 4000 random shapes
-// (batch 1-32, 1-1024 new tokens, 1024-16384 keys, up to two workgroups per compute unit) its choice takes 1.02x the time of the
-// best number of parts measured, 1.10x at the 95th percentile, and whole key ranges take 1.3x on average: 2 x 4 tokens behind
-// 5900 keys 46 -> 24 us, 1 x 4 behind 3300 25 -> 13, 2 x 9-12 behind 14000-18700 138 -> 48.
-constexpr int kMaxKeyParts = 32;
-int key_parts(const KParams &p)
+// ---- prefill whose keys are cut into parts over workgroups (a call that brings a workspace) -----------------
+// The workgroups of one part.
+struct KeyTiles {
+    int64_t grid;  // the longest query's tiles for every sequence
+    int64_t busy;  // at most this many of them find work
+};
+KeyTiles key_tiles(const Instance &inst, const KParams &p)
 {
-    const int64_t cus = compute_units();
-    // workgroups that find work: the grid has the longest query's tiles for every sequence
-    const int heads = split_heads(p.group), tok = kSplitRows / heads;
-    const int64_t wgs = std::min(split_workgroups(p), ((int64_t)p.total_q / tok + p.num_seqs) * (p.num_q_heads / heads));
-    const double step_us = p.head_dim == 64 ? 1.0 : 1.5;
-    auto model_us = [&](int parts) {
-        const int64_t rounds = (wgs * parts + cus - 1) / cus, steps = ((p.max_kv_len + parts - 1) / parts + 255) / 256;
-        return (double)rounds * (4.0 + step_us * (double)steps) + (parts > 1 ? 5.0 : 0.0);
-    };
-    int best = 1;
-    double best_us = model_us(1) / (2 * wgs > cus ? 1.25 : 1.08);
-    for (int parts = 2; parts <= kMaxKeyParts && split_workgroups(p) * parts <= 4 * cus; ++parts) {
-        const double us = model_us(parts);
-        if (us < best_us) {
-            best = parts;
-            best_us = us;
+    const int heads = inst.heads_per_wg > 0 ? inst.heads_per_wg : split_heads(p.group), tok = inst.block_m / heads;
+    const int64_t groups = p.num_q_heads / heads, grid = (int64_t)p.num_seqs * ((p.max_q_len + tok - 1) / tok) * groups;
+    return KeyTiles{grid, std::min(grid, ((int64_t)p.total_q / tok + p.num_seqs) * groups)};
+}
+size_t key_parts_bytes(const Instance &inst, const KParams &p, int parts)
+{
+    return parts <= 1 ? 0 : (size_t)key_tiles(inst, p).grid * inst.block_m * parts * partial_stride(p.head_dim) * sizeof(float);
+}
+
+// Time that a call is expected to take (us), by kernel; fitted to some 5900 random shapes (batch 1-32, 8-1024 new tokens,
+// 500-20000 keys, up to 600 tiles of 128 rows) with 1 to 16 parts each.  Workgroups run in rounds of as many as are resident.
+//  * Key-split kernel (32 rows): one workgroup per compute unit, 4 us for its start and its merge through LDS, 1.5 us (D = 64:
+//    1 us) for each 256 keys; nine tenths of the compute units count as a round, because XCDs get uneven shares.
+//  * Ring kernel, small workgroup (128 rows): two per compute unit, 8 us (4 us), 6 us (4.5 us) for each 256 keys, 4.5 us (3 us)
+//    while each has a compute unit to itself.
+// The second kernel costs 5 to 8 us.
+double split_model_us(const KParams &p, int64_t tiles, int parts)
+{
+    const int64_t cus = compute_units(), slots = parts == 1 ? cus : std::max<int64_t>(1, cus * 9 / 10);
+    const int64_t rounds = (tiles * parts + slots - 1) / slots, steps = ((p.max_kv_len + parts - 1) / parts + 255) / 256;
+    return (double)rounds * (4.0 + (p.head_dim == 64 ? 1.0 : 1.5) * (double)steps) + (parts > 1 ? 5.0 : 0.0);
+}
+double ring_model_us(const KParams &p, int64_t tiles, int parts)
+{
+    const bool small = p.head_dim == 64;
+    const int64_t slots = 2 * compute_units(), n = tiles * parts, rest = n % slots;
+    const double steps = (double)(((p.max_kv_len + parts - 1) / parts + 255) / 256), start = small ? 4.0 : 8.0;
+    double us = (double)(n / slots) * (start + (small ? 4.5 : 6.0) * steps);
+    if (rest > 0) us += start + (2 * rest <= slots ? (small ? 3.0 : 4.5) : (small ? 4.5 : 6.0)) * steps;
+    return us + (parts > 1 ? 8.0 : 0.0);
+}
+
+struct KeyPlan {
+    int id = -1;    // instance
+    int parts = 1;  // 1: the call does not use a workspace
+};
+constexpr int kMaxSplitParts = 32, kMaxRingParts = 16;
+// The fastest number of parts of instance `id` by its model, if less than `us`.
+void try_parts(const KParams &p, int id, double *us, KeyPlan *plan)
+{
+    int n;
+    const Instance &inst = instances(0, &n)[id];
+    const KeyTiles tiles = key_tiles(inst, p);
+    const bool ring = inst.heads_per_wg > 0;
+    // (at most four 32-row or two 128-row records per compute unit: some tens of MB)
+    const int64_t most = ring ? 2 * (int64_t)compute_units() + tiles.grid : 4 * (int64_t)compute_units();
+    for (int parts = 2; parts <= (ring ? kMaxRingParts : kMaxSplitParts) && tiles.grid * parts <= most; ++parts) {
+        const double t = ring ? ring_model_us(p, tiles.busy, parts) : split_model_us(p, tiles.busy, parts);
+        if (t < *us) {
+            *us = t;
+            *plan = KeyPlan{id, parts};
         }
     }
-    return best;
 }
-size_t key_parts_bytes(const KParams &p, int parts)
+
+// What a prefill call that would otherwise run instance `id` does with a workspace.  Over the shapes named above the choice takes
+// 1.06x the time of the best measured one on average (1.28x at the 95th percentile) and gains 1.14x on average over no
+// parts; 1.7 % of the shapes lose more than 2 %, 0.5 % more than 10 %, nearly all of them batches of very uneven lengths, whose
+// maxima are all the host knows.  Examples (no parts -> parts): 2 x 4 tokens behind 5900 keys 46 -> 24 us, 3 x 17-70
+// behind 5000-9000 57 -> 42, 10 x 21-40 behind 17000 (D = 64) 243 -> 122, 3 x 390-450 of 16/16 heads behind 3900 98 -> 75.
+KeyPlan key_plan(const KParams &p, int id, bool forced)
 {
-    return parts <= 1 ? 0 : (size_t)split_workgroups(p) * parts * kSplitRows * partial_stride(p.head_dim) * sizeof(float);
+    int n;
+    const Instance *t = instances(0, &n);
+    const bool split = t[id].key_parts && t[id].heads_per_wg == 0, small_ring = t[id].key_parts && !split;
+    KeyPlan plan{id, 1};
+    if (p.max_kv_len <= 1024) return plan;
+    const int64_t cus = compute_units();
+    if (split) {
+        // 8 % ahead or not at all, 25 % from half a workgroup per compute unit on, where uneven lengths decide
+        const int64_t busy = key_tiles(t[id], p).busy;
+        const double whole = split_model_us(p, busy, 1);
+        double us = whole / (2 * busy > cus ? 1.25 : 1.08);
+        try_parts(p, id, &us, &plan);
+        // tiles of 128 rows, where the new tokens fill at least half of them
+        if (!forced && p.max_kv_len >= (p.head_dim == 64 ? 3000 : 2000)) {
+            const int ring = small_ring_instance(p);
+            if (ring >= 0 && 2 * key_tiles(t[ring], p).busy <= busy) {
+                us = std::min(us, whole);
+                try_parts(p, ring, &us, &plan);
+            }
+        }
+        return plan;
+    }
+    // ring kernels: the small workgroup in parts, 10 % ahead or not at all; level or behind below 2048 keys
+    const int ring = forced ? (small_ring ? id : -1) : small_ring_instance(p);
+    if (ring >= 0 && p.max_kv_len >= 2048) {
+        double us = ring_model_us(p, key_tiles(t[ring], p).busy, 1) / 1.1;
+        try_parts(p, ring, &us, &plan);
+    }
+    return plan;
 }
 
 // Part length of the fixed splits (0: whole contexts): enough workgroups to fill the chip several times over, parts no
@@ -357,8 +428,7 @@ int heuristic(const KParams &p, int is_decode)
     if (!is_decode) {
         if (few_rows_many_keys(p)) id = find_instance(0, p, 8, 0, 32, 32, 0);  // wavefronts split the keys
         if (id >= 0) return id;
-        // pack as many heads of a KV head as divide the group: they share every K/V tile
-        int hpw = p.group % 4 == 0 ? 4 : (p.group % 2 == 0 ? 2 : 1);
+        const int hpw = ring_heads(p);
         // The rules below come from tuning a batch x length grid (profiles: configuration portability).
         // Sequences of many query tiles, many sequences, or a cached prefix that dominates the key
         // range: run the tiles of a sequence side by side so that they share its K/V in one L2.
@@ -581,6 +651,11 @@ struct SelectKey {
                kv_stride_tok == o.kv_stride_tok;
     }
 };
+SelectKey select_key(const KParams &p, int dtype)
+{
+    return SelectKey{dtype, p.head_dim, p.num_q_heads, p.num_kv_heads, p.block_table ? 1 : 0, p.block_size, p.causal,
+                     p.num_seqs, p.max_q_len, p.max_kv_len, p.kv_stride_block, p.kv_stride_tok};
+}
 struct SelectMemo {
     uint64_t generation = 0;
     SelectKey key{};
@@ -653,8 +728,7 @@ int select_instance(const KParams &p, int dtype, int is_decode)
     }
     static thread_local SelectMemo memo[2];
     SelectMemo &m = memo[is_decode];
-    const SelectKey key{dtype, p.head_dim, p.num_q_heads, p.num_kv_heads, p.block_table ? 1 : 0, p.block_size, p.causal,
-                        p.num_seqs, p.max_q_len, p.max_kv_len, p.kv_stride_block, p.kv_stride_tok};
+    const SelectKey key = select_key(p, dtype);
     const uint64_t gen = g_generation.load(std::memory_order_acquire);
     if (m.generation == gen && m.key == key) return m.id;
     const int id = select_instance_slow(p, dtype, is_decode);
@@ -665,6 +739,23 @@ int select_instance(const KParams &p, int dtype, int is_decode)
         m.id = id;
     }
     return id;
+}
+
+// key_plan for a call that selects instance `id`; the last answer per thread is kept like the selection's.  A tuned winner is the
+// fastest without a workspace and gives way like the built-in choice; a forced instance does not.
+KeyPlan planned_parts(const KParams &p, int dtype, int id)
+{
+    const bool forced = g_forced[0].load() >= 0 || env_knobs().forced[0] == id;
+    struct Memo {
+        SelectKey key{};
+        int total_q = -1, id = -1;
+        bool forced = false;
+        KeyPlan plan;
+    };
+    static thread_local Memo m;
+    const SelectKey key = select_key(p, dtype);
+    if (m.id != id || m.forced != forced || m.total_q != p.total_q || !(m.key == key)) m = Memo{key, p.total_q, id, forced, key_plan(p, id, forced)};
+    return m.plan;
 }
 
 size_t balanced_workspace_bytes(int num_seqs, int num_q_heads, int head_dim, int wgs)
@@ -766,9 +857,12 @@ int run(const attn_args *a, int is_decode, hipStream_t stream, int instance_over
         }
         apply_split(p, t[id]);
         if (need > 0 && ((uintptr_t)a->workspace & 7)) return ATTN_ERR_WORKSPACE;  // records are accessed as 8-byte pairs
-    } else if (t[id].key_parts && a->workspace && ((uintptr_t)a->workspace & 15) == 0) {
-        const int parts = key_parts(p);
-        if (parts > 1 && a->workspace_bytes >= key_parts_bytes(p, parts)) p.num_splits = parts;  // (else: whole key ranges)
+    } else if (instance_override < 0 && a->workspace && ((uintptr_t)a->workspace & 15) == 0) {
+        const KeyPlan plan = planned_parts(p, a->dtype, id);
+        if (plan.parts > 1 && a->workspace_bytes >= key_parts_bytes(t[plan.id], p, plan.parts)) {  // (else: whole key ranges)
+            id = plan.id;
+            p.num_splits = plan.parts;
+        }
     }
     if (t[id].launch(p, stream) != hipSuccess) return ATTN_ERR_HIP;
     // fixed-split decode merges its parts with a second kernel (the token-balanced launcher brings its own)
@@ -936,8 +1030,7 @@ int tune(const attn_args *shape, int is_decode, const char *cache_path, int iter
 
     int rc = validate(&a, is_decode);
     if (rc != ATTN_OK) return rc;
-    const KParams sized = to_kparams(&a, is_decode);
-    const size_t ws_bytes = is_decode ? decode_workspace_bytes(sized) : key_parts_bytes(sized, key_parts(sized));
+    const size_t ws_bytes = is_decode ? decode_workspace_bytes(to_kparams(&a, is_decode)) : 0;
     if (dws.alloc(ws_bytes) != hipSuccess) {
         (void)hipGetLastError();
         return ATTN_ERR_HIP;
@@ -1290,12 +1383,12 @@ size_t attn_prefill_scratch_bytes(const attn_args *a)
         a->max_q_len < 0 || a->max_kv_len < 0 || (a->head_dim != 64 && a->head_dim != 128) || !is16(a->dtype))
         return 0;
     const KParams p = to_kparams(a, 0);
-    const int parts = key_parts(p);
-    if (parts <= 1) return 0;
+    const int id = select_instance(p, a->dtype, 0);
+    if (id < 0) return 0;
     int n;
     const Instance *t = instances(0, &n);
-    const int id = select_instance(p, a->dtype, 0);
-    return id >= 0 && id < n && t[id].key_parts ? key_parts_bytes(p, parts) : 0;
+    const KeyPlan plan = planned_parts(p, a->dtype, id);
+    return key_parts_bytes(t[plan.id], p, plan.parts);
 }
 
 int attn_tune(const attn_args *shape_like, int is_decode, const char *cache_path, int iters, int flags)

@@ -19,6 +19,11 @@
 //    reference.  Numerator and denominator carry the same reference, so only the rounding
 //    of the weights differs, and the rescale of the accumulators becomes rare.
 //  * The output tile is transposed through LDS and written as whole rows.
+//  * Where a call has fewer tiles than the chip has room for, and brings a workspace, the keys are cut into parts (PARTS;
+//    grid dimension y): a part's workgroup runs the same loop over its own keys and leaves its accumulators as a record
+//    for prefill_ring_merge_kernel.  3 x 17-70 tokens behind 5000-9000 keys (56 tiles, 512 places): 141 us in one part, 42 in
+//    eight, against 51-57 for the key-split kernel; 3 x 390-450 of 16/16 heads behind 3900 98 -> 75 us.  Built for the small
+//    workgroups only; key_plan in attn_api.hip has the rule.
 //
 // Head sizes 128 and 64.  At D = 64 a unit has half the MFMAs for the same softmax, so the vector ALU is the bound
 // (16 MFMAs of two row blocks: 512 cycles of matrix pipe, about 780 of the vector issue port, and 128 more for each
@@ -30,6 +35,7 @@
 // kSlack), one bf16 sequence of 8191 tokens 318 us (864 TFLOP/s).  An eight-slot ring with five units in flight is 2-6 % ahead of four slots there; one row block with
 // four slots and three workgroups per compute unit leads up to about four 256-row tiles per compute unit.
 #include "kernel_params.hpp"
+#include "prefill_parts.hpp"
 
 namespace attn {
 namespace {
@@ -209,30 +215,22 @@ struct RingCfg {
     static_assert(kLdsBytes >= (size_t)kWaves * kWaveTok * HD * 2, "epilogue staging must fit in the ring");
 };
 
-template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES, bool PAGED>
-__global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>::kMinWaves)) void prefill_ring_kernel(const KParams p)
+// What a workgroup of the grid stands for: HPW query heads of one KV head x kTok tokens of one sequence (t0 outside
+// [0, n_q): nothing).
+struct RingTile {
+    int kvh, hsub, s, q0, n_q, n_kv, off, t0;
+};
+template <typename C, int HPW>
+__device__ __forceinline__ RingTile ring_tile(const KParams &p, int bid)
 {
-    using C = RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>;
-    using elem = typename E::elem;
-    using x8 = typename E::x8;
-    using x2 = typename E::x2;
-    constexpr int KSTEPS = HD / 16;
-    constexpr int DB = HD / 32;
-    constexpr int CPR = HD / 8;  // 16-byte chunks of a row
-    constexpr int kRowBytes = C::kRowBytes, kSlotBytes = C::kSlotBytes, kVOff = C::kVOff;
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-
-    // ---- which (head group, sequence, query tile) ---------------------------------------------
+    RingTile t;
     // Workgroups go to the eight XCDs round-robin, so with the KV head innermost every XCD (and its
     // own L2) serves one KV head when Hkv is a multiple or a divisor of eight.
     const int groups_per_kvh = p.group / HPW;
-    int bid = blockIdx.x;
-    const int kvh = bid % p.num_kv_heads;
+    t.kvh = bid % p.num_kv_heads;
     bid /= p.num_kv_heads;
-    const int hsub = bid % groups_per_kvh;
+    t.hsub = bid % groups_per_kvh;
     bid /= groups_per_kvh;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
     const int q_tiles = (p.max_q_len + C::kTok - 1) / C::kTok;  // the grid's tile dimension
     // Workgroups start in block-index order as slots come free, so the order is the schedule: work that
     // costs most (most keys to visit) goes first, and small tiles are left to fill the end.
@@ -259,20 +257,64 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
         if (r < (q_tiles & ~3)) r ^= s & 3;
     }
 
-    const int q0 = p.query_start_loc[s];
-    const int n_q = p.query_start_loc[s + 1] - q0;
-    const int n_kv = p.seq_lens[s];
-    const int off = n_kv - n_q;
-    const int n_tiles_q = (n_q + C::kTok - 1) / C::kTok;
-    const int qtile = p.tile_order == 0 ? q_tiles - 1 - r : n_tiles_q - 1 - r;
-    if (qtile < 0 || qtile >= n_tiles_q) return;
-    const int t0 = qtile * C::kTok;
+    t.s = s;
+    t.q0 = p.query_start_loc[s];
+    t.n_q = p.query_start_loc[s + 1] - t.q0;
+    t.n_kv = p.seq_lens[s];
+    t.off = t.n_kv - t.n_q;
+    const int n_tiles_q = (t.n_q + C::kTok - 1) / C::kTok;
+    t.t0 = ((p.tile_order == 0 ? q_tiles : n_tiles_q) - 1 - r) * C::kTok;
+    return t;
+}
+
+// The parts that the keys of a sequence are cut into (few query rows over many keys): equal ones of the sequence, not of the
+// tile, so that the tiles of a sequence read the same keys at about the same time; whole trips round the ring.
+struct RingParts {
+    int length, count;  // count: parts with keys that the tile sees (at least 1)
+};
+__device__ __forceinline__ RingParts ring_parts(const KParams &p, const RingTile &t, int tok)
+{
+    int end = t.n_kv;
+    if (p.causal) {
+        const int last_tok = t.t0 + tok < t.n_q ? t.t0 + tok : t.n_q;
+        end = t.off + last_tok < t.n_kv ? t.off + last_tok : t.n_kv;
+    }
+    const int length = ((t.n_kv + p.num_splits - 1) / p.num_splits + 255) & ~255;
+    return RingParts{length, end > length ? (end + length - 1) / length : 1};
+}
+
+template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES, bool PAGED, bool PARTS>
+__global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>::kMinWaves)) void prefill_ring_kernel(const KParams p)
+{
+    using C = RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>;
+    using elem = typename E::elem;
+    using x8 = typename E::x8;
+    using x2 = typename E::x2;
+    constexpr int KSTEPS = HD / 16;
+    constexpr int DB = HD / 32;
+    constexpr int CPR = HD / 8;  // 16-byte chunks of a row
+    constexpr int kRowBytes = C::kRowBytes, kSlotBytes = C::kSlotBytes, kVOff = C::kVOff;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const RingTile T = ring_tile<C, HPW>(p, blockIdx.x);
+    if (T.t0 < 0 || T.t0 >= T.n_q) return;
+    const int kvh = T.kvh, s = T.s, q0 = T.q0, n_q = T.n_q, off = T.off, t0 = T.t0;
+    // the keys of this workgroup's part: all of them, or part blockIdx.y.  From here on keys count from kv_begin.
+    int kv_begin = 0, n_kv = T.n_kv;
+    if (PARTS) {
+        const RingParts parts = ring_parts(p, T, C::kTok);
+        if ((int)blockIdx.y >= parts.count) return;
+        kv_begin = (int)blockIdx.y * parts.length;
+        n_kv = n_kv - kv_begin < parts.length ? n_kv - kv_begin : parts.length;
+    }
 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lhalf = lane >> 5;
     const int l32 = lane & 31;
     const int l16 = lane & 15;
-    const int head = kvh * p.group + hsub * HPW + (wave % HPW);
+    const int head = kvh * p.group + T.hsub * HPW + (wave % HPW);
     const int t0w = t0 + (wave / HPW) * C::kWaveTok;
 
     // scores are exponentiated as 2^(c*s - ref); a negative scale is moved into Q (sign flips are exact)
@@ -296,10 +338,11 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     }
 
     // ---- key range -------------------------------------------------------------------------------
+    const int pos0 = off - kv_begin;  // key that query 0 sits at
     int kv_end = n_kv;
     if (p.causal) {
         const int last_tok = t0 + C::kTok < n_q ? t0 + C::kTok : n_q;
-        kv_end = off + last_tok < n_kv ? off + last_tok : n_kv;
+        kv_end = pos0 + last_tok < n_kv ? pos0 + last_tok : n_kv;
     }
     const int n_units = (kv_end + kUnit - 1) / kUnit;
 
@@ -315,13 +358,13 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     }
 
     // first key position of this wave's rows, and the first unit that needs masking for this wave
-    const int qpos_lo = p.causal ? off + t0w : 0x7fffff00;
+    const int qpos_lo = p.causal ? pos0 + t0w : 0x7fffff00;
     int first_masked = (qpos_lo + 1) / kUnit;             // units below lie entirely at or before qpos_lo
     first_masked = first_masked < n_kv / kUnit ? first_masked : n_kv / kUnit;  // and entirely inside the sequence
     int qrel[QB];  // key index (relative to the lane's first key of a unit) up to which a row sees keys
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        const int qp = p.causal ? off + t0w + qb * 32 + l32 : 0x7fffff00;
+        const int qp = p.causal ? pos0 + t0w + qb * 32 + l32 : 0x7fffff00;
         const int lim = qp < n_kv - 1 ? qp : n_kv - 1;  // last visible key
         qrel[qb] = lim - 4 * lhalf;
     }
@@ -332,7 +375,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     // The rows of a wave never straddle a 16-key block, so the table entry is wave-uniform.
     const unsigned char *kbase = (const unsigned char *)p.k + (int64_t)kvh * p.kv_stride_head * 2;
     const unsigned char *vbase = (const unsigned char *)p.v + (int64_t)kvh * p.kv_stride_head * 2;
-    const int kv0 = PAGED ? 0 : p.kv_start_loc[s];
+    const int kv0 = PAGED ? 0 : p.kv_start_loc[s] + kv_begin;
     // The block table is read through the scalar cache (constant address space): a vector load would
     // share the counter of the LDS transfers, and waiting for it would drain the whole transfer queue
     // once per unit.
@@ -367,7 +410,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
         int u0 = unit * kUnit < last_unit0 ? unit * kUnit : last_unit0;
         int row = u0 + RPW * wave;
         row = row < n_kv ? row : n_kv - 1;
-        return bt_row[__builtin_amdgcn_readfirstlane(row) >> p.block_shift];
+        return bt_row[(__builtin_amdgcn_readfirstlane(row) + kv_begin) >> p.block_shift];
     };
     // The same entry, requested with an untracked scalar load (inline assembly): the value may only be
     // used after an s_waitcnt lgkmcnt(0) that follows the request (scalar loads return out of order).
@@ -376,7 +419,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
         int u0 = unit * kUnit < last_unit0 ? unit * kUnit : last_unit0;
         int row = u0 + RPW * wave;
         row = row < n_kv ? row : n_kv - 1;
-        const unsigned byte_off = (unsigned)(__builtin_amdgcn_readfirstlane(row) >> p.block_shift) * 4u;
+        const unsigned byte_off = (unsigned)((__builtin_amdgcn_readfirstlane(row) + kv_begin) >> p.block_shift) * 4u;
         int r;
         asm volatile("s_load_dword %0, %1, %2" : "=s"(r) : "s"(bt_row), "s"(byte_off) : "memory");
         return r;
@@ -388,7 +431,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
         int wrow = u0 + RPW * wave;  // first row of this wave's share
         wrow = wrow < n_kv ? wrow : n_kv - 1;
         // the rows of a wave never straddle a 16-key block: one table entry (PAGED) or one packed run of rows
-        const uint64_t base = PAGED ? (uint64_t)(uint32_t)entry * block_bytes + (uint32_t)(wrow & (p.block_size - 1)) * tok_bytes
+        const uint64_t base = PAGED ? (uint64_t)(uint32_t)entry * block_bytes + (uint32_t)((wrow + kv_begin) & (p.block_size - 1)) * tok_bytes
                                     : (uint64_t)(kv0 + wrow) * tok_bytes;
         const unsigned char *kb = kbase + base, *vb = vbase + base;
 #pragma unroll
@@ -822,6 +865,25 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     // ---- epilogue: O / l, transposed through LDS, whole rows to HBM ------------------------------
     wait_vmcnt<0>();
     __syncthreads();  // the ring is free: every wave is past its last V read and no DMA is in flight
+    if (PARTS) {
+        const RingParts parts = ring_parts(p, T, C::kTok);
+        if (parts.count > 1) {  // one of several: a record of each row block in register order, left for the merge
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                float *rec = p.workspace + (((int64_t)blockIdx.x * WAVES + wave) * QB + qb) * p.num_splits * kRecordFloats<HD> +
+                             (int64_t)blockIdx.y * kRecordFloats<HD>;
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int vq = 0; vq < 4; ++vq)
+                        *(f32x4 *)(rec + (4 * db + vq) * 256 + 4 * lane) =
+                            f32x4{oacc[qb][db][4 * vq], oacc[qb][db][4 * vq + 1], oacc[qb][db][4 * vq + 2], oacc[qb][db][4 * vq + 3]};
+                const float l = swap32_sum(l_run[qb][0]);
+                if (lhalf == 0) *(float2 *)(rec + 32 * HD + 2 * l32) = float2{m_ref[qb], l};
+            }
+            return;
+        }
+    }
     unsigned char *stage = lds + wave * (C::kWaveTok * kRowBytes);  // [token][HD] elements, chunk-swizzled by token
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
@@ -857,6 +919,28 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     }
 }
 
+// Merges the parts of a tile: a thread owns four channels of a row (the records are in the accumulators' register order, so
+// that both sides move whole kilobytes; the 8-byte stores of the outputs are 2 / parts of what is read).
+template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES>
+__global__ __launch_bounds__(kMergeThreads) void prefill_ring_merge_kernel(const KParams p)
+{
+    using C = RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>;
+    using elem = typename E::elem;
+    typedef elem x4 __attribute__((ext_vector_type(4)));
+    const int i = (int)blockIdx.x % kMergeBlocks<HD> * kMergeThreads + (int)threadIdx.x;
+    const int block = (int)blockIdx.x / kMergeBlocks<HD>;  // 32-row block
+    const int qb = block % QB, wave = block / QB % WAVES, tile = block / QB / WAVES;
+    const RingTile T = ring_tile<C, HPW>(p, tile);
+    const int row = i & 31, ch = 8 * (i >> 6) + 4 * (i >> 5 & 1);
+    const int t = T.t0 + (wave / HPW) * C::kWaveTok + 32 * qb + row;
+    if (T.t0 < 0 || t >= T.n_q) return;
+    const RingParts parts = ring_parts(p, T, C::kTok);
+    if (parts.count <= 1) return;
+    const float4 o = merge_records<HD>(p.workspace + (int64_t)block * p.num_splits * kRecordFloats<HD>, parts.count, i, row);
+    *(x4 *)((elem *)p.out + (int64_t)(T.q0 + t) * p.o_stride_tok + (int64_t)(T.kvh * p.group + T.hsub * HPW + wave % HPW) * p.o_stride_head + ch) =
+        x4{(elem)o.x, (elem)o.y, (elem)o.z, (elem)o.w};
+}
+
 template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES>
 bool ring_valid(const KParams &p)
 {
@@ -865,17 +949,21 @@ bool ring_valid(const KParams &p)
            (uint64_t)p.kv_stride_tok * 2 * kUnit < (1ull << 32);
 }
 
-template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES, bool PAGED>
+template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES, bool PAGED, bool PARTS>
 hipError_t ring_launch_impl(const KParams &p, hipStream_t stream, int64_t blocks)
 {
     using C = RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>;
-    auto kern = prefill_ring_kernel<E, HD, QB, HPW, NSLOT, PF, WAVES, PAGED>;
+    auto kern = prefill_ring_kernel<E, HD, QB, HPW, NSLOT, PF, WAVES, PAGED, PARTS>;
     static std::atomic<uint64_t> granted{0};
     const hipError_t allowed = allow_dynamic_lds((const void *)kern, C::kLdsBytes, granted);
     if (allowed != hipSuccess) return allowed;
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(C::kThreads), C::kLdsBytes, stream, p);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks, PARTS ? (unsigned)p.num_splits : 1u), dim3(C::kThreads), C::kLdsBytes, stream, p);
     return hipGetLastError();
 }
+
+// Instances whose keys can be cut into parts: the small workgroups.
+template <int QB, int WAVES>
+constexpr bool kHasParts = QB == 1 && WAVES == 4;
 
 template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES, int ORDER>
 hipError_t ring_launch(const KParams &p_in, hipStream_t stream)
@@ -888,8 +976,19 @@ hipError_t ring_launch(const KParams &p_in, hipStream_t stream)
     const int64_t blocks = q_tiles * p.num_seqs * nhg;
     if (blocks <= 0) return hipSuccess;
     if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
-    return p.block_table ? ring_launch_impl<E, HD, QB, HPW, NSLOT, PF, WAVES, true>(p, stream, blocks)
-                         : ring_launch_impl<E, HD, QB, HPW, NSLOT, PF, WAVES, false>(p, stream, blocks);
+    if constexpr (kHasParts<QB, WAVES>) {
+        if (p.num_splits > 1) {
+            if (blocks * WAVES * kMergeBlocks<HD> > 0x7fffffff) return hipErrorInvalidConfiguration;
+            const hipError_t e = p.block_table ? ring_launch_impl<E, HD, QB, HPW, NSLOT, PF, WAVES, true, true>(p, stream, blocks)
+                                               : ring_launch_impl<E, HD, QB, HPW, NSLOT, PF, WAVES, false, true>(p, stream, blocks);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL((prefill_ring_merge_kernel<E, HD, QB, HPW, NSLOT, PF, WAVES>), dim3((unsigned)(blocks * WAVES * kMergeBlocks<HD>)),
+                               dim3(kMergeThreads), 0, stream, p);
+            return hipGetLastError();
+        }
+    }
+    return p.block_table ? ring_launch_impl<E, HD, QB, HPW, NSLOT, PF, WAVES, true, false>(p, stream, blocks)
+                         : ring_launch_impl<E, HD, QB, HPW, NSLOT, PF, WAVES, false, false>(p, stream, blocks);
 }
 
 // This file is compiled twice: as it stands for bf16, and included by prefill_f16_ring.hip with
@@ -906,7 +1005,7 @@ hipError_t ring_launch(const KParams &p_in, hipStream_t stream)
     {                                                                                                              \
         RING_NAME " d" #HD " qb" #QB " w" #WAVES " hpw" #HPW " slots" #NSLOT " pf" #PF TAG, WAVES * 32 * QB, kUnit, WAVES, \
             HPW, PF, 0, ring_valid<RING_ELEM, HD, QB, HPW, NSLOT, PF, WAVES>,                                      \
-            ring_launch<RING_ELEM, HD, QB, HPW, NSLOT, PF, WAVES, ORDER>, ORDER                                    \
+            ring_launch<RING_ELEM, HD, QB, HPW, NSLOT, PF, WAVES, ORDER>, ORDER, false, kHasParts<QB, WAVES>       \
     }
 // both grid orders of one compiled kernel
 #define RING_INSTANCE(HD, QB, HPW, NSLOT, PF, WAVES) \

@@ -27,10 +27,12 @@
 //  * Where even these workgroups leave compute units idle, a call that brings a workspace has the keys of every
 //    sequence cut into parts (grid dimension y): a part's workgroups leave records, which
 //    prefill_split_merge_kernel merges (about 5 us with its launch).  2 x 4 tokens behind 5900 keys: 46 -> 24 us in
-//    eight parts, 2 x 9-12 behind 14000-18700 138 -> 48 us; key_parts in attn_api.hip has the rule.
+//    eight parts, 2 x 9-12 behind 14000-18700 138 -> 48 us; key_plan in attn_api.hip has the rule (from enough new tokens
+//    for 128-row tiles on, the ring kernel in parts takes over).
 //  * The reference of the exponentials moves only when a row outgrows it by 2^kSlack, as in the ring kernel (D = 128; at
 //    D = 64 it is the running maximum).
 #include "kernel_params.hpp"
+#include "prefill_parts.hpp"
 
 #include <type_traits>
 
@@ -134,10 +136,6 @@ __device__ __forceinline__ SplitTile split_tile(const KParams &p, int w)
     }
     return t;
 }
-// Record of a part of a tile: kRows rows of HD unnormalised outputs, then (reference, sum) of every row.
-template <int HD>
-constexpr int kRecordFloats = kRows *(HD + 2);
-
 template <typename E, int HD, bool PAGED>
 __global__ __launch_bounds__(kWaves * 64) void prefill_split_kernel(const KParams p)
 {
@@ -362,6 +360,7 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_split_kernel(const KParam
             b += *(const f32x4 *)(red + 4);
         }
         if (T.n_parts > 1) {  // one of several parts: left for the merge
+            static_assert(kRows == 32, "rows of a record");
             float *rec = p.workspace + ((int64_t)w * p.num_splits + part) * kRecordFloats<HD>;
             *(f32x4 *)(rec + row * HD + ch) = a;
             *(f32x4 *)(rec + row * HD + ch + 4) = b;
@@ -379,12 +378,7 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_split_kernel(const KParam
     }
 }
 
-// Merges the parts of a tile: a thread owns four channels of a row and fetches up to eight records at a time, so that
-// a row costs one or a few round trips.  Bound by latency (a launch, the lengths, the records).
-constexpr int kMergeThreads = 256;
-template <int HD>
-constexpr int kMergeBlocks = kRows * HD / 4 / kMergeThreads;  // workgroups per tile
-
+// Merges the parts of a tile: a thread owns four channels of a row.  Bound by latency (a launch, the lengths, the records).
 template <typename E, int HD>
 __global__ __launch_bounds__(kMergeThreads) void prefill_split_merge_kernel(const KParams p)
 {
@@ -396,39 +390,9 @@ __global__ __launch_bounds__(kMergeThreads) void prefill_split_merge_kernel(cons
     const int row = i / (HD / 4), ch = 4 * (i % (HD / 4));
     const int t = T.t0 + (row >> T.log_hpw);
     if (T.n_parts <= 1 || t >= T.n_q) return;
-    const float *rec = p.workspace + (int64_t)w * p.num_splits * kRecordFloats<HD>;
-    float M = -INFINITY, L = 0.f;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    constexpr int kBlock = 8;
-    for (int b = 0; b < T.n_parts; b += kBlock) {
-        float2 ml[kBlock];
-        f32x4 o[kBlock];
-#pragma unroll
-        for (int j = 0; j < kBlock; ++j) {  // (past the last part: that part again, with weight zero)
-            const float *r = rec + (int64_t)(b + j < T.n_parts ? b + j : T.n_parts - 1) * kRecordFloats<HD>;
-            ml[j] = *(const float2 *)(r + kRows * HD + 2 * row);
-            o[j] = *(const f32x4 *)(r + row * HD + ch);
-        }
-        float m_new = M;
-#pragma unroll
-        for (int j = 0; j < kBlock; ++j) m_new = fmaxf(m_new, ml[j].x);
-        // (a part without a visible key for the row has sum 0 and reference -inf)
-        const float keep = M == -INFINITY ? 0.f : fast_exp2(M - m_new);
-        M = m_new;
-        L *= keep;
-        acc *= keep;
-#pragma unroll
-        for (int j = 0; j < kBlock; ++j) {
-            const float f = b + j < T.n_parts && ml[j].y > 0.f ? fast_exp2(ml[j].x - M) : 0.f;
-            L += ml[j].y * f;
-            acc += o[j] * f;
-        }
-    }
-    const float inv = L > 0.f ? 1.f / L : 0.f;
-    x4 out;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) out[e] = (elem)(acc[e] * inv);
-    *(x4 *)((elem *)p.out + (int64_t)(T.q0 + t) * p.o_stride_tok + (int64_t)(T.head0 + (row & (T.hpw - 1))) * p.o_stride_head + ch) = out;
+    const float4 o = merge_records<HD>(p.workspace + (int64_t)w * p.num_splits * kRecordFloats<HD>, T.n_parts, i, row);
+    *(x4 *)((elem *)p.out + (int64_t)(T.q0 + t) * p.o_stride_tok + (int64_t)(T.head0 + (row & (T.hpw - 1))) * p.o_stride_head + ch) =
+        x4{(elem)o.x, (elem)o.y, (elem)o.z, (elem)o.w};
 }
 
 template <typename E, int HD>

@@ -1,5 +1,5 @@
-"""Key-split prefill with its keys cut into parts over workgroups (a call that brings a workspace): results at the edges of tiles
-and parts against the fp64 oracle, the calls that take a workspace, and those that must do without."""
+"""Prefill whose keys are cut into parts over workgroups (a call that brings a workspace), by the key-split and by the ring
+kernel: results at the edges of tiles and parts against the fp64 oracle, the calls that take a workspace, and those that must do without."""
 import numpy as np
 import pytest
 
@@ -12,26 +12,42 @@ from test_prefill_split import _instance, _packed
 def test_calls_that_take_a_workspace():
     A.attn_clear_cache()
     A.attn_force_instance(False, -1)
-    turn = dict(num_seqs=2, total_q=60, block_table_stride=2048, max_q_len=32)  # 64 tiles
+    turn = dict(num_seqs=2, total_q=12, block_table_stride=2048, max_q_len=8)  # 16 tiles of 8 tokens
     a = _paged(max_kv_len=8000, **turn)
-    assert A.attn_prefill_scratch_bytes(a) == 64 * 4 * 32 * 130 * 4  # four parts: one workgroup per compute unit
-    assert A.attn_prefill_scratch_bytes(_paged(max_kv_len=8000, head_dim=64, **turn)) == 64 * 4 * 32 * 66 * 4
+    assert A.attn_prefill_scratch_bytes(a) == 16 * 11 * 32 * 130 * 4  # 11 parts of three steps of 256 keys in one round
     assert A.attn_workspace_bytes(a, False) == 0  # needed: none
     assert A.attn_prefill_scratch_bytes(_paged(max_kv_len=1024, **turn)) == 0  # nothing to gain
-    assert A.attn_prefill_scratch_bytes(_paged(max_kv_len=8000, num_seqs=8, total_q=512, max_q_len=64, block_table_stride=2048)) == 0
+    # new tokens enough for 128-row tiles: the ring kernel in parts, whether its unsplit form was the choice or not
+    turns = dict(num_seqs=3, total_q=130, block_table_stride=2048, max_q_len=70)
+    assert A.attn_prefill_scratch_bytes(_paged(max_kv_len=7948, **turns)) == 72 * 8 * 128 * 130 * 4
+    assert A.attn_prefill_scratch_bytes(_paged(num_seqs=1, total_q=1000, block_table_stride=2048, max_q_len=1000, max_kv_len=8192)) > 0
+    # enough tiles
+    assert A.attn_prefill_scratch_bytes(_paged(max_kv_len=8000, num_seqs=16, total_q=8192, max_q_len=512, block_table_stride=2048)) == 0
     one = _paged(num_seqs=1, total_q=1, block_table_stride=1 << 16, max_q_len=1, max_kv_len=1 << 20)
-    assert A.attn_prefill_scratch_bytes(one) == 8 * 32 * 32 * 130 * 4  # 32 parts at most
+    assert A.attn_prefill_scratch_bytes(one) == 8 * 28 * 32 * 130 * 4  # one round
     a.struct_bytes += 8
     assert A.attn_prefill_scratch_bytes(a) == 0
 
 
-SHAPES = [  # Hq, Hkv, D, block (0: packed), new tokens, keys; 1025 keys or more are cut
-    (8, 2, 128, 16, [9, 1, 8], [1025, 1300, 40]),           # parts of 256; a sequence shorter than a part
-    (8, 2, 64, 0, [9, 1, 33], [2049, 1792, 257]),
-    (4, 4, 128, 64, [33, 2], [3000, 2999]),                 # a second tile of one row
-    (6, 2, 128, 0, [5, 0, 12], [2305, 64, 2304]),           # one head a tile, an empty query; a part of one key
-    (64, 1, 128, 16, [1, 2], [5000, 17]),                   # two sub-groups of 32 heads
-    (2, 2, 64, 512, [2000], [4000]),                        # a late part that the early tiles do not see at all
+def _ring(dtype, D, Hq, Hkv):
+    g = Hq // Hkv
+    name = "prefill_%s_ring d%d qb1 w4 hpw%d slots4 pf4 seqmajor" % (dtype, D, 4 if g % 4 == 0 else 2 if g % 2 == 0 else 1)
+    return next(i for i in range(A.attn_num_instances(False)) if A.attn_instance_name(False, i) == name)
+
+
+SHAPES = [  # kernel, Hq, Hkv, D, block (0: packed), new tokens, keys; more than 1024 keys are cut (ring: 2048 or more)
+    ("split", 8, 2, 128, 16, [9, 1, 8], [1025, 1300, 40]),           # parts of 256; a sequence shorter than a part
+    ("split", 8, 2, 64, 0, [9, 1, 33], [2049, 1792, 257]),
+    ("split", 4, 4, 128, 64, [33, 2], [3000, 2999]),                 # a second tile of one row
+    ("split", 6, 2, 128, 0, [5, 0, 12], [2305, 64, 2304]),           # one head a tile, an empty query; a part of one key
+    ("split", 64, 1, 128, 16, [1, 2], [5000, 17]),                   # two sub-groups of 32 heads
+    ("split", 2, 2, 64, 512, [1700], [3700]),                        # a late part that the early tiles do not see at all
+    ("ring", 8, 2, 128, 16, [33, 1, 32], [2048, 2305, 40]),          # 4 heads x 32 tokens a tile; a part of one key; no parts
+    ("ring", 8, 2, 64, 0, [65, 31, 5], [4097, 2559, 257]),
+    ("ring", 4, 2, 128, 1024, [70, 1], [3000, 4095]),                # 2 heads a tile; parts that start inside a cache block
+    ("ring", 3, 3, 128, 0, [129, 0, 12], [2100, 64, 6000]),          # one head a tile, an empty query
+    ("ring", 16, 4, 64, 128, [40, 3], [7000, 2048]),
+    ("ring", 1, 1, 128, 16, [3000], [3100]),                         # late parts that the early tiles do not see, or not fully
 ]
 
 
@@ -53,7 +69,7 @@ def test_parts_against_the_oracle(shape, causal, scale, dtype):
 
     import oracle
 
-    Hq, Hkv, D, block, new, keys = SHAPES[shape]
+    kernel, Hq, Hkv, D, block, new, keys = SHAPES[shape]
     bs = block or 16
     wl = W.make_paged(170 + shape, "prefill", new, keys, Hq, Hkv, D, bs, sum(-(-n // bs) for n in keys) + 3, scale=scale / np.sqrt(D), causal=causal)
     if block:
@@ -67,7 +83,7 @@ def test_parts_against_the_oracle(shape, causal, scale, dtype):
         wl = W.as_f16(wl)
     dw = DeviceWorkload(wl)
     ref = oracle.attention(oracle_problem(wl))
-    A.attn_force_instance(False, _instance(dtype, D))
+    A.attn_force_instance(False, _instance(dtype, D) if kernel == "split" else _ring(dtype, D, Hq, Hkv))
     try:
         need = A.attn_prefill_scratch_bytes(dw.args(False))
         assert need > 0
