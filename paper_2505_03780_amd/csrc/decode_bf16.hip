@@ -89,72 +89,77 @@ __global__ __launch_bounds__(WAVES * 64) void decode_bf16_kernel(const KParams p
     __shared__ __attribute__((aligned(16))) unsigned char lds[C::kLdsBytes];
 
     // ---- which (KV head, sequence, part) -----------------------------------------------------
-    int bid = blockIdx.x;
-    const int kvh = bid % p.num_kv_heads;  // fastest: one KV head per XCD when Hkv == 8
-    bid /= p.num_kv_heads;
+    touch_args(p);
+    const QuotRem by_kvh = divmod_uniform(blockIdx.x, p.num_kv_heads);
+    const int kvh = by_kvh.rem;  // fastest: one KV head per XCD when Hkv == 8
     // The sequence index rotates with the part index: workgroups are dealt to XCDs, and inside an XCD to
     // its shader engines, round-robin by index, so a fixed map would pin every part of a long sequence
     // to one engine.
-    const int part = bid / p.num_seqs;
-    const int s = (bid % p.num_seqs + part) % p.num_seqs;
-    const int n_kv = p.seq_lens[s];
+    const QuotRem by_seq = divmod_uniform(by_kvh.quot, p.num_seqs);
+    const int part = by_seq.quot;
+    const int s = divmod_uniform(by_seq.rem + part, p.num_seqs).rem;
+    const int n_kv = load_uniform(p.seq_lens, s);
     const int k_lo = part * p.split_len;
-    if (k_lo >= n_kv && !(part == 0)) return;  // parts past the end write nothing
-    const int k_hi = k_lo + p.split_len < n_kv ? k_lo + p.split_len : n_kv;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15;
     const int lg = lane >> 4;  // k-group of the MFMA operands
     const int G = p.group;
 
     // ---- Q fragment (B operand): lane holds head column l16, channels 32*ks + 8*lg .. +7 ----
-    ex8 qf[KS];
+    u32x4 qraw[KS];
     {
         const elem_t *qrow = (const elem_t *)p.q + (int64_t)s * p.q_stride_tok +
                              (int64_t)(kvh * G + (l16 < G ? l16 : 0)) * p.q_stride_head + 8 * lg;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            ex8 t = *(const ex8 *)(qrow + 32 * ks);
-            if (l16 >= G) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) t[e] = (elem_t)0.f;
-            }
-            qf[ks] = t;
-        }
+        for (int ks = 0; ks < KS; ++ks) qraw[ks] = *(const u32x4 *)(qrow + 32 * ks);
     }
+    if (k_lo >= n_kv && part != 0) {  // parts past the end write nothing
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) asm volatile("" : : "v"(qraw[ks]));  // (a use here, or the loads sink below the wait for the length)
+        return;
+    }
+    ex8 qf[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = __builtin_bit_cast(ex8, l16 >= G ? u32x4{0u, 0u, 0u, 0u} : qraw[ks]);
+    const int k_hi = k_lo + p.split_len < n_kv ? k_lo + p.split_len : n_kv;
 
     const elem_t *kbase = (const elem_t *)p.k + (int64_t)kvh * p.kv_stride_head;
     const elem_t *vbase = (const elem_t *)p.v + (int64_t)kvh * p.kv_stride_head;
-    const int32_t *bt_row = p.block_table + (int64_t)s * p.block_table_stride;
+    // (read-only, and the index is the wavefront's: scalar loads)
+    typedef const __attribute__((address_space(4))) int32_t *table_ptr;
+    const table_ptr bt_row = (table_ptr)(p.block_table + (int64_t)s * p.block_table_stride);
     unsigned char *vst = lds + wave * C::kVBytes;
 
-    // element offset of the first row of the 16-key group that starts at key `key` (16 | block_size)
-    auto group_offset = [&](int key) -> int64_t {
-        key = key < n_kv ? key : (n_kv - 1) & ~15;
-        const int blk = bt_row[key >> p.block_shift];
-        return (int64_t)blk * p.kv_stride_block + (int64_t)(key & (p.block_size - 1)) * p.kv_stride_tok;
-    };
-
     u32x4 kreg[2][KS], vreg[VLD];
-    auto load_chunk = [&](int c0) {
-        const int64_t g0 = group_offset(c0), g1 = group_offset(c0 + 16);
+    // element offsets of this lane's rows and vector inside a 16-key group (ready before the table entries arrive)
+    static_assert(VROWS * KS == 16 && VLD == 2 * KS, "KS loads per 16-key group");
+    int64_t lane_off[KS];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            // whole head slices (four rows x 256 bytes per wave-wide load at D = 128), like V
+    for (int i = 0; i < KS; ++i) lane_off[i] = (int64_t)(lane / (HD / 8) + VROWS * i) * p.kv_stride_tok + 8 * (lane % (HD / 8));
+    // table entries of the two 16-key groups of the chunk at c0 (16 | block_size; groups past the end: the last one), asked for
+    // together, and for all chunks but the first while the one before is consumed
+    struct Groups {
+        int k0, k1, b0, b1;
+    };
+    auto groups = [&](int c0) -> Groups {
+        const int end = (n_kv - 1) & ~15, k0 = c0 < end ? c0 : end, k1 = c0 + 16 < end ? c0 + 16 : end;
+        return Groups{k0, k1, bt_row[k0 >> p.block_shift], bt_row[k1 >> p.block_shift]};
+    };
+    auto load_chunk = [&](Groups c) {
+        asm volatile("" : "+s"(c.b0), "+s"(c.b1));
+        const int64_t g0 = (int64_t)c.b0 * p.kv_stride_block + (int64_t)(c.k0 & (p.block_size - 1)) * p.kv_stride_tok;
+        const int64_t g1 = (int64_t)c.b1 * p.kv_stride_block + (int64_t)(c.k1 & (p.block_size - 1)) * p.kv_stride_tok;
+        // whole head slices (four rows x 256 bytes per wave-wide load at D = 128)
 #pragma unroll
-            for (int i = 0; i < KS; ++i) {
-                const int row = lane / (HD / 8) + VROWS * i;  // 0..15
-                kreg[t][i] = kv_load(kbase + (t ? g1 : g0) + (int64_t)row * p.kv_stride_tok + 8 * (lane % (HD / 8)));
-            }
-        }
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int i = 0; i < VLD; ++i) {
-            const int row = lane / (HD / 8) + VROWS * i;  // 0..31
-            const elem_t *vr = vbase + (row < 16 ? g0 : g1) + (int64_t)(row & 15) * p.kv_stride_tok + 8 * (lane % (HD / 8));
-            vreg[i] = kv_load(vr);
-        }
+            for (int i = 0; i < KS; ++i) kreg[t][i] = kv_load(kbase + (t ? g1 : g0) + lane_off[i]);
+        __builtin_amdgcn_sched_barrier(0);  // K first: it is needed first (the compiler would pair the loads that share an offset)
+#pragma unroll
+        for (int i = 0; i < VLD; ++i) vreg[i] = kv_load(vbase + (i < KS ? g0 : g1) + lane_off[i % KS]);
     };
 
     f32x4 oacc[DB];
@@ -166,8 +171,9 @@ __global__ __launch_bounds__(WAVES * 64) void decode_bf16_kernel(const KParams p
     const int v_rd = (4 * lg + (l16 >> 2)) * C::kVPitch + 8 * (l16 & 3);
 
     int c0 = k_lo + wave * kChunk;
-    if (c0 < k_hi) load_chunk(c0);
+    if (c0 < k_hi) load_chunk(groups(c0));
     for (; c0 < k_hi; c0 += WAVES * kChunk) {
+        const int next = c0 + WAVES * kChunk;
         // consume the registers of this chunk: K, then V, pass through the wave's LDS tile
         f32x4 sacc[2];
         // the wave's LDS tile turns the K rows into MFMA operand order; V takes the tile over below
@@ -188,6 +194,8 @@ __global__ __launch_bounds__(WAVES * 64) void decode_bf16_kernel(const KParams p
                 sacc[t] = DECODE_MFMA(kf, qf[ks], sacc[t], 0, 0, 0);
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
+        const Groups after = groups(next);  // (behind the K reads: a scalar load in flight makes their counted waits full ones)
         const bool tail = c0 + kChunk > k_hi;
 #pragma unroll
         for (int i = 0; i < VLD; ++i) {
@@ -196,8 +204,7 @@ __global__ __launch_bounds__(WAVES * 64) void decode_bf16_kernel(const KParams p
             const u32x4 val = (tail && c0 + row >= k_hi) ? u32x4{0u, 0u, 0u, 0u} : vreg[i];
             *(u32x4 *)(vst + row * C::kVPitch + 16 * (lane % (HD / 8))) = val;
         }
-        const int next = c0 + WAVES * kChunk;
-        if (next < k_hi) load_chunk(next);
+        if (next < k_hi) load_chunk(after);
 
         // ---- online softmax over the 32 keys of the chunk -----------------------------------
         float x[8];
@@ -574,17 +581,16 @@ __global__ __launch_bounds__(WAVES * 64, 8 / WAVES) void decode_seq_kernel(const
 {
     using C = DecodeCfg<HD, WAVES>;
     __shared__ __attribute__((aligned(16))) unsigned char lds[WAVES * C::kVBytes];
-    const int head_blocks = (p.num_kv_heads + WAVES - 1) / WAVES;
-    int bid = blockIdx.x;
-    const int hb = bid % head_blocks;
-    bid /= head_blocks;
-    const int part = bid / p.num_seqs;
-    const int s = (bid % p.num_seqs + part) % p.num_seqs;  // rotated: the parts of a sequence spread over XCDs and engines
+    touch_args(p);
+    const QuotRem by_block = divmod_uniform(blockIdx.x, (p.num_kv_heads + WAVES - 1) / WAVES);
+    const QuotRem by_seq = divmod_uniform(by_block.quot, p.num_seqs);
+    const int hb = by_block.rem, part = by_seq.quot;
+    const int s = divmod_uniform(by_seq.rem + part, p.num_seqs).rem;  // rotated: the parts of a sequence spread over XCDs and engines
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int kvh = hb * WAVES + wave;
     if (kvh >= p.num_kv_heads) return;
-    const int n_kv = p.seq_lens[s];
+    const int n_kv = load_uniform(p.seq_lens, s);
     const int k_lo = part * p.split_len;
     if (k_lo >= n_kv && part != 0) return;
     const int k_hi = k_lo + p.split_len < n_kv ? k_lo + p.split_len : n_kv;
@@ -686,27 +692,36 @@ struct MergeState {
         *(exC *)o = w;
     }
 };
+// The records of a block, requested before it need be known how many of them count: record b0 + j of `slots` (at least 1; past
+// the end the last one again).
 template <int HD, int BLK>
-__device__ __forceinline__ void merge_parts(MergeState<HD> &st, const float *r, int parts, int64_t stride, int lane)
-{
-    constexpr int CPL = HD / 32;
-    const int sub = lane & 31;
-    for (int b0 = 0; b0 < parts; b0 += BLK) {
-        float2 ml[BLK], d[BLK][CPL / 2];
+struct MergeBlock {
+    static constexpr int CPL = HD / 32;
+    float2 ml[BLK], d[BLK][CPL / 2];
+    __device__ __forceinline__ void request(const float *r, int b0, int slots, int64_t stride, int lane)
+    {
 #pragma unroll
         for (int j = 0; j < BLK; ++j) {
-            const float *rj = r + (int64_t)(b0 + j < parts ? b0 + j : parts - 1) * stride;
+            const float *rj = r + (int64_t)(b0 + j < slots ? b0 + j : slots - 1) * stride;
             ml[j] = *(const float2 *)(rj + HD);
 #pragma unroll
-            for (int c = 0; c < CPL / 2; ++c) d[j][c] = *(const float2 *)(rj + CPL * sub + 2 * c);
+            for (int c = 0; c < CPL / 2; ++c) d[j][c] = *(const float2 *)(rj + CPL * (lane & 31) + 2 * c);
         }
+    }
+    // Adds the block's first `count` records; the others may hold anything.
+    __device__ __forceinline__ void add_to(MergeState<HD> &st, int count)
+    {
         float m_new = st.M;
 #pragma unroll
         for (int j = 0; j < BLK; ++j) {
-            if (b0 + j >= parts) ml[j].x = -INFINITY;
+            if (j >= count) {
+                ml[j] = float2{-INFINITY, 0.f};
+#pragma unroll
+                for (int c = 0; c < CPL / 2; ++c) d[j][c] = float2{0.f, 0.f};
+            }
             m_new = fmaxf(m_new, ml[j].x);
         }
-        if (m_new == -INFINITY) continue;  // nothing but empty parts so far (uniform over the half)
+        if (m_new == -INFINITY) return;  // nothing but empty parts so far (uniform over the half)
         const float keep = fast_exp2(st.M - m_new);  // 0 for the first block
         st.M = m_new;
         st.L *= keep;
@@ -722,6 +737,15 @@ __device__ __forceinline__ void merge_parts(MergeState<HD> &st, const float *r, 
                 st.acc[2 * c + 1] += d[j][c].y * w;
             }
         }
+    }
+};
+template <int HD, int BLK>
+__device__ __forceinline__ void merge_parts(MergeState<HD> &st, const float *r, int parts, int64_t stride, int lane)
+{
+    for (int b0 = 0; b0 < parts; b0 += BLK) {
+        MergeBlock<HD, BLK> b;
+        b.request(r, b0, parts, stride, lane);
+        b.add_to(st, parts - b0);
     }
 }
 
@@ -866,9 +890,9 @@ __global__ __launch_bounds__(WAVES * 64, 8 / WAVES) void decode_balanced_kernel(
 {
     using C = DecodeCfg<HD, WAVES>;
     __shared__ __attribute__((aligned(16))) unsigned char lds[WAVES * C::kVBytes];
-    const int head_blocks = (p.num_kv_heads + WAVES - 1) / WAVES;
-    const int hb = blockIdx.x % head_blocks;
-    const int w = blockIdx.x / head_blocks;
+    touch_args(p);
+    const QuotRem by_block = divmod_uniform(blockIdx.x, (p.num_kv_heads + WAVES - 1) / WAVES);
+    const int hb = by_block.rem, w = by_block.quot;
     const int num_wgs = p.num_splits;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -918,9 +942,10 @@ __device__ __forceinline__ int sequence_of_chunk(const int32_t *prefix, int B, i
 template <int HD, int BLK>
 __global__ __launch_bounds__(64 * kMergeWaves) void decode_balanced_combine_kernel(const KParams p)
 {
+    touch_args(p);
     const int pairs = (p.group + 1) / 2;
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int num_wgs = p.num_splits;
     const int B = p.num_seqs;
     const int32_t *prefix = (const int32_t *)(p.workspace + (int64_t)(num_wgs + B) * p.num_q_heads * (HD + 2));
@@ -930,11 +955,11 @@ __global__ __launch_bounds__(64 * kMergeWaves) void decode_balanced_combine_kern
     if ((int)blockIdx.x >= merge_blocks) {
         const int units = p.num_kv_heads * pairs, h = blockIdx.x - merge_blocks;
         const int j = h / units, unit = h % units;
-        const int total = prefix[B];
+        const int total = load_uniform(prefix, B);
         const int end = run_begin(total, num_wgs, j * kLongParts + 1);  // first chunk behind run j * kLongParts
         if (end <= 0 || end >= total) return;
         const int s = sequence_of_chunk(prefix, B, end, lane);
-        const int c0 = prefix[s], c1 = prefix[s + 1];
+        const int c0 = load_uniform(prefix, s), c1 = load_uniform(prefix, s + 1);
         const int w0 = run_of(total, num_wgs, c0), parts = run_of(total, num_wgs, c1 - 1) - w0 + 1;
         if (parts <= kLongParts || j * kLongParts < w0 || j * kLongParts - w0 >= kLongParts) return;  // (the same for all wavefronts)
         const int kvh = unit / pairs, hl = 2 * (unit % pairs) + (lane >> 5);  // (an idle half repeats the last head)
@@ -965,13 +990,12 @@ __global__ __launch_bounds__(64 * kMergeWaves) void decode_balanced_combine_kern
         all.store((elem_t *)p.out + (int64_t)s * p.o_stride_tok + (int64_t)(kvh * p.group + hc) * p.o_stride_head + (HD / 32) * (lane & 31));
         return;
     }
-    int bid = blockIdx.x * kMergeWaves + wave;
-    if (bid >= B * p.num_kv_heads * pairs) return;
-    const int pair = bid % pairs;
-    bid /= pairs;
-    const int kvh = bid % p.num_kv_heads;
-    const int s = bid / p.num_kv_heads;
-    const int c0 = prefix[s], c1 = prefix[s + 1], total = prefix[B];
+    const int unit = blockIdx.x * kMergeWaves + wave;
+    if (unit >= B * p.num_kv_heads * pairs) return;
+    const QuotRem by_pair = divmod_uniform(unit, pairs);
+    const QuotRem by_kvh = divmod_uniform(by_pair.quot, p.num_kv_heads);
+    const int pair = by_pair.rem, kvh = by_kvh.rem, s = by_kvh.quot;
+    const int c0 = load_uniform(prefix, s), c1 = load_uniform(prefix, s + 1), total = load_uniform(prefix, B);
     // an empty context has no piece: parts = 0 makes the merge write zeros
     const int w0 = c1 > c0 ? run_of(total, num_wgs, c0) : 0;
     const int parts = c1 > c0 ? run_of(total, num_wgs, c1 - 1) - w0 + 1 : 0;
@@ -985,20 +1009,33 @@ __global__ __launch_bounds__(64 * kMergeWaves) void decode_balanced_combine_kern
 template <int HD, int BLK>
 __global__ __launch_bounds__(64 * kMergeWaves) void decode_combine_kernel(const KParams p)
 {
+    touch_args(p);
     const int pairs = (p.group + 1) / 2;
     const int lane = threadIdx.x & 63;
-    int bid = blockIdx.x * kMergeWaves + (threadIdx.x >> 6);
-    if (bid >= p.num_seqs * p.num_kv_heads * pairs) return;
-    const int pair = bid % pairs;
-    bid /= pairs;
-    const int kvh = bid % p.num_kv_heads;
-    const int s = bid / p.num_kv_heads;
-    const int n_kv = p.seq_lens[s];
-    int parts = (n_kv + p.split_len - 1) / p.split_len;
-    parts = parts < 1 ? 1 : parts;  // part 0 is always written (m = -inf, l = 0 for an empty context)
+    const int unit = blockIdx.x * kMergeWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (unit >= p.num_seqs * p.num_kv_heads * pairs) return;
+    const QuotRem by_pair = divmod_uniform(unit, pairs);
+    const QuotRem by_kvh = divmod_uniform(by_pair.quot, p.num_kv_heads);
+    const int pair = by_pair.rem, kvh = by_kvh.rem, s = by_kvh.quot;
     const int64_t head_stride = (int64_t)p.num_splits * (HD + 2);
-    merge_pair<HD, BLK>(p, lane, s, kvh, pair, p.workspace + ((int64_t)s * p.num_q_heads + (int64_t)kvh * p.group) * head_stride, parts,
-                          head_stride, HD + 2);
+    const float *rec = p.workspace + ((int64_t)s * p.num_q_heads + (int64_t)kvh * p.group) * head_stride;
+    // part 0 is always written (m = -inf, l = 0 for an empty context)
+    const auto count = [&]() { const int n = div_uniform(load_uniform(p.seq_lens, s) + p.split_len - 1, p.split_len); return n < 1 ? 1 : n; };
+    if constexpr (BLK < 32) {
+        // The first block of records is requested together with the length that says how many of them were written (the
+        // workspace has room for num_splits): one round trip instead of two.
+        const int hl = 2 * pair + (lane >> 5), hc = hl < p.group ? hl : p.group - 1;  // (an idle half repeats the last head)
+        const float *r = rec + (int64_t)hc * head_stride;
+        MergeState<HD> st;
+        MergeBlock<HD, BLK> first;
+        first.request(r, 0, p.num_splits, HD + 2, lane);
+        const int parts = count();
+        first.add_to(st, parts);
+        if (parts > BLK) merge_parts<HD, BLK>(st, r + (int64_t)BLK * (HD + 2), parts - BLK, HD + 2, lane);
+        st.store((elem_t *)p.out + (int64_t)s * p.o_stride_tok + (int64_t)(kvh * p.group + hc) * p.o_stride_head + (HD / 32) * (lane & 31));
+    } else {
+        merge_pair<HD, BLK>(p, lane, s, kvh, pair, rec, count(), head_stride, HD + 2);
+    }
 }
 
 template <int HD, int WAVES>

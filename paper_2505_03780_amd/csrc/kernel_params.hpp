@@ -7,6 +7,7 @@
 // with its block table is the PagedAttention layout the paper cites.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include <atomic>
@@ -45,6 +46,46 @@ struct KParams {
     // 1 = sequences outermost (all tiles of a sequence run together and share its K/V in one L2)
     int32_t tile_order;
 };
+
+// First statement of a kernel: asks for one field of each of the four cache lines that the argument struct spans, so that they
+// arrive together.  Left alone the compiler loads a field where it is first needed, and the start of a kernel is a chain of
+// misses, one after the other.  With the divisions below, scalar table entries and the merge's early requests, GPU time of
+// whole calls: one context of 1900 keys 8.1 -> 7.5 us, 17 of 33-271 6.8 -> 6.3, 14 of 402 at D = 64 6.4 -> 5.7, 40 of 100-400
+// 12.2 -> 11.8, fp32 prefill of 2 x 7-21 tokens 4.4 -> 4.2, 8 x 400-1800 bf16 tokens 125.3 -> 123.5; contexts of 400 to 1000 keys whole
+// to one eight-wavefront workgroup each lose 1-2 % (20 of 500-1000 15.9 -> 16.2).
+static_assert(offsetof(KParams, seq_lens) / 64 == 0 && offsetof(KParams, kv_stride_tok) / 64 == 1 && offsetof(KParams, group) / 64 == 2 &&
+                  offsetof(KParams, num_splits) / 64 == 3 && sizeof(KParams) <= 256,
+              "a field of every line");
+__device__ __forceinline__ void touch_args(const KParams &p)
+{
+    asm volatile("" : : "s"(p.seq_lens), "s"(p.kv_stride_tok), "s"(p.group), "s"(p.num_splits));
+}
+
+// Block-index arithmetic at the start of a kernel: x / d and x % d of wave-uniform, non-negative values.  The divisors are head
+// counts more often than not, i.e. powers of two: a shift then, instead of some thirty dependent instructions each
+// (three or four of them stood in front of the first load of every kernel).
+__device__ __forceinline__ int div_uniform(int x, int d)
+{
+    if ((d & (d - 1)) == 0) return x >> __builtin_ctz(d);
+    int q = __builtin_amdgcn_readfirstlane(x / d);
+    asm volatile("" : "+s"(q));  // (keeps the division in a branch of its own)
+    return q;
+}
+struct QuotRem {
+    int quot, rem;
+};
+__device__ __forceinline__ QuotRem divmod_uniform(int x, int d)
+{
+    const int q = div_uniform(x, d);
+    return QuotRem{q, x - q * d};
+}
+
+// Element i of a read-only array that every lane wants (a length, an offset): through the scalar cache.  (The compiler cannot
+// know that no store changes it and would take a vector load.)
+__device__ __forceinline__ int32_t load_uniform(const int32_t *base, int64_t i)
+{
+    return ((const __attribute__((address_space(4))) int32_t *)base)[i];
+}
 
 // One ahead-of-time compiled template instance: the unit the autotuner sweeps
 // (the paper's "kernel configuration"; its requirement list asks for a way to

@@ -219,18 +219,23 @@ struct RingCfg {
 // [0, n_q): nothing).
 struct RingTile {
     int kvh, hsub, s, q0, n_q, n_kv, off, t0;
+    int kv0;  // packed keys: row of the sequence's first one
 };
 template <typename C, int HPW>
 __device__ __forceinline__ RingTile ring_tile(const KParams &p, int bid)
 {
+    touch_args(p);
+    // (and the fields that the block index is taken apart with, or their loads end up inside the divisions' branches)
+    asm volatile("" : : "s"(p.num_kv_heads), "s"(p.num_seqs), "s"(p.max_q_len), "s"(p.tile_order), "s"(p.causal), "s"(p.scale_log2e),
+                 "s"(p.workspace));
     RingTile t;
     // Workgroups go to the eight XCDs round-robin, so with the KV head innermost every XCD (and its
     // own L2) serves one KV head when Hkv is a multiple or a divisor of eight.
-    const int groups_per_kvh = p.group / HPW;
-    t.kvh = bid % p.num_kv_heads;
-    bid /= p.num_kv_heads;
-    t.hsub = bid % groups_per_kvh;
-    bid /= groups_per_kvh;
+    const QuotRem by_kvh = divmod_uniform(bid, p.num_kv_heads);
+    const QuotRem by_hsub = divmod_uniform(by_kvh.quot, p.group / HPW);
+    t.kvh = by_kvh.rem;
+    t.hsub = by_hsub.rem;
+    bid = by_hsub.quot;
     const int q_tiles = (p.max_q_len + C::kTok - 1) / C::kTok;  // the grid's tile dimension
     // Workgroups start in block-index order as slots come free, so the order is the schedule: work that
     // costs most (most keys to visit) goes first, and small tiles are left to fill the end.
@@ -243,8 +248,9 @@ __device__ __forceinline__ RingTile ring_tile(const KParams &p, int bid)
         // so with a fixed sequence-to-index map (say 8 sequences) a long sequence would load one
         // engine with all of its tiles and the other three would wait for it (measured: 20 % imbalance
         // on 8 sequences of 400-1800 tokens).
-        r = bid / p.num_seqs;
-        s = (bid % p.num_seqs + r) % p.num_seqs;
+        const QuotRem by_seq = divmod_uniform(bid, p.num_seqs);
+        r = by_seq.quot;
+        s = divmod_uniform(by_seq.rem + r, p.num_seqs).rem;
     } else {
         // sequences outermost (all tiles of a sequence run side by side on the XCD of their KV head and
         // stream its K/V together), heaviest tile first.  For the same reason as above the tiles swap
@@ -252,15 +258,20 @@ __device__ __forceinline__ RingTile ring_tile(const KParams &p, int bid)
         // count that is a multiple of four every engine would otherwise get the same tile of each
         // group from all sequences, the first engine always the heaviest); the order stays heaviest
         // first to within three places, which matters for the last sequence.
-        s = bid / q_tiles;
-        r = bid % q_tiles;
+        const QuotRem by_tile = divmod_uniform(bid, q_tiles);
+        s = by_tile.quot;
+        r = by_tile.rem;
         if (r < (q_tiles & ~3)) r ^= s & 3;
     }
 
     t.s = s;
-    t.q0 = p.query_start_loc[s];
-    t.n_q = p.query_start_loc[s + 1] - t.q0;
-    t.n_kv = p.seq_lens[s];
+    int q0 = load_uniform(p.query_start_loc, s), q1 = load_uniform(p.query_start_loc, s + 1), n_kv = load_uniform(p.seq_lens, s), kv0 = 0;
+    if (!p.block_table) kv0 = load_uniform(p.kv_start_loc, s);
+    asm volatile("" : "+s"(q0), "+s"(q1), "+s"(n_kv), "+s"(kv0));  // one round trip, ahead of every branch
+    t.q0 = q0;
+    t.n_q = q1 - q0;
+    t.n_kv = n_kv;
+    t.kv0 = kv0;
     t.off = t.n_kv - t.n_q;
     const int n_tiles_q = (t.n_q + C::kTok - 1) / C::kTok;
     t.t0 = ((p.tile_order == 0 ? q_tiles : n_tiles_q) - 1 - r) * C::kTok;
@@ -375,7 +386,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     // The rows of a wave never straddle a 16-key block, so the table entry is wave-uniform.
     const unsigned char *kbase = (const unsigned char *)p.k + (int64_t)kvh * p.kv_stride_head * 2;
     const unsigned char *vbase = (const unsigned char *)p.v + (int64_t)kvh * p.kv_stride_head * 2;
-    const int kv0 = PAGED ? 0 : p.kv_start_loc[s] + kv_begin;
+    const int kv0 = T.kv0 + kv_begin;
     // The block table is read through the scalar cache (constant address space): a vector load would
     // share the counter of the LDS transfers, and waiting for it would drain the whole transfer queue
     // once per unit.

@@ -52,22 +52,21 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_f32_kernel(const KParams 
     constexpr int VJ = HD / 64;  // 16-byte V loads of a lane per key
     extern __shared__ __attribute__((aligned(16))) float red[];  // [wave][row][HD + 4], then (max, sum) of every wave and row
 
+    touch_args(p);
     const int hpw = f32_heads(p.group);
     const int log_hpw = __builtin_ctz(hpw);
     const int tok = kRows >> log_hpw;
-    int bid = blockIdx.x;
-    const int kvh = bid % p.num_kv_heads;
-    bid /= p.num_kv_heads;
-    const int hsubs = p.group >> log_hpw;
-    const int hsub = bid % hsubs;
-    bid /= hsubs;
-    const int s = bid % p.num_seqs;
-    const int q_tiles = (p.max_q_len + tok - 1) / tok;
-    const int t0 = (q_tiles - 1 - bid / p.num_seqs) * tok;  // costly (late) tiles first
-    const int q0 = p.query_start_loc[s];
-    const int n_q = p.query_start_loc[s + 1] - q0;
+    const QuotRem by_kvh = divmod_uniform(blockIdx.x, p.num_kv_heads);
+    const QuotRem by_hsub = divmod_uniform(by_kvh.quot, p.group >> log_hpw);
+    const QuotRem by_seq = divmod_uniform(by_hsub.quot, p.num_seqs);
+    const int kvh = by_kvh.rem, hsub = by_hsub.rem, s = by_seq.rem;
+    const int q_tiles = (p.max_q_len + tok - 1) >> (__builtin_ctz(kRows) - log_hpw);
+    const int t0 = (q_tiles - 1 - by_seq.quot) * tok;  // costly (late) tiles first
+    int q0 = load_uniform(p.query_start_loc, s), q1 = load_uniform(p.query_start_loc, s + 1), n_kv = load_uniform(p.seq_lens, s), kv0 = 0;
+    if (!p.block_table) kv0 = load_uniform(p.kv_start_loc, s);
+    asm volatile("" : "+s"(q0), "+s"(q1), "+s"(n_kv), "+s"(kv0));  // one round trip, ahead of the branch
+    const int n_q = q1 - q0;
     if (t0 >= n_q) return;
-    const int n_kv = p.seq_lens[s];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -94,14 +93,13 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_f32_kernel(const KParams 
 
     const float *kbase = (const float *)p.k + (int64_t)kvh * p.kv_stride_head + 4 * g;
     const float *vbase = (const float *)p.v + (int64_t)kvh * p.kv_stride_head + 4 * i;
-    const int kv0 = p.block_table ? 0 : p.kv_start_loc[s];
     const int32_t *bt_row = p.block_table ? p.block_table + (int64_t)s * p.block_table_stride : nullptr;
 
     f32x4 kf[KJ], vf[4][VJ];
     // element offset of the chunk of keys at c0 < n_kv (a multiple of 16: one cache block)
     auto chunk_base = [&](int c0) -> int64_t {
         if (!bt_row) return (int64_t)(kv0 + c0) * p.kv_stride_tok;
-        return (int64_t)bt_row[c0 >> p.block_shift] * p.kv_stride_block + (int64_t)(c0 & (p.block_size - 1)) * p.kv_stride_tok;
+        return (int64_t)load_uniform(bt_row, c0 >> p.block_shift) * p.kv_stride_block + (int64_t)(c0 & (p.block_size - 1)) * p.kv_stride_tok;
     };
     // rows past the end re-read the last key
     auto load_k = [&](int c0, int64_t base) {

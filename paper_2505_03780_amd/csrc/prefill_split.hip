@@ -100,27 +100,33 @@ __device__ __forceinline__ float swap32_sum(float x)
 struct SplitTile {
     int hpw, log_hpw, tok;
     int kvh, head0, s, q0, n_q, n_kv, off, t0;
+    int kv0;       // packed keys: row of the sequence's first one
     int kv_end;    // keys that any row of the tile sees
     int part_len;  // keys of a part, a multiple of kStep
     int n_parts;   // parts of the tile that hold keys it sees (at least 1)
 };
 __device__ __forceinline__ SplitTile split_tile(const KParams &p, int w)
 {
+    touch_args(p);
     SplitTile t;
     t.hpw = split_heads(p.group);
     t.log_hpw = __builtin_ctz(t.hpw);
     t.tok = kRows >> t.log_hpw;
-    const int hsubs = p.group >> t.log_hpw;
-    const int q_tiles = (p.max_q_len + t.tok - 1) / t.tok;
-    t.kvh = w % p.num_kv_heads;  // KV head fastest, as in the other kernels
-    w /= p.num_kv_heads;
-    t.head0 = t.kvh * p.group + ((w % hsubs) << t.log_hpw);
-    w /= hsubs;
-    t.s = w % p.num_seqs;
-    t.t0 = (q_tiles - 1 - w / p.num_seqs) * t.tok;  // costly (late) tiles first
-    t.q0 = p.query_start_loc[t.s];
-    t.n_q = p.query_start_loc[t.s + 1] - t.q0;
-    t.n_kv = p.seq_lens[t.s];
+    const int q_tiles = (p.max_q_len + t.tok - 1) >> (__builtin_ctz(kRows) - t.log_hpw);
+    const QuotRem by_kvh = divmod_uniform(w, p.num_kv_heads);  // KV head fastest, as in the other kernels
+    const QuotRem by_hsub = divmod_uniform(by_kvh.quot, p.group >> t.log_hpw);
+    const QuotRem by_seq = divmod_uniform(by_hsub.quot, p.num_seqs);
+    t.kvh = by_kvh.rem;
+    t.head0 = t.kvh * p.group + (by_hsub.rem << t.log_hpw);
+    t.s = by_seq.rem;
+    t.t0 = (q_tiles - 1 - by_seq.quot) * t.tok;  // costly (late) tiles first
+    int q0 = load_uniform(p.query_start_loc, t.s), q1 = load_uniform(p.query_start_loc, t.s + 1), n_kv = load_uniform(p.seq_lens, t.s), kv0 = 0;
+    if (!p.block_table) kv0 = load_uniform(p.kv_start_loc, t.s);
+    asm volatile("" : "+s"(q0), "+s"(q1), "+s"(n_kv), "+s"(kv0));  // one round trip, ahead of every branch
+    t.q0 = q0;
+    t.n_q = q1 - q0;
+    t.n_kv = n_kv;
+    t.kv0 = kv0;
     t.off = t.n_kv - t.n_q;
     t.kv_end = t.n_kv;
     if (p.causal) {
@@ -194,7 +200,7 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_split_kernel(const KParam
     const unsigned char *vbase = (const unsigned char *)p.v + (int64_t)kvh * p.kv_stride_head * 2;
     typedef const __attribute__((address_space(4))) int32_t *table_ptr;  // read-only, scalar loads
     const table_ptr bt_row = PAGED ? (table_ptr)(p.block_table + (int64_t)s * p.block_table_stride) : (table_ptr) nullptr;
-    const int kv0 = PAGED ? 0 : p.kv_start_loc[s];
+    const int kv0 = T.kv0;
     const uint32_t tok_bytes = (uint32_t)p.kv_stride_tok * 2;
     const int ld_row = lane / CPR;
     const uint32_t ld_col = 16 * (lane % CPR);
