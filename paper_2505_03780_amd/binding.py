@@ -184,13 +184,24 @@ def attn_status_string(status: int) -> str:
 
 
 _codes = None
+# The native path of the tensor calls (csrc/fast_call.cpp) once torch has been seen: takes plain tensors on the current
+# stream, returns the status, or None for a call that the general path below has to decide.
+_fast = None
 
 
 def _dtype_codes():
     """torch dtype -> attn_dtype (torch is imported by the first call that sees a tensor)."""
-    global _codes, _int32, _raw_stream, _current_stream, _current_device
+    global _codes, _int32, _raw_stream, _current_stream, _current_device, _fast
     if _codes is None:
         import torch
+
+        lib = load_library()
+        from . import _fastcall  # (built next to the library; needs torch loaded)
+
+        address = lambda name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
+        _fastcall.bind(*(address(name) for name in ("attn_prefill_varlen", "attn_decode_paged", "attn_decode_paged_static",
+                                                    "attn_kv_cache_write", "rmsnorm_fused_add")))
+        _fast = _fastcall
 
         _int32 = torch.int32
         _current_stream, _current_device = torch.cuda.current_stream, torch.cuda.current_device
@@ -322,9 +333,12 @@ def attn_prefill_varlen(q, k, v, out, query_start_loc, seq_lens, scale, *, max_q
     stream, so that its keys can be split over the whole GPU; not under graph capture, where nobody would hold the memory for
     the replays (pass ``args`` with a workspace of attn_prefill_scratch_bytes there)."""
     lib = _lib or load_library()
+    rc = None
     if args:
         rc = lib.attn_prefill_varlen(ctypes.byref(args), _stream_ptr(stream))
-    else:
+    elif _fast is not None and stream is None and not max_kv_len > 1024:  # (longer ones may take a workspace)
+        rc = _fast.attn(0, q, k, v, out, seq_lens, scale, max_q_len, max_kv_len, query_start_loc, kv_start_loc, block_table, causal, None)
+    if rc is None:
         a = _packed(_pack_attn, AttnArgs, _attn_fields(q, k, v, out, seq_lens, scale, max_q_len, max_kv_len, query_start_loc, kv_start_loc,
                                                        block_table, causal, None))
         # (necessary conditions of the library's own rule, to save short calls the question)
@@ -340,9 +354,12 @@ def attn_decode_paged(q, k_cache, v_cache, out, block_table, seq_lens, scale, *,
                       args: Optional[AttnArgs] = None) -> None:
     """Enqueue paged-KV decode (one query token per sequence) on ``stream``."""
     lib = _lib or load_library()
+    rc = None
     if args:
         rc = lib.attn_decode_paged(ctypes.byref(args), _stream_ptr(stream))
-    else:
+    elif _fast is not None and stream is None:
+        rc = _fast.attn(1, q, k_cache, v_cache, out, seq_lens, scale, 1, max_kv_len, None, None, block_table, True, workspace)
+    if rc is None:
         a = _packed(_pack_attn, AttnArgs, _attn_fields(q, k_cache, v_cache, out, seq_lens, scale, 1, max_kv_len, None, None, block_table,
                                                        True, workspace))
         rc = _hot["attn_decode_paged"](a, _stream_ptr(stream))
@@ -355,9 +372,12 @@ def attn_decode_paged_static(q, k_cache, v_cache, out, block_table, seq_lens, sc
     """attn_decode_paged with the split-K records in the library's own static device array: no workspace
     argument, nothing allocated."""
     lib = _lib or load_library()
+    rc = None
     if args:
         rc = lib.attn_decode_paged_static(ctypes.byref(args), _stream_ptr(stream))
-    else:
+    elif _fast is not None and stream is None:
+        rc = _fast.attn(2, q, k_cache, v_cache, out, seq_lens, scale, 1, max_kv_len, None, None, block_table, True, None)
+    if rc is None:
         a = _packed(_pack_attn, AttnArgs, _attn_fields(q, k_cache, v_cache, out, seq_lens, scale, 1, max_kv_len, None, None, block_table,
                                                        True, None))
         rc = _hot["attn_decode_paged_static"](a, _stream_ptr(stream))
@@ -447,9 +467,12 @@ def make_rmsnorm_args(x, weight, out, eps, residual=None) -> RmsNormArgs:
 def rmsnorm_fused_add(x, weight, out, eps, residual=None, stream=None, args: Optional[RmsNormArgs] = None) -> None:
     """Enqueue out = rmsnorm(x + residual) * weight and residual <- x + residual (residual optional)."""
     lib = _lib or load_library()
+    rc = None
     if args:
         rc = lib.rmsnorm_fused_add(ctypes.byref(args), _stream_ptr(stream))
-    else:
+    elif _fast is not None and stream is None:
+        rc = _fast.rmsnorm(x, weight, out, eps, residual)
+    if rc is None:
         rc = _hot["rmsnorm_fused_add"](_packed(_pack_rmsnorm, RmsNormArgs, _rmsnorm_fields(x, weight, out, eps, residual)), _stream_ptr(stream))
     if rc != 0:
         raise AttnError(rc, "rmsnorm_fused_add")
@@ -515,9 +538,12 @@ def make_kv_write_args(k_new, v_new, k_cache, v_cache, slot_mapping) -> KvWriteA
 def attn_kv_cache_write(k_new, v_new, k_cache, v_cache, slot_mapping, stream=None, args: Optional[KvWriteArgs] = None) -> None:
     """Enqueue the scatter of new keys/values into the paged caches."""
     lib = _lib or load_library()
+    rc = None
     if args:
         rc = lib.attn_kv_cache_write(ctypes.byref(args), _stream_ptr(stream))
-    else:
+    elif _fast is not None and stream is None:
+        rc = _fast.kv_write(k_new, v_new, k_cache, v_cache, slot_mapping)
+    if rc is None:
         a = _packed(_pack_kv_write, KvWriteArgs, _kv_write_fields(k_new, v_new, k_cache, v_cache, slot_mapping))
         rc = _hot["attn_kv_cache_write"](a, _stream_ptr(stream))
     if rc != 0:

@@ -38,12 +38,36 @@ def _compile(src: str) -> str:
     return obj
 
 
+# the tensor calls' native marshalling: a CPython extension on torch's C++ interface (host code only)
+FAST_LIB = os.path.join(HERE, "_fastcall.so")
+
+
+def _build_fastcall() -> None:
+    import sysconfig
+
+    import torch
+
+    root = os.path.dirname(torch.__file__)
+    inc = os.path.join(root, "include")
+    tmp = FAST_LIB + ".tmp.%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-isystem", inc, "-isystem",
+           os.path.join(inc, "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "fast_call.cpp"), "-o", tmp, "-L" + os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for fast_call.cpp:\n" + r.stderr[-4000:])
+    os.replace(tmp, FAST_LIB)
+
+
 def build(verbose: bool = False) -> str:
-    """Build the library."""
+    """Build the library and the tensor calls' extension."""
     os.makedirs(BUILD, exist_ok=True)
     lib = LIB
     with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+        fast = ex.submit(_build_fastcall)
         objs = list(ex.map(_compile, SOURCES))
+        fast.result()
     tmp = lib + ".tmp.%d" % os.getpid()
     r = subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], capture_output=True, text=True)
     if r.returncode != 0:

@@ -1,0 +1,120 @@
+"""The native marshalling of the tensor calls against the general Python path: the same struct for every plain call, and None (the
+general path decides) for everything else.  The structs hold CPU pointers and nothing is called with them, but for the GPU test."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2505_03780_amd as A
+from paper_2505_03780_amd import binding as B
+from test_binding_args import _case
+
+B._dtype_codes()  # loads the extension
+F = B._fast
+
+
+def _pack(c):
+    return F.attn(-1, *c.values())
+
+
+@pytest.mark.parametrize("paged", [True, False])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16, torch.float32])
+def test_the_same_struct(paged, dtype):
+    base = _case(paged, dtype)
+    other = [{}, dict(workspace=None), dict(causal=True, scale=1), dict(scale=float("nan")), dict(query_start_loc=None, kv_start_loc=None),
+             dict(max_q_len=0, max_kv_len=2 ** 31 - 1), dict(scale=-1e-50), dict(scale=float("inf")), dict(seq_lens=torch.zeros(0, dtype=torch.int32)),
+             dict(q=torch.zeros(0, 4, 128, dtype=dtype), out=torch.zeros(0, 4, 128, dtype=dtype)),
+             dict(q=torch.zeros(4, 3, 128, dtype=dtype).transpose(0, 1)), dict(q=torch.nn.Parameter(base["q"].clone()))]
+    for change in other:
+        c = dict(base, **change)
+        a = A.AttnArgs(*B._attn_fields(*c.values()))
+        assert _pack(c) == bytes(a), change
+        assert len(bytes(a)) == ctypes.sizeof(A.AttnArgs)
+    x, w, out = torch.zeros(3, 64, dtype=dtype), torch.zeros(64, dtype=dtype), torch.zeros(3, 72, dtype=dtype)[:, :64]
+    for res in (None, torch.zeros(3, 64, dtype=dtype)):
+        assert F.pack_rmsnorm(x, w, out, 1e-5, res) == bytes(A.make_rmsnorm_args(x, w, out, 1e-5, res))
+    kn, cache, slots = torch.zeros(3, 2, 64, dtype=dtype), torch.zeros(4, 16, 2, 64, dtype=dtype), torch.zeros(3, dtype=torch.int32)
+    assert F.pack_kv_write(kn, kn, cache, cache, slots) == bytes(A.make_kv_write_args(kn, kn, cache, cache, slots))
+
+
+class _Sub(torch.Tensor):
+    pass
+
+
+@pytest.mark.parametrize("name,value", [
+    ("q", torch.zeros(3, 4, 128, dtype=torch.bfloat16).as_subclass(_Sub)), ("q", torch.zeros(3, 4, 128, dtype=torch.bfloat16).transpose(1, 2)),
+    ("q", torch.zeros(12, 128, dtype=torch.bfloat16)), ("out", torch.zeros(3, 4, 128)), ("q", np.zeros((3, 4, 128))),
+    ("k", torch.zeros(5, 16, 2, 64, dtype=torch.bfloat16)), ("v", torch.zeros(5, 16, 2, 128, dtype=torch.float16)),
+    ("v", torch.zeros(5, 2, 16, 128, dtype=torch.bfloat16).transpose(1, 2)), ("seq_lens", torch.zeros(2, dtype=torch.int64)), ("seq_lens", None),
+    ("seq_lens", torch.tensor(3, dtype=torch.int32)), ("block_table", torch.zeros(5, 2, dtype=torch.int32).t()), ("block_table", None),
+    ("query_start_loc", torch.zeros(6, dtype=torch.int32)[::2]), ("kv_start_loc", torch.zeros(3)), ("scale", np.float32(0.5)), ("scale", 1e39),
+    ("scale", torch.tensor(0.5)), ("scale", True), ("scale", 10 ** 400), ("max_q_len", 3.0), ("max_kv_len", 1 << 31), ("max_kv_len", 1 << 80),
+    ("max_kv_len", np.int32(70)), ("max_kv_len", True), ("causal", 1), ("causal", None), ("workspace", 7)])
+def test_everything_else_is_left_to_the_general_path(name, value):
+    assert _pack(_case()) is not None
+    assert _pack(dict(_case(), **{name: value})) is None
+
+
+def test_modes_wrappers_and_cpu_tensors_are_left_to_the_general_path():
+    from torch.overrides import TorchFunctionMode
+
+    class Mode(TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+
+    c = _case()
+    with Mode():
+        assert _pack(c) is None
+    seen = []
+
+    def f(q):
+        seen.append(_pack(dict(_case(), q=q)))  # a batched wrapper: exactly a torch.Tensor, without storage of its own
+        return q
+
+    torch.vmap(f)(torch.zeros(2, 3, 4, 128, dtype=torch.bfloat16))
+    assert seen == [None]
+    assert F.attn(0, *_case().values()) is None  # CPU tensors are never launched with
+    kn, cache, slots = torch.zeros(3, 2, 64), torch.zeros(4, 16, 2, 64), torch.zeros(3, dtype=torch.int32)
+    assert F.kv_write(kn, kn, cache, cache, slots) is None
+    x = torch.zeros(3, 64)
+    assert F.rmsnorm(x, x[0], x, 1e-5, None) is None and F.rmsnorm(x, None, x, 1e-5, None) is None
+    assert F.pack_rmsnorm(x.t(), x[0], x, 1e-5, None) is None and F.pack_kv_write(kn, torch.zeros(3, 2, 128)[:, :, :64], cache, cache, slots) is None
+    with pytest.raises(TypeError):
+        F.kv_write(kn)
+
+
+@pytest.mark.gpu
+def test_both_paths_give_the_same_result(monkeypatch):
+    from attn_testlib import DeviceWorkload
+    import workloads as W
+
+    dw = DeviceWorkload(W.make_paged(190, "prefill", [5, 30], [300, 64], 8, 2, 128, 16, 40))
+    dec = DeviceWorkload(W.make_paged(191, "decode", [1, 1], [700, 40], 8, 2, 128, 16, 60))
+    dec.args(True)
+    x, w = torch.randn(5, 1024, device="cuda", dtype=torch.bfloat16), torch.ones(1024, device="cuda", dtype=torch.bfloat16)
+    kn, slots = torch.randn(5, 2, 128, device="cuda", dtype=torch.bfloat16), torch.arange(5, dtype=torch.int32, device="cuda") * 3
+
+    def calls():
+        for t in (dw.out, dec.out):
+            t.fill_(float("nan"))
+        y, cache = torch.empty_like(x), torch.zeros(2, 2, 16, 2, 128, device="cuda", dtype=torch.bfloat16)
+        A.attn_prefill_varlen(dw.q, dw.k, dw.v, dw.out, dw.qsl, dw.seq_lens, dw.wl.scale, max_q_len=dw.max_q, max_kv_len=dw.max_kv, block_table=dw.bt)
+        A.attn_decode_paged(dec.q, dec.k, dec.v, dec.out, dec.bt, dec.seq_lens, dec.wl.scale, max_kv_len=dec.max_kv, workspace=dec.ws)
+        first = dec.out.clone()
+        A.attn_decode_paged_static(dec.q, dec.k, dec.v, dec.out, dec.bt, dec.seq_lens, dec.wl.scale, max_kv_len=dec.max_kv)
+        A.rmsnorm_fused_add(x, w, y, 1e-5)
+        A.attn_kv_cache_write(kn, kn, cache[0], cache[1], slots)
+        return [dw.out.clone(), first, dec.out.clone(), y, cache]
+
+    native = calls()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):  # the current stream, whichever it is
+        on_side = calls()
+    side.synchronize()
+    with pytest.raises(A.AttnError):  # the library's refusal comes back as the same error
+        A.attn_decode_paged(dec.q, dec.k, dec.v, dec.out, dec.bt, dec.seq_lens, dec.wl.scale, max_kv_len=1 << 20, workspace=dec.ws)
+    monkeypatch.setattr(B, "_fast", None)
+    for a, b, c in zip(native, on_side, calls()):
+        assert torch.equal(a, c) and torch.equal(b, c)
