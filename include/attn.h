@@ -118,7 +118,8 @@ typedef struct attn_args {
  * Few query rows over many keys (a chat's next turn behind a long cached history) leave compute units
  * idle unless their keys are split over several workgroups, whose records a second kernel merges.  That takes a
  * workspace: with at least attn_prefill_scratch_bytes(args) bytes, 16-byte aligned, in args->workspace the
- * keys are split; with less, or NULL, the call runs without it (slower, same result within rounding).
+ * keys are split; with less, or NULL, the call runs without it (slower, same result within rounding).  Calls
+ * that overlap in time need a workspace each, as for decode.
  * Returns ATTN_OK after enqueueing, or a negative attn_status.
  */
 int attn_prefill_varlen(const attn_args *args, void *hip_stream);
