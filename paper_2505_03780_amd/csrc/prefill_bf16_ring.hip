@@ -44,13 +44,11 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
 
-// The two 16-bit element types the kernel is instantiated for: how a 32x32x16 product, the sum of four weights
-// per lane (a 4x4x4 product, sixteen blocks of four columns) and the packing of two weights are spelled.  Everything else (transfers, swizzles,
+// The two 16-bit element types the kernel is instantiated for: how a 32x32x16 product and the packing
+// of two weights are spelled.  Everything else (transfers, swizzles,
 // transposing reads, masks, the fp32 softmax) is the same code.
 struct ElemBf16 {
     typedef __bf16 elem;
@@ -58,8 +56,6 @@ struct ElemBf16 {
     typedef bf16x2 x2;
     static constexpr int kDtype = kDtypeBf16;
     static __device__ __forceinline__ f32x16 mfma(x8 a, x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
-    static __device__ __forceinline__ f32x4 sum4(s16x4 ones, s16x4 w, f32x4 c) { return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, w, c, 0, 0, 0); }
-    static constexpr short kOne = 0x3F80;  // 1.0
 };
 struct ElemF16 {
     typedef _Float16 elem;
@@ -67,12 +63,8 @@ struct ElemF16 {
     typedef f16x2 x2;
     static constexpr int kDtype = kDtypeF16;
     static __device__ __forceinline__ f32x16 mfma(x8 a, x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
-    static __device__ __forceinline__ f32x4 sum4(s16x4 ones, s16x4 w, f32x4 c)
-    {
-        return __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(f16x4, ones), __builtin_bit_cast(f16x4, w), c, 0, 0, 0);
-    }
-    static constexpr short kOne = 0x3C00;
 };
+typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -514,14 +506,11 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     // ---- state ---------------------------------------------------------------------------------------
     f32x16 oacc[QB][DB];
     f32x16 s_cur[QB], s_nxt[QB];
-    float m_ref[QB];
-    f32x4 l_run[QB];  // row sums of this lane's keys in element 0 (the others stay zero)
-    const short one = (lane & 3) == 0 ? E::kOne : (short)0;
-    const s16x4 ones = {one, one, one, one};
+    float m_ref[QB], l_run[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         m_ref[qb] = -INFINITY;
-        l_run[qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        l_run[qb] = 0.f;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -552,7 +541,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
         m_new = fmaxf(m_new, kLowest);
         const float alpha = fast_exp2(m_ref[qb] - m_new);
         m_ref[qb] = m_new;
-        l_run[qb][0] *= alpha;
+        l_run[qb] *= alpha;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -659,19 +648,20 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
         const unsigned img_wr = lds_addr(img_base + ((u + 1) & 1) * C::kImgBytes + lane * 16);
         const unsigned char *kt2 = lds + ((u + 2) % NSLOT) * kSlotBytes;
 
-        u32x4 pf[QB][2];  // the weights, two to a word
+        x8 pf[QB][2];
         u32x4 vfrag[2 * DB];
         s16x4 raw[C::kFragsPerWave][2];
+        float sum[QB][2];
         const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         int seq = 0;        // LDS operations issued so far in this iteration
         int vpos[2 * DB];   // position of image fragment f in this iteration's sequence
         int tr_last = 0;    // position of the last transposing read
         int entry_nxt = table_entry_request(u + 1 + PF);
-        // weights 2p, 2p+1 of row block qb: exponentials, rounding.  The exponentials are spread over
+        // weights 2p, 2p+1 of row block qb: exponentials, rounding, row sum.  The exponentials are spread over
         // both phases (half under the score MFMAs, half under the first PV MFMAs, which only need the
         // first half), so that neither phase has more vector work than matrix work to hide it under.
         // Two steps, a group apart: the exponentials are issued under one MFMA and their results are
-        // rounded under the next, so that nothing waits for the transcendental unit's
+        // rounded and summed under the next, so that nothing waits for the transcendental unit's
         // latency (a wavefront issues in order: a use right behind the exponential stalls it).
         float e_pending[QB][2][2];  // two pairs may be pending (D = 64)
         auto exp_issue = [&](int qb, int pair) {
@@ -687,17 +677,13 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
             x2 pr;
             pr[0] = (elem)e0;
             pr[1] = (elem)e1;
-            pf[qb][v >> 3][(v & 7) >> 1] = __builtin_bit_cast(uint32_t, pr);
-        };
-        // Row sums: four weights of every lane added to its running sum by one 4x4x4 product with a row of ones (two
-        // passes of the matrix pipe in place of four additions; adding a pair at a time with the dot product
-        // costs that pipe twice as much for half the weights).  A lane is a column, so no lane sees another's weights.
-        // A group after the weights were rounded, so that the product does not wait for them.  Against additions
-        // (32/8 heads, calls in turn): 8191 bf16 tokens 489 -> 480 us, 8 x 400-1800 tokens 127.6 -> 126.1, 16 x 512 behind
-        // 0-8192 keys 667 -> 661, 6 fp16 sequences at D = 64 187.4 -> 185.3.
-        auto row_sum = [&](int qb, int quad) {
-            const u32x2 w = {pf[qb][quad >> 1][2 * (quad & 1)], pf[qb][quad >> 1][2 * (quad & 1) + 1]};
-            l_run[qb] = E::sum4(ones, __builtin_bit_cast(s16x4, w), l_run[qb]);
+            // Row sums with plain adds, two chains per row block (even and odd pairs).  The dot-product
+            // instruction that would sum the rounded pair in one go occupies the matrix pipe for about
+            // half an MFMA (measured), so it is not free under the MFMAs; the sum of the unrounded
+            // weights differs from the sum of the rounded ones by rounding errors that average out.
+            sum[qb][pair & 1] = pair < 2 ? e0 + e1 : sum[qb][pair & 1] + (e0 + e1);  // pairs come in order: 0 and 1 start the chains
+            pf[qb][v >> 3][v & 7] = pr[0];
+            pf[qb][v >> 3][(v & 7) + 1] = pr[1];
         };
 #pragma unroll
         for (int g = 0; g < G; ++g) {
@@ -715,7 +701,6 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
                 exp_issue(qb, ks / 2);
             else
                 exp_finish(qb, ks / 2);
-            if (ks == (HD == 64 ? 3 : 4)) row_sum(qb, 0);
             if (qb == QB - 1) {
                 const int f = ks;
                 vfrag[f] = lds_read_fragment(img_rd, f);
@@ -758,9 +743,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
             } else if (f >= 1 && f <= DB)
                 exp_finish(qb, 3 + f);
             if (qb == 0) lds_wait_upto(seq - 1 - vpos[f], vfrag[f]);
-            oacc[qb][f % DB] = E::mfma(__builtin_bit_cast(x8, vfrag[f]), __builtin_bit_cast(x8, pf[qb][f / DB]), oacc[qb][f % DB]);
-            // (weights 4q..4q+3 were rounded a group earlier at the latest)
-            if (HD == 64 ? f > 0 : f == 0 || f == 3 || f == 5) row_sum(qb, HD == 64 ? f : 1 + f / 2);
+            oacc[qb][f % DB] = E::mfma(__builtin_bit_cast(x8, vfrag[f]), pf[qb][f / DB], oacc[qb][f % DB]);
             if (HD == 64 && f < DB) {
                 exp_issue(qb, 4 + 2 * f);
                 exp_issue(qb, 5 + 2 * f);
@@ -811,6 +794,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
         }
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
+            l_run[qb] += sum[qb][0] + sum[qb][1];
             if (outgrown[qb]) rescale_to(qb, bm[qb]);
         }
         // Publish.  This wave's transfers of every unit but the newest PF-3 have landed (see ring_barrier);
@@ -889,7 +873,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
                     for (int vq = 0; vq < 4; ++vq)
                         *(f32x4 *)(rec + (4 * db + vq) * 256 + 4 * lane) =
                             f32x4{oacc[qb][db][4 * vq], oacc[qb][db][4 * vq + 1], oacc[qb][db][4 * vq + 2], oacc[qb][db][4 * vq + 3]};
-                const float l = swap32_sum(l_run[qb][0]);
+                const float l = swap32_sum(l_run[qb]);
                 if (lhalf == 0) *(float2 *)(rec + 32 * HD + 2 * l32) = float2{m_ref[qb], l};
             }
             return;
@@ -898,7 +882,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     unsigned char *stage = lds + wave * (C::kWaveTok * kRowBytes);  // [token][HD] elements, chunk-swizzled by token
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        const float l = swap32_sum(l_run[qb][0]);
+        const float l = swap32_sum(l_run[qb]);
         const float inv = l > 0.f ? 1.f / l : 0.f;
         const int tl = qb * 32 + l32;
 #pragma unroll
