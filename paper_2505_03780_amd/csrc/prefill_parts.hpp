@@ -26,11 +26,19 @@ __device__ __forceinline__ float4 merge_records(const float *rec, int n_parts, i
         float2 ml[kBlock];
         float4 o[kBlock];
 #pragma unroll
-        for (int j = 0; j < kBlock; ++j) {  // (past the last part: that part again, with weight zero)
+        for (int j = 0; j < kBlock; ++j) {  // (past the last part: that part again, cleared below)
             const float *r = rec + (int64_t)(b + j < n_parts ? b + j : n_parts - 1) * kRecordFloats<HD>;
             ml[j] = *(const float2 *)(r + 32 * HD + 2 * row);
             o[j] = *(const float4 *)(r + 4 * i);
         }
+        // Cleared, not weighted with zero: the last part may hold an infinity.  (Real records are weighted whatever they hold, as the
+        // unsplit kernels weight every key: zero times infinity is NaN in both.)
+#pragma unroll
+        for (int j = 1; j < kBlock; ++j)
+            if (b + j >= n_parts) {
+                ml[j] = float2{-INFINITY, 0.f};
+                o[j] = float4{0.f, 0.f, 0.f, 0.f};
+            }
         float m_new = M;
 #pragma unroll
         for (int j = 0; j < kBlock; ++j) m_new = ml[j].y > 0.f ? fmaxf(m_new, ml[j].x) : m_new;
@@ -40,7 +48,7 @@ __device__ __forceinline__ float4 merge_records(const float *rec, int n_parts, i
         acc.x *= keep, acc.y *= keep, acc.z *= keep, acc.w *= keep;
 #pragma unroll
         for (int j = 0; j < kBlock; ++j) {
-            const float f = b + j < n_parts && ml[j].y > 0.f ? __builtin_amdgcn_exp2f(ml[j].x - M) : 0.f;
+            const float f = ml[j].y > 0.f ? __builtin_amdgcn_exp2f(ml[j].x - M) : 0.f;
             L += ml[j].y * f;
             acc.x += o[j].x * f, acc.y += o[j].y * f, acc.z += o[j].z * f, acc.w += o[j].w * f;
         }

@@ -101,6 +101,39 @@ def test_parts_against_the_oracle(shape, causal, scale, dtype):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("tensor,value", [("v", 0x7F80), ("v", 0xFF80), ("v", 0x7FC0), ("k", 0x7F80), ("k", 0x7FC0)])
+@pytest.mark.parametrize("kernel,D,new,keys", [("split", 128, 9, 3000), ("split", 64, 9, 2700), ("ring", 128, 33, 3000), ("ring", 64, 40, 4200)])
+def test_infinities_and_nan_through_the_merge(kernel, D, new, keys, tensor, value):
+    """A non-finite key or value in the first, the last or several parts reaches the outputs that it reaches without parts, as the
+    same infinity or as NaN: where the number of parts is no multiple of the merge's eight, too."""
+    import torch
+    from attn_testlib import DeviceWorkload, to_host_f64
+
+    for at in ([keys - new - 3], [5], [5, keys - new - 3], [keys - 3]):  # (the last: seen by some queries only)
+        wl = W.make_paged(175, "prefill", [new], [keys], 8, 2, D, 16, -(-keys // 16) + 3)
+        for key in at:
+            getattr(wl, tensor)[wl.block_table[0, key // 16], key % 16, 0, 7] = value
+        dw = DeviceWorkload(wl)
+        A.attn_force_instance(False, _instance("bf16", D) if kernel == "split" else _ring("bf16", D, 8, 2))
+        try:
+            need = A.attn_prefill_scratch_bytes(dw.args(False))
+            rows = 32 if kernel == "split" else 128
+            tiles = 2 * -(-new // (rows // 4))
+            parts = need // (tiles * rows * (D + 2) * 4)
+            assert parts > 1 and parts % 8 != 0
+            split = to_host_f64(_run(dw, torch.full((need // 4,), float("nan"), dtype=torch.float32, device="cuda")))
+            whole = to_host_f64(dw.run(False))
+        finally:
+            A.attn_force_instance(False, -1)
+        assert not np.isfinite(whole[-1]).all() and np.isfinite(whole[:, 4:]).all()  # (the other KV head)
+        if (tensor, value) == ("v", 0x7F80):
+            assert (whole[-1, :4, 7] == np.inf).all()
+        for pattern in (np.isnan, np.isposinf, np.isneginf):
+            differ = int((pattern(split) != pattern(whole)).sum())
+            assert differ == 0, (at, pattern.__name__)
+
+
+@pytest.mark.gpu
 def test_tensor_call_takes_and_leaves_the_workspace():
     """A call with tensors gives the bits of a call with a workspace, on a side stream too; under capture it does without."""
     import torch
