@@ -101,7 +101,7 @@ typedef struct attn_args {
     int32_t causal; /* 1: query i sees keys j <= (seq_lens[s] - n_q(s)) + i (bottom-right aligned); 0: all keys.
                      * Requires seq_lens[s] >= n_q(s); a query that would sit before key 0 gets zeros. */
 
-    void *workspace; /* device scratch for split-K partials; may be NULL if attn_workspace_bytes() == 0, and for prefill */
+    void *workspace; /* decode: device scratch for split-K partials; may be NULL if attn_workspace_bytes() == 0.  Prefill: ignored */
     uint64_t workspace_bytes;
 } attn_args;
 
@@ -115,16 +115,20 @@ typedef struct attn_args {
  * Infinities and NaN: in fp32 a value of V reaches only the queries that see its key.  The 16-bit
  * kernels multiply the keys of a tile that a query does not see by a weight of zero, so a non-finite
  * value in V can also make NaN of queries shortly before its key (never of another sequence's).
- * Few query rows over many keys (a chat's next turn behind a long cached history) leave compute units
- * idle unless their keys are split over several workgroups, whose records a second kernel merges.  That takes a
- * workspace: with at least attn_prefill_scratch_bytes(args) bytes, 16-byte aligned, in args->workspace the
- * keys are split; with less, or NULL, the call runs without it (slower, same result within rounding).  Calls
- * that overlap in time need a workspace each, as for decode.
  * Returns ATTN_OK after enqueueing, or a negative attn_status.
  */
 int attn_prefill_varlen(const attn_args *args, void *hip_stream);
-/* Bytes of workspace with which the next attn_prefill_varlen call with these args splits its keys over workgroups (at most
- * some tens of MB; pointer fields other than block_table are ignored).  0: the call does not use a workspace. */
+
+/*
+ * attn_prefill_varlen with device scratch memory.  Few query rows over many keys (a chat's next turn behind a long
+ * cached history) leave compute units idle unless their keys are split over several workgroups, which leave records
+ * that a second kernel merges.  With at least attn_prefill_scratch_bytes(args) bytes, 16-byte aligned, the keys of a
+ * call for which that is expected to pay are split; with less, or NULL, this is attn_prefill_varlen (slower, same result
+ * within rounding).  args->workspace is ignored.  Calls that overlap in time need scratch memory each.
+ */
+int attn_prefill_varlen_parts(const attn_args *args, void *scratch, size_t scratch_bytes, void *hip_stream);
+/* Bytes of scratch memory with which the next attn_prefill_varlen_parts call with these args splits its keys over workgroups (at
+ * most some tens of MB; pointer fields other than block_table are ignored).  0: the call does not use any. */
 size_t attn_prefill_scratch_bytes(const attn_args *args);
 
 /*
@@ -190,8 +194,8 @@ int attn_kv_cache_write(const attn_kv_write_args *args, void *hip_stream);
  * may be chosen for it, whatever the winner cache holds.  Fixed-split instances cut a context into at
  * most 64 parts and a batch into at most two parts per compute unit; the token-balanced ones use one
  * record per workgroup (at most four per compute unit) and per sequence.  is_decode = 1 for
- * attn_decode_paged.  Returns 0 when args is NULL or malformed, and for prefill, which needs none
- * (attn_prefill_scratch_bytes says what it can use).
+ * attn_decode_paged.  Returns 0 when args is NULL or malformed, and for prefill, which uses none (the scratch memory of
+ * attn_prefill_varlen_parts is an argument of its own).
  */
 size_t attn_workspace_bytes(const attn_args *args, int is_decode);
 

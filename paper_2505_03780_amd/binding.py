@@ -88,6 +88,8 @@ def load_library():
     lib.attn_workspace_bytes.argtypes = [P, ctypes.c_int]
     lib.attn_prefill_scratch_bytes.restype = ctypes.c_size_t
     lib.attn_prefill_scratch_bytes.argtypes = [P]
+    lib.attn_prefill_varlen_parts.restype = ctypes.c_int
+    lib.attn_prefill_varlen_parts.argtypes = [P, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
     lib.attn_tune.restype = ctypes.c_int
     lib.attn_tune.argtypes = [P, ctypes.c_int, ctypes.c_char_p, ctypes.c_int, ctypes.c_int]
     lib.attn_environment_key.restype = ctypes.c_int
@@ -133,6 +135,10 @@ def load_library():
     f.restype = ctypes.c_size_t
     f.argtypes = [ctypes.c_char_p]
     _hot["attn_prefill_scratch_bytes"] = f
+    f = lib["attn_prefill_varlen_parts"]
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_char_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
+    _hot["attn_prefill_varlen_parts"] = f
     _lib = lib
     return lib
 
@@ -272,7 +278,6 @@ def _attn_fields(q, k, v, out, seq_lens, scale, max_q_len, max_kv_len, query_sta
 
 _ATTN_BYTES = ctypes.sizeof(AttnArgs)
 _pack_attn = struct.Struct("@I8iPqqPqqPPqqqPiiiPPPfiPQ").pack
-_pack_workspace = struct.Struct("@PQ").pack  # the last two fields of AttnArgs
 _pack_kv_write = struct.Struct("@I7iPPqqPPqqqP").pack
 _pack_rmsnorm = struct.Struct("@IiiiPqPqPPqf4x").pack
 
@@ -303,7 +308,7 @@ def _stream_ptr(stream) -> int:
 
 
 def _prefill_scratch(packed: bytes, stream):
-    """A workspace for the prefill call described by ``packed`` on ``stream``, or None.  The block belongs to that stream's pool
+    """Scratch memory for the prefill call described by ``packed`` on ``stream``, or None.  The block belongs to that stream's pool
     of the caching allocator: once freed it is only handed out to later work of the same stream."""
     n = _hot["attn_prefill_scratch_bytes"](packed)
     if n == 0:
@@ -326,26 +331,32 @@ def _scratch_block(torch, n: int):
 
 
 def attn_prefill_varlen(q, k, v, out, query_start_loc, seq_lens, scale, *, max_q_len, max_kv_len, causal=True,
-                        block_table=None, kv_start_loc=None, stream=None, args: Optional[AttnArgs] = None) -> None:
+                        block_table=None, kv_start_loc=None, stream=None, args: Optional[AttnArgs] = None, workspace=None) -> None:
     """Enqueue causal variable-length (or chunked, over a paged prefix) prefill on ``stream``.
 
-    A call of few query rows over many keys takes a workspace from torch's caching allocator for its time on the
-    stream, so that its keys can be split over the whole GPU; not under graph capture, where nobody would hold the memory for
-    the replays (pass ``args`` with a workspace of attn_prefill_scratch_bytes there)."""
+    The keys of few query rows over many keys are split over the whole GPU, which takes scratch memory.  ``workspace`` is a
+    16-byte aligned device tensor for that, of at least attn_prefill_scratch_bytes; a smaller one is not used.  Without it a call
+    with tensors takes memory from torch's caching allocator for its time on the stream, but for a call under graph capture, where
+    nobody would hold the memory for the replays, and a call with ``args`` does without.  The result is the same within rounding."""
     lib = _lib or load_library()
     rc = None
     if args:
-        rc = lib.attn_prefill_varlen(ctypes.byref(args), _stream_ptr(stream))
-    elif _fast is not None and stream is None and not max_kv_len > 1024:  # (longer ones may take a workspace)
+        if workspace is None:
+            rc = lib.attn_prefill_varlen(ctypes.byref(args), _stream_ptr(stream))
+        else:
+            rc = lib.attn_prefill_varlen_parts(ctypes.byref(args), workspace.data_ptr(), workspace.nbytes, _stream_ptr(stream))
+    elif _fast is not None and stream is None and not max_kv_len > 1024:  # (longer ones may use scratch memory)
         rc = _fast.attn(0, q, k, v, out, seq_lens, scale, max_q_len, max_kv_len, query_start_loc, kv_start_loc, block_table, causal, None)
     if rc is None:
         a = _packed(_pack_attn, AttnArgs, _attn_fields(q, k, v, out, seq_lens, scale, max_q_len, max_kv_len, query_start_loc, kv_start_loc,
                                                        block_table, causal, None))
         # (necessary conditions of the library's own rule, to save short calls the question)
-        scratch = _prefill_scratch(a, stream) if max_kv_len > 1024 and q.shape[0] * q.shape[1] <= 131072 else None
-        if scratch is not None:
-            a = a[:-16] + _pack_workspace(scratch.data_ptr(), scratch.nbytes)
-        rc = _hot["attn_prefill_varlen"](a, _stream_ptr(stream))
+        if workspace is None and max_kv_len > 1024 and q.shape[0] * q.shape[1] <= 131072:
+            workspace = _prefill_scratch(a, stream)
+        if workspace is None:
+            rc = _hot["attn_prefill_varlen"](a, _stream_ptr(stream))
+        else:
+            rc = _hot["attn_prefill_varlen_parts"](a, workspace.data_ptr(), workspace.nbytes, _stream_ptr(stream))
     if rc != 0:
         raise AttnError(rc, "attn_prefill_varlen")
 

@@ -141,7 +141,7 @@ KParams to_kparams(const attn_args *a, int is_decode)
     p.scale = a->scale;
     p.scale_log2e = a->scale * 1.4426950408889634f;
     p.causal = a->causal ? 1 : 0;
-    p.workspace = (float *)a->workspace;
+    p.workspace = is_decode ? (float *)a->workspace : nullptr;
     p.num_splits = 1;
     p.split_len = 0;
     return p;
@@ -273,7 +273,7 @@ bool few_rows_many_keys(const KParams &p)
     return (p.max_kv_len >= 160 && wgs <= compute_units()) || (p.max_kv_len > two_from && wgs <= 2 * compute_units());
 }
 
-// ---- prefill whose keys are cut into parts over workgroups (a call that brings a workspace) -----------------
+// ---- prefill whose keys are cut into parts over workgroups (a call that brings scratch memory) -----------------
 // The workgroups of one part.
 struct KeyTiles {
     int64_t grid;  // the longest query's tiles for every sequence
@@ -315,7 +315,7 @@ double ring_model_us(const KParams &p, int64_t tiles, int parts)
 
 struct KeyPlan {
     int id = -1;    // instance
-    int parts = 1;  // 1: the call does not use a workspace
+    int parts = 1;  // 1: the call does not use scratch memory
 };
 constexpr int kMaxSplitParts = 32, kMaxRingParts = 16;
 // The fastest number of parts of instance `id` by its model, if less than `us`.
@@ -336,7 +336,7 @@ void try_parts(const KParams &p, int id, double *us, KeyPlan *plan)
     }
 }
 
-// What a prefill call that would otherwise run instance `id` does with a workspace.  Over the shapes named above the choice takes
+// What a prefill call that would otherwise run instance `id` does with scratch memory.  Over the shapes named above the choice takes
 // 1.06x the time of the best measured one on average (1.28x at the 95th percentile) and gains 1.14x on average over no
 // parts; 1.7 % of the shapes lose more than 2 %, 0.5 % more than 10 %, nearly all of them batches of very uneven lengths, whose
 // maxima are all the host knows.  Examples (no parts -> parts): 2 x 4 tokens behind 5900 keys 46 -> 24 us, 3 x 17-70
@@ -825,7 +825,8 @@ int debug_validate_device_side(const attn_args *a, int is_decode, hipStream_t st
     return ATTN_OK;
 }
 
-int run(const attn_args *a, int is_decode, hipStream_t stream, int instance_override)
+// scratch: prefill in parts only
+int run(const attn_args *a, int is_decode, hipStream_t stream, int instance_override, void *scratch = nullptr, size_t scratch_bytes = 0)
 {
     int rc = validate(a, is_decode);
     if (rc != ATTN_OK) return rc;
@@ -857,11 +858,12 @@ int run(const attn_args *a, int is_decode, hipStream_t stream, int instance_over
         }
         apply_split(p, t[id]);
         if (need > 0 && ((uintptr_t)a->workspace & 7)) return ATTN_ERR_WORKSPACE;  // records are accessed as 8-byte pairs
-    } else if (instance_override < 0 && a->workspace && ((uintptr_t)a->workspace & 15) == 0) {
+    } else if (scratch && ((uintptr_t)scratch & 15) == 0) {
         const KeyPlan plan = planned_parts(p, a->dtype, id);
-        if (plan.parts > 1 && a->workspace_bytes >= key_parts_bytes(t[plan.id], p, plan.parts)) {  // (else: whole key ranges)
+        if (plan.parts > 1 && scratch_bytes >= key_parts_bytes(t[plan.id], p, plan.parts)) {  // (else: whole key ranges)
             id = plan.id;
             p.num_splits = plan.parts;
+            p.workspace = (float *)scratch;
         }
     }
     if (t[id].launch(p, stream) != hipSuccess) return ATTN_ERR_HIP;
@@ -1356,6 +1358,11 @@ int attn_decode_paged_static(const attn_args *args, void *hip_stream)
 size_t attn_static_scratch_bytes(void) { return kScratchBytes; }
 
 int attn_prefill_varlen(const attn_args *args, void *hip_stream) { return run(args, 0, (hipStream_t)hip_stream, -1); }
+
+int attn_prefill_varlen_parts(const attn_args *args, void *scratch, size_t scratch_bytes, void *hip_stream)
+{
+    return run(args, 0, (hipStream_t)hip_stream, -1, scratch, scratch_bytes);
+}
 
 int attn_decode_paged(const attn_args *args, void *hip_stream) { return run(args, 1, (hipStream_t)hip_stream, -1); }
 

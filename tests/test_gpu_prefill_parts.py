@@ -1,4 +1,4 @@
-"""Prefill whose keys are cut into parts over workgroups (a call that brings a workspace), by the key-split and by the ring
+"""Prefill whose keys are cut into parts over workgroups (a call that brings scratch memory), by the key-split and by the ring
 kernel: results at the edges of tiles and parts against the fp64 oracle, the calls that take a workspace, and those that must do without."""
 import numpy as np
 import pytest
@@ -52,10 +52,11 @@ SHAPES = [  # kernel, Hq, Hkv, D, block (0: packed), new tokens, keys; more than
 
 
 def _run(dw, ws, nbytes=None):
-    a = dw.args(False)
-    a.workspace, a.workspace_bytes = ws.data_ptr(), ws.nbytes if nbytes is None else nbytes
+    import torch
+
+    ws = ws.view(torch.uint8)
     dw.out.fill_(float("nan"))
-    A.attn_prefill_varlen(None, None, None, None, None, None, None, max_q_len=0, max_kv_len=0, args=a)
+    A.attn_prefill_varlen(None, None, None, None, None, None, None, max_q_len=0, max_kv_len=0, args=dw.args(False), workspace=ws[:nbytes])
     return dw.out
 
 
@@ -131,6 +132,56 @@ def test_infinities_and_nan_through_the_merge(kernel, D, new, keys, tensor, valu
         for pattern in (np.isnan, np.isposinf, np.isneginf):
             differ = int((pattern(split) != pattern(whole)).sum())
             assert differ == 0, (at, pattern.__name__)
+
+
+def test_refusals_are_those_of_the_call_without_scratch_memory():
+    args = dict(num_seqs=2, total_q=12, block_table_stride=2048, max_q_len=8, max_kv_len=8000)
+    for change in (dict(dtype=7), dict(num_kv_heads=3), dict(head_dim=80), dict(block_size=24), dict(q=0), dict(seq_lens=0), dict(k=0x100008)):
+        a = _paged(**dict(args, **change))
+        status = []
+        for call in (lambda: A.load_library().attn_prefill_varlen(a, None), lambda: A.load_library().attn_prefill_varlen_parts(a, 0x100000, 1 << 30, None)):
+            status.append(call())
+        assert status[0] == status[1] < 0, change
+
+
+@pytest.mark.gpu
+def test_a_workspace_in_the_struct_is_not_touched():
+    """One workspace pointer in the structs of decode and prefill calls that overlap is safe: prefill ignores it."""
+    import torch
+    from attn_testlib import DeviceWorkload
+
+    dw = DeviceWorkload(W.make_paged(181, "prefill", [5, 3], [4000, 3000], 8, 2, 128, 16, 450))
+    whole = dw.run(False).clone()
+    a = dw.args(False)
+    need = A.attn_prefill_scratch_bytes(a)
+    assert need > 0
+    ws = torch.full((2 * need,), 7, dtype=torch.uint8, device="cuda")
+    a.workspace, a.workspace_bytes = ws.data_ptr(), ws.nbytes
+    dw.out.fill_(float("nan"))
+    A.attn_prefill_varlen(None, None, None, None, None, None, None, max_q_len=0, max_kv_len=0, args=a)
+    assert torch.equal(dw.out, whole) and bool((ws == 7).all())
+
+
+@pytest.mark.gpu
+def test_a_captured_call_with_a_workspace_gives_the_eager_bits():
+    import torch
+    from attn_testlib import DeviceWorkload
+
+    dw = DeviceWorkload(W.make_paged(182, "prefill", [5, 3], [4000, 3000], 8, 2, 128, 16, 450))
+    ws = torch.empty(A.attn_prefill_scratch_bytes(dw.args(False)), dtype=torch.uint8, device="cuda")
+    run = lambda **kw: A.attn_prefill_varlen(dw.q, dw.k, dw.v, dw.out, dw.qsl, dw.seq_lens, dw.wl.scale, max_q_len=dw.max_q, max_kv_len=dw.max_kv,
+                                             block_table=dw.bt, **kw)
+    run()
+    eager = dw.out.clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run(workspace=ws)
+    for _ in range(3):
+        dw.out.fill_(float("nan"))
+        ws.fill_(255)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(dw.out, eager)
 
 
 @pytest.mark.gpu
