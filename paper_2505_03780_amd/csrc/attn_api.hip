@@ -297,17 +297,18 @@ size_t key_parts_bytes(const Instance &inst, const KParams &p, int parts)
 //  * Ring kernel, small workgroup (128 rows): two per compute unit, 8 us (4 us), 6 us (4.5 us) for each 256 keys, 4.5 us (3 us)
 //    while each has a compute unit to itself.
 // The second kernel costs 5 to 8 us.
+int64_t key_steps(const KParams &p, int parts) { return (((int64_t)p.max_kv_len + parts - 1) / parts + 255) / 256; }
 double split_model_us(const KParams &p, int64_t tiles, int parts)
 {
     const int64_t cus = compute_units(), slots = parts == 1 ? cus : std::max<int64_t>(1, cus * 9 / 10);
-    const int64_t rounds = (tiles * parts + slots - 1) / slots, steps = ((p.max_kv_len + parts - 1) / parts + 255) / 256;
+    const int64_t rounds = (tiles * parts + slots - 1) / slots, steps = key_steps(p, parts);
     return (double)rounds * (4.0 + (p.head_dim == 64 ? 1.0 : 1.5) * (double)steps) + (parts > 1 ? 5.0 : 0.0);
 }
 double ring_model_us(const KParams &p, int64_t tiles, int parts)
 {
     const bool small = p.head_dim == 64;
     const int64_t slots = 2 * compute_units(), n = tiles * parts, rest = n % slots;
-    const double steps = (double)(((p.max_kv_len + parts - 1) / parts + 255) / 256), start = small ? 4.0 : 8.0;
+    const double steps = (double)key_steps(p, parts), start = small ? 4.0 : 8.0;
     double us = (double)(n / slots) * (start + (small ? 4.5 : 6.0) * steps);
     if (rest > 0) us += start + (2 * rest <= slots ? (small ? 3.0 : 4.5) : (small ? 4.5 : 6.0)) * steps;
     return us + (parts > 1 ? 8.0 : 0.0);
@@ -325,7 +326,8 @@ void try_parts(const KParams &p, int id, double *us, KeyPlan *plan)
     const Instance &inst = instances(0, &n)[id];
     const KeyTiles tiles = key_tiles(inst, p);
     const bool ring = inst.heads_per_wg > 0;
-    // (at most four 32-row or two 128-row records per compute unit: some tens of MB)
+    // Four records of 32 rows per compute unit (17 MB); of 128 rows two, not counting every tile's first part, so four at two parts
+    // (68 MB) and fewer at more.
     const int64_t most = ring ? 2 * (int64_t)compute_units() + tiles.grid : 4 * (int64_t)compute_units();
     for (int parts = 2; parts <= (ring ? kMaxRingParts : kMaxSplitParts) && tiles.grid * parts <= most; ++parts) {
         const double t = ring ? ring_model_us(p, tiles.busy, parts) : split_model_us(p, tiles.busy, parts);

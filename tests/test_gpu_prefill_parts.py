@@ -5,7 +5,7 @@ import pytest
 
 import paper_2505_03780_amd as A
 import workloads as W
-from test_host_api import _paged
+from test_host_api import _args, _paged
 from test_prefill_split import _instance, _packed
 
 
@@ -27,6 +27,11 @@ def test_calls_that_take_a_workspace():
     assert A.attn_prefill_scratch_bytes(one) == 8 * 28 * 32 * 130 * 4  # one round
     a.struct_bytes += 8
     assert A.attn_prefill_scratch_bytes(a) == 0
+    # a bound that says nothing, as packed keys may have, is a very long context
+    free = lambda n: A.attn_prefill_scratch_bytes(_args(num_seqs=1, total_q=8, max_q_len=8, max_kv_len=n))
+    assert free(2 ** 31 - 1) == free(2 ** 30) > 0
+    # no more than four records of 128 rows per compute unit
+    assert A.attn_prefill_scratch_bytes(_paged(num_seqs=16, total_q=144, max_q_len=128, max_kv_len=3000, block_table_stride=256)) <= 1024 * 128 * 130 * 4
 
 
 def _ring(dtype, D, Hq, Hkv):
