@@ -658,10 +658,15 @@ SelectKey select_key(const KParams &p, int dtype)
     return SelectKey{dtype, p.head_dim, p.num_q_heads, p.num_kv_heads, p.block_table ? 1 : 0, p.block_size, p.causal,
                      p.num_seqs, p.max_q_len, p.max_kv_len, p.kv_stride_block, p.kv_stride_tok};
 }
+enum class Origin { built_in, tuned, forced };
+struct Selection {
+    int id = -1;  // or a negative attn_status
+    Origin origin = Origin::built_in;
+};
 struct SelectMemo {
     uint64_t generation = 0;
     SelectKey key{};
-    int id = -1;
+    Selection sel;
 };
 
 // ATTN_FORCE_INSTANCE=<exact instance name>: calls of the kind that has an instance of that name use
@@ -689,7 +694,7 @@ const EnvKnobs &env_knobs()
     return k;
 }
 
-int select_instance_slow(const KParams &p, int dtype, int is_decode)
+Selection selection_slow(const KParams &p, int dtype, int is_decode)
 {
     int n;
     const Instance *t = instances(is_decode, &n);
@@ -697,66 +702,70 @@ int select_instance_slow(const KParams &p, int dtype, int is_decode)
     const EnvKnobs &env = env_knobs();
     const std::string key = bucket_key(p, dtype, is_decode);
     int id = -1;
-    const char *why = "heuristic";
+    Origin origin = Origin::built_in;
     if (env.forced[is_decode] >= 0 && usable(t[env.forced[is_decode]], p, is_decode)) {
         id = env.forced[is_decode];
-        why = "ATTN_FORCE_INSTANCE";
+        origin = Origin::forced;
     }
     if (id < 0) {
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_winner[is_decode].find(key);
         if (it != g_winner[is_decode].end() && it->second < n && usable(t[it->second], p, is_decode)) {
             id = it->second;
-            why = "tuned";
+            origin = Origin::tuned;
         }
     }
     if (id < 0) id = heuristic(p, is_decode);
     if (env.log) {
+        const char *why = origin == Origin::forced ? "ATTN_FORCE_INSTANCE" : origin == Origin::tuned ? "tuned" : "heuristic";
         if (id >= 0)
             fprintf(stderr, "[attn] %s %s -> %s (%s)\n", is_decode ? "decode" : "prefill", key.c_str(), t[id].name, why);
         else
             fprintf(stderr, "[attn] %s %s -> no valid instance\n", is_decode ? "decode" : "prefill", key.c_str());
     }
-    return id >= 0 ? id : ATTN_ERR_UNSUPPORTED;
+    return Selection{id >= 0 ? id : ATTN_ERR_UNSUPPORTED, origin};
 }
 
-int select_instance(const KParams &p, int dtype, int is_decode)
+Selection selection(const KParams &p, int dtype, int is_decode)
 {
     const int forced = g_forced[is_decode].load();
     if (forced >= 0) {
         int n;
         const Instance *t = instances(is_decode, &n);
-        return forced < n && usable(t[forced], p, is_decode) ? forced : ATTN_ERR_UNSUPPORTED;
+        return Selection{forced < n && usable(t[forced], p, is_decode) ? forced : ATTN_ERR_UNSUPPORTED, Origin::forced};
     }
     static thread_local SelectMemo memo[2];
     SelectMemo &m = memo[is_decode];
     const SelectKey key = select_key(p, dtype);
     const uint64_t gen = g_generation.load(std::memory_order_acquire);
-    if (m.generation == gen && m.key == key) return m.id;
-    const int id = select_instance_slow(p, dtype, is_decode);
+    if (m.generation == gen && m.key == key) return m.sel;
+    const Selection sel = selection_slow(p, dtype, is_decode);
     // the generation is read again: a table change that raced with the slow path must not be memoised
     if (g_generation.load(std::memory_order_acquire) == gen) {
         m.generation = gen;
         m.key = key;
-        m.id = id;
+        m.sel = sel;
     }
-    return id;
+    return sel;
 }
+int select_instance(const KParams &p, int dtype, int is_decode) { return selection(p, dtype, is_decode).id; }
 
-// key_plan for a call that selects instance `id`; the last answer per thread is kept like the selection's.  A tuned winner is the
-// fastest without a workspace and gives way like the built-in choice; a forced instance does not.
-KeyPlan planned_parts(const KParams &p, int dtype, int id)
+// What a prefill call with scratch memory runs in place of the selected instance; the last answer per thread is kept like the
+// selection's.  Only the built-in choice gives way to another kernel: a tuned winner was measured on this GPU, which the models were
+// not, and stands as it is; a forced instance takes parts of its own at most.
+KeyPlan planned_parts(const KParams &p, int dtype, Selection sel)
 {
-    const bool forced = g_forced[0].load() >= 0 || env_knobs().forced[0] == id;
+    if (sel.origin == Origin::tuned) return KeyPlan{sel.id, 1};
     struct Memo {
         SelectKey key{};
-        int total_q = -1, id = -1;
-        bool forced = false;
+        int total_q = -1;
+        Selection sel;
         KeyPlan plan;
     };
     static thread_local Memo m;
     const SelectKey key = select_key(p, dtype);
-    if (m.id != id || m.forced != forced || m.total_q != p.total_q || !(m.key == key)) m = Memo{key, p.total_q, id, forced, key_plan(p, id, forced)};
+    if (m.sel.id != sel.id || m.sel.origin != sel.origin || m.total_q != p.total_q || !(m.key == key))
+        m = Memo{key, p.total_q, sel, key_plan(p, sel.id, sel.origin == Origin::forced)};
     return m.plan;
 }
 
@@ -846,7 +855,8 @@ int run(const attn_args *a, int is_decode, hipStream_t stream, int instance_over
     }
     int n;
     const Instance *t = instances(is_decode, &n);
-    int id = instance_override >= 0 ? instance_override : select_instance(p, a->dtype, is_decode);
+    const Selection sel = instance_override >= 0 ? Selection{instance_override, Origin::forced} : selection(p, a->dtype, is_decode);
+    int id = sel.id;
     if (id < 0) return id;
     if (id >= n || !usable(t[id], p, is_decode)) return ATTN_ERR_UNSUPPORTED;
     if (is_decode) {
@@ -861,7 +871,7 @@ int run(const attn_args *a, int is_decode, hipStream_t stream, int instance_over
         apply_split(p, t[id]);
         if (need > 0 && ((uintptr_t)a->workspace & 7)) return ATTN_ERR_WORKSPACE;  // records are accessed as 8-byte pairs
     } else if (scratch && ((uintptr_t)scratch & 15) == 0) {
-        const KeyPlan plan = planned_parts(p, a->dtype, id);
+        const KeyPlan plan = planned_parts(p, a->dtype, sel);
         if (plan.parts > 1 && scratch_bytes >= key_parts_bytes(t[plan.id], p, plan.parts)) {  // (else: whole key ranges)
             id = plan.id;
             p.num_splits = plan.parts;
@@ -1392,11 +1402,11 @@ size_t attn_prefill_scratch_bytes(const attn_args *a)
         a->max_q_len < 0 || a->max_kv_len < 0 || (a->head_dim != 64 && a->head_dim != 128) || !is16(a->dtype))
         return 0;
     const KParams p = to_kparams(a, 0);
-    const int id = select_instance(p, a->dtype, 0);
-    if (id < 0) return 0;
+    const Selection sel = selection(p, a->dtype, 0);
+    if (sel.id < 0) return 0;
     int n;
     const Instance *t = instances(0, &n);
-    const KeyPlan plan = planned_parts(p, a->dtype, id);
+    const KeyPlan plan = planned_parts(p, a->dtype, sel);
     return key_parts_bytes(t[plan.id], p, plan.parts);
 }
 

@@ -139,6 +139,23 @@ def test_infinities_and_nan_through_the_merge(kernel, D, new, keys, tensor, valu
             assert differ == 0, (at, pattern.__name__)
 
 
+def test_a_tuned_winner_stands(tmp_path):
+    """Only the built-in choice gives way to parts by the library's models; a winner was measured."""
+    A.attn_clear_cache()
+    A.attn_force_instance(False, -1)
+    a = _paged(num_seqs=3, total_q=130, block_table_stride=2048, max_q_len=70, max_kv_len=7948)
+    need = A.attn_prefill_scratch_bytes(a)
+    assert need > 0
+    built_in = A.attn_selected_instance(a, False)
+    for winner in (built_in, _instance("bf16", 128), _ring("bf16", 128, 32, 8)):
+        f = tmp_path / "c.txt"
+        f.write_text("attn-tune-cache-v1\n%s\tprefill|bf16|d128|hq32|hkv8|paged|bs16|c1|B2|q7|kv13\t%s\t1.0\n" % (A.attn_environment_key(), A.attn_instance_name(False, winner)))
+        assert A.attn_load_cache(str(f)) == 0
+        assert A.attn_selected_instance(a, False) == winner and A.attn_prefill_scratch_bytes(a) == 0
+    A.attn_clear_cache()
+    assert A.attn_selected_instance(a, False) == built_in and A.attn_prefill_scratch_bytes(a) == need
+
+
 def test_refusals_are_those_of_the_call_without_scratch_memory():
     args = dict(num_seqs=2, total_q=12, block_table_stride=2048, max_q_len=8, max_kv_len=8000)
     for change in (dict(dtype=7), dict(num_kv_heads=3), dict(head_dim=80), dict(block_size=24), dict(q=0), dict(seq_lens=0), dict(k=0x100008)):
