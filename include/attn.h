@@ -130,6 +130,9 @@ int attn_prefill_varlen_parts(const attn_args *args, void *scratch, size_t scrat
 /* Bytes of scratch memory with which the next attn_prefill_varlen_parts call with these args splits its keys over workgroups (at
  * most some tens of MB; pointer fields other than block_table are ignored).  0: the call does not use any. */
 size_t attn_prefill_scratch_bytes(const attn_args *args);
+/* Instance that call would launch with that much scratch memory, and in *parts (unless NULL) the number of parts of the keys (1: it
+ * splits none, and the instance is that of attn_selected_instance); or < 0. */
+int attn_prefill_parts_instance(const attn_args *args, int32_t *parts);
 
 /*
  * Paged-KV decode: one query token per sequence (q is [B, Hq, D]) attending to
@@ -247,7 +250,8 @@ int attn_num_instances(int is_decode);
  * "prefill_bf16_ring d128 qb1 w8 hpw4 slots8 pf5 seqmajor" or "decode_bf16_balanced d128 w4 percu1"),
  * truncated to buf_bytes - 1 characters; returns the length written, or a negative attn_status for a bad id. */
 int attn_instance_name(int is_decode, int id, char *buf, size_t buf_bytes);
-/* Instance the next hot call with these args would launch (cache winner, else heuristic), or <0. */
+/* Instance the next hot call with these args would launch (cache winner, else heuristic), or <0.  For prefill: the next
+ * attn_prefill_varlen call (attn_prefill_parts_instance: the next call with scratch memory). */
 int attn_selected_instance(const attn_args *args, int is_decode);
 /* Force an instance id for all later hot calls of that kind (-1 = back to automatic).  Invalid
  * combinations are rejected by the hot call with ATTN_ERR_UNSUPPORTED. */

@@ -88,6 +88,8 @@ def load_library():
     lib.attn_workspace_bytes.argtypes = [P, ctypes.c_int]
     lib.attn_prefill_scratch_bytes.restype = ctypes.c_size_t
     lib.attn_prefill_scratch_bytes.argtypes = [P]
+    lib.attn_prefill_parts_instance.restype = ctypes.c_int
+    lib.attn_prefill_parts_instance.argtypes = [P, ctypes.POINTER(ctypes.c_int32)]
     lib.attn_prefill_varlen_parts.restype = ctypes.c_int
     lib.attn_prefill_varlen_parts.argtypes = [P, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
     lib.attn_tune.restype = ctypes.c_int
@@ -406,6 +408,15 @@ def attn_workspace_bytes(args: AttnArgs, is_decode: bool) -> int:
 
 def attn_prefill_scratch_bytes(args: AttnArgs) -> int:
     return int(load_library().attn_prefill_scratch_bytes(ctypes.byref(args)))
+
+
+def attn_prefill_parts_instance(args: AttnArgs):
+    """(instance, parts of the keys) that the next prefill call with these args and scratch memory would launch."""
+    parts = ctypes.c_int32(1)
+    rc = int(load_library().attn_prefill_parts_instance(ctypes.byref(args), ctypes.byref(parts)))
+    if rc < 0:
+        raise AttnError(rc, "attn_prefill_parts_instance")
+    return rc, parts.value
 
 
 def attn_tune(args: AttnArgs, is_decode: bool, cache_path: Optional[str] = None, iters: int = 20, flags: int = 0) -> None:

@@ -764,9 +764,31 @@ KeyPlan planned_parts(const KParams &p, int dtype, Selection sel)
     };
     static thread_local Memo m;
     const SelectKey key = select_key(p, dtype);
-    if (m.sel.id != sel.id || m.sel.origin != sel.origin || m.total_q != p.total_q || !(m.key == key))
+    if (m.sel.id != sel.id || m.sel.origin != sel.origin || m.total_q != p.total_q || !(m.key == key)) {
         m = Memo{key, p.total_q, sel, key_plan(p, sel.id, sel.origin == Origin::forced)};
+        if (env_knobs().log && m.plan.parts > 1) {
+            int n;
+            fprintf(stderr, "[attn] prefill %s with scratch memory -> %s in %d parts\n", bucket_key(p, dtype, 0).c_str(),
+                    instances(0, &n)[m.plan.id].name, m.plan.parts);
+        }
+    }
     return m.plan;
+}
+
+// The plan of the prefill call `a` with scratch memory (pointer fields but block_table are ignored).
+int prefill_plan(const attn_args *a, KeyPlan *plan)
+{
+    if (!a) return ATTN_ERR_NULL;
+    if (a->struct_bytes != sizeof(attn_args) || a->num_seqs <= 0 || a->total_q <= 0 || a->num_q_heads <= 0 || a->num_kv_heads <= 0 ||
+        a->num_q_heads % a->num_kv_heads || a->max_q_len < 0 || a->max_kv_len < 0)
+        return ATTN_ERR_SHAPE;
+    if (a->head_dim != 64 && a->head_dim != 128) return ATTN_ERR_UNSUPPORTED;
+    if (!is16(a->dtype)) return ATTN_ERR_DTYPE;
+    const KParams p = to_kparams(a, 0);
+    const Selection sel = selection(p, a->dtype, 0);
+    if (sel.id < 0) return sel.id;
+    *plan = planned_parts(p, a->dtype, sel);
+    return ATTN_OK;
 }
 
 size_t balanced_workspace_bytes(int num_seqs, int num_q_heads, int head_dim, int wgs)
@@ -1397,17 +1419,19 @@ size_t attn_workspace_bytes(const attn_args *a, int is_decode)
 
 size_t attn_prefill_scratch_bytes(const attn_args *a)
 {
-    if (!a || a->struct_bytes != sizeof(attn_args)) return 0;
-    if (a->num_seqs <= 0 || a->total_q <= 0 || a->num_q_heads <= 0 || a->num_kv_heads <= 0 || a->num_q_heads % a->num_kv_heads ||
-        a->max_q_len < 0 || a->max_kv_len < 0 || (a->head_dim != 64 && a->head_dim != 128) || !is16(a->dtype))
-        return 0;
-    const KParams p = to_kparams(a, 0);
-    const Selection sel = selection(p, a->dtype, 0);
-    if (sel.id < 0) return 0;
+    KeyPlan plan;
+    if (prefill_plan(a, &plan) != ATTN_OK) return 0;
     int n;
-    const Instance *t = instances(0, &n);
-    const KeyPlan plan = planned_parts(p, a->dtype, sel);
-    return key_parts_bytes(t[plan.id], p, plan.parts);
+    return key_parts_bytes(instances(0, &n)[plan.id], to_kparams(a, 0), plan.parts);
+}
+
+int attn_prefill_parts_instance(const attn_args *a, int32_t *parts)
+{
+    KeyPlan plan;
+    const int rc = prefill_plan(a, &plan);
+    if (rc != ATTN_OK) return rc;
+    if (parts) *parts = plan.parts;
+    return plan.id;
 }
 
 int attn_tune(const attn_args *shape_like, int is_decode, const char *cache_path, int iters, int flags)

@@ -156,6 +156,31 @@ def test_a_tuned_winner_stands(tmp_path):
     assert A.attn_selected_instance(a, False) == built_in and A.attn_prefill_scratch_bytes(a) == need
 
 
+def test_the_plan_is_reported():
+    """The instance and the parts that a call with scratch memory launches; attn_selected_instance speaks of the call without."""
+    import os
+    import subprocess
+    import sys
+
+    A.attn_clear_cache()
+    A.attn_force_instance(False, -1)
+    a = _paged(num_seqs=3, total_q=130, block_table_stride=2048, max_q_len=70, max_kv_len=7948)
+    selected, (planned, parts) = A.attn_selected_instance(a, False), A.attn_prefill_parts_instance(a)
+    assert "keysplit" in A.attn_instance_name(False, selected) and planned == _ring("bf16", 128, 32, 8)
+    assert A.attn_prefill_scratch_bytes(a) == 72 * parts * 128 * 130 * 4
+    short = _paged(num_seqs=3, total_q=130, block_table_stride=2048, max_q_len=70, max_kv_len=1000)
+    assert A.attn_prefill_parts_instance(short) == (A.attn_selected_instance(short, False), 1)
+    with pytest.raises(A.AttnError):
+        A.attn_prefill_parts_instance(_paged(head_dim=80))
+    here = os.path.dirname(os.path.abspath(__file__))
+    code = ("import sys; sys.path[:0] = [%r, %r]\nimport test_host_api as T, paper_2505_03780_amd as A\n"
+            "A.attn_prefill_scratch_bytes(T._paged(num_seqs=3, total_q=130, block_table_stride=2048, max_q_len=70, max_kv_len=7948))\n" % (os.path.dirname(here), here))
+    env = dict(os.environ, ATTN_LOG="1")
+    env.pop("ATTN_FORCE_INSTANCE", None)
+    log = subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True, timeout=100).stderr
+    assert "with scratch memory -> %s in %d parts" % (A.attn_instance_name(False, planned), parts) in log
+
+
 def test_refusals_are_those_of_the_call_without_scratch_memory():
     args = dict(num_seqs=2, total_q=12, block_table_stride=2048, max_q_len=8, max_kv_len=8000)
     for change in (dict(dtype=7), dict(num_kv_heads=3), dict(head_dim=80), dict(block_size=24), dict(q=0), dict(seq_lens=0), dict(k=0x100008)):
