@@ -293,25 +293,40 @@ size_t key_parts_bytes(const Instance &inst, const KParams &p, int parts)
 // Time that a call is expected to take (us), by kernel; fitted to some 5900 random shapes (batch 1-32, 8-1024 new tokens,
 // 500-20000 keys, up to 600 tiles of 128 rows) with 1 to 16 parts each.  Workgroups run in rounds of as many as are resident.
 //  * Key-split kernel (32 rows): one workgroup per compute unit, 4 us for its start and its merge through LDS, 1.5 us (D = 64:
-//    1 us) for each 256 keys; nine tenths of the compute units count as a round, because XCDs get uneven shares.
+//    1 us) for each 256 keys.  A few workgroups beyond a round share compute units at little cost while the keys are whole (264 to
+//    280 tiles take 1.0 to 1.2 rounds with uneven lengths or at D = 64, and two with even ones).  In parts the empty workgroups of the grid count too: they end at once, but XCDs are dealt
+//    workgroups blindly, and some get full ones in excess (counting only the full ones, 2 x 52-133 tokens of 16/16 heads behind 5400 keys, 320
+//    workgroups and 224 of them full, were expected to take 26 us, and took 52).
 //  * Ring kernel, small workgroup (128 rows): two per compute unit, 8 us (4 us), 6 us (4.5 us) for each 256 keys, 4.5 us (3 us)
-//    while each has a compute unit to itself.
+//    while each has a compute unit to itself.  Large workgroup (256 rows): one per compute unit, 8 us, 5.5 us for each 256 keys.
 // The second kernel costs 5 to 8 us.
 int64_t key_steps(const KParams &p, int parts) { return (((int64_t)p.max_kv_len + parts - 1) / parts + 255) / 256; }
-double split_model_us(const KParams &p, int64_t tiles, int parts)
+double split_model_us(const KParams &p, const KeyTiles &tiles, int parts)
 {
-    const int64_t cus = compute_units(), slots = parts == 1 ? cus : std::max<int64_t>(1, cus * 9 / 10);
-    const int64_t rounds = (tiles * parts + slots - 1) / slots, steps = key_steps(p, parts);
-    return (double)rounds * (4.0 + (p.head_dim == 64 ? 1.0 : 1.5) * (double)steps) + (parts > 1 ? 5.0 : 0.0);
+    const int64_t cus = compute_units(), n = parts == 1 ? tiles.busy : tiles.grid * parts;
+    double rounds = (double)((n + cus - 1) / cus);
+    if (parts == 1) {
+        const double full = (double)n / (double)cus;
+        rounds = std::min(rounds, full <= 1.1 ? std::max(1.0, 1.2 * full) : 1.4 * full);
+    }
+    return rounds * (4.0 + (p.head_dim == 64 ? 1.0 : 1.5) * (double)key_steps(p, parts)) + (parts > 1 ? 5.0 : 0.0);
 }
-double ring_model_us(const KParams &p, int64_t tiles, int parts)
+double ring_model_us(const KParams &p, const KeyTiles &tiles, int parts)
 {
     const bool small = p.head_dim == 64;
-    const int64_t slots = 2 * compute_units(), n = tiles * parts, rest = n % slots;
+    const int64_t slots = 2 * compute_units(), n = tiles.busy * parts, rest = n % slots;
     const double steps = (double)key_steps(p, parts), start = small ? 4.0 : 8.0;
     double us = (double)(n / slots) * (start + (small ? 4.5 : 6.0) * steps);
     if (rest > 0) us += start + (2 * rest <= slots ? (small ? 3.0 : 4.5) : (small ? 4.5 : 6.0)) * steps;
     return us + (parts > 1 ? 8.0 : 0.0);
+}
+// The instance that a plan would replace, with whole keys.
+double whole_model_us(const Instance &inst, const KParams &p)
+{
+    const KeyTiles tiles = key_tiles(inst, p);
+    if (inst.heads_per_wg == 0) return split_model_us(p, tiles, 1);
+    if (inst.block_m == 128) return ring_model_us(p, tiles, 1);
+    return std::max(1.0, (double)tiles.busy / (double)compute_units()) * (8.0 + 5.5 * (double)key_steps(p, 1));
 }
 
 struct KeyPlan {
@@ -330,7 +345,7 @@ void try_parts(const KParams &p, int id, double *us, KeyPlan *plan)
     // (68 MB) and fewer at more.
     const int64_t most = ring ? 2 * (int64_t)compute_units() + tiles.grid : 4 * (int64_t)compute_units();
     for (int parts = 2; parts <= (ring ? kMaxRingParts : kMaxSplitParts) && tiles.grid * parts <= most; ++parts) {
-        const double t = ring ? ring_model_us(p, tiles.busy, parts) : split_model_us(p, tiles.busy, parts);
+        const double t = ring ? ring_model_us(p, tiles, parts) : split_model_us(p, tiles, parts);
         if (t < *us) {
             *us = t;
             *plan = KeyPlan{id, parts};
@@ -338,11 +353,11 @@ void try_parts(const KParams &p, int id, double *us, KeyPlan *plan)
     }
 }
 
-// What a prefill call that would otherwise run instance `id` does with scratch memory.  Over the shapes named above the choice takes
-// 1.06x the time of the best measured one on average (1.28x at the 95th percentile) and gains 1.14x on average over no
-// parts; 1.7 % of the shapes lose more than 2 %, 0.5 % more than 10 %, nearly all of them batches of very uneven lengths, whose
-// maxima are all the host knows.  Examples (no parts -> parts): 2 x 4 tokens behind 5900 keys 46 -> 24 us, 3 x 17-70
-// behind 5000-9000 57 -> 42, 10 x 21-40 behind 17000 (D = 64) 243 -> 122, 3 x 390-450 of 16/16 heads behind 3900 98 -> 75.
+// What a prefill call that would otherwise run instance `id` does with scratch memory.  The margins are set so that next to
+// nothing loses: of 57100 random calls that take parts (half of the ranges above, down to one new token and with uneven lengths; half
+// drawn like the calls of perf/cases.py) 0.2 % are more than 2 % behind no parts and 0.04 % more than 10 %, nearly all of them batches of
+// very uneven lengths, whose maxima are all that the host knows; the average gain is 1.7x.  Examples (no parts -> parts): 2 x 4 tokens behind 5900 keys 46 -> 24 us, 3 x 17-70
+// behind 5000-9000 51 -> 41, 10 x 21-40 behind 17000 (D = 64) 243 -> 122, 3 x 390-450 of 16/16 heads behind 3900 98 -> 75.
 KeyPlan key_plan(const KParams &p, int id, bool forced)
 {
     int n;
@@ -351,26 +366,27 @@ KeyPlan key_plan(const KParams &p, int id, bool forced)
     KeyPlan plan{id, 1};
     if (p.max_kv_len <= 1024) return plan;
     const int64_t cus = compute_units();
+    const double whole = whole_model_us(t[id], p);
     if (split) {
-        // 8 % ahead or not at all, 25 % from half a workgroup per compute unit on, where uneven lengths decide
+        // 15 % ahead or not at all, 25 % from half a workgroup per compute unit on, where uneven lengths decide
         const int64_t busy = key_tiles(t[id], p).busy;
-        const double whole = split_model_us(p, busy, 1);
-        double us = whole / (2 * busy > cus ? 1.25 : 1.08);
+        double us = whole / (2 * busy > cus ? 1.25 : 1.15);
         try_parts(p, id, &us, &plan);
-        // tiles of 128 rows, where the new tokens fill at least half of them
+        // tiles of 128 rows, where the new tokens fill at least half of them and that is well ahead
         if (!forced && p.max_kv_len >= (p.head_dim == 64 ? 3000 : 2000)) {
             const int ring = small_ring_instance(p);
             if (ring >= 0 && 2 * key_tiles(t[ring], p).busy <= busy) {
-                us = std::min(us, whole);
+                us = std::min(us, whole / (p.head_dim == 64 ? 1.3 : 1.2));
                 try_parts(p, ring, &us, &plan);
             }
         }
         return plan;
     }
-    // ring kernels: the small workgroup in parts, 10 % ahead or not at all; level or behind below 2048 keys
+    // ring kernels: the small workgroup in parts; level or behind below 2048 keys.  10 % ahead of the instance that it replaces or
+    // not at all, 50 % where nearly every compute unit has a tile already and parts only pair them up.
     const int ring = forced ? (small_ring ? id : -1) : small_ring_instance(p);
     if (ring >= 0 && p.max_kv_len >= 2048) {
-        double us = ring_model_us(p, key_tiles(t[ring], p).busy, 1) / 1.1;
+        double us = whole / (8 * key_tiles(t[ring], p).busy > 7 * cus ? 1.5 : 1.1);
         try_parts(p, ring, &us, &plan);
     }
     return plan;
