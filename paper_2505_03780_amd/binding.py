@@ -310,26 +310,17 @@ def _stream_ptr(stream) -> int:
 
 
 def _prefill_scratch(packed: bytes, stream):
-    """Scratch memory for the prefill call described by ``packed`` on ``stream``, or None.  The block belongs to that stream's pool
-    of the caching allocator: once freed it is only handed out to later work of the same stream."""
+    """(address, bytes) of scratch memory for the prefill call described by ``packed`` on ``stream``; (0, 0) for a call that does
+    without: one that uses none, on a stream that is not torch's or not the current device's, under capture, or when memory is short."""
     n = _hot["attn_prefill_scratch_bytes"](packed)
     if n == 0:
-        return None
-    import torch
-
+        return 0, 0
     if stream is not None:
-        with torch.cuda.stream(stream):
-            return _scratch_block(torch, n)
-    return _scratch_block(torch, n)
+        import torch
 
-
-def _scratch_block(torch, n: int):
-    if torch.cuda.is_current_stream_capturing():
-        return None
-    try:
-        return torch.empty(n, dtype=torch.uint8, device="cuda")
-    except torch.cuda.OutOfMemoryError:
-        return None  # the call runs without
+        if not isinstance(stream, torch.cuda.Stream) or stream.device_index != _current_device():
+            return 0, 0
+    return _fast.scratch(n, _stream_ptr(stream)), n
 
 
 def attn_prefill_varlen(q, k, v, out, query_start_loc, seq_lens, scale, *, max_q_len, max_kv_len, causal=True,
@@ -352,13 +343,19 @@ def attn_prefill_varlen(q, k, v, out, query_start_loc, seq_lens, scale, *, max_q
     if rc is None:
         a = _packed(_pack_attn, AttnArgs, _attn_fields(q, k, v, out, seq_lens, scale, max_q_len, max_kv_len, query_start_loc, kv_start_loc,
                                                        block_table, causal, None))
-        # (necessary conditions of the library's own rule, to save short calls the question)
-        if workspace is None and max_kv_len > 1024 and q.shape[0] * q.shape[1] <= 131072:
-            workspace = _prefill_scratch(a, stream)
-        if workspace is None:
-            rc = _hot["attn_prefill_varlen"](a, _stream_ptr(stream))
-        else:
+        ptr = 0
+        if workspace is not None:
             rc = _hot["attn_prefill_varlen_parts"](a, workspace.data_ptr(), workspace.nbytes, _stream_ptr(stream))
+        # (necessary conditions of the library's own rule, to save short calls the question)
+        elif max_kv_len > 1024 and q.shape[0] * q.shape[1] <= 131072:
+            ptr, n = _prefill_scratch(a, stream)
+        if ptr:
+            try:
+                rc = _hot["attn_prefill_varlen_parts"](a, ptr, n, _stream_ptr(stream))
+            finally:
+                _fast.release(ptr)
+        elif rc is None:
+            rc = _hot["attn_prefill_varlen"](a, _stream_ptr(stream))
     if rc != 0:
         raise AttnError(rc, "attn_prefill_varlen")
 

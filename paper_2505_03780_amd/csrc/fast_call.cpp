@@ -9,6 +9,7 @@
 // the general way, which also raises the errors.
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
+#include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -228,6 +229,55 @@ PyObject *py_pack_rmsnorm(PyObject *, PyObject *const *o, Py_ssize_t n)
 {
     return arguments(n, 5) ? call<rmsnorm_args>(nullptr, o, fill_rmsnorm) : nullptr;
 }
+// Scratch memory for a prefill call: bytes and stream handle -> address, or 0 where the call has to do without.  The block belongs
+// to the stream's pool of torch's caching allocator, so once released it only goes to later work of the same stream.  Taken from the
+// allocator itself and not as a tensor, which modes (fake tensors, deterministic filling) would see.
+PyObject *py_scratch(PyObject *, PyObject *const *o, Py_ssize_t n)
+{
+    if (!arguments(n, 2)) return nullptr;
+    const size_t bytes = PyLong_AsSize_t(o[0]);
+    const hipStream_t stream = PyErr_Occurred() ? nullptr : (hipStream_t)PyLong_AsVoidPtr(o[1]);
+    if (PyErr_Occurred()) return nullptr;
+    // A failed request makes the allocator give its whole cache back and wait for the GPU: after one the thread's next calls do not ask.
+    static thread_local int do_without = 0;
+    if (do_without > 0) {
+        --do_without;
+        return PyLong_FromLong(0);
+    }
+    void *p = nullptr;
+    Py_BEGIN_ALLOW_THREADS
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (stream == hipStreamPerThread) {  // (one handle for the streams of all threads)
+    } else if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
+        (void)hipGetLastError();
+    } else if (status == hipStreamCaptureStatusNone) {  // (else: nobody would hold the memory for the replays)
+        // another stream may be capturing, which an allocation must not end
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        try {
+            p = c10::hip::HIPCachingAllocator::raw_alloc_with_stream(bytes, stream);
+        } catch (...) {
+            p = nullptr;
+        }
+        if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (!p) do_without = 1000;
+    }
+    Py_END_ALLOW_THREADS
+    return PyLong_FromVoidPtr(p);
+}
+PyObject *py_release(PyObject *, PyObject *const *o, Py_ssize_t n)
+{
+    if (!arguments(n, 1)) return nullptr;
+    void *p = PyLong_AsVoidPtr(o[0]);
+    if (PyErr_Occurred()) return nullptr;
+    try {
+        c10::hip::HIPCachingAllocator::raw_delete(p);
+    } catch (const std::exception &e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what());
+        return nullptr;
+    }
+    Py_RETURN_NONE;
+}
 // addresses of attn_prefill_varlen, attn_decode_paged, attn_decode_paged_static, attn_kv_cache_write, rmsnorm_fused_add
 PyObject *py_bind(PyObject *, PyObject *const *o, Py_ssize_t n)
 {
@@ -249,6 +299,8 @@ PyMethodDef methods[] = {
     {"attn", FASTCALL(py_attn), nullptr},
     {"kv_write", FASTCALL(py_kv_write), nullptr},
     {"rmsnorm", FASTCALL(py_rmsnorm), nullptr},
+    {"scratch", FASTCALL(py_scratch), nullptr},
+    {"release", FASTCALL(py_release), nullptr},
     {"pack_kv_write", FASTCALL(py_pack_kv_write), nullptr},
     {"pack_rmsnorm", FASTCALL(py_pack_rmsnorm), nullptr},
     {nullptr, nullptr, 0, nullptr},

@@ -262,3 +262,68 @@ def test_tensor_call_takes_and_leaves_the_workspace():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(dw.out, whole)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("how", ["handle", "fake tensors", "another capture", "short memory"])
+def test_calls_that_taking_scratch_memory_must_not_disturb(how):
+    """What a call served before it took scratch memory it serves still: on a stream object that only has a handle, under a mode that
+    makes new tensors fake ones, beside another stream's capture, and with no memory left (which must not cost the
+    allocator's cache on every call)."""
+    import threading
+    import types
+
+    import torch
+    from attn_testlib import DeviceWorkload
+
+    dw = DeviceWorkload(W.make_paged(183, "prefill", [5, 3], [4000, 3000], 8, 2, 128, 16, 450))
+    assert A.attn_prefill_scratch_bytes(dw.args(False)) > 0
+    run = lambda **kw: A.attn_prefill_varlen(dw.q, dw.k, dw.v, dw.out, dw.qsl, dw.seq_lens, dw.wl.scale, max_q_len=dw.max_q, max_kv_len=dw.max_kv,
+                                             block_table=dw.bt, **kw)
+    side = torch.cuda.Stream()
+    whole = dw.run(False).clone()
+    run(stream=side)
+    torch.cuda.synchronize()
+    split = dw.out.clone()
+    assert not torch.equal(split, whole)
+    dw.out.fill_(float("nan"))
+    torch.cuda.synchronize()
+    if how == "handle":
+        run(stream=types.SimpleNamespace(cuda_stream=side.cuda_stream))
+        torch.cuda.synchronize()
+        assert torch.equal(dw.out, whole)
+    elif how == "fake tensors":
+        from torch._subclasses.fake_tensor import FakeTensorMode
+
+        with FakeTensorMode():
+            run()
+        torch.cuda.synchronize()
+        assert torch.equal(dw.out, split)
+    elif how == "another capture":
+        x, graph = torch.zeros(64, device="cuda"), torch.cuda.CUDAGraph()
+        torch.cuda.empty_cache()  # the scratch memory has to come from the device
+        with torch.cuda.graph(graph):
+            x += 1
+            run(stream=side)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(dw.out, split) and bool((x == 1).all())
+    else:
+        failed = []
+
+        def calls():  # (in a thread of its own: it does without for a while)
+            torch.cuda.empty_cache()
+            before = torch.cuda.memory_stats()["num_alloc_retries"]
+            torch.cuda.set_per_process_memory_fraction(1e-6)
+            try:
+                for _ in range(5):
+                    run(stream=side)
+            finally:
+                torch.cuda.set_per_process_memory_fraction(1.0)
+            failed.append(torch.cuda.memory_stats()["num_alloc_retries"] - before)
+
+        t = threading.Thread(target=calls)
+        t.start()
+        t.join()
+        torch.cuda.synchronize()
+        assert torch.equal(dw.out, whole) and failed[0] <= 1
