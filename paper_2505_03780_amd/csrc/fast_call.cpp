@@ -4,7 +4,7 @@
 // other, through Python and through here: that prefill 6.4 -> 5.3 us, that decode 9.1 -> 8.2, short cache writes, norms and decodes
 // 5.1-6.0 -> 4.1-4.3.
 //
-// Only the plain case is taken: exact torch tensors on the GPU, built-in ints and floats, values that fit their fields, every check
+// Only the plain case is taken: exact torch tensors on one GPU, built-in ints and floats, values that fit their fields, every check
 // of the Python path passed, no torch function mode.  Anything else returns None with nothing enqueued, and the caller goes
 // the general way, which also raises the errors.
 #include <ATen/ATen.h>
@@ -17,6 +17,7 @@
 #include <cmath>
 #include <cstring>
 #include <exception>
+#include <initializer_list>
 
 #include "../../include/attn.h"
 #include "../../include/rmsnorm.h"
@@ -65,6 +66,15 @@ bool as_float(PyObject *o, float *out)
     *out = (float)x;
     return true;
 }
+// Whether all tensors (null pointers aside) are where the first one is, and that is on a GPU if a kernel is to be launched with them.
+bool together(std::initializer_list<const at::Tensor *> tensors, bool launch)
+{
+    const at::Tensor *first = *tensors.begin();
+    if (launch && !first->is_cuda()) return false;
+    for (const at::Tensor *t : tensors)
+        if (t && t->device() != first->device()) return false;
+    return true;
+}
 // None or a contiguous int32 tensor; *t stays null for None
 bool int32_tensor(PyObject *o, const at::Tensor **t)
 {
@@ -76,13 +86,15 @@ bool int32_tensor(PyObject *o, const at::Tensor **t)
 
 // The 13 values of binding._attn_fields: q, k, v, out, seq_lens, scale, max_q_len, max_kv_len, query_start_loc, kv_start_loc,
 // block_table, causal, workspace.
-bool fill_attn(PyObject *const *o, attn_args *a, bool need_gpu)
+bool fill_attn(PyObject *const *o, attn_args *a, bool launch)
 {
     const at::Tensor *q = plain(o[0]), *k = plain(o[1]), *v = plain(o[2]), *out = plain(o[3]), *lens, *qsl, *kvsl, *table;
     if (!q || !k || !v || !out || !int32_tensor(o[4], &lens) || !lens || !int32_tensor(o[8], &qsl) || !int32_tensor(o[9], &kvsl) ||
         !int32_tensor(o[10], &table) || !PyBool_Check(o[11]))
         return false;
-    if (need_gpu && !(q->is_cuda() && k->is_cuda() && v->is_cuda() && out->is_cuda() && lens->is_cuda())) return false;
+    const at::Tensor *ws = o[12] == Py_None ? nullptr : plain(o[12]);
+    if (!ws && o[12] != Py_None) return false;
+    if (!together({q, k, v, out, lens, qsl, kvsl, table, ws}, launch)) return false;
     if (q->dim() != 3 || out->dim() != 3 || k->dim() != (table ? 4 : 3) || lens->dim() < 1 || (table && table->dim() < 1)) return false;
     memset(a, 0, sizeof *a);
     a->struct_bytes = sizeof *a;
@@ -115,9 +127,7 @@ bool fill_attn(PyObject *const *o, attn_args *a, bool need_gpu)
     a->kv_start_loc = kvsl ? (const int32_t *)kvsl->data_ptr() : nullptr;
     a->seq_lens = (const int32_t *)lens->data_ptr();
     a->causal = o[11] == Py_True ? 1 : 0;
-    if (o[12] != Py_None) {
-        const at::Tensor *ws = plain(o[12]);
-        if (!ws) return false;
+    if (ws) {
         a->workspace = ws->data_ptr();
         a->workspace_bytes = (uint64_t)ws->numel() * ws->element_size();
     }
@@ -125,11 +135,11 @@ bool fill_attn(PyObject *const *o, attn_args *a, bool need_gpu)
 }
 
 // k_new, v_new, k_cache, v_cache, slot_mapping
-bool fill_kv_write(PyObject *const *o, attn_kv_write_args *a, bool need_gpu)
+bool fill_kv_write(PyObject *const *o, attn_kv_write_args *a, bool launch)
 {
     const at::Tensor *kn = plain(o[0]), *vn = plain(o[1]), *kc = plain(o[2]), *vc = plain(o[3]), *slots;
     if (!kn || !vn || !kc || !vc || !int32_tensor(o[4], &slots) || !slots) return false;
-    if (need_gpu && !(kn->is_cuda() && vn->is_cuda() && kc->is_cuda() && vc->is_cuda() && slots->is_cuda())) return false;
+    if (!together({kn, vn, kc, vc, slots}, launch)) return false;
     if (kn->dim() != 3 || vn->dim() != 3 || kc->dim() != 4 || vc->dim() != 4) return false;
     if (kn->strides() != vn->strides() || kc->strides() != vc->strides() || kn->stride(2) != 1 || kc->stride(3) != 1) return false;
     memset(a, 0, sizeof *a);
@@ -151,11 +161,11 @@ bool fill_kv_write(PyObject *const *o, attn_kv_write_args *a, bool need_gpu)
 }
 
 // x, weight, out, eps, residual
-bool fill_rmsnorm(PyObject *const *o, rmsnorm_args *a, bool need_gpu)
+bool fill_rmsnorm(PyObject *const *o, rmsnorm_args *a, bool launch)
 {
     const at::Tensor *x = plain(o[0]), *w = plain(o[1]), *out = plain(o[2]), *res = o[4] == Py_None ? nullptr : plain(o[4]);
     if (!x || !w || !out || (!res && o[4] != Py_None)) return false;
-    if (need_gpu && !(x->is_cuda() && w->is_cuda() && out->is_cuda() && (!res || res->is_cuda()))) return false;
+    if (!together({x, w, out, res}, launch)) return false;
     if (x->dim() != 2 || out->dim() != 2 || w->dim() != 1 || (res && res->dim() != 2)) return false;
     if (x->stride(1) != 1 || out->stride(1) != 1 || w->stride(0) != 1 || (res && res->stride(1) != 1)) return false;
     memset(a, 0, sizeof *a);

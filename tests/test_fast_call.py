@@ -8,7 +8,7 @@ import torch
 
 import paper_2505_03780_amd as A
 from paper_2505_03780_amd import binding as B
-from test_binding_args import _case
+from test_binding_args import _case, _NoStream
 
 B._dtype_codes()  # loads the extension
 F = B._fast
@@ -82,6 +82,69 @@ def test_modes_wrappers_and_cpu_tensors_are_left_to_the_general_path():
     assert F.pack_rmsnorm(x.t(), x[0], x, 1e-5, None) is None and F.pack_kv_write(kn, torch.zeros(3, 2, 128)[:, :, :64], cache, cache, slots) is None
     with pytest.raises(TypeError):
         F.kv_write(kn)
+
+
+@pytest.mark.parametrize("name", ["seq_lens", "query_start_loc", "kv_start_loc", "block_table", "workspace", "k", "out"])
+def test_a_tensor_elsewhere_than_the_others_is_left_to_the_general_path(name):
+    c = _case(paged=name != "kv_start_loc")
+    assert _pack(c) is not None
+    assert _pack(dict(c, **{name: c[name].to("meta")})) is None
+
+
+def _host_calls():
+    """(what is refused, call) with one small call of every kind, all tensors in host memory."""
+    c = _case()
+    q = c["q"]
+    yield "q", lambda: A.attn_prefill_varlen(q, c["k"], c["v"], c["out"], c["query_start_loc"], c["seq_lens"], 1.0, max_q_len=2, max_kv_len=20,
+                                             block_table=c["block_table"])
+    yield "q", lambda: A.attn_decode_paged(q, c["k"], c["v"], c["out"], c["block_table"], c["seq_lens"], 1.0, max_kv_len=20)
+    yield "q", lambda: A.attn_decode_paged_static(q, c["k"], c["v"], c["out"], c["block_table"], c["seq_lens"], 1.0, max_kv_len=20)
+    x = torch.zeros(3, 64, dtype=torch.bfloat16)
+    yield "x", lambda: A.rmsnorm_fused_add(x, x[0], x, 1e-5)
+    kn, cache, slots = torch.zeros(3, 2, 64), torch.zeros(4, 16, 2, 64), torch.zeros(3, dtype=torch.int32)
+    yield "k_new", lambda: A.attn_kv_cache_write(kn, kn, cache, cache, slots)
+
+
+def test_host_tensors_are_refused_before_a_launch():
+    for name, call in _host_calls():
+        with pytest.raises(ValueError, match="^%s: " % name):
+            call()
+    empty = torch.zeros(0, 64, dtype=torch.bfloat16)
+    A.rmsnorm_fused_add(empty, torch.zeros(64, dtype=torch.bfloat16), empty, 1e-5, stream=_NoStream)  # nothing to launch
+
+
+@pytest.mark.gpu
+def test_one_host_tensor_among_device_tensors_is_refused():
+    """Nothing is launched with a host pointer: every tensor of a decode and of a prefill call in turn; pinned memory serves."""
+    c = {n: t.cuda() if torch.is_tensor(t) else t for n, t in _case().items()}
+    c["seq_lens"].fill_(7)
+    c["query_start_loc"].copy_(torch.arange(c["query_start_loc"].numel(), dtype=torch.int32))
+    c["block_table"].zero_()
+    big = torch.zeros(1 << 22, dtype=torch.uint8, device="cuda")
+    B_ = c["seq_lens"].shape[0]
+    q, out = c["q"][:B_], c["out"][:B_]
+
+    def prefill(d):
+        A.attn_prefill_varlen(d["q"], d["k"], d["v"], d["out"], d["query_start_loc"], d["seq_lens"], 1.0, max_q_len=1, max_kv_len=20,
+                              block_table=d["block_table"])
+
+    def decode(d):
+        A.attn_decode_paged(d["q"], d["k"], d["v"], d["out"], d["block_table"], d["seq_lens"], 1.0, max_kv_len=20, workspace=d["workspace"])
+
+    c.update(q=q, out=out, workspace=big, query_start_loc=torch.arange(B_ + 1, dtype=torch.int32, device="cuda"))
+    for call, names in ((prefill, ("q", "k", "v", "out", "query_start_loc", "seq_lens", "block_table")),
+                        (decode, ("q", "k", "v", "out", "seq_lens", "block_table", "workspace"))):
+        call(c)
+        torch.cuda.synchronize()
+        want = c["out"].clone()
+        for name in names:
+            with pytest.raises(ValueError, match="host memory"):
+                call(dict(c, **{name: c[name].cpu()}))
+        out.zero_()
+        torch.cuda.synchronize()
+        call(dict(c, seq_lens=c["seq_lens"].cpu().pin_memory()))
+        torch.cuda.synchronize()
+        assert torch.equal(c["out"], want)
 
 
 @pytest.mark.gpu
