@@ -193,7 +193,8 @@ def attn_status_string(status: int) -> str:
 
 _codes = None
 # The native path of the tensor calls (csrc/fast_call.cpp) once torch has been seen: takes plain tensors on the current
-# stream, returns the status, or None for a call that the general path below has to decide.
+# stream, returns the status, or None for a call that the general path below has to decide.  It is tied to one Python and one torch;
+# where it cannot be loaded every call goes the general way.
 _fast = None
 
 
@@ -203,13 +204,19 @@ def _dtype_codes():
     if _codes is None:
         import torch
 
-        lib = load_library()
-        from . import _fastcall  # (built next to the library; needs torch loaded)
+        try:
+            from . import _fastcall  # (built next to the library, for this Python and torch; needs torch loaded)
+        except ImportError as e:
+            import warnings
 
-        address = lambda name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
-        _fastcall.bind(*(address(name) for name in ("attn_prefill_varlen", "attn_decode_paged", "attn_decode_paged_static",
-                                                    "attn_kv_cache_write", "rmsnorm_fused_add")))
-        _fast = _fastcall
+            warnings.warn("the tensor calls' native path cannot be loaded (%s): they are marshalled in Python, and long prefill contexts "
+                          "are not split; `python -m paper_2505_03780_amd.build` builds it for this torch" % e)
+        else:
+            lib = load_library()
+            address = lambda name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
+            _fastcall.bind(*(address(name) for name in ("attn_prefill_varlen", "attn_decode_paged", "attn_decode_paged_static",
+                                                        "attn_kv_cache_write", "rmsnorm_fused_add")))
+            _fast = _fastcall
 
         _int32 = torch.int32
         _current_stream, _current_device = torch.cuda.current_stream, torch.cuda.current_device
@@ -318,8 +325,9 @@ def _refuse_host_tensors(**tensors):
 
 def _prefill_scratch(packed: bytes, stream):
     """(address, bytes) of scratch memory for the prefill call described by ``packed`` on ``stream``; (0, 0) for a call that does
-    without: one that uses none, on a stream that is not torch's or not the current device's, under capture, or when memory is short."""
-    n = _hot["attn_prefill_scratch_bytes"](packed)
+    without: one that uses none, on a stream that is not torch's or not the current device's, under capture, when memory is short, or
+    without the native path, which takes the memory."""
+    n = _hot["attn_prefill_scratch_bytes"](packed) if _fast is not None else 0
     if n == 0:
         return 0, 0
     if stream is not None:

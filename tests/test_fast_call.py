@@ -113,6 +113,30 @@ def test_host_tensors_are_refused_before_a_launch():
     A.rmsnorm_fused_add(empty, torch.zeros(64, dtype=torch.bfloat16), empty, 1e-5, stream=_NoStream)  # nothing to launch
 
 
+def test_without_the_extension_the_general_path_takes_every_call():
+    """An extension that is missing or built for another torch costs the native path and a warning, not the calls."""
+    import os
+    import subprocess
+    import sys
+
+    here = os.path.dirname(os.path.abspath(__file__))
+    code = ("import sys, types; sys.path[:0] = [%r, %r]\n"
+            "sys.modules['paper_2505_03780_amd._fastcall'] = None\n"
+            "import torch, paper_2505_03780_amd as A\n"
+            "from paper_2505_03780_amd import binding as B\n"
+            "from test_binding_args import _case, _NoStream\n"
+            "c = _case()\n"
+            "assert bytes(A.make_args(*[c[n] for n in ('q', 'k', 'v', 'out', 'seq_lens', 'scale')], max_q_len=3, max_kv_len=70, block_table=c['block_table'])) and B._fast is None\n"
+            "x = torch.zeros(0, 64, dtype=torch.bfloat16)\n"
+            "A.rmsnorm_fused_add(x, torch.zeros(64, dtype=torch.bfloat16), x, 1e-5, stream=_NoStream)\n"
+            "q, kv = torch.zeros(0, 4, 128, dtype=torch.bfloat16), torch.zeros(1, 2, 128, dtype=torch.bfloat16)\n"
+            "i = torch.zeros(2, dtype=torch.int32)\n"
+            "A.attn_prefill_varlen(q, kv, kv, q, i, i[:1], 1.0, max_q_len=8, max_kv_len=8000, stream=_NoStream)\n"
+            "print('served')\n" % (os.path.dirname(here), here))
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and r.stdout.strip() == "served" and r.stderr.count("native path cannot be loaded") == 1, r.stderr
+
+
 @pytest.mark.gpu
 def test_one_host_tensor_among_device_tensors_is_refused():
     """Nothing is launched with a host pointer: every tensor of a decode and of a prefill call in turn; pinned memory serves."""
