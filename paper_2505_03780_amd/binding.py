@@ -354,7 +354,7 @@ def attn_prefill_varlen(q, k, v, out, query_start_loc, seq_lens, scale, *, max_q
         else:
             _refuse_host_tensors(workspace=workspace)
             rc = lib.attn_prefill_varlen_parts(ctypes.byref(args), workspace.data_ptr(), workspace.nbytes, _stream_ptr(stream))
-    elif _fast is not None and stream is None and not max_kv_len > 1024:  # (longer ones may use scratch memory)
+    elif _fast is not None and stream is None and int(max_kv_len) <= 1024:  # (longer ones may use scratch memory)
         rc = _fast.attn(0, q, k, v, out, seq_lens, scale, max_q_len, max_kv_len, query_start_loc, kv_start_loc, block_table, causal, None)
     if rc is None:
         a = _packed(_pack_attn, AttnArgs, _attn_fields(q, k, v, out, seq_lens, scale, max_q_len, max_kv_len, query_start_loc, kv_start_loc,
@@ -366,7 +366,7 @@ def attn_prefill_varlen(q, k, v, out, query_start_loc, seq_lens, scale, *, max_q
         if workspace is not None:
             rc = _hot["attn_prefill_varlen_parts"](a, workspace.data_ptr(), workspace.nbytes, _stream_ptr(stream))
         # (necessary conditions of the library's own rule, to save short calls the question)
-        elif max_kv_len > 1024 and q.shape[0] * q.shape[1] <= 131072:
+        elif int(max_kv_len) > 1024 and q.shape[0] * q.shape[1] <= 131072:
             ptr, n = _prefill_scratch(a, stream)
         if ptr:
             try:

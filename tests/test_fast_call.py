@@ -113,6 +113,12 @@ def test_host_tensors_are_refused_before_a_launch():
     A.rmsnorm_fused_add(empty, torch.zeros(64, dtype=torch.bfloat16), empty, 1e-5, stream=_NoStream)  # nothing to launch
 
 
+def test_a_bound_is_whatever_int_takes():
+    q, kv, i = torch.zeros(0, 4, 128, dtype=torch.bfloat16), torch.zeros(1, 2, 128, dtype=torch.bfloat16), torch.zeros(2, dtype=torch.int32)
+    for bound in (8000, 8000.5, "8000", np.int64(8000), torch.tensor(8000), True):
+        A.attn_prefill_varlen(q, kv, kv, q, i, i[:1], 1.0, max_q_len=8, max_kv_len=bound, stream=_NoStream)
+
+
 def test_without_the_extension_the_general_path_takes_every_call():
     """An extension that is missing or built for another torch costs the native path and a warning, not the calls."""
     import os
