@@ -29,6 +29,8 @@
 // stream through decode_stream_run.
 #include "kernel_params.hpp"
 
+#include <type_traits>
+
 namespace attn {
 namespace {
 
@@ -78,8 +80,10 @@ struct DecodeCfg {
     static constexpr int kLdsBytes = WAVES * kVBytes > kRedBytes ? WAVES * kVBytes : kRedBytes;
 };
 
+// (D = 64, four wavefronts: 128 registers, i.e. four workgroups per compute unit; with the 144 that the compiler would take 48
+// contexts of 63-189 keys take 5.46 us instead of 5.38, one of 29-59 3.73 instead of 3.61.)
 template <int HD, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void decode_bf16_kernel(const KParams p)
+__global__ __launch_bounds__(WAVES * 64, HD == 64 && WAVES == 4 ? 4 : 1) void decode_bf16_kernel(const KParams p)
 {
     using C = DecodeCfg<HD, WAVES>;
     constexpr int KS = HD / 32;   // MFMA steps along the head dimension for S^T
@@ -140,7 +144,7 @@ __global__ __launch_bounds__(WAVES * 64) void decode_bf16_kernel(const KParams p
 #pragma unroll
     for (int i = 0; i < KS; ++i) lane_off[i] = (int64_t)(lane / (HD / 8) + VROWS * i) * p.kv_stride_tok + 8 * (lane % (HD / 8));
     // table entries of the two 16-key groups of the chunk at c0 (16 | block_size; groups past the end: the last one), asked for
-    // together, and for all chunks but the first while the one before is consumed
+    // together, and for all chunks but the first a chunk ahead of the loads that need them
     struct Groups {
         int k0, k1, b0, b1;
     };
@@ -148,18 +152,26 @@ __global__ __launch_bounds__(WAVES * 64) void decode_bf16_kernel(const KParams p
         const int end = (n_kv - 1) & ~15, k0 = c0 < end ? c0 : end, k1 = c0 + 16 < end ? c0 + 16 : end;
         return Groups{k0, k1, bt_row[k0 >> p.block_shift], bt_row[k1 >> p.block_shift]};
     };
-    auto load_chunk = [&](Groups c) {
+    struct Bases {
+        int64_t g0, g1;
+    };
+    auto bases = [&](Groups c) -> Bases {
         asm volatile("" : "+s"(c.b0), "+s"(c.b1));
-        const int64_t g0 = (int64_t)c.b0 * p.kv_stride_block + (int64_t)(c.k0 & (p.block_size - 1)) * p.kv_stride_tok;
-        const int64_t g1 = (int64_t)c.b1 * p.kv_stride_block + (int64_t)(c.k1 & (p.block_size - 1)) * p.kv_stride_tok;
-        // whole head slices (four rows x 256 bytes per wave-wide load at D = 128)
+        return Bases{(int64_t)c.b0 * p.kv_stride_block + (int64_t)(c.k0 & (p.block_size - 1)) * p.kv_stride_tok,
+                     (int64_t)c.b1 * p.kv_stride_block + (int64_t)(c.k1 & (p.block_size - 1)) * p.kv_stride_tok};
+    };
+    // whole head slices (four rows x 256 bytes per wave-wide load at D = 128), K and V apart, each in program order
+    auto load_k = [&](Bases b) {
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int i = 0; i < KS; ++i) kreg[t][i] = kv_load(kbase + (t ? g1 : g0) + lane_off[i]);
-        __builtin_amdgcn_sched_barrier(0);  // K first: it is needed first (the compiler would pair the loads that share an offset)
+            for (int i = 0; i < KS; ++i) kreg[t][i] = kv_load(kbase + (t ? b.g1 : b.g0) + lane_off[i]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto load_v = [&](Bases b) {
 #pragma unroll
-        for (int i = 0; i < VLD; ++i) vreg[i] = kv_load(vbase + (i < KS ? g0 : g1) + lane_off[i % KS]);
+        for (int i = 0; i < VLD; ++i) vreg[i] = kv_load(vbase + (i < KS ? b.g0 : b.g1) + lane_off[i % KS]);
+        __builtin_amdgcn_sched_barrier(0);
     };
 
     f32x4 oacc[DB];
@@ -171,11 +183,19 @@ __global__ __launch_bounds__(WAVES * 64) void decode_bf16_kernel(const KParams p
     const int v_rd = (4 * lg + (l16 >> 2)) * C::kVPitch + 8 * (l16 & 3);
 
     int c0 = k_lo + wave * kChunk;
-    if (c0 < k_hi) load_chunk(groups(c0));
-    for (; c0 < k_hi; c0 += WAVES * kChunk) {
+    // One chunk.  The next one's K is requested as soon as this one's has left the registers, before the wait for this one's V: requesting
+    // K and V together behind V left the memory idle for the rest of the chunk, and the scalar entries in front of them made
+    // every LDS wait a full one.  All K fragments are read before the first product, so that they wait once and not one by one.
+    // Whole contexts to an eight-wavefront workgroup each (entries and loads together behind V -> now): 20 of 500-1000 keys 16.5 -> 15.3 us,
+    // 24 of 300-512 9.8 -> 9.3, 20 of 177-710 (16 KV heads) 20.0 -> 18.5; parts: 3 of 12500-25000 38.7 -> 37.7.
+    Groups after{0, 0, 0, 0};
+    auto step = [&](auto more_tag) {
+        constexpr bool more = decltype(more_tag)::value;
         const int next = c0 + WAVES * kChunk;
+        Bases nb{0, 0};
         // consume the registers of this chunk: K, then V, pass through the wave's LDS tile
         f32x4 sacc[2];
+        ex8 kf[2][KS];
         // the wave's LDS tile turns the K rows into MFMA operand order; V takes the tile over below
         // (LDS instructions of one wave execute in order, so no wait is needed between the two uses)
 #pragma unroll
@@ -186,16 +206,21 @@ __global__ __launch_bounds__(WAVES * 64) void decode_bf16_kernel(const KParams p
                 *(u32x4 *)(vst + row * C::kKPitch + 16 * (lane % (HD / 8))) = kreg[t][i];
             }
 #pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) kf[t][ks] = *(const ex8 *)(vst + (16 * t + l16) * C::kKPitch + 16 * lg + 64 * ks);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
         for (int t = 0; t < 2; ++t) {
             sacc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const ex8 kf = *(const ex8 *)(vst + (16 * t + l16) * C::kKPitch + 16 * lg + 64 * ks);
-                sacc[t] = DECODE_MFMA(kf, qf[ks], sacc[t], 0, 0, 0);
-            }
+            for (int ks = 0; ks < KS; ++ks) sacc[t] = DECODE_MFMA(kf[t][ks], qf[ks], sacc[t], 0, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
-        const Groups after = groups(next);  // (behind the K reads: a scalar load in flight makes their counted waits full ones)
+        if constexpr (more) {
+            nb = bases(after);
+            load_k(nb);
+        }
         const bool tail = c0 + kChunk > k_hi;
 #pragma unroll
         for (int i = 0; i < VLD; ++i) {
@@ -204,7 +229,10 @@ __global__ __launch_bounds__(WAVES * 64) void decode_bf16_kernel(const KParams p
             const u32x4 val = (tail && c0 + row >= k_hi) ? u32x4{0u, 0u, 0u, 0u} : vreg[i];
             *(u32x4 *)(vst + row * C::kVPitch + 16 * (lane % (HD / 8))) = val;
         }
-        if (next < k_hi) load_chunk(after);
+        if constexpr (more) {
+            load_v(nb);
+            after = groups(next + WAVES * kChunk);
+        }
 
         // ---- online softmax over the 32 keys of the chunk -----------------------------------
         float x[8];
@@ -244,6 +272,14 @@ __global__ __launch_bounds__(WAVES * 64) void decode_bf16_kernel(const KParams p
             const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
             oacc[db] = DECODE_MFMA(__builtin_bit_cast(ex8, both), pf, oacc[db], 0, 0, 0);
         }
+    };
+    if (c0 < k_hi) {
+        const Bases b = bases(groups(c0));
+        load_k(b);
+        load_v(b);
+        after = groups(c0 + WAVES * kChunk);
+        for (; c0 + WAVES * kChunk < k_hi; c0 += WAVES * kChunk) step(std::integral_constant<bool, true>{});
+        step(std::integral_constant<bool, false>{});
     }
 
     // ---- merge the wavefronts of this workgroup ----------------------------------------------
