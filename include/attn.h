@@ -124,7 +124,8 @@ int attn_prefill_varlen(const attn_args *args, void *hip_stream);
  * cached history) leave compute units idle unless their keys are split over several workgroups, which leave records
  * that a second kernel merges.  With at least attn_prefill_scratch_bytes(args) bytes, 16-byte aligned, the keys of a
  * call for which that is expected to pay are split; with less, or NULL, this is attn_prefill_varlen (slower, same result
- * within rounding).  args->workspace is ignored.  Calls that overlap in time need scratch memory each.
+ * within rounding).  So it is where attn_tune has a winner for the call: that was measured with whole keys, and stands.
+ * args->workspace is ignored.  Calls that overlap in time need scratch memory each.
  */
 int attn_prefill_varlen_parts(const attn_args *args, void *scratch, size_t scratch_bytes, void *hip_stream);
 /* Bytes of scratch memory with which the next attn_prefill_varlen_parts call with these args splits its keys over workgroups (at

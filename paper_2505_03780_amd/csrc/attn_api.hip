@@ -356,8 +356,9 @@ void try_parts(const KParams &p, int id, double *us, KeyPlan *plan)
 // What a prefill call that would otherwise run instance `id` does with scratch memory.  The margins are set so that next to
 // nothing loses: of 57100 random calls that take parts (half of the ranges above, down to one new token and with uneven lengths; half
 // drawn like the calls of perf/cases.py) 0.2 % are more than 2 % behind no parts and 0.04 % more than 10 %, nearly all of them batches of
-// very uneven lengths, whose maxima are all that the host knows; the average gain is 1.7x.  Examples (no parts -> parts): 2 x 4 tokens behind 5900 keys 46 -> 24 us, 3 x 17-70
-// behind 5000-9000 51 -> 41, 10 x 21-40 behind 17000 (D = 64) 243 -> 122, 3 x 390-450 of 16/16 heads behind 3900 98 -> 75.
+// very uneven lengths, whose maxima are all that the host knows; the average gain is 1.7x.  Examples (no parts ->
+// parts, GPU time): 2 x 4 tokens behind 5900 keys 44 -> 18 us, 2 x 9-12 behind 14000-18700 103 -> 32, 3 x 17-70 behind 5000-9000 54 -> 42,
+// 4 x 200 behind 6000 137 -> 112, 3 x 390-450 of 16/16 heads behind 3900 99 -> 79.
 KeyPlan key_plan(const KParams &p, int id, bool forced)
 {
     int n;

@@ -17,7 +17,7 @@
 //    line (as MFMA operand order would) pays for the line twice under that hint.
 //    A wave-private LDS tile turns K into A-operand order (plain 128-bit reads)
 //    and then V into key-contiguous operands (ds_read_b64_tr_b16).  The next
-//    chunk's loads are issued before the current chunk is consumed.
+//    chunk's K, and then its V, are requested as soon as this one's have left the registers.
 //  * Each part leaves an fp32 (partial output, max, sum) triple per query head;
 //    a second kernel merges the parts, one wavefront per (sequence, head).
 //

@@ -51,7 +51,7 @@ struct KParams {
 // arrive together.  Left alone the compiler loads a field where it is first needed, and the start of a kernel is a chain of
 // misses, one after the other.  With the divisions below, scalar table entries and the merge's early requests, GPU time of
 // whole calls: one context of 1900 keys 8.1 -> 7.5 us, 17 of 33-271 6.8 -> 6.3, 14 of 402 at D = 64 6.4 -> 5.7, 40 of 100-400
-// 12.2 -> 11.8, fp32 prefill of 2 x 7-21 tokens 4.4 -> 4.2, 8 x 400-1800 bf16 tokens 125.3 -> 123.5.
+// 12.2 -> 11.8, fp32 prefill of 2 x 7-21 tokens 4.4 -> 4.2, 8 x 400-1800 bf16 tokens 128.3 -> 127.3.
 static_assert(offsetof(KParams, seq_lens) / 64 == 0 && offsetof(KParams, kv_stride_tok) / 64 == 1 && offsetof(KParams, group) / 64 == 2 &&
                   offsetof(KParams, num_splits) / 64 == 3 && sizeof(KParams) <= 256,
               "a field of every line");

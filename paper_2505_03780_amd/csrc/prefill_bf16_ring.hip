@@ -19,10 +19,10 @@
 //    reference.  Numerator and denominator carry the same reference, so only the rounding
 //    of the weights differs, and the rescale of the accumulators becomes rare.
 //  * The output tile is transposed through LDS and written as whole rows.
-//  * Where a call has fewer tiles than the chip has room for, and brings a workspace, the keys are cut into parts (PARTS;
+//  * Where a call has fewer tiles than the chip has room for, and brings scratch memory, the keys are cut into parts (PARTS;
 //    grid dimension y): a part's workgroup runs the same loop over its own keys and leaves its accumulators as a record
 //    for prefill_ring_merge_kernel.  3 x 17-70 tokens behind 5000-9000 keys (56 tiles, 512 places): 141 us in one part, 42 in
-//    eight, against 51-57 for the key-split kernel; 3 x 390-450 of 16/16 heads behind 3900 98 -> 75 us.  Built for the small
+//    eight, against 51-57 for the key-split kernel; 3 x 390-450 of 16/16 heads behind 3900 99 -> 79 us.  Built for the small
 //    workgroups only; key_plan in attn_api.hip has the rule.
 //
 // Head sizes 128 and 64.  At D = 64 a unit has half the MFMAs for the same softmax, so the vector ALU is the bound

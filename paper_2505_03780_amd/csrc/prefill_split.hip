@@ -24,10 +24,10 @@
 //    at different places of the key axis, so that each fetches another part first, lost that sharing:
 //    121 against 76 us for 3 sequences of 64 tokens behind 8192 keys.  Idle compute units that touched the keys
 //    ahead gave 1 % on some shapes and cost as much on others.)
-//  * Where even these workgroups leave compute units idle, a call that brings a workspace has the keys of every
+//  * Where even these workgroups leave compute units idle, a call that brings scratch memory has the keys of every
 //    sequence cut into parts (grid dimension y): a part's workgroups leave records, which
-//    prefill_split_merge_kernel merges (about 5 us with its launch).  2 x 4 tokens behind 5900 keys: 46 -> 24 us in
-//    eight parts, 2 x 9-12 behind 14000-18700 138 -> 48 us; key_plan in attn_api.hip has the rule (from enough new tokens
+//    prefill_split_merge_kernel merges (about 5 us with its launch).  2 x 4 tokens behind 5900 keys: 44 -> 18 us in
+//    twelve parts, 2 x 9-12 behind 14000-18700 103 -> 32 us in eight; key_plan in attn_api.hip has the rule (from enough new tokens
 //    for 128-row tiles on, the ring kernel in parts takes over).
 //  * The reference of the exponentials moves only when a row outgrows it by 2^kSlack, as in the ring kernel (D = 128; at
 //    D = 64 it is the running maximum).
