@@ -316,9 +316,14 @@ def _stream_ptr(stream) -> int:
     return _raw_stream(_current_device())
 
 
-def _refuse_host_tensors(**tensors):
+def _refuse_host_tensors(names, *tensors):
     """Raises for a tensor in host memory that kernels cannot read (a launch with it would fault the GPU); pinned memory they can."""
-    for name, t in tensors.items():
+    if _fast is not None and not _fast.any_on_host(*tensors):
+        return
+    named = dict(zip(names.split(), tensors))
+    if any(len(t) == 0 for t in (tensors[0], named.get("seq_lens")) if t is not None):
+        return  # nothing to launch
+    for name, t in named.items():
         if t is not None and getattr(t, "is_cpu", False) and t.numel() > 0 and not t.is_pinned():
             raise ValueError("%s: a tensor on the GPU is needed, this one is in host memory" % name)
 
@@ -352,16 +357,15 @@ def attn_prefill_varlen(q, k, v, out, query_start_loc, seq_lens, scale, *, max_q
         if workspace is None:
             rc = lib.attn_prefill_varlen(ctypes.byref(args), _stream_ptr(stream))
         else:
-            _refuse_host_tensors(workspace=workspace)
+            _refuse_host_tensors("workspace", workspace)
             rc = lib.attn_prefill_varlen_parts(ctypes.byref(args), workspace.data_ptr(), workspace.nbytes, _stream_ptr(stream))
     elif _fast is not None and stream is None and int(max_kv_len) <= 1024:  # (longer ones may use scratch memory)
         rc = _fast.attn(0, q, k, v, out, seq_lens, scale, max_q_len, max_kv_len, query_start_loc, kv_start_loc, block_table, causal, None)
     if rc is None:
         a = _packed(_pack_attn, AttnArgs, _attn_fields(q, k, v, out, seq_lens, scale, max_q_len, max_kv_len, query_start_loc, kv_start_loc,
                                                        block_table, causal, None))
-        if q.shape[0] and seq_lens.shape[0]:
-            _refuse_host_tensors(q=q, k=k, v=v, out=out, query_start_loc=query_start_loc, seq_lens=seq_lens, block_table=block_table,
-                                 kv_start_loc=kv_start_loc, workspace=workspace)
+        _refuse_host_tensors("q k v out query_start_loc seq_lens block_table kv_start_loc workspace", q, k, v, out, query_start_loc, seq_lens,
+                             block_table, kv_start_loc, workspace)
         ptr = 0
         if workspace is not None:
             rc = _hot["attn_prefill_varlen_parts"](a, workspace.data_ptr(), workspace.nbytes, _stream_ptr(stream))
@@ -391,8 +395,7 @@ def attn_decode_paged(q, k_cache, v_cache, out, block_table, seq_lens, scale, *,
     if rc is None:
         a = _packed(_pack_attn, AttnArgs, _attn_fields(q, k_cache, v_cache, out, seq_lens, scale, 1, max_kv_len, None, None, block_table,
                                                        True, workspace))
-        if q.shape[0] and seq_lens.shape[0]:
-            _refuse_host_tensors(q=q, k_cache=k_cache, v_cache=v_cache, out=out, block_table=block_table, seq_lens=seq_lens, workspace=workspace)
+        _refuse_host_tensors("q k_cache v_cache out block_table seq_lens workspace", q, k_cache, v_cache, out, block_table, seq_lens, workspace)
         rc = _hot["attn_decode_paged"](a, _stream_ptr(stream))
     if rc != 0:
         raise AttnError(rc, "attn_decode_paged")
@@ -411,8 +414,7 @@ def attn_decode_paged_static(q, k_cache, v_cache, out, block_table, seq_lens, sc
     if rc is None:
         a = _packed(_pack_attn, AttnArgs, _attn_fields(q, k_cache, v_cache, out, seq_lens, scale, 1, max_kv_len, None, None, block_table,
                                                        True, None))
-        if q.shape[0] and seq_lens.shape[0]:
-            _refuse_host_tensors(q=q, k_cache=k_cache, v_cache=v_cache, out=out, block_table=block_table, seq_lens=seq_lens)
+        _refuse_host_tensors("q k_cache v_cache out block_table seq_lens", q, k_cache, v_cache, out, block_table, seq_lens)
         rc = _hot["attn_decode_paged_static"](a, _stream_ptr(stream))
     if rc != 0:
         raise AttnError(rc, "attn_decode_paged_static")
@@ -516,8 +518,8 @@ def rmsnorm_fused_add(x, weight, out, eps, residual=None, stream=None, args: Opt
         rc = _fast.rmsnorm(x, weight, out, eps, residual)
     if rc is None:
         a = _packed(_pack_rmsnorm, RmsNormArgs, _rmsnorm_fields(x, weight, out, eps, residual))
-        if x.shape[0] and weight is not None:  # (a missing weight is the library's to refuse)
-            _refuse_host_tensors(x=x, weight=weight, out=out, residual=residual)
+        if weight is not None:  # (a missing weight is the library's to refuse)
+            _refuse_host_tensors("x weight out residual", x, weight, out, residual)
         rc = _hot["rmsnorm_fused_add"](a, _stream_ptr(stream))
     if rc != 0:
         raise AttnError(rc, "rmsnorm_fused_add")
@@ -590,8 +592,7 @@ def attn_kv_cache_write(k_new, v_new, k_cache, v_cache, slot_mapping, stream=Non
         rc = _fast.kv_write(k_new, v_new, k_cache, v_cache, slot_mapping)
     if rc is None:
         a = _packed(_pack_kv_write, KvWriteArgs, _kv_write_fields(k_new, v_new, k_cache, v_cache, slot_mapping))
-        if k_new.shape[0]:
-            _refuse_host_tensors(k_new=k_new, v_new=v_new, k_cache=k_cache, v_cache=v_cache, slot_mapping=slot_mapping)
+        _refuse_host_tensors("k_new v_new k_cache v_cache slot_mapping", k_new, v_new, k_cache, v_cache, slot_mapping)
         rc = _hot["attn_kv_cache_write"](a, _stream_ptr(stream))
     if rc != 0:
         raise AttnError(rc, "attn_kv_cache_write")

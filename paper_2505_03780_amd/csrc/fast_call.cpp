@@ -275,6 +275,13 @@ PyObject *py_scratch(PyObject *, PyObject *const *o, Py_ssize_t n)
     Py_END_ALLOW_THREADS
     return PyLong_FromVoidPtr(p);
 }
+// Whether any of the arguments is a tensor in host memory.
+PyObject *py_any_on_host(PyObject *, PyObject *const *o, Py_ssize_t n)
+{
+    for (Py_ssize_t i = 0; i < n; ++i)
+        if (THPVariable_Check(o[i]) && THPVariable_Unpack(o[i]).device().is_cpu()) Py_RETURN_TRUE;
+    Py_RETURN_FALSE;
+}
 PyObject *py_release(PyObject *, PyObject *const *o, Py_ssize_t n)
 {
     if (!arguments(n, 1)) return nullptr;
@@ -311,6 +318,7 @@ PyMethodDef methods[] = {
     {"rmsnorm", FASTCALL(py_rmsnorm), nullptr},
     {"scratch", FASTCALL(py_scratch), nullptr},
     {"release", FASTCALL(py_release), nullptr},
+    {"any_on_host", FASTCALL(py_any_on_host), nullptr},
     {"pack_kv_write", FASTCALL(py_pack_kv_write), nullptr},
     {"pack_rmsnorm", FASTCALL(py_pack_rmsnorm), nullptr},
     {nullptr, nullptr, 0, nullptr},
