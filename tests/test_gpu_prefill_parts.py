@@ -107,6 +107,33 @@ def test_parts_against_the_oracle(shape, causal, scale, dtype):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("kernel,D", [("split", 128), ("split", 64), ("ring", 128), ("ring", 64)])
+def test_layouts_in_parts_give_the_same_bits(kernel, D):
+    """Queries, outputs and caches with other strides, and packed keys, through the records and the merge."""
+    import torch
+    from attn_testlib import DeviceWorkload, to_host_f64
+
+    paged = W.make_paged(184, "prefill", [40, 9], [4100, 2333], 8, 2, D, 16, 420)
+    dw = DeviceWorkload(paged)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    A.attn_force_instance(False, _instance("bf16", D) if kernel == "split" else _ring("bf16", D, 8, 2))
+    try:
+        assert A.attn_prefill_parts_instance(dw.args(False))[1] > 1
+        ref = to_host_f64(_run(dw, ws))
+        assert np.array_equal(to_host_f64(_run(DeviceWorkload(_packed(paged)), ws)), ref)
+        q, out, k, v = dw.q, dw.out, dw.k, dw.v
+        for name, t in (("q", q), ("out", out)):
+            wide = torch.zeros(49, 8, 2 * D + 8, dtype=torch.bfloat16, device="cuda")
+            wide[:, :, D:2 * D] = t
+            setattr(dw, name, wide[:, :, D:2 * D])
+        assert np.array_equal(to_host_f64(_run(dw, ws)), ref)
+        dw.k, dw.v = (x.transpose(1, 2).contiguous().transpose(1, 2) for x in (k, v))  # heads outside the slots of a block
+        assert np.array_equal(to_host_f64(_run(dw, ws)), ref)
+    finally:
+        A.attn_force_instance(False, -1)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("tensor,value", [("v", 0x7F80), ("v", 0xFF80), ("v", 0x7FC0), ("k", 0x7F80), ("k", 0x7FC0)])
 @pytest.mark.parametrize("kernel,D,new,keys", [("split", 128, 9, 3000), ("split", 64, 9, 2700), ("ring", 128, 33, 3000), ("ring", 64, 40, 4200)])
 def test_infinities_and_nan_through_the_merge(kernel, D, new, keys, tensor, value):
