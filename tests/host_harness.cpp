@@ -149,6 +149,20 @@ static void selftest(const std::string &dir)
                             a.max_q_len = kv < 512 ? kv : 512;
                             const int id = attn_selected_instance(&a, 0);
                             CHECK(id >= 0 && id < np);
+                            // the plan of key parts, up to bounds that say nothing: its records stay within four per compute unit
+                            for (int bound : {kv, 0x7fffffff - kv, 0x7fffffff})
+                                for (int q : {1, 40, 700}) {
+                                    attn_args s = a;
+                                    s.max_kv_len = bound;
+                                    s.max_q_len = q;
+                                    s.total_q = B * q;
+                                    int32_t parts = 0;
+                                    const int planned = attn_prefill_parts_instance(&s, &parts);
+                                    const size_t bytes = attn_prefill_scratch_bytes(&s);
+                                    CHECK(planned >= 0 && planned < np && parts >= 1 && parts <= 32 && (parts > 1) == (bytes > 0));
+                                    CHECK(bytes <= (size_t)1024 * 128 * (hd + 2) * 4);
+                                    if (parts == 1) CHECK(planned == attn_selected_instance(&s, 0));
+                                }
                             attn_args d = paged_args(B, kv);
                             d.dtype = dtypes[dt];
                             d.head_dim = hd;
