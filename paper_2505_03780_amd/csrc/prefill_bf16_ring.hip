@@ -18,7 +18,13 @@
 //    (then O and l are rescaled); otherwise exponentials are taken against the stale
 //    reference.  Numerator and denominator carry the same reference, so only the rounding
 //    of the weights differs, and the rescale of the accumulators becomes rare.
-//  * The output tile is transposed through LDS and written as whole rows.
+//  * The output tile is transposed through LDS and written as whole rows, and the queries arrive the same way.
+//  * Start of a workgroup: everything that can be asked for is asked for before anything is waited for (table entries, whole
+//    query rows, the first units), the first scores wait for the queries and unit 0 alone, and units past the last one are not
+//    requested at all.  With the queries loaded in operand order, the sign of the scale applied to them as they came, all
+//    units of the ring awaited and the last unit repeated to fill it (GPU time, rotating buffers, before -> now): 8 x 30 tokens, paged,
+//    32/8 heads 6.6 -> 6.0 us, 4 x 40-100 behind 10-100 keys 9.2 -> 8.5, 16 x 100-500 40.3 -> 36.7, 24 x 100-1200 of 16/4
+//    heads 95.8 -> 89.8, 8 x 256-2048 140.7 -> 136.9, D = 64 4 x 40-100 5.8 -> 5.6.
 //  * Where a call has fewer tiles than the chip has room for, and brings scratch memory, the keys are cut into parts (PARTS;
 //    grid dimension y): a part's workgroup runs the same loop over its own keys and leaves its accumulators as a record
 //    for prefill_ring_merge_kernel.  3 x 17-70 tokens behind 5000-9000 keys (56 tiles, 512 places): 141 us in one part, 42 in
@@ -143,8 +149,6 @@ __device__ __forceinline__ void lds_write_b128_untracked(unsigned addr, s16x8 v)
 {
     asm volatile("ds_write_b128 %0, %1" : : "v"(addr), "v"(v) : "memory");
 }
-// all LDS operations of this wave have returned; ties the registers so that their uses stay below
-__device__ __forceinline__ void lds_wait(s16x4 &a, s16x4 &b) { asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a), "+v"(b)::"memory"); }
 // at most n LDS operations of this wave are still outstanding (n is a constant once the loops around
 // the call are unrolled, so the switch folds to one instruction); `r` is tied so that its use stays below
 template <typename T>
@@ -197,6 +201,13 @@ struct RingCfg {
     // two waves per SIMD for the small workgroups (four of one row block at D = 64: 40 KB of LDS, 168 registers)
     static constexpr int kMinWaves = WAVES == 4 && QB == 1 && HD == 64 ? 3 : WAVES == 4 && QB * HD <= 128 ? 2 : 1;
     static constexpr size_t kLdsBytes = (size_t)NSLOT * kSlotBytes + 2 * kImgBytes;
+    // Queries reach the registers through LDS too: a wavefront's own share of the V^T images and of the K and V rows of the last
+    // kLate slots (kShare bytes each) holds its rows until it has read them.
+    static constexpr int kShare = kRowsPerWave * kRowBytes;
+    static constexpr int kQRegions = kWaveTok / kRowsPerWave;
+    static constexpr int kLate = (kQRegions - 2) / 2;
+    static constexpr int kEarly = PF < NSLOT - kLate ? PF : NSLOT - kLate;  // units whose slots are free from the start
+    static_assert(kShare == kFragsPerWave * 1024 && kQRegions * kShare == kWaveTok * kRowBytes && kEarly >= 3, "room for the queries");
     static_assert(WAVES == 4 || WAVES == 8, "4 or 8 wavefronts");
     static_assert(kDmaPerWave >= 1 && kFragsPerWave >= 1, "every wave transfers and transposes its share");
     // during iteration u the slots of units u+1 (V, transposed for the next iteration) and u+2 (K) are
@@ -216,10 +227,11 @@ struct RingTile {
 template <typename C, int HPW>
 __device__ __forceinline__ RingTile ring_tile(const KParams &p, int bid)
 {
-    touch_args(p);
-    // (and the fields that the block index is taken apart with, or their loads end up inside the divisions' branches)
-    asm volatile("" : : "s"(p.num_kv_heads), "s"(p.num_seqs), "s"(p.max_q_len), "s"(p.tile_order), "s"(p.causal), "s"(p.scale_log2e),
-                 "s"(p.workspace));
+    // All lines of the argument struct at once (touch_args in kernel_params.hpp), with the fields that the block index is taken
+    // apart with, or their loads end up inside the divisions' branches.
+    asm volatile("" : : "s"(p.seq_lens), "s"(p.kv_stride_tok), "s"(p.group), "s"(p.num_splits), "s"(p.num_kv_heads), "s"(p.num_seqs),
+                 "s"(p.max_q_len), "s"(p.tile_order), "s"(p.causal), "s"(p.scale_log2e), "s"(p.workspace), "s"(p.query_start_loc),
+                 "s"(p.kv_start_loc), "s"(p.block_table), "s"(p.q), "s"(p.q_stride_tok), "s"(p.q_stride_head), "s"(p.k), "s"(p.v));
     RingTile t;
     // Workgroups go to the eight XCDs round-robin, so with the KV head innermost every XCD (and its
     // own L2) serves one KV head when Hkv is a multiple or a divisor of eight.
@@ -324,22 +336,6 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     const float c = fabsf(p.scale_log2e);
     const bool negate_q = p.scale_log2e < 0.f;
 
-    // ---- Q fragments ---------------------------------------------------------------------------
-    const elem *qbase = (const elem *)p.q;
-    x8 qf[QB][KSTEPS];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        int t = t0w + qb * 32 + l32;
-        t = t < n_q ? t : n_q - 1;
-        const elem *src = qbase + (int64_t)(q0 + t) * p.q_stride_tok + (int64_t)head * p.q_stride_head + 8 * lhalf;
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) {
-            u32x4 raw = *(const u32x4 *)(src + 16 * ks);
-            if (negate_q) raw ^= 0x80008000u;
-            qf[qb][ks] = __builtin_bit_cast(x8, raw);
-        }
-    }
-
     // ---- key range -------------------------------------------------------------------------------
     const int pos0 = off - kv_begin;  // key that query 0 sits at
     int kv_end = n_kv;
@@ -358,6 +354,49 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
                     u32x4{0u, 0u, 0u, 0u};
         }
         return;
+    }
+
+    // ---- table entries of the first units, queries: requested before anything else is worked out -----------
+    constexpr int RPW = C::kRowsPerWave, NDMA = C::kDmaPerWave;
+    const int last_unit0 = (n_kv - 1) & ~(kUnit - 1);  // first key of the last unit that holds a real key
+    // The block table is read through the scalar cache (constant address space): a vector load would
+    // share the counter of the LDS transfers, and waiting for it would drain the whole transfer queue
+    // once per unit.
+    typedef const __attribute__((address_space(4))) int32_t *table_ptr;
+    const table_ptr bt_row = PAGED ? (table_ptr)(p.block_table + (int64_t)s * p.block_table_stride) : (table_ptr) nullptr;
+    // Wave-uniform table entry of the block that holds this wave's rows of `unit` (clamped to the sequence), requested with an
+    // untracked scalar load (inline assembly): the value may only be used after an s_waitcnt lgkmcnt(0) that follows
+    // the request (scalar loads return out of order).
+    auto table_entry_request = [&](int unit) -> int {
+        if (!PAGED) return 0;
+        int u0 = unit * kUnit < last_unit0 ? unit * kUnit : last_unit0;
+        int row = u0 + RPW * wave;
+        row = row < n_kv ? row : n_kv - 1;
+        const unsigned byte_off = (unsigned)((__builtin_amdgcn_readfirstlane(row) + kv_begin) >> p.block_shift) * 4u;
+        int r;
+        asm volatile("s_load_dword %0, %1, %2" : "=s"(r) : "s"(bt_row), "s"(byte_off) : "memory");
+        return r;
+    };
+    int entries[PF + 1];
+#pragma unroll
+    for (int u = 0; u <= PF; ++u) entries[u] = table_entry_request(u);
+    // ---- queries: whole rows to LDS, 1 KB a transfer --------------------------------------------------
+    // (Loaded in MFMA operand order straight from memory, an instruction touches 32 rows: the address unit takes twice as long, and a
+    // row's lines are asked for four times over.)
+    constexpr int RPD = C::kRowsPerDma;
+    const elem *qbase = (const elem *)p.q + (int64_t)head * p.q_stride_head;
+    // where the wave's rows 0..RPW-1 of region r go
+    auto q_region = [&](int r) -> unsigned {
+        const bool image = r >= C::kQRegions - 2;
+        return (unsigned)((image ? NSLOT * kSlotBytes + (r - (C::kQRegions - 2)) * C::kImgBytes : (NSLOT - C::kLate + r / 2) * kSlotBytes + (r & 1) * kVOff) +
+                          wave * C::kShare);
+    };
+#pragma unroll
+    for (int i = 0; i < C::kWaveTok / RPD; ++i) {
+        const int row = RPD * i + lane / CPR;
+        const int t = t0w + row < n_q ? t0w + row : n_q - 1;
+        const elem *src = qbase + (int64_t)(q0 + t) * p.q_stride_tok + 8 * ((lane % CPR) ^ swz<HD>(row & 31));
+        __builtin_amdgcn_global_load_lds((gbl_void *)src, (lds_void *)(lds + q_region(RPD * i / RPW) + RPD * i % RPW * kRowBytes), 16, 0, 0);
     }
 
     // first key position of this wave's rows, and the first unit that needs masking for this wave
@@ -379,16 +418,8 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     const unsigned char *kbase = (const unsigned char *)p.k + (int64_t)kvh * p.kv_stride_head * 2;
     const unsigned char *vbase = (const unsigned char *)p.v + (int64_t)kvh * p.kv_stride_head * 2;
     const int kv0 = T.kv0 + kv_begin;
-    // The block table is read through the scalar cache (constant address space): a vector load would
-    // share the counter of the LDS transfers, and waiting for it would drain the whole transfer queue
-    // once per unit.
-    typedef const __attribute__((address_space(4))) int32_t *table_ptr;
-    const table_ptr bt_row = PAGED ? (table_ptr)(p.block_table + (int64_t)s * p.block_table_stride) : (table_ptr) nullptr;
-    constexpr int RPW = C::kRowsPerWave, NDMA = C::kDmaPerWave;
-    constexpr int RPD = C::kRowsPerDma;
     const int dma_row = RPW * wave + lane / CPR;  // + RPD*i, row inside the unit
     const uint32_t tok_bytes = (uint32_t)p.kv_stride_tok * 2;
-    const int last_unit0 = (n_kv - 1) & ~(kUnit - 1);  // first key of the last unit that holds a real key
     // Per-lane byte offset of a transfer from the first row of this wave's share of a unit: the lane's
     // row and its swizzled 16-byte chunk.  It is the same in every unit whose rows all exist; in a
     // ragged last unit (and in the repeats of it past the end) the rows past the end re-read the last
@@ -407,26 +438,6 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
             dma_off_last[i] = (uint32_t)(row - wrow_last) * tok_bytes + chunk;
         }
     }
-    // wave-uniform table entry of the block that holds this wave's rows of `unit` (clamped to the sequence)
-    auto table_entry = [&](int unit) -> int {
-        if (!PAGED) return 0;
-        int u0 = unit * kUnit < last_unit0 ? unit * kUnit : last_unit0;
-        int row = u0 + RPW * wave;
-        row = row < n_kv ? row : n_kv - 1;
-        return bt_row[(__builtin_amdgcn_readfirstlane(row) + kv_begin) >> p.block_shift];
-    };
-    // The same entry, requested with an untracked scalar load (inline assembly): the value may only be
-    // used after an s_waitcnt lgkmcnt(0) that follows the request (scalar loads return out of order).
-    auto table_entry_request = [&](int unit) -> int {
-        if (!PAGED) return 0;
-        int u0 = unit * kUnit < last_unit0 ? unit * kUnit : last_unit0;
-        int row = u0 + RPW * wave;
-        row = row < n_kv ? row : n_kv - 1;
-        const unsigned byte_off = (unsigned)((__builtin_amdgcn_readfirstlane(row) + kv_begin) >> p.block_shift) * 4u;
-        int r;
-        asm volatile("s_load_dword %0, %1, %2" : "=s"(r) : "s"(bt_row), "s"(byte_off) : "memory");
-        return r;
-    };
     auto issue_unit = [&](int unit, int entry) {
         unsigned char *slot = lds + (unit % NSLOT) * kSlotBytes + RPW * wave * kRowBytes;
         const int u0 = unit * kUnit < last_unit0 ? unit * kUnit : last_unit0;  // units past the end repeat the last one
@@ -448,17 +459,19 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
         }
     };
 
-    // Publish the ring.  Each wave issues 2*NDMA transfers per unit and memory operations complete in order,
-    // so once at most 2*NDMA*(PF-3) are outstanding, this wave's transfers of every unit but the newest PF-3
-    // have landed (a table load that sits between them only makes the wait stricter).  All LDS reads of
-    // the slot about to be refilled have returned, because their values fed MFMAs issued earlier.  A
-    // bare s_barrier is used: the fence of __syncthreads would drain vmcnt to zero and with it the
-    // whole prefetch queue.
-    auto ring_barrier = [&]() {
-        wait_vmcnt<2 * NDMA * (PF - 3)>();
-        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's LDS write of transposed V has been performed
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
+    // Publish the ring: this wait, then a bare s_barrier (the fence of __syncthreads would drain vmcnt to zero and with it the
+    // whole prefetch queue).  Each wave issues 2*NDMA transfers per unit and memory operations complete in order, so once at
+    // most 2*NDMA*n are outstanding, this wave's transfers of every unit but the newest n have landed.  All LDS reads of
+    // the slot about to be refilled have returned, because their values fed MFMAs issued earlier.
+    // `units`: how many of the units requested so far may still be on their way; towards the end of the keys, where nothing
+    // more is requested, fewer than PF-3 (the wait may then be stricter than asked).
+    auto wait_units = [&](int units) {
+        if (units >= PF - 3)
+            wait_vmcnt<2 * NDMA * (PF - 3)>();
+        else if (PF > 4 && units >= 1)
+            wait_vmcnt<2 * NDMA>();
+        else
+            wait_vmcnt<0>();
     };
     // V^T fragment images: a wave transposes its share of the V fragments of a unit once
     // (ds_read_b64_tr_b16, the slow path) and stores them in MFMA A-operand order; every wave then
@@ -485,17 +498,6 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
             for (int rd = 0; rd < 2; ++rd) raw[i][rd] = lds_read_tr16_b64_untracked(vt + tr_off[i][rd]);
         }
     };
-    auto transpose_store = [&](int unit, s16x4 (&raw)[C::kFragsPerWave][2]) {
-        unsigned char *img = img_base + (unit & 1) * C::kImgBytes;
-#pragma unroll
-        for (int i = 0; i < C::kFragsPerWave; ++i) {
-            lds_wait(raw[i][0], raw[i][1]);
-            const int f = wave * C::kFragsPerWave + i;
-            const s16x8 both = __builtin_shufflevector(raw[i][0], raw[i][1], 0, 1, 2, 3, 4, 5, 6, 7);
-            *(s16x8 *)(img + f * 1024 + lane * 16) = both;
-        }
-    };
-
     // ---- per-lane LDS read offsets ----------------------------------------------------------------
     int koff[KSTEPS];
     {
@@ -517,22 +519,6 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
             for (int v = 0; v < 16; ++v) oacc[qb][db][v] = 0.f;
     }
 
-    // S(u) = K(u) Q^T for both query blocks
-    auto qk = [&](int unit, f32x16 (&sacc)[QB]) {
-        const unsigned char *kt = lds + (unit % NSLOT) * kSlotBytes;
-        x8 kf[KSTEPS];
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) kf[ks] = *(const x8 *)(kt + koff[ks]);
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) sacc[qb][v] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) {
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) sacc[qb] = E::mfma(kf[ks], qf[qb][ks], sacc[qb]);
-        }
-    };
     // Move the reference of the rows whose new maximum outgrew it by more than the slack; wave-uniform per
     // row block, so that a block's accumulators are only touched when one of its rows needs it.
     auto reference_outgrown = [&](int qb, float bm) -> bool { return __builtin_amdgcn_ballot_w64(bm > m_ref[qb] + kSlack<HD>) != 0; };
@@ -570,35 +556,91 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
         }
     };
     // ---- prologue: PF units in flight, S(0) ready ------------------------------------------------
+    // Everything that can be asked for is asked for before anything is waited for: the queries and all table entries, then
+    // the transfers of the first units, then (when those are there) the fragments of K(0) and K(1) and V(0) to transpose.
+    if (PAGED) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-    for (int u = 0; u < PF; ++u) issue_unit(u, table_entry(u));
-    ring_barrier();
-    qk(0, s_cur);
+        for (int u = 0; u <= PF; ++u) asm volatile("" : "+s"(entries[u]));
+    }
+    // (units past the last are not requested, here and in the loop; their slots then hold anything, and all their scores are hidden)
+#pragma unroll
+    for (int u = 0; u < C::kEarly; ++u)
+        if (u < n_units) issue_unit(u, entries[u]);
+    int entry_cur = entries[PF];
+    // the queries and unit 0
+    if (n_units >= C::kEarly)
+        wait_vmcnt<2 * NDMA * (C::kEarly - 1)>();
+    else
+        wait_vmcnt<0>();
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    x8 qf[QB][KSTEPS];
+    u32x4 kf[KSTEPS];  // K fragments of the next unit, fetched one iteration ahead
+    bool cur_masked = first_masked <= 0;
     using Masked = std::integral_constant<bool, true>;
     using Plain = std::integral_constant<bool, false>;
-    bool cur_masked = first_masked <= 0;
-    if (cur_masked)
-        settle(0, s_cur, Masked{});
-    else
-        settle(0, s_cur, Plain{});
-    u32x4 kf[KSTEPS];  // K fragments of the next unit, fetched one iteration ahead
-#pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) kf[ks] = *(const u32x4 *)(lds + (1 % NSLOT) * kSlotBytes + koff[ks]);
-    int entry_cur = table_entry(PF);  // (a tracked scalar load: the wait below covers it)
     {
+        u32x4 k0[KSTEPS], qraw[QB][KSTEPS];
         s16x4 raw[C::kFragsPerWave][2];
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            const int row = 32 * qb + l32;
+            const unsigned at = lds_addr(lds) + q_region(row / RPW) + row % RPW * kRowBytes;
+#pragma unroll
+            for (int ks = 0; ks < KSTEPS; ++ks) qraw[qb][ks] = lds_read_b128_untracked<0>(at + 16 * ((2 * ks + lhalf) ^ swz<HD>(l32)));
+        }
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) k0[ks] = lds_read_b128_untracked<0>(lds_addr(lds + koff[ks]));
         transpose_load(0, raw);
-        transpose_store(0, raw);
-        asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(entry_cur)::"memory");
-        __builtin_amdgcn_s_waitcnt(0xC07F);
+        constexpr int kBehindQ = KSTEPS + 2 * C::kFragsPerWave;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+            for (int ks = 0; ks < KSTEPS; ++ks) {
+                lds_wait_upto(kBehindQ, qraw[qb][ks]);
+                if (negate_q) qraw[qb][ks] ^= 0x80008000u;
+                qf[qb][ks] = __builtin_bit_cast(x8, qraw[qb][ks]);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = C::kEarly; u < PF; ++u)  // the slots that held queries
+            if (u < n_units) issue_unit(u, entries[u]);
+        __builtin_amdgcn_sched_barrier(0);
+        const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        const unsigned img = lds_addr(img_base + lane * 16);
+        int stored = 0;
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) {
+            lds_wait_upto(KSTEPS - 1 - ks + 2 * C::kFragsPerWave + stored, k0[ks]);
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) s_cur[qb] = E::mfma(__builtin_bit_cast(x8, k0[ks]), qf[qb][ks], ks == 0 ? zero : s_cur[qb]);
+            if (ks == KSTEPS - 2) {
+#pragma unroll
+                for (int i = 0; i < C::kFragsPerWave; ++i) {
+                    lds_wait_upto(2 * (C::kFragsPerWave - 1 - i) + stored, raw[i][0]);
+                    lds_wait_upto(15, raw[i][1]);  // already there: only ties the register below the wait
+                    lds_write_b128_untracked(img + (wave * C::kFragsPerWave + i) * 1024, __builtin_shufflevector(raw[i][0], raw[i][1], 0, 1, 2, 3, 4, 5, 6, 7));
+                    ++stored;
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (cur_masked)
+            settle(0, s_cur, Masked{});
+        else
+            settle(0, s_cur, Plain{});
+        wait_units(n_units < PF ? 0 : PF - 3);  // units 1 and 2
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the image is written
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) kf[ks] = lds_read_b128_untracked<(1 % NSLOT) * kSlotBytes>(lds_addr(lds + koff[ks]));
     }
 
     // ---- main loop ------------------------------------------------------------------------------------
     // Invariant at the top of iteration u: S(u) settled in `cur`; units u and u+1 resident; units up to
-    // u+PF-1 issued.  S(u+1) is always computed, also past the last unit (the ring slot then holds
-    // the clamped rows of a dummy transfer): that keeps every iteration one straight-line block.
+    // u+PF-1 issued.
     // One iteration is written as groups of "one MFMA plus the vector and LDS work that hides under
     // it", fenced by scheduling barriers, because a wavefront issues in order: the matrix pipe only
     // stays busy if independent ALU work sits between consecutive MFMAs in program order.
@@ -607,8 +649,8 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     //   phase Y: O += V(u) P(u), one MFMA per group, with the row maxima (and masks) of S(u+1), the
     //            K(u+2) fragment reads for the next iteration and the transfers of unit u+PF.
     // Invariant at the top of iteration u: S(u) settled in `cur`; kf = K(u+1); units <= u+2 resident;
-    // units <= u+PF-1 issued.  S(u+1) is computed even past the last unit (its ring slot then holds the
-    // re-read rows of a dummy transfer and every entry is masked): no branch inside the iteration.
+    // units <= u+PF-1 issued.  S(u+1) is computed even past the last unit (its ring slot then holds
+    // whatever was there and every entry is masked): no branch around products inside the iteration.
     // LDS operations of one iteration, in issue order (the same in every iteration, so the position of
     // an operation of the previous iteration is known too):
     //   phase X: V^T image fragments f = 0..KSTEPS-1 (one per step of the phase), after fragment kTrAfter the wave's
@@ -789,7 +831,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
                     ++seq;
                 }
             }
-            if (g == G - 3) issue_unit(u + PF, entry_cur);  // refill: unit u+PF replaces unit u+PF-NSLOT <= u
+            if (g == G - 3 && (SLOT2 >= 0 || u + PF < n_units)) issue_unit(u + PF, entry_cur);  // refill: unit u+PF replaces unit u+PF-NSLOT <= u
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
@@ -797,11 +839,14 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
             l_run[qb] += sum[qb][0] + sum[qb][1];
             if (outgrown[qb]) rescale_to(qb, bm[qb]);
         }
-        // Publish.  This wave's transfers of every unit but the newest PF-3 have landed (see ring_barrier);
+        // Publish.  This wave's transfers of every unit up to u+3 have landed (wait_units; the plain loop requests one in every iteration);
         // its image stores have been performed (phase Y waited for younger reads); its K reads may still
         // be in flight, they target a slot that no transfer touches before the barrier after next.
-        wait_vmcnt<2 * NDMA * (PF - 3)>();
         if (PAGED) asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(entry_nxt)::"memory");
+        if (SLOT2 >= 0)
+            wait_vmcnt<2 * NDMA * (PF - 3)>();
+        else
+            wait_units(n_units - 4 - u);
         entry_cur = entry_nxt;
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
@@ -850,7 +895,6 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     // The last iteration's K reads are still in flight and nobody will use them: wait for them here,
     // with their registers tied, so that the compiler cannot hand those registers to anything else
     // while a read may still land in them.
-    static_assert(KSTEPS == 8 || KSTEPS == 4, "the drain below names every fragment");
     if constexpr (KSTEPS == 8)
         asm volatile("s_waitcnt lgkmcnt(0)"
                      : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]), "+v"(kf[4]), "+v"(kf[5]), "+v"(kf[6]), "+v"(kf[7])::"memory");
