@@ -403,6 +403,9 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     const int qpos_lo = p.causal ? pos0 + t0w : 0x7fffff00;
     int first_masked = (qpos_lo + 1) / kUnit;             // units below lie entirely at or before qpos_lo
     first_masked = first_masked < n_kv / kUnit ? first_masked : n_kv / kUnit;  // and entirely inside the sequence
+    // The last unit goes the masked way in every wave, whether it hides a key or not: all waves meet at the same barriers, and that
+    // unit's iteration has none.
+    first_masked = first_masked < n_units - 1 ? first_masked : n_units - 1;
     int qrel[QB];  // key index (relative to the lane's first key of a unit) up to which a row sees keys
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
@@ -563,7 +566,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
 #pragma unroll
         for (int u = 0; u <= PF; ++u) asm volatile("" : "+s"(entries[u]));
     }
-    // (units past the last are not requested, here and in the loop; their slots then hold anything, and all their scores are hidden)
+    // (units past the last are not requested, here and in the loop; their slots then hold anything, which nothing uses)
 #pragma unroll
     for (int u = 0; u < C::kEarly; ++u)
         if (u < n_units) issue_unit(u, entries[u]);
@@ -649,9 +652,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     //   phase Y: O += V(u) P(u), one MFMA per group, with the row maxima (and masks) of S(u+1), the
     //            K(u+2) fragment reads for the next iteration and the transfers of unit u+PF.
     // Invariant at the top of iteration u: S(u) settled in `cur`; kf = K(u+1); units <= u+2 resident;
-    // units <= u+PF-1 issued.  The last unit of a tile has an iteration of its own (LAST) if it is a masked one; behind a
-    // last plain unit (no causal mask, whole units) S(u+1) is computed all the same: its ring slot holds whatever was there
-    // and every entry is masked.
+    // units <= u+PF-1 issued.  The last unit of a tile has an iteration of its own (LAST).
     // LDS operations of one iteration, in issue order (the same in every iteration, so the position of
     // an operation of the previous iteration is known too):
     //   phase X: V^T image fragments f = 0..KSTEPS-1 (one per step of the phase), after fragment kTrAfter the wave's
@@ -893,7 +894,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
         copy_back();
         ++u;
     }
-    if (!cur_masked) {  // the last plain unit: its successor (if any) is masked
+    if (!cur_masked) {  // the last plain unit: its successor is masked
         iteration(u, s_cur, s_nxt, Plain{}, Masked{}, AnySlot{}, More{});
         copy_back();
         ++u;
@@ -907,7 +908,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
         copy_back();
         ++u;
     }
-    if (u < n_units) iteration(u, s_cur, s_nxt, Masked{}, Masked{}, AnySlot{}, Last{});
+    iteration(u, s_cur, s_nxt, Masked{}, Masked{}, AnySlot{}, Last{});
     // The last iteration's K reads are still in flight and nobody will use them: wait for them here,
     // with their registers tied, so that the compiler cannot hand those registers to anything else
     // while a read may still land in them.

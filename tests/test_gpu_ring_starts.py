@@ -22,7 +22,9 @@ LENS = [1, 31, 32, 33, 63, 64, 65, 96, 97, 128, 129, 160, 161, 192, 224, 225, 25
 def test_every_instance_from_one_unit_to_a_full_ring(D, dtype, paged, causal, sign):
     scale = sign / np.sqrt(D)
     if paged:
-        wl = W.make_paged(95, "prefill", [min(n, 40) for n in LENS], LENS, 8, 2, D, 16, sum(-(-n // 16) for n in LENS) + 3, scale=scale, causal=causal)
+        # (the last: a wavefront whose one token is the tile's last one and sees whole units, next to others that do not)
+        q_lens, kv_lens = [min(n, 40) for n in LENS] + [33, 65], LENS + [64, 128]
+        wl = W.make_paged(95, "prefill", q_lens, kv_lens, 8, 2, D, 16, sum(-(-n // 16) for n in kv_lens) + 3, scale=scale, causal=causal)
     else:
         wl = W.make_prefill_contiguous(96, LENS, 8, 2, D, scale=scale, causal=causal)
     poison = W.make_prefill_contiguous(97, [256] * 64, 8, 2, D, scale=scale, causal=False)
