@@ -273,8 +273,7 @@ bool few_rows_many_keys(const KParams &p)
     return (p.max_kv_len >= 160 && wgs <= compute_units()) || (p.max_kv_len > two_from && wgs <= 2 * compute_units());
 }
 
-// ---- prefill whose keys are cut into parts over workgroups (a call that brings scratch memory) -----------------
-// The workgroups of one part.
+// The workgroups of a prefill call (of one part of the keys).
 struct KeyTiles {
     int64_t grid;  // the longest query's tiles for every sequence
     int64_t busy;  // at most this many of them find work
@@ -285,6 +284,25 @@ KeyTiles key_tiles(const Instance &inst, const KParams &p)
     const int64_t groups = p.num_q_heads / heads, grid = (int64_t)p.num_seqs * ((p.max_q_len + tok - 1) / tok) * groups;
     return KeyTiles{grid, std::min(grid, ((int64_t)p.total_q / tok + p.num_seqs) * groups)};
 }
+// Whether the ring kernel's 128-row tiles are so few that a workgroup of two wavefront groups, each with half of the keys, is ahead of
+// one group per tile (`id`: that instance).  GPU time on 4000 random causal shapes (batch 1-16, 8-8192 new tokens, 0-16384 cached ones,
+// 32/8, 64/8, 16/16, 16/4 and 8/2 heads, bf16, built-in choice before against halves):
+//  * at most one tile per compute unit: from 700 keys on 1.18x on average at D = 128 and 1.21x at D = 64 (1.24x and 1.25x from 1200
+//    keys on), 0.5 and 1.4 % of the shapes lose more than 2 %; at 300-700 keys level on average, with shapes down to 0.77x, and
+//    from 8192 keys on 1.07x against the ring kernel in parts (below), which is left to take over where a call brings scratch memory;
+//  * up to two per compute unit one whole prompt gains from 1400 keys on (a triangle: the mean tile has half of the longest one's
+//    keys): 1.11-1.46x at D = 128, 1.08-1.28x at D = 64, none of 130 loses; with less than 1400 keys 0.93-1.17x, with more tiles
+//    0.80-1.18x, behind a cached prefix 0.89-1.0x, several sequences 0.79-1.3x.
+bool halves_pay(const KParams &p, int id)
+{
+    int n;
+    if (id < 0) return false;
+    const int64_t busy = key_tiles(instances(0, &n)[id], p).busy, cus = compute_units();
+    const bool whole_prompt = p.num_seqs == 1 && p.causal && p.max_kv_len == p.max_q_len;
+    return (busy <= cus && p.max_kv_len >= 700 && p.max_kv_len < 8192) || (whole_prompt && busy <= 2 * cus && p.max_kv_len >= 1400);
+}
+
+// ---- prefill whose keys are cut into parts over workgroups (a call that brings scratch memory) -----------------
 size_t key_parts_bytes(const Instance &inst, const KParams &p, int parts)
 {
     return parts <= 1 ? 0 : (size_t)key_tiles(inst, p).grid * inst.block_m * parts * partial_stride(p.head_dim) * sizeof(float);
@@ -325,6 +343,10 @@ double whole_model_us(const Instance &inst, const KParams &p)
 {
     const KeyTiles tiles = key_tiles(inst, p);
     if (inst.heads_per_wg == 0) return split_model_us(p, tiles, 1);
+    if (inst.block_m == 128 && inst.waves == 8) {  // halves; the tiles of a whole prompt are a triangle
+        const double rounds = (double)tiles.busy / (double)compute_units() * (p.num_seqs == 1 && p.max_kv_len == p.max_q_len ? 0.7 : 1.0);
+        return std::max(1.0, rounds) * (7.0 + (p.head_dim == 64 ? 2.5 : 3.6) * (double)p.max_kv_len / 256.0);
+    }
     if (inst.block_m == 128) return ring_model_us(p, tiles, 1);
     return std::max(1.0, (double)tiles.busy / (double)compute_units()) * (8.0 + 5.5 * (double)key_steps(p, 1));
 }
@@ -448,6 +470,9 @@ int heuristic(const KParams &p, int is_decode)
         if (few_rows_many_keys(p)) id = find_instance(0, p, 8, 0, 32, 32, 0);  // wavefronts split the keys
         if (id >= 0) return id;
         const int hpw = ring_heads(p);
+        id = find_instance(0, p, 8, hpw, 32, 128, 0, 1);  // two wavefront groups per 128-row tile
+        if (halves_pay(p, id)) return id;
+        id = -1;
         // The rules below come from tuning a batch x length grid (profiles: configuration portability).
         // Sequences of many query tiles, many sequences, or a cached prefix that dominates the key
         // range: run the tiles of a sequence side by side so that they share its K/V in one L2.
@@ -661,10 +686,11 @@ void maybe_load_env_cache()
 // instead of building the bucket string, taking the lock and walking the instance table.
 struct SelectKey {
     int32_t dtype, head_dim, num_q_heads, num_kv_heads, paged, block_size, causal, num_seqs, max_q_len, max_kv_len;
+    int32_t total_q;  // (bounds the tiles of a prefill call)
     int64_t kv_stride_block, kv_stride_tok;  // (kernels with 32-bit offsets inside a block refuse large ones)
     bool operator==(const SelectKey &o) const
     {
-        return dtype == o.dtype && head_dim == o.head_dim && num_q_heads == o.num_q_heads && num_kv_heads == o.num_kv_heads &&
+        return total_q == o.total_q && dtype == o.dtype && head_dim == o.head_dim && num_q_heads == o.num_q_heads && num_kv_heads == o.num_kv_heads &&
                paged == o.paged && block_size == o.block_size && causal == o.causal && num_seqs == o.num_seqs &&
                max_q_len == o.max_q_len && max_kv_len == o.max_kv_len && kv_stride_block == o.kv_stride_block &&
                kv_stride_tok == o.kv_stride_tok;
@@ -673,7 +699,7 @@ struct SelectKey {
 SelectKey select_key(const KParams &p, int dtype)
 {
     return SelectKey{dtype, p.head_dim, p.num_q_heads, p.num_kv_heads, p.block_table ? 1 : 0, p.block_size, p.causal,
-                     p.num_seqs, p.max_q_len, p.max_kv_len, p.kv_stride_block, p.kv_stride_tok};
+                     p.num_seqs, p.max_q_len, p.max_kv_len, p.total_q, p.kv_stride_block, p.kv_stride_tok};
 }
 enum class Origin { built_in, tuned, forced };
 struct Selection {
@@ -775,14 +801,13 @@ KeyPlan planned_parts(const KParams &p, int dtype, Selection sel)
     if (sel.origin == Origin::tuned) return KeyPlan{sel.id, 1};
     struct Memo {
         SelectKey key{};
-        int total_q = -1;
         Selection sel;
         KeyPlan plan;
     };
     static thread_local Memo m;
     const SelectKey key = select_key(p, dtype);
-    if (m.sel.id != sel.id || m.sel.origin != sel.origin || m.total_q != p.total_q || !(m.key == key)) {
-        m = Memo{key, p.total_q, sel, key_plan(p, sel.id, sel.origin == Origin::forced)};
+    if (m.sel.id != sel.id || m.sel.origin != sel.origin || !(m.key == key)) {
+        m = Memo{key, sel, key_plan(p, sel.id, sel.origin == Origin::forced)};
         if (env_knobs().log && m.plan.parts > 1) {
             int n;
             fprintf(stderr, "[attn] prefill %s with scratch memory -> %s in %d parts\n", bucket_key(p, dtype, 0).c_str(),

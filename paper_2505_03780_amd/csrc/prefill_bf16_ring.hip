@@ -30,6 +30,12 @@
 //    for prefill_ring_merge_kernel.  3 x 17-70 tokens behind 5000-9000 keys (56 tiles, 512 places): 141 us in one part, 42 in
 //    eight, against 51-57 for the key-split kernel; 3 x 390-450 of 16/16 heads behind 3900 99 -> 79 us.  Built for the small
 //    workgroups only; key_plan in attn_api.hip has the rule.
+//  * Where a call has about as many 128-row tiles as there are compute units, two groups of four wavefronts ("halves", KG = 2) share
+//    a tile: each walks half of its keys through a ring of its own, which is the work of two small workgroups on a compute
+//    unit, and their states meet in LDS at the end (each group finishes half of the channels).  The longest tile's serial walk bounds such
+//    calls, and one small workgroup alone takes 0.57 us for 32 keys where two take 1.0 us together.  One prompt of 1500 tokens of
+//    32/8 heads 37.9 -> 33.2 us, 2000 of 16/16 44.5 -> 36.9, 4000 of 16/4 99.8 -> 81.8, 2 x 300-450 behind 500-1500
+//    30.8 -> 26.0, 1 x 900 behind 4000 113 -> 82; the meeting costs about 1 us.  halves_pay in attn_api.hip has the rule.
 //
 // Head sizes 128 and 64.  At D = 64 a unit has half the MFMAs for the same softmax, so the vector ALU is the bound
 // (16 MFMAs of two row blocks: 512 cycles of matrix pipe, about 780 of the vector issue port, and 128 more for each
@@ -182,7 +188,7 @@ __device__ __forceinline__ int swz(int row)
     return ((row & 3) << 2) | ((row >> 2) & 3);
 }
 
-template <int HD, int QB, int HPW, int NSLOT, int PF, int WAVES>
+template <int HD, int QB, int HPW, int NSLOT, int PF, int WAVES, int KG>
 struct RingCfg {
     static constexpr int kWaves = WAVES;
     static constexpr int kRowBytes = HD * 2;
@@ -194,13 +200,17 @@ struct RingCfg {
     static constexpr int kTSub = kWaves / HPW;
     static constexpr int kWaveTok = 32 * QB;
     static constexpr int kTok = kTSub * kWaveTok;
-    static constexpr int kThreads = WAVES * 64;
+    static constexpr int kThreads = KG * WAVES * 64;
     static constexpr int kFrags = HD / 16;               // V^T fragments of one unit (1 KB each)
     static constexpr int kImgBytes = kFrags * 1024;      // all of them, in MFMA operand order
     static constexpr int kFragsPerWave = kFrags / WAVES; // fragments each wave transposes per unit
     // two waves per SIMD for the small workgroups (four of one row block at D = 64: 40 KB of LDS, 168 registers)
-    static constexpr int kMinWaves = WAVES == 4 && QB == 1 && HD == 64 ? 3 : WAVES == 4 && QB * HD <= 128 ? 2 : 1;
-    static constexpr size_t kLdsBytes = (size_t)NSLOT * kSlotBytes + 2 * kImgBytes;
+    static constexpr int kMinWaves = KG > 1 ? 2 : WAVES == 4 && QB == 1 && HD == 64 ? 3 : WAVES == 4 && QB * HD <= 128 ? 2 : 1;
+    static constexpr int kGroupBytes = NSLOT * kSlotBytes + 2 * kImgBytes;  // ring and images of the wavefronts that walk the same keys
+    static constexpr size_t kLdsBytes = (size_t)KG * kGroupBytes;
+    // epilogue of two key groups: accumulators that change wavefronts, (reference, sum) of every row, output staging
+    static constexpr int kSwapBytes = 32 * HD * 4 / 2, kPairsAt = KG * WAVES * kSwapBytes, kStageAt = KG > 1 ? kPairsAt + KG * WAVES * 32 * 8 : 0;
+    static constexpr int kOutRowBytes = kRowBytes / KG;  // what a wavefront stores of a row
     // Queries reach the registers through LDS too: a wavefront's own share of the V^T images and of the K and V rows of the last
     // kLate slots (kShare bytes each) holds its rows until it has read them.
     static constexpr int kShare = kRowsPerWave * kRowBytes;
@@ -215,7 +225,8 @@ struct RingCfg {
     static_assert(NSLOT >= PF, "ring too small for the prefetch distance");
     static_assert(PF >= 3, "K of unit u+2 is read one iteration ahead, so three units must be resident");
     static_assert(kWaves % HPW == 0, "waves must split evenly over heads");
-    static_assert(kLdsBytes >= (size_t)kWaves * kWaveTok * HD * 2, "epilogue staging must fit in the ring");
+    static_assert(KG == 1 || (KG == 2 && QB == 1), "one key group or two");
+    static_assert(kLdsBytes >= (size_t)kStageAt + KG * kWaves * kWaveTok * kOutRowBytes, "epilogue staging must fit in the ring");
 };
 
 // What a workgroup of the grid stands for: HPW query heads of one KV head x kTok tokens of one sequence (t0 outside
@@ -298,10 +309,10 @@ __device__ __forceinline__ RingParts ring_parts(const KParams &p, const RingTile
     return RingParts{length, end > length ? (end + length - 1) / length : 1};
 }
 
-template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES, bool PAGED, bool PARTS>
-__global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>::kMinWaves)) void prefill_ring_kernel(const KParams p)
+template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES, int KG, bool PAGED, bool PARTS>
+__global__ __launch_bounds__(KG * WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES, KG>::kMinWaves)) void prefill_ring_kernel(const KParams p)
 {
-    using C = RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>;
+    using C = RingCfg<HD, QB, HPW, NSLOT, PF, WAVES, KG>;
     using elem = typename E::elem;
     using x8 = typename E::x8;
     using x2 = typename E::x2;
@@ -309,7 +320,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     constexpr int DB = HD / 32;
     constexpr int CPR = HD / 8;  // 16-byte chunks of a row
     constexpr int kRowBytes = C::kRowBytes, kSlotBytes = C::kSlotBytes, kVOff = C::kVOff;
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_all[];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -325,7 +336,10 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
         n_kv = n_kv - kv_begin < parts.length ? n_kv - kv_begin : parts.length;
     }
 
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // (KG = 2: eight wavefronts, four for each half of the keys)
+    const int kgroup = KG > 1 ? __builtin_amdgcn_readfirstlane(tid / (WAVES * 64)) : 0;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) - kgroup * WAVES;
+    unsigned char *const lds = lds_all + kgroup * C::kGroupBytes;
     const int lhalf = lane >> 5;
     const int l32 = lane & 31;
     const int l16 = lane & 15;
@@ -337,16 +351,17 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     const bool negate_q = p.scale_log2e < 0.f;
 
     // ---- key range -------------------------------------------------------------------------------
-    const int pos0 = off - kv_begin;  // key that query 0 sits at
+    int pos0 = off - kv_begin;  // key that query 0 sits at
     int kv_end = n_kv;
     if (p.causal) {
         const int last_tok = t0 + C::kTok < n_q ? t0 + C::kTok : n_q;
         kv_end = pos0 + last_tok < n_kv ? pos0 + last_tok : n_kv;
     }
-    const int n_units = (kv_end + kUnit - 1) / kUnit;
+    int n_units = (kv_end + kUnit - 1) / kUnit;
 
     elem *obase = (elem *)p.out;
     if (n_units <= 0) {  // no visible key at all (an empty context; also lengths that break seq_lens >= n_q): zeros
+        if (kgroup > 0) return;
         for (int i = lane; i < C::kWaveTok * CPR; i += 64) {
             const int t = t0w + i / CPR;
             if (t < n_q)
@@ -354,6 +369,20 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
                     u32x4{0u, 0u, 0u, 0u};
         }
         return;
+    }
+
+    // Two key groups: the first takes the first half of the units (the larger one), the second the rest, and both count keys from
+    // their first one.  The groups meet at the same barriers; one that runs out of units early goes on with those alone (a unit of
+    // hidden keys instead would multiply their values by zero, and infinities among them would become NaN).
+    int n_share = n_units;  // units of the group that has most
+    if (KG > 1) {
+        n_share = (n_units + KG - 1) / KG;
+        const int first = kgroup * n_share;
+        n_units = n_units - first < n_share ? n_units - first : n_share;
+        kv_begin += first * kUnit;
+        pos0 -= first * kUnit;
+        n_kv -= first * kUnit;
+        if (kgroup == 0 && n_kv > n_share * kUnit) n_kv = n_share * kUnit;
     }
 
     // ---- table entries of the first units, queries: requested before anything else is worked out -----------
@@ -566,6 +595,7 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
 #pragma unroll
         for (int u = 0; u <= PF; ++u) asm volatile("" : "+s"(entries[u]));
     }
+    if (KG == 1 || n_units > 0) {  // (uniform over a group)
     // (units past the last are not requested, here and in the loop; their slots then hold anything, which nothing uses)
 #pragma unroll
     for (int u = 0; u < C::kEarly; ++u)
@@ -918,9 +948,53 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
     else
         asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3])::"memory");
 
+    }
+    if (KG > 1)  // the other group's barriers
+        for (int i = n_units > 0 ? n_units : -1; i < n_share; ++i) __builtin_amdgcn_s_barrier();
+
     // ---- epilogue: O / l, transposed through LDS, whole rows to HBM ------------------------------
     wait_vmcnt<0>();
     __syncthreads();  // the ring is free: every wave is past its last V read and no DMA is in flight
+    // What this wave finishes: all channels, or (two key groups) its group's half of them, with the other group's share added
+    constexpr int ODB = DB / KG;
+    f32x16 out[QB][ODB];
+    float l_row[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) l_row[qb] = swap32_sum(l_run[qb]);
+    if constexpr (KG > 1) {
+        unsigned char *mine = lds_all + (kgroup * WAVES + wave) * C::kSwapBytes, *theirs = lds_all + ((1 - kgroup) * WAVES + wave) * C::kSwapBytes;
+        float2 *pairs = (float2 *)(lds_all + C::kPairsAt);
+        auto leave = [&](const f32x16 &a, int i) {
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq) *(f32x4 *)(mine + ((4 * i + vq) * 64 + lane) * 16) = f32x4{a[4 * vq], a[4 * vq + 1], a[4 * vq + 2], a[4 * vq + 3]};
+        };
+        if (kgroup == 0) {
+#pragma unroll
+            for (int i = 0; i < ODB; ++i) leave(oacc[0][ODB + i], i), out[0][i] = oacc[0][i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < ODB; ++i) leave(oacc[0][i], i), out[0][i] = oacc[0][ODB + i];
+        }
+        if (lhalf == 0) pairs[(kgroup * WAVES + wave) * 32 + l32] = float2{m_ref[0], l_row[0]};
+        __syncthreads();
+        const float2 other = pairs[((1 - kgroup) * WAVES + wave) * 32 + l32];
+        const float m = fmaxf(m_ref[0], other.x), f = fast_exp2(m_ref[0] - m), g = fast_exp2(other.x - m);
+        m_ref[0] = m;
+        l_row[0] = l_row[0] * f + other.y * g;
+#pragma unroll
+        for (int i = 0; i < ODB; ++i)
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq) {
+                const f32x4 o = *(const f32x4 *)(theirs + ((4 * i + vq) * 64 + lane) * 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) out[0][i][4 * vq + e] = out[0][i][4 * vq + e] * f + o[e] * g;
+            }
+    } else {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) out[qb][db] = oacc[qb][db];
+    }
     if (PARTS) {
         const RingParts parts = ring_parts(p, T, C::kTok);
         if (parts.count > 1) {  // one of several: a record of each row block in register order, left for the merge
@@ -929,58 +1003,58 @@ __global__ __launch_bounds__(WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>
                 float *rec = p.workspace + (((int64_t)blockIdx.x * WAVES + wave) * QB + qb) * p.num_splits * kRecordFloats<HD> +
                              (int64_t)blockIdx.y * kRecordFloats<HD>;
 #pragma unroll
-                for (int db = 0; db < DB; ++db)
+                for (int db = 0; db < ODB; ++db)
 #pragma unroll
                     for (int vq = 0; vq < 4; ++vq)
-                        *(f32x4 *)(rec + (4 * db + vq) * 256 + 4 * lane) =
-                            f32x4{oacc[qb][db][4 * vq], oacc[qb][db][4 * vq + 1], oacc[qb][db][4 * vq + 2], oacc[qb][db][4 * vq + 3]};
-                const float l = swap32_sum(l_run[qb]);
-                if (lhalf == 0) *(float2 *)(rec + 32 * HD + 2 * l32) = float2{m_ref[qb], l};
+                        *(f32x4 *)(rec + (4 * (kgroup * ODB + db) + vq) * 256 + 4 * lane) =
+                            f32x4{out[qb][db][4 * vq], out[qb][db][4 * vq + 1], out[qb][db][4 * vq + 2], out[qb][db][4 * vq + 3]};
+                if (kgroup == 0 && lhalf == 0) *(float2 *)(rec + 32 * HD + 2 * l32) = float2{m_ref[qb], l_row[qb]};
             }
             return;
         }
     }
-    unsigned char *stage = lds + wave * (C::kWaveTok * kRowBytes);  // [token][HD] elements, chunk-swizzled by token
+    constexpr int OCPR = CPR / KG;  // 16-byte chunks of a row that a wave stores
+    // [token][HD / KG] elements, chunk-swizzled by token
+    unsigned char *stage = lds_all + C::kStageAt + (kgroup * WAVES + wave) * (C::kWaveTok * C::kOutRowBytes);
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        const float l = swap32_sum(l_run[qb]);
-        const float inv = l > 0.f ? 1.f / l : 0.f;
+        const float inv = l_row[qb] > 0.f ? 1.f / l_row[qb] : 0.f;
         const int tl = qb * 32 + l32;
 #pragma unroll
-        for (int db = 0; db < DB; ++db) {
+        for (int db = 0; db < ODB; ++db) {
 #pragma unroll
             for (int vq = 0; vq < 4; ++vq) {
                 x2 a, b;
-                a[0] = (elem)(oacc[qb][db][4 * vq + 0] * inv);
-                a[1] = (elem)(oacc[qb][db][4 * vq + 1] * inv);
-                b[0] = (elem)(oacc[qb][db][4 * vq + 2] * inv);
-                b[1] = (elem)(oacc[qb][db][4 * vq + 3] * inv);
+                a[0] = (elem)(out[qb][db][4 * vq + 0] * inv);
+                a[1] = (elem)(out[qb][db][4 * vq + 1] * inv);
+                b[0] = (elem)(out[qb][db][4 * vq + 2] * inv);
+                b[1] = (elem)(out[qb][db][4 * vq + 3] * inv);
                 const int chunk = 4 * db + vq;  // 16-byte chunk of the row; lhalf selects its 8-byte half
                 u32x2 w;
                 w[0] = __builtin_bit_cast(uint32_t, a);
                 w[1] = __builtin_bit_cast(uint32_t, b);
-                *(u32x2 *)(stage + tl * kRowBytes + 16 * (chunk ^ (tl % CPR)) + 8 * lhalf) = w;
+                *(u32x2 *)(stage + tl * C::kOutRowBytes + 16 * (chunk ^ (tl % OCPR)) + 8 * lhalf) = w;
             }
         }
     }
     // wave-private staging: the wave's own LDS writes are ordered before its reads
 #pragma unroll
-    for (int i = 0; i < C::kWaveTok * CPR / 64; ++i) {
-        const int tl = (64 / CPR) * i + lane / CPR;
-        const int chunk = lane % CPR;
-        const u32x4 row = *(const u32x4 *)(stage + tl * kRowBytes + 16 * (chunk ^ (tl % CPR)));
+    for (int i = 0; i < C::kWaveTok * OCPR / 64; ++i) {
+        const int tl = (64 / OCPR) * i + lane / OCPR;
+        const int chunk = lane % OCPR;
+        const u32x4 row = *(const u32x4 *)(stage + tl * C::kOutRowBytes + 16 * (chunk ^ (tl % OCPR)));
         const int t = t0w + tl;
         if (t < n_q)
-            *(u32x4 *)(obase + (int64_t)(q0 + t) * p.o_stride_tok + (int64_t)head * p.o_stride_head + 8 * chunk) = row;
+            *(u32x4 *)(obase + (int64_t)(q0 + t) * p.o_stride_tok + (int64_t)head * p.o_stride_head + 8 * (kgroup * OCPR + chunk)) = row;
     }
 }
 
 // Merges the parts of a tile: a thread owns four channels of a row (the records are in the accumulators' register order, so
 // that both sides move whole kilobytes; the 8-byte stores of the outputs are 2 / parts of what is read).
-template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES>
+template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES, int KG>
 __global__ __launch_bounds__(kMergeThreads) void prefill_ring_merge_kernel(const KParams p)
 {
-    using C = RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>;
+    using C = RingCfg<HD, QB, HPW, NSLOT, PF, WAVES, KG>;
     using elem = typename E::elem;
     typedef elem x4 __attribute__((ext_vector_type(4)));
     const int i = (int)blockIdx.x % kMergeBlocks<HD> * kMergeThreads + (int)threadIdx.x;
@@ -1005,11 +1079,11 @@ bool ring_valid(const KParams &p)
            (uint64_t)p.kv_stride_tok * 2 * kUnit < (1ull << 32);
 }
 
-template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES, bool PAGED, bool PARTS>
+template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES, int KG, bool PAGED, bool PARTS>
 hipError_t ring_launch_impl(const KParams &p, hipStream_t stream, int64_t blocks)
 {
-    using C = RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>;
-    auto kern = prefill_ring_kernel<E, HD, QB, HPW, NSLOT, PF, WAVES, PAGED, PARTS>;
+    using C = RingCfg<HD, QB, HPW, NSLOT, PF, WAVES, KG>;
+    auto kern = prefill_ring_kernel<E, HD, QB, HPW, NSLOT, PF, WAVES, KG, PAGED, PARTS>;
     static std::atomic<uint64_t> granted{0};
     const hipError_t allowed = allow_dynamic_lds((const void *)kern, C::kLdsBytes, granted);
     if (allowed != hipSuccess) return allowed;
@@ -1018,33 +1092,33 @@ hipError_t ring_launch_impl(const KParams &p, hipStream_t stream, int64_t blocks
 }
 
 // Instances whose keys can be cut into parts: the small workgroups.
-template <int QB, int WAVES>
-constexpr bool kHasParts = QB == 1 && WAVES == 4;
+template <int QB, int WAVES, int KG>
+constexpr bool kHasParts = QB == 1 && WAVES == 4 && KG == 1;
 
-template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES, int ORDER>
+template <typename E, int HD, int QB, int HPW, int NSLOT, int PF, int WAVES, int KG, int ORDER>
 hipError_t ring_launch(const KParams &p_in, hipStream_t stream)
 {
     KParams p = p_in;
     p.tile_order = ORDER;
-    using C = RingCfg<HD, QB, HPW, NSLOT, PF, WAVES>;
+    using C = RingCfg<HD, QB, HPW, NSLOT, PF, WAVES, KG>;
     const int64_t q_tiles = (p.max_q_len + C::kTok - 1) / C::kTok;
     const int64_t nhg = (int64_t)p.num_kv_heads * (p.group / HPW);
     const int64_t blocks = q_tiles * p.num_seqs * nhg;
     if (blocks <= 0) return hipSuccess;
     if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
-    if constexpr (kHasParts<QB, WAVES>) {
+    if constexpr (kHasParts<QB, WAVES, KG>) {
         if (p.num_splits > 1) {
             if (blocks * WAVES * kMergeBlocks<HD> > 0x7fffffff) return hipErrorInvalidConfiguration;
-            const hipError_t e = p.block_table ? ring_launch_impl<E, HD, QB, HPW, NSLOT, PF, WAVES, true, true>(p, stream, blocks)
-                                               : ring_launch_impl<E, HD, QB, HPW, NSLOT, PF, WAVES, false, true>(p, stream, blocks);
+            const hipError_t e = p.block_table ? ring_launch_impl<E, HD, QB, HPW, NSLOT, PF, WAVES, KG, true, true>(p, stream, blocks)
+                                               : ring_launch_impl<E, HD, QB, HPW, NSLOT, PF, WAVES, KG, false, true>(p, stream, blocks);
             if (e != hipSuccess) return e;
-            hipLaunchKernelGGL((prefill_ring_merge_kernel<E, HD, QB, HPW, NSLOT, PF, WAVES>), dim3((unsigned)(blocks * WAVES * kMergeBlocks<HD>)),
+            hipLaunchKernelGGL((prefill_ring_merge_kernel<E, HD, QB, HPW, NSLOT, PF, WAVES, KG>), dim3((unsigned)(blocks * WAVES * kMergeBlocks<HD>)),
                                dim3(kMergeThreads), 0, stream, p);
             return hipGetLastError();
         }
     }
-    return p.block_table ? ring_launch_impl<E, HD, QB, HPW, NSLOT, PF, WAVES, true, false>(p, stream, blocks)
-                         : ring_launch_impl<E, HD, QB, HPW, NSLOT, PF, WAVES, false, false>(p, stream, blocks);
+    return p.block_table ? ring_launch_impl<E, HD, QB, HPW, NSLOT, PF, WAVES, KG, true, false>(p, stream, blocks)
+                         : ring_launch_impl<E, HD, QB, HPW, NSLOT, PF, WAVES, KG, false, false>(p, stream, blocks);
 }
 
 // This file is compiled twice: as it stands for bf16, and included by prefill_f16_ring.hip with
@@ -1057,15 +1131,17 @@ hipError_t ring_launch(const KParams &p_in, hipStream_t stream)
 #define RING_NAME "prefill_bf16_ring"
 #endif
 
-#define RING_ONE(HD, QB, HPW, NSLOT, PF, WAVES, ORDER, TAG)                                                        \
+#define RING_ONE(HD, QB, HPW, NSLOT, PF, WAVES, KG, ALL_WAVES, ORDER, TAG)                                         \
     {                                                                                                              \
-        RING_NAME " d" #HD " qb" #QB " w" #WAVES " hpw" #HPW " slots" #NSLOT " pf" #PF TAG, WAVES * 32 * QB, kUnit, WAVES, \
+        RING_NAME " d" #HD " qb" #QB " w" #ALL_WAVES " hpw" #HPW " slots" #NSLOT " pf" #PF TAG, WAVES * 32 * QB, kUnit, ALL_WAVES, \
             HPW, PF, 0, ring_valid<RING_ELEM, HD, QB, HPW, NSLOT, PF, WAVES>,                                      \
-            ring_launch<RING_ELEM, HD, QB, HPW, NSLOT, PF, WAVES, ORDER>, ORDER, false, kHasParts<QB, WAVES>       \
+            ring_launch<RING_ELEM, HD, QB, HPW, NSLOT, PF, WAVES, KG, ORDER>, ORDER, false, kHasParts<QB, WAVES, KG> \
     }
 // both grid orders of one compiled kernel
 #define RING_INSTANCE(HD, QB, HPW, NSLOT, PF, WAVES) \
-    RING_ONE(HD, QB, HPW, NSLOT, PF, WAVES, 0, ""), RING_ONE(HD, QB, HPW, NSLOT, PF, WAVES, 1, " seqmajor")
+    RING_ONE(HD, QB, HPW, NSLOT, PF, WAVES, 1, WAVES, 0, ""), RING_ONE(HD, QB, HPW, NSLOT, PF, WAVES, 1, WAVES, 1, " seqmajor")
+// the keys of a tile over two groups of four wavefronts, the tiles of a sequence side by side
+#define RING_HALVES(HD, HPW) RING_ONE(HD, 1, HPW, 4, 4, 4, 2, 8, 1, " halves seqmajor")
 
 }  // namespace
 
@@ -1078,6 +1154,7 @@ const Instance *prefill_ring_f16_instances(int *count)
         RING_INSTANCE(128, 1, 1, 4, 4, 4),
         RING_INSTANCE(64, 2, 4, 8, 5, 4), RING_INSTANCE(64, 2, 2, 8, 5, 4), RING_INSTANCE(64, 2, 1, 8, 5, 4),
         RING_INSTANCE(64, 1, 4, 4, 4, 4), RING_INSTANCE(64, 1, 2, 4, 4, 4), RING_INSTANCE(64, 1, 1, 4, 4, 4),
+        RING_HALVES(64, 4), RING_HALVES(64, 2), RING_HALVES(64, 1), RING_HALVES(128, 4), RING_HALVES(128, 2), RING_HALVES(128, 1),
     };
     *count = (int)(sizeof(table) / sizeof(table[0]));
     return table;
@@ -1092,6 +1169,7 @@ const Instance *prefill_ring_instances(int *count)
         RING_INSTANCE(128, 1, 2, 8, 5, 8), RING_INSTANCE(128, 1, 1, 8, 5, 8), RING_INSTANCE(128, 1, 4, 8, 6, 8),
         RING_INSTANCE(64, 2, 4, 8, 5, 4), RING_INSTANCE(64, 2, 2, 8, 5, 4), RING_INSTANCE(64, 2, 1, 8, 5, 4),
         RING_INSTANCE(64, 1, 4, 4, 4, 4), RING_INSTANCE(64, 1, 2, 4, 4, 4), RING_INSTANCE(64, 1, 1, 4, 4, 4),
+        RING_HALVES(64, 4), RING_HALVES(64, 2), RING_HALVES(64, 1), RING_HALVES(128, 4), RING_HALVES(128, 2), RING_HALVES(128, 1),
         RING_INSTANCE(128, 1, 4, 8, 8, 8), RING_INSTANCE(128, 1, 1, 8, 8, 8), RING_INSTANCE(128, 1, 4, 4, 4, 4),
         RING_INSTANCE(128, 1, 1, 4, 4, 4), RING_INSTANCE(128, 1, 2, 4, 4, 4),
     };
