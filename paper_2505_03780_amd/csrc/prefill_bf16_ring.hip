@@ -1002,6 +1002,7 @@ __global__ __launch_bounds__(KG * WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, W
             for (int qb = 0; qb < QB; ++qb) {
                 float *rec = p.workspace + (((int64_t)blockIdx.x * WAVES + wave) * QB + qb) * p.num_splits * kRecordFloats<HD> +
                              (int64_t)blockIdx.y * kRecordFloats<HD>;
+                if (t0w + qb * 32 + l32 >= n_q) continue;  // (the merge reads no rows past the last token either)
 #pragma unroll
                 for (int db = 0; db < ODB; ++db)
 #pragma unroll
