@@ -246,8 +246,7 @@ __global__ __launch_bounds__(WAVES * 64, HD == 64 && WAVES == 4 ? 4 : 1) void de
                 x[4 * t + v] = y;
                 mloc = fmaxf(mloc, y);
             }
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+        mloc = max_over_groups(mloc);
         const float m_new = fmaxf(fmaxf(m_run, mloc), kLowest);
         const float alpha = fast_exp2(m_run - m_new);
         m_run = m_new;
@@ -283,8 +282,7 @@ __global__ __launch_bounds__(WAVES * 64, HD == 64 && WAVES == 4 ? 4 : 1) void de
     }
 
     // ---- merge the wavefronts of this workgroup ----------------------------------------------
-    l_run += __shfl_xor(l_run, 16);
-    l_run += __shfl_xor(l_run, 32);
+    l_run = sum_over_groups(l_run);
     __syncthreads();  // all waves are done with their V tiles; LDS is reused for the reduction
     float *red = (float *)lds;  // [WAVES][16 heads][HD + 2]
     {
@@ -451,8 +449,7 @@ __device__ __forceinline__ void decode_stream_run(const KParams &p, unsigned cha
     };
     // this wave's result for the piece: G heads x HD channels, no other wave involved
     auto end_piece = [&]() {
-        float l_all = l_run + __shfl_xor(l_run, 16);
-        l_all += __shfl_xor(l_all, 32);
+        const float l_all = sum_over_groups(l_run);
         float *rec_base = record(cs, c_whole);
         if (l16 < G) {
             const int head = kvh * G + l16;
@@ -526,8 +523,7 @@ __device__ __forceinline__ void decode_stream_run(const KParams &p, unsigned cha
                 x[4 * t + v] = y;
                 mloc = fmaxf(mloc, y);
             }
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+        mloc = max_over_groups(mloc);
         const float m_new = fmaxf(fmaxf(m_run, mloc), kLowest);
         const float alpha = fast_exp2(m_run - m_new);
         m_run = m_new;

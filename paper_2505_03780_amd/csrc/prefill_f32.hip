@@ -181,8 +181,7 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_f32_kernel(const KParams 
             x[v] = c0 + 4 * g + v < limit ? sacc[v] * p.scale : -INFINITY;
             mx = fmaxf(mx, x[v]);
         }
-        mx = fmaxf(mx, __shfl_xor(mx, 16));
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        mx = max_over_groups(mx);
         const float m_new = fmaxf(m, mx);
         const float m_use = m_new == -INFINITY ? 0.f : m_new;  // (no visible key so far: all weights are zero)
         const float alpha = expf(m - m_use);
@@ -219,8 +218,7 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_f32_kernel(const KParams 
     }
 
     // ---- merge the wavefronts ----
-    l += __shfl_xor(l, 16);
-    l += __shfl_xor(l, 32);
+    l = sum_over_groups(l);
     float *state = red + kWaves * kRows * C::kRedPitch;
     float *mine = red + (wave * kRows + i) * C::kRedPitch + 16 * g;
 #pragma unroll
