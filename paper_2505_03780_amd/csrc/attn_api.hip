@@ -473,18 +473,39 @@ int heuristic(const KParams &p, int is_decode)
         id = find_instance(0, p, 8, hpw, 32, 128, 0, 1);  // two wavefront groups per 128-row tile
         if (halves_pay(p, id)) return id;
         id = -1;
-        // The rules below come from tuning a batch x length grid (profiles: configuration portability).
-        // Sequences of many query tiles, many sequences, or a cached prefix that dominates the key
-        // range: run the tiles of a sequence side by side so that they share its K/V in one L2.
+        // Small (128 rows, two per compute unit, three at D = 64) or large workgroup, and the grid's order: every ring instance timed
+        // in graphs on 14000 random causal calls of 400 to 20000 tiles of 128 rows (2 to 800 GFLOP, 1-64 sequences of up to 9000
+        // keys, 32/8, 64/8, 16/16, 16/4 and 8/2 heads), and choice before against choice now on 370 of them over 100 ms without a pause
+        // (in brackets; a full grid is bound by power, and after a pause the clock starts some 20 % lower).  The large one (one
+        // workgroup, 256 rows) moves half of the bytes per flop and wins once its start and end are a small part of its walk and
+        // there are many rounds of it.
+        //  * D = 128: small up to 4096 keys (against the large one above 2048 keys 1.08x on average, 1.07x behind a prefix [1.02-1.17x,
+        //    1.01-1.11x]; at three to four tiles per compute unit the large one comes out even, 1.017x with a third of the shapes
+        //    behind), and below 8192 where its tiles make no more than two rounds (four tiles per compute unit behind a prefix:
+        //    1.09x [1.02-1.05x]; three else: 1.06x [1.03-1.1x]).  Beyond, level or behind: one sequence of 8191 tokens 474-485 us
+        //    large, 496 small; 16 x 512 behind 0-8192 654 and 680.
+        //  * D = 64: small up to 2048 keys, and up to eight tiles per compute unit (sixteen behind a prefix): 1.05-1.14x [1.03-1.22x].
+        //    Beyond, 1.07x but [0.97-1.03x]: 6 x 300-3000 tokens [178 us large, 184 small].
+        //  * Order, sequences outermost (their tiles share the keys in one L2) behind a prefix that dominates: 1.02-1.1x; else tiles outermost
+        //    (equal costs in flight, small tiles left for the end): D = 128 1.03-1.1x below 32 sequences, and between 2048 and 4096
+        //    keys to twelve tiles per compute unit; D = 64, small, also for many sequences up to eight tiles per compute unit (32-64
+        //    sequences 1.03-1.17x [1.07-1.24x], beyond 0.96-1.03x) and for five or more sequences above 4096 keys (1.2x; fewer
+        //    1.04x, down to 0.74x).
         const bool prefix = p.block_table && p.max_kv_len >= 2 * p.max_q_len;
-        const int order = (prefix || p.max_kv_len >= 4096 || p.num_seqs >= 32) ? 1 : 0;
-        // Short sequences: two small workgroups per compute unit hide each other's prologue and
-        // epilogue; long ones: one large workgroup with the deeper ring.
-        // At D = 64 the small workgroup (128 rows, three per compute unit) also stays ahead on long contexts
-        // until there are 256-row tiles for every compute unit four times over: 2 x 1000 tokens behind 3000 keys
-        // 88 against 97 us, one sequence of 8191 tokens (1024 tiles) 331 against 318 us.
-        const int64_t tiles256 = (int64_t)p.num_seqs * ((p.max_q_len + 256 / hpw - 1) / (256 / hpw)) * (p.num_q_heads / hpw);
-        const bool small_wg = p.max_kv_len <= 2048 || (p.head_dim == 64 && tiles256 < 4 * compute_units());
+        const int64_t cus = compute_units(), kv = p.max_kv_len;
+        id = small_ring_instance(p);
+        const int64_t tiles = id >= 0 ? key_tiles(instances(0, &n)[id], p).busy : 0;
+        id = -1;
+        bool small_wg, by_seq;
+        if (p.head_dim == 64) {
+            small_wg = kv <= 2048 || tiles < (prefix ? 16 : 8) * cus;
+            by_seq = !small_wg ? kv >= 4096 || p.num_seqs >= 32 : kv <= 2048 ? p.num_seqs >= 32 && tiles >= 8 * cus : kv <= 4096 ? p.num_seqs >= 32 : p.num_seqs < 5;
+        } else {
+            const bool even = !prefix && tiles > 3 * cus && tiles <= 4 * cus;
+            small_wg = kv <= 2048 || (kv <= 4096 && !even) || (kv < 8192 && tiles <= (prefix ? 4 : 3) * cus);
+            by_seq = kv <= 2048 ? p.num_seqs >= 32 : kv >= 4096 || tiles >= 12 * cus;
+        }
+        const int order = prefix || by_seq ? 1 : 0;
         // a paged context adds the table entry to every transfer's address chain: the deepest prefetch
         // (8 units) measured up to 10 % ahead of 5 on the slower machines there, level elsewhere
         if (!small_wg && p.block_table) id = find_instance(0, p, 8, hpw, 32, 256, 0, order, 8);
