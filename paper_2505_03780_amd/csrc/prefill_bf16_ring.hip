@@ -45,7 +45,7 @@
 // how many share a unit).  Against the register-staged kernel that served D = 64 before (32/8 heads, calls in turn):
 // 6 fp16 sequences of 300-3000 tokens 473 -> 190 us (289 -> 718 TFLOP/s; 171 us with a reference that may lag by 2^8, see
 // kSlack), one bf16 sequence of 8191 tokens 318 us (864 TFLOP/s).  An eight-slot ring with five units in flight is 2-6 % ahead of four slots there; one row block with
-// four slots and three workgroups per compute unit leads up to about four 256-row tiles per compute unit.
+// four slots and three workgroups per compute unit leads up to 2048 keys and up to about eight of its tiles per compute unit.
 #include "kernel_params.hpp"
 #include "prefill_parts.hpp"
 
