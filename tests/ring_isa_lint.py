@@ -9,7 +9,8 @@ then lands on top of the new contents.  This module replays every kernel's instr
 model of the LDS counter (operations of a wave complete in order; s_waitcnt lgkmcnt(N) returns when
 at most N are outstanding; scalar loads return out of order and are only known to be back after
 lgkmcnt(0)) and reports every instruction that reads or writes a register while a load into it may
-still be in flight.  Loops are replayed a second time from their head with the state of the back edge.
+still be in flight.  Both sides of every branch are followed, each with the state at the branch, until no
+new state turns up: a wait counts on the paths that run it alone.
 """
 from __future__ import annotations
 
@@ -50,47 +51,77 @@ def kernels(asm_text: str):
         body.append(s.split(";")[0].strip() if not s.startswith(";;#ASM") else s)
 
 
+# Operations that a state remembers one by one; older ones are remembered together (waits ask for at most 15).
+_REMEMBERED = 64
+
+
+def _parse(ins: str):
+    """(kind, argument, registers touched, registers loaded) of one instruction line."""
+    if not ins or ins.startswith(";;#ASM") or ins.endswith(":"):
+        return ("", None, frozenset(), frozenset())
+    op, _, operands = ins.partition(" ")
+    if op == "s_waitcnt":
+        m = re.search(r"lgkmcnt\((\d+)\)", ins)
+        return ("wait" if m else "", int(m.group(1)) if m else None, frozenset(), frozenset())
+    touched = frozenset(_regs(operands))
+    if op.startswith(("ds_read", "ds_load")):
+        return ("lds", None, touched, frozenset(_regs(operands.split(",")[0])))
+    if op.startswith(("ds_write", "ds_store")):
+        return ("lds", None, touched, frozenset())
+    if op.startswith(("s_load", "s_buffer_load")):
+        return ("scalar", None, touched, frozenset(_regs(operands.split(",")[0])))
+    if op == "s_endpgm":
+        return ("end", None, touched, frozenset())
+    if op == "s_branch" or op.startswith("s_cbranch"):
+        return ("jump" if op == "s_branch" else "branch", ins.split()[-1], touched, frozenset())
+    assert not op.startswith(("s_setpc", "s_swappc", "s_call")), "control flow that is not followed: " + ins
+    return ("", None, touched, frozenset())
+
+
 def lint(body: List[str]) -> List[Tuple[int, str, str]]:
-    """Returns (line index, instruction, reason) for every hazard found in one kernel body."""
-    problems = []
+    """Returns (line index, instruction, reason) for every hazard found in one kernel body, in order."""
     labels = {l[:-1]: i for i, l in enumerate(body) if l.startswith(".LBB") and l.endswith(":")}
-    replayed = set()
+    code = [_parse(ins) for ins in body]
+    problems = {}
+    start = (0, (), frozenset())  # line, LDS operations in flight (oldest first), scalar loads in flight
+    seen, todo = {start}, [start]
 
-    def run(lo, hi, fifo, smem):
-        i = lo
-        while i < hi:
-            ins = body[i]
+    def go(state):
+        if state not in seen:
+            seen.add(state)
+            todo.append(state)
+
+    while todo:
+        i, fifo, scalar = todo.pop()
+        fifo, scalar = list(fifo), set(scalar)
+        while i < len(body):
+            kind, arg, touched, loaded = code[i]
+            if touched:
+                for dest in fifo + list(scalar):
+                    if touched & dest:  # (a load into a register that another is in flight into is a hazard too)
+                        problems[i] = (i, body[i], "touches %s while a load into it may be in flight" % sorted(touched & dest)[:4])
+                        break
+            if kind == "wait":
+                del fifo[:max(0, len(fifo) - arg)]
+                if arg == 0:
+                    scalar.clear()
+            elif kind == "lds":
+                fifo.append(loaded)
+                if len(fifo) > _REMEMBERED:
+                    fifo[:2] = [fifo[0] | fifo[1]]
+            elif kind == "scalar":
+                scalar.add(loaded)
+            elif kind == "end":
+                break
+            elif kind == "jump":
+                go((labels[arg], tuple(fifo), frozenset(scalar)))
+                break
+            elif kind == "branch":
+                go((labels[arg], tuple(fifo), frozenset(scalar)))
+                go((i + 1, tuple(fifo), frozenset(scalar)))
+                break
             i += 1
-            if not ins or ins.startswith(";;#ASM") or ins.endswith(":"):
-                continue
-            op = ins.split()[0]
-            if op == "s_waitcnt":
-                m = re.search(r"lgkmcnt\((\d+)\)", ins)
-                if m:
-                    n = int(m.group(1))
-                    while len(fifo) > n:
-                        fifo.pop(0)
-                    if n == 0:
-                        smem.clear()
-                continue
-            touched = _regs(ins.split(None, 1)[1] if " " in ins else "")
-            for dest in list(fifo) + list(smem):
-                if dest and touched & dest:
-                    # the issuing instruction itself is handled below; anything else is a hazard
-                    problems.append((i - 1, ins, "touches %s while a load into it may be in flight" % sorted(touched & dest)[:4]))
-                    break
-            if op.startswith("ds_read") or op.startswith("ds_load"):
-                fifo.append(frozenset(_regs(ins.split(None, 1)[1].split(",")[0])))
-            elif op.startswith("ds_write") or op.startswith("ds_store"):
-                fifo.append(frozenset())
-            elif op.startswith("s_load") or op.startswith("s_buffer_load"):
-                smem.append(frozenset(_regs(ins.split(None, 1)[1].split(",")[0])))
-            elif op in ("s_branch",) or op.startswith("s_cbranch"):
-                tgt = ins.split()[-1]
-                if tgt in labels and labels[tgt] < i and (tgt, i) not in replayed:
-                    replayed.add((tgt, i))
-                    run(labels[tgt], i, list(fifo), list(smem))  # one more trip round the loop with this state
-        return fifo, smem
-
-    run(0, len(body), [], [])
-    return problems
+            if i < len(body) and body[i].endswith(":"):  # where paths meet
+                go((i, tuple(fifo), frozenset(scalar)))
+                break
+    return [problems[i] for i in sorted(problems)]
