@@ -432,9 +432,7 @@ __global__ __launch_bounds__(KG * WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, W
     const int qpos_lo = p.causal ? pos0 + t0w : 0x7fffff00;
     int first_masked = (qpos_lo + 1) / kUnit;             // units below lie entirely at or before qpos_lo
     first_masked = first_masked < n_kv / kUnit ? first_masked : n_kv / kUnit;  // and entirely inside the sequence
-    // The last unit goes the masked way in every wave, whether it hides a key or not: all waves meet at the same barriers, and that
-    // unit's iteration has none.
-    first_masked = first_masked < n_units - 1 ? first_masked : n_units - 1;
+    first_masked = first_masked < n_units ? first_masked : n_units;
     int qrel[QB];  // key index (relative to the lane's first key of a unit) up to which a row sees keys
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
@@ -715,6 +713,9 @@ __global__ __launch_bounds__(KG * WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, W
     // LAST: nothing follows, so no scores are computed, nothing is fetched for later and nobody is waited for.  Against an ordinary
     // iteration over hidden scores (GPU time): 8 x 30 tokens 6.0 -> 5.6 us, 40 x 2-17 of 16/16 heads 9.4 -> 8.6, 16 x 100-500 36.7 -> 34.0, 8 x
     // 256-2048 136.9 -> 132.4.
+    // The last unit's scores are left raw where it hides nothing from this wave (like a plain unit's) and scaled where it does; either
+    // way the exponent comes from one fused multiply-add, exact in the first case and the plain difference in the second.
+    const float c_last = first_masked == n_units ? c : 1.f;
     auto iteration = [&](int u, f32x16 (&cur)[QB], f32x16 (&nxt)[QB], auto cur_tag, auto nxt_tag, auto slot_tag, auto last_tag) {
         constexpr bool LAST = decltype(last_tag)::value;
         constexpr bool CUR_MASK = decltype(cur_tag)::value;
@@ -746,8 +747,10 @@ __global__ __launch_bounds__(KG * WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, W
         auto exp_issue = [&](int qb, int pair) {
             const int v = 2 * pair;
             float(&e)[2] = e_pending[qb][pair & 1];
-            e[0] = fast_exp2(CUR_MASK ? cur[qb][v] - m_ref[qb] : __builtin_fmaf(cur[qb][v], c, -m_ref[qb]));
-            e[1] = fast_exp2(CUR_MASK ? cur[qb][v + 1] - m_ref[qb] : __builtin_fmaf(cur[qb][v + 1], c, -m_ref[qb]));
+            const bool fma = LAST || !CUR_MASK;
+            const float f = LAST ? c_last : c;
+            e[0] = fast_exp2(fma ? __builtin_fmaf(cur[qb][v], f, -m_ref[qb]) : cur[qb][v] - m_ref[qb]);
+            e[1] = fast_exp2(fma ? __builtin_fmaf(cur[qb][v + 1], f, -m_ref[qb]) : cur[qb][v + 1] - m_ref[qb]);
             asm volatile("" : "+v"(e[0]), "+v"(e[1]));  // issued here, not where they are used
         };
         auto exp_finish = [&](int qb, int pair) {
@@ -924,19 +927,22 @@ __global__ __launch_bounds__(KG * WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, W
         copy_back();
         ++u;
     }
-    if (!cur_masked) {  // the last plain unit: its successor is masked
-        iteration(u, s_cur, s_nxt, Plain{}, Masked{}, AnySlot{}, More{});
-        copy_back();
-        ++u;
-    }
-    for (; u + 2 < n_units; u += 2) {
-        iteration(u, s_cur, s_nxt, Masked{}, Masked{}, AnySlot{}, More{});
-        iteration(u + 1, s_nxt, s_cur, Masked{}, Masked{}, AnySlot{}, More{});
-    }
-    if (u + 1 < n_units) {
-        iteration(u, s_cur, s_nxt, Masked{}, Masked{}, AnySlot{}, More{});
-        copy_back();
-        ++u;
+    // (All waves meet at the same n_units - 1 barriers whichever way their units go; the last unit's iteration has none.)
+    if (first_masked < n_units) {
+        if (!cur_masked) {  // the last plain unit: its successor is masked
+            iteration(u, s_cur, s_nxt, Plain{}, Masked{}, AnySlot{}, More{});
+            copy_back();
+            ++u;
+        }
+        for (; u + 2 < n_units; u += 2) {
+            iteration(u, s_cur, s_nxt, Masked{}, Masked{}, AnySlot{}, More{});
+            iteration(u + 1, s_nxt, s_cur, Masked{}, Masked{}, AnySlot{}, More{});
+        }
+        if (u + 1 < n_units) {
+            iteration(u, s_cur, s_nxt, Masked{}, Masked{}, AnySlot{}, More{});
+            copy_back();
+            ++u;
+        }
     }
     iteration(u, s_cur, s_nxt, Masked{}, Masked{}, AnySlot{}, Last{});
     // The last iteration's K reads are still in flight and nobody will use them: wait for them here,
