@@ -278,12 +278,18 @@ struct KeyTiles {
     int64_t grid;  // the longest query's tiles for every sequence
     int64_t busy;  // at most this many of them find work
 };
-KeyTiles key_tiles(const Instance &inst, const KParams &p)
+KeyTiles row_tiles(const KParams &p, int rows, int heads)
 {
-    const int heads = inst.heads_per_wg > 0 ? inst.heads_per_wg : split_heads(p.group), tok = inst.block_m / heads;
+    const int tok = rows / heads;
     const int64_t groups = p.num_q_heads / heads, grid = (int64_t)p.num_seqs * ((p.max_q_len + tok - 1) / tok) * groups;
     return KeyTiles{grid, std::min(grid, ((int64_t)p.total_q / tok + p.num_seqs) * groups)};
 }
+KeyTiles key_tiles(const Instance &inst, const KParams &p)
+{
+    return row_tiles(p, inst.block_m, inst.heads_per_wg > 0 ? inst.heads_per_wg : split_heads(p.group));
+}
+// The tiles of the ring kernel's 128-row workgroups, which is all that the choice of a prefill instance takes from the number of tokens.
+int64_t small_tiles(const KParams &p) { return row_tiles(p, 128, ring_heads(p)).busy; }
 // Whether the ring kernel's 128-row tiles are so few that a workgroup of two wavefront groups, each with half of the keys, is ahead of
 // one group per tile (`id`: that instance).  GPU time on 4000 random causal shapes (batch 1-16, 8-8192 new tokens, 0-16384 cached ones,
 // 32/8, 64/8, 16/16, 16/4 and 8/2 heads, bf16, built-in choice before against halves):
@@ -295,9 +301,8 @@ KeyTiles key_tiles(const Instance &inst, const KParams &p)
 //    0.80-1.18x, behind a cached prefix 0.89-1.0x, several sequences 0.79-1.3x.
 bool halves_pay(const KParams &p, int id)
 {
-    int n;
     if (id < 0) return false;
-    const int64_t busy = key_tiles(instances(0, &n)[id], p).busy, cus = compute_units();
+    const int64_t busy = small_tiles(p), cus = compute_units();
     const bool whole_prompt = p.num_seqs == 1 && p.causal && p.max_kv_len == p.max_q_len;
     return (busy <= cus && p.max_kv_len >= 700 && p.max_kv_len < 8192) || (whole_prompt && busy <= 2 * cus && p.max_kv_len >= 1400);
 }
@@ -492,10 +497,7 @@ int heuristic(const KParams &p, int is_decode)
         //    sequences 1.03-1.17x [1.07-1.24x], beyond 0.96-1.03x) and for five or more sequences above 4096 keys (1.2x; fewer
         //    1.04x, down to 0.74x).
         const bool prefix = p.block_table && p.max_kv_len >= 2 * p.max_q_len;
-        const int64_t cus = compute_units(), kv = p.max_kv_len;
-        id = small_ring_instance(p);
-        const int64_t tiles = id >= 0 ? key_tiles(instances(0, &n)[id], p).busy : 0;
-        id = -1;
+        const int64_t cus = compute_units(), kv = p.max_kv_len, tiles = small_tiles(p);
         bool small_wg, by_seq;
         if (p.head_dim == 64) {
             small_wg = kv <= 2048 || tiles < (prefix ? 16 : 8) * cus;
@@ -707,20 +709,27 @@ void maybe_load_env_cache()
 // instead of building the bucket string, taking the lock and walking the instance table.
 struct SelectKey {
     int32_t dtype, head_dim, num_q_heads, num_kv_heads, paged, block_size, causal, num_seqs, max_q_len, max_kv_len;
-    int32_t total_q;  // (bounds the tiles of a prefill call)
+    int32_t tiles;  // prefill: tile_class
     int64_t kv_stride_block, kv_stride_tok;  // (kernels with 32-bit offsets inside a block refuse large ones)
     bool operator==(const SelectKey &o) const
     {
-        return total_q == o.total_q && dtype == o.dtype && head_dim == o.head_dim && num_q_heads == o.num_q_heads && num_kv_heads == o.num_kv_heads &&
+        return tiles == o.tiles && dtype == o.dtype && head_dim == o.head_dim && num_q_heads == o.num_q_heads && num_kv_heads == o.num_kv_heads &&
                paged == o.paged && block_size == o.block_size && causal == o.causal && num_seqs == o.num_seqs &&
                max_q_len == o.max_q_len && max_kv_len == o.max_kv_len && kv_stride_block == o.kv_stride_block &&
                kv_stride_tok == o.kv_stride_tok;
     }
 };
-SelectKey select_key(const KParams &p, int dtype)
+// Between which whole numbers of tiles per compute unit a prefill call lies (or on which one): the rules compare with such
+// numbers only, 16 the largest.  Calls with the same maxima and other numbers of tokens mostly share an answer.
+int32_t tile_class(const KParams &p)
+{
+    const int64_t tiles = small_tiles(p), cus = compute_units(), whole = tiles / cus;
+    return (int32_t)std::min<int64_t>(2 * whole + (tiles > whole * cus), 32);
+}
+SelectKey select_key(const KParams &p, int dtype, int is_decode)
 {
     return SelectKey{dtype, p.head_dim, p.num_q_heads, p.num_kv_heads, p.block_table ? 1 : 0, p.block_size, p.causal,
-                     p.num_seqs, p.max_q_len, p.max_kv_len, p.total_q, p.kv_stride_block, p.kv_stride_tok};
+                     p.num_seqs, p.max_q_len, p.max_kv_len, is_decode ? 0 : tile_class(p), p.kv_stride_block, p.kv_stride_tok};
 }
 enum class Origin { built_in, tuned, forced };
 struct Selection {
@@ -800,7 +809,7 @@ Selection selection(const KParams &p, int dtype, int is_decode)
     }
     static thread_local SelectMemo memo[2];
     SelectMemo &m = memo[is_decode];
-    const SelectKey key = select_key(p, dtype);
+    const SelectKey key = select_key(p, dtype, is_decode);
     const uint64_t gen = g_generation.load(std::memory_order_acquire);
     if (m.generation == gen && m.key == key) return m.sel;
     const Selection sel = selection_slow(p, dtype, is_decode);
@@ -822,13 +831,14 @@ KeyPlan planned_parts(const KParams &p, int dtype, Selection sel)
     if (sel.origin == Origin::tuned) return KeyPlan{sel.id, 1};
     struct Memo {
         SelectKey key{};
+        int total_q = -1;  // (the models' times follow it)
         Selection sel;
         KeyPlan plan;
     };
     static thread_local Memo m;
-    const SelectKey key = select_key(p, dtype);
-    if (m.sel.id != sel.id || m.sel.origin != sel.origin || !(m.key == key)) {
-        m = Memo{key, sel, key_plan(p, sel.id, sel.origin == Origin::forced)};
+    const SelectKey key = select_key(p, dtype, 0);
+    if (m.sel.id != sel.id || m.sel.origin != sel.origin || m.total_q != p.total_q || !(m.key == key)) {
+        m = Memo{key, p.total_q, sel, key_plan(p, sel.id, sel.origin == Origin::forced)};
         if (env_knobs().log && m.plan.parts > 1) {
             int n;
             fprintf(stderr, "[attn] prefill %s with scratch memory -> %s in %d parts\n", bucket_key(p, dtype, 0).c_str(),

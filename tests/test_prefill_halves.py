@@ -3,6 +3,9 @@ among the values do to it, against the workgroup that walks all keys of a tile. 
 covered with the other ring instances in test_gpu_ring_starts.py, test_gpu_ring_d128.py and test_gpu_ring_d64.py.)"""
 import ctypes
 import math
+import os
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -45,6 +48,21 @@ def test_the_choice_follows_the_number_of_tokens():
     for _ in range(2):
         assert "halves" in _selected(8, 1000, 1000, 600)
         assert "halves" not in _selected(8, 1000, 1000, 8000)
+
+
+def test_answers_are_kept_over_other_numbers_of_tokens():
+    """Calls with the same maxima are looked up anew (a line of the log) only when their tiles come to lie between other whole numbers
+    of tiles per compute unit."""
+    code = """import sys
+sys.path.insert(0, 'tests')
+from test_prefill_halves import _selected
+for total in list(range(3700, 4500, 7)) + [8000] + list(range(3700, 4500, 7)):  # 4 to 5 tiles per compute unit, 8, 4 to 5
+    _selected(16, 1000, 1000, total)
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), env=dict(os.environ, ATTN_LOG="1"),
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    assert sum(l.startswith("[attn] prefill") for l in r.stderr.splitlines()) == 3
 
 
 @pytest.mark.gpu
