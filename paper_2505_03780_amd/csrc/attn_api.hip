@@ -496,6 +496,9 @@ int heuristic(const KParams &p, int is_decode)
         //    keys to twelve tiles per compute unit; D = 64, small, also for many sequences up to eight tiles per compute unit (32-64
         //    sequences 1.03-1.17x [1.07-1.24x], beyond 0.96-1.03x) and for five or more sequences above 4096 keys (1.2x; fewer
         //    1.04x, down to 0.74x).
+        //  * Without a causal mask all tiles of a sequence cost the same and none is left for the end.  Above 2048 keys sequences outermost:
+        //    1.14x at D = 128, 1.10x at D = 64 on 219 shapes of 2-31 sequences, 0.95-1.76x (6 of up to 8823 tokens, 8/2 heads, D = 64, take
+        //    444 us tiles outermost, as the lines above would have it, and 320); below, as long as there are fewer than 32, tiles.
         const bool prefix = p.block_table && p.max_kv_len >= 2 * p.max_q_len;
         const int64_t cus = compute_units(), kv = p.max_kv_len, tiles = small_tiles(p);
         bool small_wg, by_seq;
@@ -507,6 +510,7 @@ int heuristic(const KParams &p, int is_decode)
             small_wg = kv <= 2048 || (kv <= 4096 && !even) || (kv < 8192 && tiles <= (prefix ? 4 : 3) * cus);
             by_seq = kv <= 2048 ? p.num_seqs >= 32 : kv >= 4096 || tiles >= 12 * cus;
         }
+        if (!p.causal) by_seq = kv > 2048 || p.num_seqs >= 32;
         const int order = prefix || by_seq ? 1 : 0;
         // a paged context adds the table entry to every transfer's address chain: the deepest prefetch
         // (8 units) measured up to 10 % ahead of 5 on the slower machines there, level elsewhere
