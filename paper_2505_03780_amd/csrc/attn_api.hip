@@ -288,8 +288,18 @@ KeyTiles key_tiles(const Instance &inst, const KParams &p)
 {
     return row_tiles(p, inst.block_m, inst.heads_per_wg > 0 ? inst.heads_per_wg : split_heads(p.group));
 }
-// The tiles of the ring kernel's 128-row workgroups, which is all that the choice of a prefill instance takes from the number of tokens.
+// The tiles of the ring kernel's 128-row workgroups: what the choice of a prefill instance takes from the number of tokens (with
+// those of 256 rows in small_tiles_fit).
 int64_t small_tiles(const KParams &p) { return row_tiles(p, 128, ring_heads(p)).busy; }
+// Whether tiles that all cost about the same (no causal mask) are better off in the ring kernel's 128-row workgroups, two per compute
+// unit, than in 256-row ones, one per compute unit.  A full round takes the same time for the same rows, within some 5 % in favour of the
+// large one, so the small one gains where its last round is no more than half full (each with a compute unit to itself) while the large
+// one's is a whole one, and where it has a tenth fewer rows of padding.
+bool small_tiles_fit(const KParams &p)
+{
+    const int64_t cus = compute_units(), small = small_tiles(p), large = row_tiles(p, 256, ring_heads(p)).busy;
+    return (small + cus - 1) / cus < 2 * ((large + cus - 1) / cus) || 5 * small < 9 * large;
+}
 // Whether the ring kernel's 128-row tiles are so few that a workgroup of two wavefront groups, each with half of the keys, is ahead of
 // one group per tile (`id`: that instance).  GPU time on 4000 random causal shapes (batch 1-16, 8-8192 new tokens, 0-16384 cached ones,
 // 32/8, 64/8, 16/16, 16/4 and 8/2 heads, bf16, built-in choice before against halves):
@@ -489,6 +499,8 @@ int heuristic(const KParams &p, int is_decode)
         //    behind), and below 8192 where its tiles make no more than two rounds (four tiles per compute unit behind a prefix:
         //    1.09x [1.02-1.05x]; three else: 1.06x [1.03-1.1x]).  Beyond, level or behind: one sequence of 8191 tokens 474-485 us
         //    large, 496 small; 16 x 512 behind 0-8192 654 and 680.
+        //    Without a causal mask, 2048-8192 keys: what fits (small_tiles_fit).  On 256 shapes 1.09x against the choice before these
+        //    lines, 5 % of them more than 2 % behind it (with the lines of the causal calls 19 %, down to 0.86x).
         //  * D = 64: small up to 2048 keys, and up to eight tiles per compute unit (sixteen behind a prefix): 1.05-1.14x [1.03-1.22x].
         //    Beyond, 1.07x but [0.97-1.03x]: 6 x 300-3000 tokens [178 us large, 184 small].
         //  * Order, sequences outermost (their tiles share the keys in one L2) behind a prefix that dominates: 1.02-1.1x; else tiles outermost
@@ -508,6 +520,7 @@ int heuristic(const KParams &p, int is_decode)
         } else {
             const bool even = !prefix && tiles > 3 * cus && tiles <= 4 * cus;
             small_wg = kv <= 2048 || (kv <= 4096 && !even) || (kv < 8192 && tiles <= (prefix ? 4 : 3) * cus);
+            if (!p.causal && kv > 2048) small_wg = kv < 8192 && small_tiles_fit(p);
             by_seq = kv <= 2048 ? p.num_seqs >= 32 : kv >= 4096 || tiles >= 12 * cus;
         }
         if (!p.causal) by_seq = kv > 2048 || p.num_seqs >= 32;
@@ -724,11 +737,12 @@ struct SelectKey {
     }
 };
 // Between which whole numbers of tiles per compute unit a prefill call lies (or on which one): the rules compare with such
-// numbers only, 16 the largest.  Calls with the same maxima and other numbers of tokens mostly share an answer.
+// numbers only, 16 the largest, but for small_tiles_fit (a mark of its own).  Calls with the same maxima and other numbers of tokens mostly
+// share an answer.
 int32_t tile_class(const KParams &p)
 {
     const int64_t tiles = small_tiles(p), cus = compute_units(), whole = tiles / cus;
-    return (int32_t)std::min<int64_t>(2 * whole + (tiles > whole * cus), 32);
+    return (int32_t)std::min<int64_t>(2 * whole + (tiles > whole * cus), 32) + (!p.causal && small_tiles_fit(p) ? 64 : 0);
 }
 SelectKey select_key(const KParams &p, int dtype, int is_decode)
 {
