@@ -20,11 +20,12 @@
 //    of the weights differs, and the rescale of the accumulators becomes rare.
 //  * The output tile is transposed through LDS and written as whole rows, and the queries arrive the same way.
 //  * Start of a workgroup: everything that can be asked for is asked for before anything is waited for (table entries, whole
-//    query rows, the first units), the first scores wait for the queries and unit 0 alone, and units past the last one are not
-//    requested at all.  With the queries loaded in operand order, the sign of the scale applied to them as they came, all
-//    units of the ring awaited and the last unit repeated to fill it (GPU time, rotating buffers, before -> now): 8 x 30 tokens, paged,
+//    query rows, the first units), the first scores wait for the queries and unit 0 alone, and no unit past the last one is
+//    requested to fill the ring (only the loop unrolled once round it still asks in every iteration, and may repeat the last unit up
+//    to PF - 1 times at its end).  With the queries loaded in operand order, the sign of the scale applied to them as they came, all
+//    units of the ring awaited and the last unit repeated to fill it (GPU time, before -> now, the four together): 8 x 30 tokens, paged,
 //    32/8 heads 6.6 -> 6.0 us, 4 x 40-100 behind 10-100 keys 9.2 -> 8.5, 16 x 100-500 40.3 -> 36.7, 24 x 100-1200 of 16/4
-//    heads 95.8 -> 89.8, 8 x 256-2048 140.7 -> 136.9, D = 64 4 x 40-100 5.8 -> 5.6.
+//    heads 95.8 -> 89.8, 8 x 256-2048 128.8 -> 124.0, D = 64 4 x 40-100 5.8 -> 5.6.
 //  * Where a call has fewer tiles than the chip has room for, and brings scratch memory, the keys are cut into parts (PARTS;
 //    grid dimension y): a part's workgroup runs the same loop over its own keys and leaves its accumulators as a record
 //    for prefill_ring_merge_kernel.  3 x 17-70 tokens behind 5000-9000 keys (56 tiles, 512 places): 141 us in one part, 42 in
@@ -118,7 +119,7 @@ __device__ __forceinline__ float swap32_sum(float x)
 // the ones it still sees with lgkmcnt(0), i.e. for the read it issued a moment ago, several times per
 // unit.  LDS operations of a wave complete in order, so "at most N operations outstanding" means
 // that everything but the N youngest has returned: every consumer below waits with the number of LDS
-// operations issued after the one it needs (lds_wait), counted at compile time along the unrolled code.
+// operations issued after the one it needs (lds_wait_upto), counted at compile time along the unrolled code.
 __device__ __forceinline__ s16x4 lds_read_tr16_b64_untracked(const unsigned char *p)
 {
     s16x4 r;
@@ -594,7 +595,8 @@ __global__ __launch_bounds__(KG * WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, W
         for (int u = 0; u <= PF; ++u) asm volatile("" : "+s"(entries[u]));
     }
     if (KG == 1 || n_units > 0) {  // (uniform over a group)
-    // (units past the last are not requested, here and in the loop; their slots then hold anything, which nothing uses)
+    // (units past the last are not requested here, nor by iterations whose slots are not compile-time constants; their slots then hold
+    // anything, which nothing uses)
 #pragma unroll
     for (int u = 0; u < C::kEarly; ++u)
         if (u < n_units) issue_unit(u, entries[u]);
@@ -712,7 +714,7 @@ __global__ __launch_bounds__(KG * WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, W
     // SLOT2 >= 0: the ring slot of unit u+2, known at compile time
     // LAST: nothing follows, so no scores are computed, nothing is fetched for later and nobody is waited for.  Against an ordinary
     // iteration over hidden scores (GPU time): 8 x 30 tokens 6.0 -> 5.6 us, 40 x 2-17 of 16/16 heads 9.4 -> 8.6, 16 x 100-500 36.7 -> 34.0, 8 x
-    // 256-2048 136.9 -> 132.4.
+    // 256-2048 124 -> 122.
     // The last unit's scores are left raw where it hides nothing from this wave (like a plain unit's) and scaled where it does; either
     // way the exponent comes from one fused multiply-add, exact in the first case and the plain difference in the second.
     const float c_last = first_masked == n_units ? c : 1.f;
@@ -873,7 +875,9 @@ __global__ __launch_bounds__(KG * WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, W
                     ++seq;
                 }
             }
-            if (!LAST && g == G - 3 && (SLOT2 >= 0 || u + PF < n_units)) issue_unit(u + PF, entry_cur);  // refill: unit u+PF replaces unit u+PF-NSLOT <= u
+            // Refill: unit u+PF replaces unit u+PF-NSLOT <= u.  With compile-time slots always, which keeps the count of transfers the
+            // same in every iteration: past the last unit that is the last one again, into a slot that nothing reads any more.
+            if (!LAST && g == G - 3 && (SLOT2 >= 0 || u + PF < n_units)) issue_unit(u + PF, entry_cur);
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
@@ -882,7 +886,7 @@ __global__ __launch_bounds__(KG * WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, W
             if (!LAST && outgrown[qb]) rescale_to(qb, bm[qb]);
         }
         if (LAST) return;
-        // Publish.  This wave's transfers of every unit up to u+3 have landed (wait_units; the plain loop requests one in every iteration);
+        // Publish.  This wave's transfers of every unit up to u+3 have landed (wait_units; the unrolled loop requests one in every iteration);
         // its image stores have been performed (phase Y waited for younger reads); its K reads may still
         // be in flight, they target a slot that no transfer touches before the barrier after next.
         if (PAGED) asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(entry_nxt)::"memory");
@@ -945,9 +949,9 @@ __global__ __launch_bounds__(KG * WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, W
         }
     }
     iteration(u, s_cur, s_nxt, Masked{}, Masked{}, AnySlot{}, Last{});
-    // The last iteration's K reads are still in flight and nobody will use them: wait for them here,
-    // with their registers tied, so that the compiler cannot hand those registers to anything else
-    // while a read may still land in them.
+    // Nobody uses the K fragments that were read ahead for a unit behind the last one.  They have landed (the last iteration waited for
+    // younger reads), but the compiler does not know when: their registers are tied to a wait here, behind those waits, so that it cannot hand
+    // them to anything else while a read may still land in them.
     if constexpr (KSTEPS == 8)
         asm volatile("s_waitcnt lgkmcnt(0)"
                      : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]), "+v"(kf[4]), "+v"(kf[5]), "+v"(kf[6]), "+v"(kf[7])::"memory");
@@ -1001,6 +1005,7 @@ __global__ __launch_bounds__(KG * WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, W
 #pragma unroll
             for (int db = 0; db < DB; ++db) out[qb][db] = oacc[qb][db];
     }
+    static_assert(!PARTS || KG == 1, "records are those of one group");
     if (PARTS) {
         const RingParts parts = ring_parts(p, T, C::kTok);
         if (parts.count > 1) {  // one of several: a record of each row block in register order, left for the merge
@@ -1013,9 +1018,9 @@ __global__ __launch_bounds__(KG * WAVES * 64, (RingCfg<HD, QB, HPW, NSLOT, PF, W
                 for (int db = 0; db < ODB; ++db)
 #pragma unroll
                     for (int vq = 0; vq < 4; ++vq)
-                        *(f32x4 *)(rec + (4 * (kgroup * ODB + db) + vq) * 256 + 4 * lane) =
+                        *(f32x4 *)(rec + (4 * db + vq) * 256 + 4 * lane) =
                             f32x4{out[qb][db][4 * vq], out[qb][db][4 * vq + 1], out[qb][db][4 * vq + 2], out[qb][db][4 * vq + 3]};
-                if (kgroup == 0 && lhalf == 0) *(float2 *)(rec + 32 * HD + 2 * l32) = float2{m_ref[qb], l_row[qb]};
+                if (lhalf == 0) *(float2 *)(rec + 32 * HD + 2 * l32) = float2{m_ref[qb], l_row[qb]};
             }
             return;
         }

@@ -1,6 +1,7 @@
 """The ring prefill kernel where its start and its end meet: sequences of one unit of 32 keys up to more than the ring holds, a
-key to either side of every edge, by every instance.  Units past the last are never requested, so their slots hold what an
-earlier workgroup left there; here that is NaN, by a call over NaN that reaches every compute unit twice."""
+key to either side of every edge, by every instance.  Units past the last are not requested to fill the ring, so their slots hold
+what an earlier workgroup left there (but at the end of a whole trip round the ring, which may repeat the last unit); here that is NaN, by a
+call over NaN that reaches every compute unit twice."""
 import numpy as np
 import pytest
 import torch
