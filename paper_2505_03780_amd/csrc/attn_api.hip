@@ -309,6 +309,10 @@ bool small_tiles_fit(const KParams &p)
 //  * up to two per compute unit one whole prompt gains from 1400 keys on (a triangle: the mean tile has half of the longest one's
 //    keys): 1.11-1.46x at D = 128, 1.08-1.28x at D = 64, none of 130 loses; with less than 1400 keys 0.93-1.17x, with more tiles
 //    0.80-1.18x, behind a cached prefix 0.89-1.0x, several sequences 0.79-1.3x.
+// On 1212 other random shapes that take halves, 407 of them without a causal mask and a third fp16: 1.20x, without a mask 1.21x; 8 of 805 and 6
+// of 407 lose more than 2 % (0.90x at worst), nearly all of them several sequences with 0.95 to 1 tile per compute unit in a larger
+// grid, of which some XCDs are dealt more than their share.  Lines that keep those out (no grid beyond the compute units, or 7/8 of a tile each)
+// take 33 to 102 shapes back that gain 1.09-1.18x from it.
 bool halves_pay(const KParams &p, int id)
 {
     if (id < 0) return false;
@@ -495,14 +499,17 @@ int heuristic(const KParams &p, int is_decode)
         // workgroup, 256 rows) moves half of the bytes per flop and wins once its start and end are a small part of its walk and
         // there are many rounds of it.
         //  * D = 128: small up to 4096 keys (against the large one above 2048 keys 1.08x on average, 1.07x behind a prefix [1.02-1.17x,
-        //    1.01-1.11x]; at three to four tiles per compute unit the large one comes out even, 1.017x with a third of the shapes
-        //    behind), and below 8192 where its tiles make no more than two rounds (four tiles per compute unit behind a prefix:
+        //    1.01-1.11x]; but for three to four tiles per compute unit without a prefix, two full rounds of the large one: small there too
+        //    is level on average and doubles the shapes that lose more than 2 %, from 3.6 to 6.7 % of 386), and below 8192 where its tiles make no more than two rounds (four tiles per compute unit behind a prefix:
         //    1.09x [1.02-1.05x]; three else: 1.06x [1.03-1.1x]).  Beyond, level or behind: one sequence of 8191 tokens 474-485 us
         //    large, 496 small; 16 x 512 behind 0-8192 654 and 680.
+        //    Behind a prefix 414 shapes above 2048 keys gain 1.060x, 16 % of them lose more than 2 % (0.90x at worst); small_tiles_fit
+        //    there would be 1.052x and 7 %, and 167 shapes 0.98x against these lines, down to 0.73x.
         //    Without a causal mask, 2048-8192 keys: what fits (small_tiles_fit).  On 256 shapes 1.09x against the choice before these
         //    lines, 5 % of them more than 2 % behind it (with the lines of the causal calls 19 %, down to 0.86x).
         //  * D = 64: small up to 2048 keys, and up to eight tiles per compute unit (sixteen behind a prefix): 1.05-1.14x [1.03-1.22x].
-        //    Beyond, 1.07x but [0.97-1.03x]: 6 x 300-3000 tokens [178 us large, 184 small].
+        //    Beyond, 1.07x but [0.97-1.03x]: 6 x 300-3000 tokens [178 us large, 184 small].  Without a causal mask too (1225 shapes 1.046x
+        //    against the choice before, 1.045x with the lines before).
         //  * Order, sequences outermost (their tiles share the keys in one L2) behind a prefix that dominates: 1.02-1.1x; else tiles outermost
         //    (equal costs in flight, small tiles left for the end): D = 128 1.03-1.1x below 32 sequences, and between 2048 and 4096
         //    keys to twelve tiles per compute unit; D = 64, small, also for many sequences up to eight tiles per compute unit (32-64

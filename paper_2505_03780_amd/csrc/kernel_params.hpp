@@ -89,7 +89,7 @@ __device__ __forceinline__ int32_t load_uniform(const int32_t *base, int64_t i)
 // Values of the lanes 16 and 32 apart, through the vector pipe (__shfl_xor goes through LDS: some 120 cycles each, one after the other
 // in the middle of every chunk's softmax).  A pair comes in either order, which is all that a maximum or a sum asks for.  GPU time,
 // the same bits: fp32 prefill of 128 tokens 5.3 -> 5.2 us, 2 x 100-250 10.0 -> 9.8, decode of 14 x 99-495 at D = 64 7.1 -> 7.0, 23 x
-// 60-304 7.7 -> 7.6, one context of 1900 7.5 -> 7.4.
+// 60-304 7.7 -> 7.6; one context of 1900 level.
 struct LanePair {
     float a, b;
 };
