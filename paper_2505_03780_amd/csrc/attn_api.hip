@@ -500,9 +500,10 @@ int heuristic(const KParams &p, int is_decode)
         // there are many rounds of it.
         //  * D = 128: small up to 4096 keys (against the large one above 2048 keys 1.08x on average, 1.07x behind a prefix [1.02-1.17x,
         //    1.01-1.11x]; but for three to four tiles per compute unit without a prefix, two full rounds of the large one: small there too
-        //    is level on average and doubles the shapes that lose more than 2 %, from 3.6 to 6.7 % of 386), and below 8192 where its tiles make no more than two rounds (four tiles per compute unit behind a prefix:
-        //    1.09x [1.02-1.05x]; three else: 1.06x [1.03-1.1x]).  Beyond, level or behind: one sequence of 8191 tokens 474-485 us
-        //    large, 496 small; 16 x 512 behind 0-8192 654 and 680.
+        //    is level on average and doubles the shapes that lose more than 2 %, from 3.6 to 6.7 % of 386), and below 8192 where its
+        //    tiles make no more than two rounds (four tiles per compute unit behind a prefix: 1.09x [1.02-1.05x]; three else: 1.06x
+        //    [1.03-1.1x]).  Beyond, level or behind: one sequence of 8191 tokens 474-485 us large, 496 small; 16 x 512 behind 0-8192
+        //    654 and 680.
         //    Behind a prefix 414 shapes above 2048 keys gain 1.060x, 16 % of them lose more than 2 % (0.90x at worst); small_tiles_fit
         //    there would be 1.052x and 7 %, and 167 shapes 0.98x against these lines, down to 0.73x.
         //    Without a causal mask, 2048-8192 keys: what fits (small_tiles_fit).  On 256 shapes 1.09x against the choice before these
