@@ -734,11 +734,10 @@ void maybe_load_env_cache()
 // instead of building the bucket string, taking the lock and walking the instance table.
 struct SelectKey {
     int32_t dtype, head_dim, num_q_heads, num_kv_heads, paged, block_size, causal, num_seqs, max_q_len, max_kv_len;
-    int32_t tiles;  // prefill: tile_class
     int64_t kv_stride_block, kv_stride_tok;  // (kernels with 32-bit offsets inside a block refuse large ones)
     bool operator==(const SelectKey &o) const
     {
-        return tiles == o.tiles && dtype == o.dtype && head_dim == o.head_dim && num_q_heads == o.num_q_heads && num_kv_heads == o.num_kv_heads &&
+        return dtype == o.dtype && head_dim == o.head_dim && num_q_heads == o.num_q_heads && num_kv_heads == o.num_kv_heads &&
                paged == o.paged && block_size == o.block_size && causal == o.causal && num_seqs == o.num_seqs &&
                max_q_len == o.max_q_len && max_kv_len == o.max_kv_len && kv_stride_block == o.kv_stride_block &&
                kv_stride_tok == o.kv_stride_tok;
@@ -752,10 +751,10 @@ int32_t tile_class(const KParams &p)
     const int64_t tiles = small_tiles(p), cus = compute_units(), whole = tiles / cus;
     return (int32_t)std::min<int64_t>(2 * whole + (tiles > whole * cus), 32) + (!p.causal && small_tiles_fit(p) ? 64 : 0);
 }
-SelectKey select_key(const KParams &p, int dtype, int is_decode)
+SelectKey select_key(const KParams &p, int dtype)
 {
     return SelectKey{dtype, p.head_dim, p.num_q_heads, p.num_kv_heads, p.block_table ? 1 : 0, p.block_size, p.causal,
-                     p.num_seqs, p.max_q_len, p.max_kv_len, is_decode ? 0 : tile_class(p), p.kv_stride_block, p.kv_stride_tok};
+                     p.num_seqs, p.max_q_len, p.max_kv_len, p.kv_stride_block, p.kv_stride_tok};
 }
 enum class Origin { built_in, tuned, forced };
 struct Selection {
@@ -765,6 +764,7 @@ struct Selection {
 struct SelectMemo {
     uint64_t generation = 0;
     SelectKey key{};
+    int32_t total_q = -1, tiles = 0;  // prefill: a call with the number of tokens, and its tile_class
     Selection sel;
 };
 
@@ -835,14 +835,22 @@ Selection selection(const KParams &p, int dtype, int is_decode)
     }
     static thread_local SelectMemo memo[2];
     SelectMemo &m = memo[is_decode];
-    const SelectKey key = select_key(p, dtype, is_decode);
+    const SelectKey key = select_key(p, dtype);
     const uint64_t gen = g_generation.load(std::memory_order_acquire);
-    if (m.generation == gen && m.key == key) return m.sel;
+    const bool known = m.generation == gen && m.key == key;
+    if (known && (is_decode || m.total_q == p.total_q)) return m.sel;
+    const int32_t tiles = is_decode ? 0 : tile_class(p);  // (its divisions are spared where the number of tokens is the same too)
+    if (known && m.tiles == tiles) {
+        m.total_q = p.total_q;
+        return m.sel;
+    }
     const Selection sel = selection_slow(p, dtype, is_decode);
     // the generation is read again: a table change that raced with the slow path must not be memoised
     if (g_generation.load(std::memory_order_acquire) == gen) {
         m.generation = gen;
         m.key = key;
+        m.total_q = p.total_q;
+        m.tiles = tiles;
         m.sel = sel;
     }
     return sel;
@@ -862,7 +870,7 @@ KeyPlan planned_parts(const KParams &p, int dtype, Selection sel)
         KeyPlan plan;
     };
     static thread_local Memo m;
-    const SelectKey key = select_key(p, dtype, 0);
+    const SelectKey key = select_key(p, dtype);
     if (m.sel.id != sel.id || m.sel.origin != sel.origin || m.total_q != p.total_q || !(m.key == key)) {
         m = Memo{key, p.total_q, sel, key_plan(p, sel.id, sel.origin == Origin::forced)};
         if (env_knobs().log && m.plan.parts > 1) {
